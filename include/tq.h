@@ -56,10 +56,11 @@ enum { TQ_LAYOUT_CANONICAL = 0 };
  * group_size 32 is what the matrix-core kernels are built for (one matrix instruction per group).  Sec. 2.1
  * states the scheme for groups of g consecutive elements: 64 and 128 are accepted by every call (same
  * arithmetic per group, same bit-exact stores).  At head_dim 128 they take the matrix-core kernel as well
- * (group_size 128: with an even capacity and no sliding window); otherwise the generic vector-ALU kernels,
- * where options that only the matrix-core kernels offer (variant 2, n_queries > 1) answer UNSUPPORTED.
- * (With group_size 128 that kernel reads the scale / zero-point arrays two tokens at a time: up to one token
- * past seq_len, inside the row.) */
+ * (group_size 128: with an even capacity and no sliding window), and at head_dim 256 by default; otherwise the
+ * generic vector-ALU kernels.  At head_dim 256 and 512 options that only the matrix-core kernels offer (variant 2,
+ * n_queries > 1) answer UNSUPPORTED with these groups.
+ * (With group_size 128 at head_dim 128 that kernel reads the scale / zero-point arrays two tokens at a time: up to
+ * one token past seq_len, inside the row.) */
 typedef struct tq_kv_cache {
   void* k_codes;
   void* v_codes;

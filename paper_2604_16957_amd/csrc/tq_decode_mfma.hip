@@ -98,7 +98,7 @@ constexpr uint32_t kMaskLo = 0x000F000Fu;   // nibbles 0 and 4 of a word -> fp16
 constexpr uint32_t kMaskHi = 0x00F000F0u;   // nibbles 1 and 5           -> c * 2^-20
 constexpr uint32_t kPos15Odd = 0x4B800000u; // fp16 pair (0, 15): k-slots alternate first tile, second tile
 
-template <int D, int GP, int NW>
+template <int D, int GP, int NW, int GS = 0>
 struct Cfg {
   static constexpr int NG = D / kGroup;          // quantisation groups per token
   static constexpr int GR = 16 / GP;             // group replicas among the 16 columns / rows
@@ -128,7 +128,10 @@ struct Cfg {
   static constexpr int TB = D / 2;               // bytes of codes per token
   static constexpr int KT = 16 * TB;             // one 16-token K tile
   static constexpr int VB = 32 * TB;             // V codes of the supertile
-  static constexpr int SZ = 32 * NG * 2;         // one fp16 scale (or zero-point) array of the supertile
+  // one fp16 scale (or zero-point) array of the supertile.  Where it lies token by token in LDS (d = 256), larger
+  // groups keep it compact, NGM values per token; the gathered layouts (PERM, WIDE below) always fill NG places.
+  static constexpr int NGM = D == 256 ? NG >> GS : NG;
+  static constexpr int SZ = 32 * NGM * 2 > 256 ? 32 * NGM * 2 : 256;
   static constexpr int OFF_V = 2 * KT, OFF_KS = OFF_V + VB, OFF_KZ = OFF_KS + SZ, OFF_VS = OFF_KZ + SZ,
                        OFF_VZ = OFF_VS + SZ, STAGE = OFF_VZ + SZ;
   static constexpr int NS = 2;                  // ring depth per wave (LDS: 160 KB per CU)
@@ -159,10 +162,10 @@ struct Cfg {
   static constexpr bool PFK = !(D == 256 && NA == 2);
   static __device__ constexpr int sz_token(int P) {       // token (0..31) whose dword sits at stage dword P
     return WIDE ? 16 * ((P >> 2) & 1) + 4 * (P & 3) + (P >> 4)
-                : PERM ? 16 * ((P >> 2) & 1) + 4 * (P & 3) + (P >> 3) / GR : P / (NG / 2);
+                : PERM ? 16 * ((P >> 2) & 1) + 4 * (P & 3) + (P >> 3) / GR : (P / (NGM / 2)) & 31;
   }
   static __device__ constexpr int sz_column(int P) {      // which dword of that token's NG/2
-    return WIDE ? (P >> 3) & 1 : PERM ? (P >> 3) % GR : P % (NG / 2);
+    return WIDE ? (P >> 3) & 1 : PERM ? (P >> 3) % GR : P % (NGM / 2);
   }
 };
 
@@ -298,11 +301,23 @@ __device__ __forceinline__ void wait_loads() {               // until at most N 
 // MEAN, not what the kernel does with them: the direct loads fetch, for every 32-dim block of a token, the dword
 // that holds its group's value (one dword of two groups per token at 64, one dword of two TOKENS at 128), and the
 // lane copies the half it needs into both halves of the register, after which everything is as with groups of 32.
-// Instantiated for the layouts whose metadata is gathered dword by dword (d = 128 with 8 or 16 rows).
+// That is for the layouts whose metadata is gathered dword by dword (d = 128 with 8 or 16 rows).  At d = 256 a lane
+// reads one halfword per token and array anyway: the stage holds the arrays as they are, and only the halfword's
+// address changes with the group.
+//
+// SPLIT (d = 256 with larger groups): the weights p s_v go through the matrix core as TWO fp16 operands, their
+// leading part and the rest, so that they count as in fp32 (22 bits), as they do in the generic kernel that served
+// these shapes before; the reference of the exponentials then also carries an offset that keeps the largest weight
+// near 2^10 whatever the size of the scales (see `softmax`), or small scales would push the rest below fp16's range.
+// The matrix cores have the room (52 instructions per supertile instead of 34, a quarter of its time), and the kernel
+// is bound by the stream like its groups-of-32 instance: 32 heads on 16 KV heads, one sequence of 32K tokens, groups of
+// 64 (151 MB), the whole step 305.5 us on the generic kernel, 35.6 us here.
 template <int D, int GP, int NW, bool NT, bool PLAIN, int GS = 0>
 __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_kernel(DecodeParams p) {
-  using C = Cfg<D, GP, NW>;
-  static_assert(GS == 0 || ((C::PERM || C::WIDE) && !PLAIN), "larger groups: the gathered metadata layouts only");
+  using C = Cfg<D, GP, NW, GS>;
+  static_assert(GS == 0 || D == 256 || ((C::PERM || C::WIDE) && !PLAIN), "larger groups at d = 128: the gathered layouts");
+  constexpr bool SPLIT = GS > 0 && D == 256;
+  constexpr int NGM = C::NGM;
   constexpr int SZB = (D / kGroup * 2) >> GS;     // bytes of one metadata array per token
   constexpr int NG = C::NG, NA = C::NA, NJ = C::NJ, NCS = C::NCS, TB = C::TB, NS = C::NS, LPS = C::LPS, GR = C::GR;
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -496,7 +511,7 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   uint32_t szoff[C::SZ / 256];
 #pragma unroll
   for (int u = 0; u < C::SZ / 256; ++u)           // (larger groups: the token's only dword, or the dword it shares)
-    szoff[u] = GS == 0 ? (sz_tok[u] * (NG / 2) + sz_col[u]) * 4 : GS == 1 ? sz_tok[u] * 4 : (sz_tok[u] >> 1) * 4;
+    szoff[u] = GS == 0 || D == 256 ? (sz_tok[u] * (NGM / 2) + sz_col[u]) * 4 : GS == 1 ? sz_tok[u] * 4 : (sz_tok[u] >> 1) * 4;
   auto issue_at = [&](uint32_t l, const Bases& B, uint32_t off_c, uint32_t vk, uint32_t vv,
                       const uint32_t (&vs)[C::SZ / 256]) {
     const uint32_t off_s = off_c >> (3 + GS);     // SZB / TB: metadata bytes per code byte
@@ -550,7 +565,7 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
 #pragma unroll
       for (int u = 0; u < C::SZ / 256; ++u) {
         const int tok = min(base + (int)sz_tok[u], last_tok);
-        const int64_t src = GS == 0 ? (int64_t)tok * (NG * 2) + sz_col[u] * 4 : GS == 1 ? (int64_t)tok * 4 : (int64_t)(tok >> 1) * 4;
+        const int64_t src = GS == 0 || D == 256 ? (int64_t)tok * (NGM * 2) + sz_col[u] * 4 : GS == 1 ? (int64_t)tok * 4 : (int64_t)(tok >> 1) * 4;
         dma4_lane(sz_row[a] + src, l + C::OFF_KS + a * C::SZ + u * 256);
       }
   };
@@ -690,6 +705,8 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   // for c(2j) + 16 c(2j+1), less 255 sum_t1 w.  WIDE: [2g], [2g+1] are the even and the mixed sum of group g, whose
   // column c stands for byte c / 4 of the group's word c % 4; one accumulator each.
   constexpr int NAO = C::WIDE ? 1 : NA;
+  static_assert(!SPLIT || NA == 1, "one group per lane");
+  constexpr int NPA = SPLIT ? 2 : NA;             // A operands of P V: one per group of the lane, or the two parts of one
   float4v oacc[NCS][8][NAO];
 #pragma unroll
   for (int a = 0; a < NA; ++a) zacc[a] = float4v{0, 0, 0, 0};
@@ -715,8 +732,8 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   // array's own stride
   // (WIDE: the zero-point operand's column c stands for group c % 4)
   const int gz = C::WIDE ? (c & 3) : (c * NCS) >> 2;
-  const uint32_t sz_rd = C::WIDE ? kq * 64 : C::PERM ? (kq * GR + rep) * 32 : (kq * NG + rep * NA) * 2;
-  const uint32_t zb_rd = C::WIDE ? kq * 64 + (gz >> 1) * 32 : C::PERM ? (kq * GR + (gz >> 1)) * 32 : (kq * NG + gz) * 2;
+  const uint32_t sz_rd = C::WIDE ? kq * 64 : C::PERM ? (kq * GR + rep) * 32 : (kq * NGM + ((rep * NA) >> GS)) * 2;
+  const uint32_t zb_rd = C::WIDE ? kq * 64 + (gz >> 1) * 32 : C::PERM ? (kq * GR + (gz >> 1)) * 32 : (kq * NGM + (gz >> GS)) * 2;
   // which half of a zero-point dword: the group's place in its pair; with larger groups the pair's place among the
   // token's two groups, or the token's place in its pair of tokens (this lane's tokens are kq, kq + 4, ...)
   const bool zb_hi = GS == 0 ? (gz & 1) : GS == 1 ? ((gz >> 1) & 1) : (kq & 1);
@@ -744,14 +761,14 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
       for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-          dst[t][i] = *reinterpret_cast<const uint16_t*>(arr + (t * 16 + i * 4) * NG * 2 + rd);
+          dst[t][i] = *reinterpret_cast<const uint16_t*>(arr + (t * 16 + i * 4) * NGM * 2 + rd);
     }
   };
   auto load_sz = [&](const char* arr, uint32_t rd, uint32_t (&dst)[NDW][2][4]) {
 #pragma unroll
     for (int dw = 0; dw < NDW; ++dw) {
       load_sz1(arr + dw * 32, rd, dst[dw]);
-      if constexpr (GS > 0) {
+      if constexpr (GS > 0 && D == 128) {
         const uint32_t sel = (GS == 1 && C::WIDE) ? (dw ? dup_hi : dup_lo) : dup_lane;
 #pragma unroll
         for (int t = 0; t < 2; ++t)
@@ -843,17 +860,57 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   //    Then A = fp16(+-p * s_v) (minus on the second tile's k-slots), rows (head, replica), one operand
   //    per group of the lane; the zero-point term goes through the matrix core with the stored fp16
   //    zero-points (sign flipped on the second tile's k-slots) as B operand.
-  auto softmax = [&](const float (&sc)[2][4], const VRegs& r, half8v (&pa)[NA]) {
+  //    SPLIT: the weights are 2^off p s_v with a wave-wide off, lowered when a larger scale turns up, that keeps
+  //    them below 2^12; off is part of the reference the partial is published with.  A = leading fp16 part, then
+  //    the rest (both rounded towards zero: what the first leaves out the second takes).
+  //    SPLIT also turns the sign of everything half way through the wave's supertiles: the matrix core's truncation
+  //    pulls an accumulator the same way at every step, and what it takes from the first half it gives back in the
+  //    second (32K tokens, flat softmax: 1.4 % of the output's error against 64 bits, most of it fp16 rounding).
+  uint32_t sv_top = 0;                            // (SPLIT) bits of the power of two no scale so far reaches
+  float off = 0.0f, sgn = 1.0f;
+  auto negate_sums = [&] {
+    sgn = -sgn;
+#pragma unroll
+    for (int a = 0; a < NA; ++a) zacc[a] = -zacc[a];
+#pragma unroll
+    for (int cs = 0; cs < NCS; ++cs)
+#pragma unroll
+      for (int m = 0; m < 8; ++m)
+#pragma unroll
+        for (int a = 0; a < NAO; ++a) oacc[cs][m][a] = -oacc[cs][m][a];
+  };
+  auto softmax = [&](const float (&sc)[2][4], const VRegs& r, half8v (&pa)[NPA]) {
     const float mx = fmaxf(fmaxf(fmaxf(sc[0][0], sc[0][1]), fmaxf(sc[0][2], sc[0][3])),
                            fmaxf(fmaxf(sc[1][0], sc[1][1]), fmaxf(sc[1][2], sc[1][3])));
-    if (__builtin_amdgcn_ballot_w64(mx > m_run + slack) != 0) {   // wave-uniform, rare
+    bool move = mx > m_run + slack;
+    uint32_t sv = 0;                              // (SPLIT) the largest of this lane's scales (positive fp16: ordered as integers)
+    if constexpr (SPLIT) {
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sv = max(sv, r.vs[0][t][i]);
+      move = move || sv >= sv_top;
+    }
+    if (__builtin_amdgcn_ballot_w64(move) != 0) {   // wave-uniform, rare
       // Every head's reference becomes at least its own current maximum plus kSlack (for the heads that outgrew
       // theirs the next move is then 2*kSlack away; the others get their headroom back while the rescale is being
       // paid for anyway).  A reference is thus never more than kSlack above its head's running maximum: one that
       // followed every move of a neighbour instead would creep up and push the head's own weights p * s_v down
       // into fp16's subnormals on a sharp softmax.
       const float m_new = fmaxf(m_run, blocks_max(mx) + slack);
-      const float f = __builtin_amdgcn_exp2f((m_run - m_new) * kappa);
+      float df = (m_run - m_new) * kappa;
+      if constexpr (SPLIT) {
+        if (__builtin_amdgcn_ballot_w64(sv >= sv_top) != 0) {
+#pragma unroll
+          for (int o = 32; o >= 1; o >>= 1) sv = max(sv, (uint32_t)__shfl_xor((int)sv, o));
+          const int e = __builtin_amdgcn_readfirstlane((int)(sv >> 10));   // biased exponent: every scale so far < 2^(e - 14)
+          sv_top = (uint32_t)(e + 1) << 10;
+          const float off_new = (float)(24 - e);                           // p <= 4: weights below 2^12
+          df += off_new - off;
+          off = off_new;
+        }
+      }
+      const float f = __builtin_amdgcn_exp2f(df);
       m_run = m_new;
       l_run *= f;
       float fr[4];                                           // accumulator row 4kq+i belongs to head (4kq+i) % GP
@@ -872,7 +929,7 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
 #pragma unroll
             for (int i = 0; i < 4; ++i) oacc[cs][m][a][i] *= fr[i];
     }
-    const float mk = fmaxf(m_run * kappa, -3.0e38f);         // (finite also for a column that has seen no token yet)
+    const float mk = fmaxf(m_run * kappa, -3.0e38f) - off;   // (finite also for a column that has seen no token yet)
     float pr[2][4];
 #pragma unroll
     for (int t = 0; t < 2; ++t)
@@ -884,6 +941,15 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
     half8v zb;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {                 // k-slots 2i, 2i+1: tokens 4i + kq of tile 0 and of tile 1
+      if constexpr (SPLIT) {
+        const float w0 = sgn * pr[0][i] * (float)sz_half(r.vs[0][0][i], 0);
+        const float w1 = -(sgn * pr[1][i] * (float)sz_half(r.vs[0][1][i], 0));
+        const auto hi = __builtin_amdgcn_cvt_pkrtz(w0, w1);
+        const auto lo = __builtin_amdgcn_cvt_pkrtz(w0 - (float)hi[0], w1 - (float)hi[1]);
+        pa[0][2 * i] = hi[0]; pa[0][2 * i + 1] = hi[1];
+        pa[NPA - 1][2 * i] = lo[0]; pa[NPA - 1][2 * i + 1] = lo[1];
+        continue;
+      }
 #pragma unroll
       for (int a = 0; a < NA; ++a) {
         pa[a][2 * i] = (_Float16)__builtin_fmaf(pr[0][i], (float)sz_half(r.vs[a >> 1][0][i], a & 1), 0.0f);
@@ -903,9 +969,9 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
       }
     }
 #pragma unroll
-    for (int a = 0; a < NA; ++a) zacc[a] = mfma16(pa[a], zb, zacc[a]);
+    for (int a = 0; a < NPA; ++a) zacc[SPLIT ? 0 : a] = mfma16(pa[a], zb, zacc[SPLIT ? 0 : a]);
 #pragma unroll
-    for (int a = 0; a < NA; ++a) zacc[a] = mfma16(pa[a], pos15_odd, zacc[a]);
+    for (int a = 0; a < NPA; ++a) zacc[SPLIT ? 0 : a] = mfma16(pa[a], pos15_odd, zacc[SPLIT ? 0 : a]);
   };
 
   // -- V codes: each lane holds the same packed word (8 dims) of 8 tokens and needs, per dim, the 8 tokens in
@@ -921,7 +987,7 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   //    (mixed - even) / 16 carries the same -15 sum_t1 w that the zero-point sum cancels.
   //    WIDE: the 16 columns of a matrix instruction are the 4 words x 4 bytes of ONE group (column c = byte c / 4
   //    of word c % 4), so the lane holds that word of every group and picks its byte with a selector of its own.
-  auto pv = [&](const VRegs& r, const half8v (&pa)[NA]) {
+  auto pv = [&](const VRegs& r, const half8v (&pa)[NPA]) {
     if constexpr (C::WIDE) {
 #pragma unroll
       for (int g = 0; g < NG; ++g) {
@@ -953,6 +1019,10 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
           oacc[cs][2 * j][a] = mfma16(pa[a], v_even, oacc[cs][2 * j][a]);
           oacc[cs][2 * j + 1][a] = mfma16(pa[a], v_mixed, oacc[cs][2 * j + 1][a]);
         }
+        if constexpr (SPLIT) {
+          oacc[cs][2 * j][0] = mfma16(pa[NPA - 1], v_even, oacc[cs][2 * j][0]);
+          oacc[cs][2 * j + 1][0] = mfma16(pa[NPA - 1], v_mixed, oacc[cs][2 * j + 1][0]);
+        }
       }
     }
   };
@@ -972,6 +1042,9 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   int slot = 0;
   for (int i = 0; i < n_mine; ++i) {
     const int next = (slot + 1 == NS) ? 0 : slot + 1;
+    if constexpr (SPLIT) {
+      if (2 * i >= n_mine && sgn > 0.0f) negate_sums();
+    }
     load_v(slot, vr);
     // The slot's bytes all sit in registers from here on; its refill with supertile i + NS is issued after the
     // softmax all the same.  (Measured at 128K / at the d = 256 instance: issued here, +0.4 / +0.6 us; issued after
@@ -1004,7 +1077,7 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
       wait_loads<0>();
       load_k(next, kr);
     }
-    half8v pa[NA];
+    half8v pa[NPA];
     softmax(sc, vr, pa);
     refill();
     pv(vr, pa);
@@ -1020,7 +1093,7 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
     wait_loads<0>();
     load_k(0, kr);
     load_v(0, vr);
-    if constexpr (GS == 2) {
+    if constexpr (GS == 2 && D == 128) {
       // a token pair's dword may reach one token past the sequence's last: whatever lies there must not meet the
       // (zero) weights of the masked tokens as an Inf or NaN (the scores of such tokens are replaced, not scaled)
 #pragma unroll
@@ -1035,11 +1108,14 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
     }
     float sc[2][4];
     scores(kr, sidx, std::true_type{}, sc);
-    half8v pa[NA];
+    half8v pa[NPA];
     softmax(sc, vr, pa);
     pv(vr, pa);
   }
 
+  if constexpr (SPLIT) {
+    if (sgn < 0.0f) negate_sums();
+  }
   // ---- wave result -> LDS.  Of a lane's NA accumulators per row only the one whose group the lane's packed
   //      word belongs to is meaningful (and, the zero-point operand being laid out to match, the same one of its
   //      NA zero-point sums): it is selected, brought to common units (the 2^24 / 2^20 of the two nibble
@@ -1052,7 +1128,7 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   const float l_tot = blocks_sum(l_run);
   if (kq == 0 && rep == 0) {
     // (a row whose tokens were all masked still has the initial reference: it counts as empty)
-    lds_m[hl * NW + wave] = (active && m_run > kNegBig) ? m_run * kappa : kNegBig;
+    lds_m[hl * NW + wave] = (active && m_run > kNegBig) ? m_run * kappa - off : kNegBig;
     lds_l[hl * NW + wave] = active ? l_tot : 0.0f;
   }
   if constexpr (C::WIDE) {
@@ -1255,10 +1331,10 @@ int kv_share_of(int head_dim, int gqa) {
 
 template <int D, int GP, bool NT, bool PLAIN, int GS = 0>
 hipError_t launch_as(const DecodeParams& p, dim3 grid, hipStream_t s) {
-  static_assert((64 + (2 * GP * kMaxSplits + GP) ) * 4 <= Cfg<D, GP, 8>::SMEM, "the chunk merge reuses the block's LDS");
+  static_assert((64 + (2 * GP * kMaxSplits + GP) ) * 4 <= Cfg<D, GP, 8, GS>::SMEM, "the chunk merge reuses the block's LDS");
   // one block of 8 waves per compute unit: 8 rings of 2 x 5 KB (d=128) or 2 x 10 KB (d=256, all 160 KB of LDS)
   constexpr int NW = 8;
-  constexpr int smem = Cfg<D, GP, NW>::SMEM;
+  constexpr int smem = Cfg<D, GP, NW, GS>::SMEM;
   static_assert(smem <= 160 * 1024, "LDS budget of one compute unit");
   // dynamic LDS above 64 KB has to be opted into, once per device and kernel instance (any thread may get here first)
   static std::once_flag configured[kMaxDevices];
@@ -1278,15 +1354,20 @@ hipError_t launch_as(const DecodeParams& p, dim3 grid, hipStream_t s) {
 // the stream is read once (non-temporal loads) unless several blocks share a KV head
 template <int D, int GP>
 hipError_t launch(const DecodeParams& p, dim3 grid, hipStream_t s) {
-  if constexpr (D == 128 && GP >= 8) {            // groups of 64 / 128 elements
-    if (p.group == 2 * kGroup)
-      return p.kv_share == 1 ? launch_as<D, GP, true, false, 1>(p, grid, s) : launch_as<D, GP, false, false, 1>(p, grid, s);
-    if (p.group == 4 * kGroup)
-      return p.kv_share == 1 ? launch_as<D, GP, true, false, 2>(p, grid, s) : launch_as<D, GP, false, false, 2>(p, grid, s);
-  }
-  if (p.group != kGroup) return hipErrorNotSupported;
   const bool plain = p.kv_share == 1 && p.n_queries == 1 && p.waves_per_row == 8 && p.var_chunks == 0 &&
                      p.seq_lens == nullptr && p.block_table == nullptr;
+  if constexpr (D == 256 || GP >= 8) {            // groups of 64 / 128 elements
+    constexpr bool P256 = D == 256;               // (the plain instance of larger groups: d = 256 only)
+    if (p.group == 2 * kGroup) {
+      if (P256 && plain) return launch_as<D, GP, true, P256, 1>(p, grid, s);
+      return p.kv_share == 1 ? launch_as<D, GP, true, false, 1>(p, grid, s) : launch_as<D, GP, false, false, 1>(p, grid, s);
+    }
+    if (p.group == 4 * kGroup) {
+      if (P256 && plain) return launch_as<D, GP, true, P256, 2>(p, grid, s);
+      return p.kv_share == 1 ? launch_as<D, GP, true, false, 2>(p, grid, s) : launch_as<D, GP, false, false, 2>(p, grid, s);
+    }
+  }
+  if (p.group != kGroup) return hipErrorNotSupported;
   if (plain) return launch_as<D, GP, true, true>(p, grid, s);
   return p.kv_share == 1 ? launch_as<D, GP, true, false>(p, grid, s) : launch_as<D, GP, false, false>(p, grid, s);
 }
@@ -1297,10 +1378,11 @@ int mfma_kv_share(int head_dim, int gqa) { return kv_share_of(head_dim, gqa); }
 
 bool mfma_supported(int head_dim, int gqa) { return kv_share_of(head_dim, gqa) > 0; }
 
-// Groups of 64 or 128 elements: head_dim 128 only; at 128 two tokens share a dword of every metadata array, which
-// has to be aligned and must not straddle two (sequence, KV head) rows: an even number of tokens per row.
+// Groups of 64 or 128 elements: at head_dim 256 always (a token's values fill whole dwords); at head_dim 128 two
+// tokens share a dword of every metadata array where groups are 128 elements, and that dword has to be aligned and
+// must not straddle two (sequence, KV head) rows: an even number of tokens per row.
 bool mfma_supports_group(int head_dim, int group, int capacity) {
-  if (group == kGroup) return true;
+  if (group == kGroup || head_dim == 256) return true;
   return head_dim == 128 && (group == 2 * kGroup || (group == 4 * kGroup && capacity % 2 == 0));
 }
 
@@ -1343,7 +1425,7 @@ hipError_t launch_partial_mfma(const DecodeParams& p_in, int batch, int head_dim
                     : per_block > 1  ? dim3(1, (batch * rows_y + per_block - 1) / per_block, 1)
                                      : dim3(p.n_splits, rows_y, batch);
   int gp = padded_gqa(head_dim, p.gqa);
-  if (p.group != kGroup && gp == 4) gp = 8;       // (larger groups: the 8- and 16-row layouts only)
+  if (p.group != kGroup && gp == 4) gp = 8;       // (larger groups at d = 128: the 8- and 16-row layouts only)
   if (head_dim == 128 && gp == 16) return launch<128, 16>(p, grid, s);
   if (head_dim == 128 && gp == 8) return launch<128, 8>(p, grid, s);
   if (head_dim == 128 && gp == 4) return launch<128, 4>(p, grid, s);

@@ -264,6 +264,49 @@ def test_larger_groups_on_the_matrix_cores(shape, group):
 
 
 @pytest.mark.parametrize("group", [64, 128])
+@pytest.mark.parametrize("n_q,n_kv", [(2, 2), (4, 2), (3, 1), (8, 1)])
+def test_larger_groups_at_256_keep_fp32_weights(n_q, n_kv, group):
+    """Groups of 64 / 128 at d = 256 on the matrix cores: one to four blocks per KV head, an odd capacity, lengths
+    around the 32-token supertile, windows that start at odd tokens, lengths of their own, a paged pool.  The weights
+    p s_v enter as two fp16 operands and count as in fp32 whatever the size of V's scales (spreads of 1 and 1e-4,
+    flat and sharp softmaxes).  Per element: half an fp16 ulp of the output (2^-25 in the subnormal range), plus the
+    fp32 arithmetic: scores are sums of terms q c s, |terms| up to 400 together at these sizes, truncated at 2^-23 of
+    that, 2^-14.3 relative on a weight, on both sides of a mean of values: 2^-13 of the largest |v|."""
+    d = 256
+    for S, v_std, qk_std in ((1, 1.0, 0.1), (31, 1e-4, 1.0), (33, 1.0, 1.0), (65, 1e-4, 0.1), (700, 1.0, 0.1),
+                             (2049, 1e-4, 1.0), (4133, 1.0, 0.1)):
+        w = wl.custom(batch=2, n_q_heads=n_q, n_kv_heads=n_kv, head_dim=d, seq_len=S, seed=256 + group + S,
+                      attn_scale=1.0, qk_std=qk_std, v_std=v_std)
+        q, k, v = make(w)
+        cache = gpu_cache_from(k, v, capacity=S + (S & 1) + 1, group=group)
+        ocache = oracle_cache_from(k, v, group=group)
+
+        def check(out, ref, what):
+            torch.cuda.synchronize()
+            got = np16(out).astype(np.float64)
+            over = np.abs(got - ref) - (np.maximum(2.0 ** -11 * np.abs(ref), 2.0 ** -25) + 2.0 ** -13 * float(v.abs().max()))
+            assert np.isfinite(got).all() and over.max() <= 0, f"{what} g={group} S={S}: over by {over.max():.2e}"
+
+        for n_splits in (0, 3):
+            check(tq.tq_sdpa_int4_decode(cache, q.cuda(), S, 1.0, n_splits=n_splits), oracle_attend(q, ocache, S, 1.0), "decode")
+        lens = [S, max(1, S // 2)]
+        lens_dev = torch.tensor(lens, dtype=torch.int32).cuda()
+        check(tq.tq_sdpa_int4_decode_varlen(cache, q.cuda(), lens_dev, S, 1.0), _oracle_varlen(q, ocache, lens, 1.0), "lengths")
+        win = max(1, S - S // 3 - 1)
+        check(tq.tq_sdpa_int4_decode(cache, q.cuda(), S, 1.0, window=win), _oracle_window(q, ocache, [S] * 2, win, 1.0), "window")
+        pages = -(-S // 64)
+        pool = tq.KVCache(2 * pages, n_kv, d, 64, group_size=group)
+        for t in pool.tensors():
+            t.view(torch.uint8).fill_(0xEE)
+        table = torch.randperm(2 * pages, generator=torch.Generator().manual_seed(S)).to(torch.int32).reshape(2, pages).cuda()
+        tq.tq_quantize_kv_paged(pool, table, k.cuda(), v.cuda(), torch.zeros(2, dtype=torch.int32).cuda())
+        check(tq.tq_sdpa_int4_decode_paged(pool, table, q.cuda(), lens_dev, S, 1.0), _oracle_varlen(q, ocache, lens, 1.0), "paged")
+    with pytest.raises(tq.TqError) as e:            # several query tokens stay refused with these groups
+        tq.tq_sdpa_int4_decode(cache, torch.zeros(2, 2, n_q, d, dtype=torch.float16, device="cuda"), S, 1.0)
+    assert e.value.status == -6
+
+
+@pytest.mark.parametrize("group", [64, 128])
 def test_larger_groups_full_size(group):
     """The headline shape (64 / 8 heads, d = 128, 131072 tokens) quantised in groups of 64 / 128: cache bit-exact,
     every output element against the oracle."""

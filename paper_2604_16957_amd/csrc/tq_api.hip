@@ -181,7 +181,9 @@ Route route_of(const tq_kv_cache* cache, int n_q_heads, int seq_len, float attn_
   // (a 16-row tile leaves the last block twice the partials to fetch: there the merge kernel is the faster end,
   //  measured 21.8 against 24.1 us with 16 heads per KV head at 32K tokens)
   const bool small_tile = rows_per_batch == 0 || rows * cache->n_kv_heads / rows_per_batch <= 8;
+  // (larger groups at head_dim 256 keep the two launches tq_decode_launches has always answered for them)
   const bool merge = use_mfma && (single || (bytes <= kMergeInKernelMaxBytes && small_tile &&
+                                             !(larger && cache->head_dim == 256) &&
                                              tq::mfma_can_merge(cache->batch, rows_per_batch)));
   return {true, use_mfma, merge, single && merge, false};
 }

@@ -216,8 +216,8 @@ struct PartialRequest {
   void* out = nullptr;                 // non-null: the kernel may merge the chunks itself and write it
   void* workspace = nullptr;
   const tq_decode_opts* opts = nullptr;
-  const void* k_new = nullptr;         // append-and-attend: the step's new token (then seq_len includes it),
-  const void* v_new = nullptr;         // taken in by the merge kernel, which then has to run
+  const void* k_new = nullptr;         // append-and-attend: the step's new token (then seq_len includes it), taken in
+  const void* v_new = nullptr;         // by the matrix-core kernel, or by the merge kernel behind the others
   const tq::PagedView* paged = nullptr;
   void* stream = nullptr;
   // results
@@ -240,15 +240,15 @@ int run_partial(PartialRequest& rq) {
   // (paged cache: counted from the supertile boundary before the window, see var_start)
   if (rq.paged && attended < seq_len) attended = std::min(seq_len, attended + tq::kTile - 1);
   // append-and-attend: the new token (the last attended one) does not come from the cache
-  const bool append_in_merge = rq.k_new != nullptr;
+  const bool append = rq.k_new != nullptr;
   const int first = seq_len - attended;           // first attended token
-  if (append_in_merge) --attended;
+  if (append) --attended;
   const int row_tiles = r.wide ? tq::wide_row_tiles(rows_of(cache, n_q_heads, opts),
                                                     (int64_t)cache->batch * cache->n_kv_heads, std::max(1, attended))
                                : 1;
   const int mfma_share = use_mfma ? mfma_share_of(cache, n_q_heads, opts) : 1;
   const int rows_per_batch = cache->n_kv_heads * (use_mfma ? mfma_share : row_tiles);
-  const bool one_chunk_rows = seq_lens && rq.out != nullptr && !append_in_merge &&
+  const bool one_chunk_rows = seq_lens && rq.out != nullptr &&
                               rows_as_chunks(cache, n_q_heads, seq_len, rq.attn_scale, opts, rq.paged != nullptr);
   const Plan plan = plan_splits(cache->batch, rows_per_batch, attended, one_chunk_rows ? 1 : opts ? opts->n_splits : 0,
                                 target, use_mfma ? 8 : r.wide ? 2 : 1);
@@ -259,7 +259,7 @@ int run_partial(PartialRequest& rq) {
   if (seq_lens) {
     // the kernels window every sequence's own length (append-and-attend: the lengths count the new token, the
     // chunks and the window over them do not)
-    p.len_bias = append_in_merge ? -1 : 0;
+    p.len_bias = append ? -1 : 0;
     p.window = (opts && opts->window > 0) ? opts->window + queries_of(opts) - 1 + p.len_bias : 0;
   } else {
     p.seq_len = attended;
@@ -285,14 +285,15 @@ int run_partial(PartialRequest& rq) {
     if (use_mfma) p.waves_per_row = rounds > 4 ? 1 : rounds > 2 ? 2 : rounds > 1 ? 4 : 8;
   }
   rq.params = p;
-  if (append_in_merge) {
-    rq.params.k_new = static_cast<const half_t*>(rq.k_new);
-    rq.params.v_new = static_cast<const half_t*>(rq.v_new);
-    rq.params.append_pos = seq_len - 1;
+  if (append) {                                   // one of the two kernels takes the token in
+    DecodeParams& taker = use_mfma ? p : rq.params;
+    taker.k_new = static_cast<const half_t*>(rq.k_new);
+    taker.v_new = static_cast<const half_t*>(rq.v_new);
+    taker.append_pos = seq_len - 1;
   }
   rq.n_splits = plan.n_splits;
   hipStream_t s = static_cast<hipStream_t>(rq.stream);
-  rq.merged = one_chunk_rows || (rq.out != nullptr && r.merge && !seq_lens && !append_in_merge);
+  rq.merged = one_chunk_rows || (rq.out != nullptr && r.merge && !seq_lens);
   int merge_slot = -1;
   if (rq.merged) {
     // several chunks: the arrival counters of this workspace (none left: the merge kernel does it); rows that are
@@ -531,10 +532,10 @@ int tq_sdpa_int4_append_decode(const tq_kv_cache* cache, const void* k_new, cons
   rq.workspace = workspace;
   rq.opts = opts;
   rq.stream = stream;
-  // The merge kernel takes the token in (one query token, at least one cached token to attend: no append launch,
-  // nothing read back); else the append kernel runs first.  Where every sequence is a single chunk there is no
-  // merge kernel to begin with (the decode kernel writes the output itself): the append kernel, then that.
-  if (queries_of(opts) == 1 && windowed(seq_len, opts) >= 2 && !r.single && cache->group_size == tq::kGroup) {
+  // The matrix-core kernel takes the token in, or the merge kernel behind the others (there with groups of 32 only);
+  // one query token, at least one cached token to attend: no append launch, nothing read back.  Else the append
+  // kernel runs first.
+  if (queries_of(opts) == 1 && windowed(seq_len, opts) >= 2 && (r.use_mfma || cache->group_size == tq::kGroup)) {
     rq.k_new = k_new;
     rq.v_new = v_new;
   } else {                                        // the append kernel first, then the plain decode
@@ -584,14 +585,14 @@ int tq_sdpa_int4_decode_paged(const tq_kv_cache* pool, const int32_t* block_tabl
 }
 
 namespace {
-// One decode step with per-sequence lengths that count the step's new token: the merge kernel takes the token
-// in where it can (one query token; a window, if any, of at least two tokens), else the append kernel runs first.
+// One decode step with per-sequence lengths that count the step's new token: the matrix-core kernel (or the merge
+// kernel behind the others) takes the token in where it can (one query token; a window, if any, of at least two
+// tokens), else the append kernel runs first.
 int append_decode_with_lengths(PartialRequest& rq, const void* k_new, const void* v_new) {
   const tq_decode_opts* opts = rq.opts;
-  // (where every row is a single chunk there is no merge kernel to take the token in: the append kernel, then the decode)
-  const bool one_chunk_rows = rows_as_chunks(rq.cache, rq.n_q_heads, rq.seq_len, rq.attn_scale, opts, rq.paged != nullptr);
-  if (queries_of(opts) == 1 && !(opts && opts->window == 1) && rq.seq_len >= 2 && !one_chunk_rows &&
-      rq.cache->group_size == tq::kGroup) {
+  const bool taken_in = route_of(rq.cache, rq.n_q_heads, rq.seq_len, rq.attn_scale, opts).use_mfma ||
+                        rq.cache->group_size == tq::kGroup;
+  if (queries_of(opts) == 1 && !(opts && opts->window == 1) && rq.seq_len >= 2 && taken_in) {
     rq.k_new = k_new;
     rq.v_new = v_new;
   } else {

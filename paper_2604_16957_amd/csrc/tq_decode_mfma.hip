@@ -141,17 +141,19 @@ struct Cfg {
   static constexpr int PER = (D == 128 && GP == 8) ? 32 : 16;
   static constexpr int LPS = 2 * (KT / 1024) + VB / 1024 + 4 * (SZ / 256);   // load instructions per stage
   static constexpr int RING = NW * NS * STAGE;
-  static constexpr int MERGE = (NW * GP * D + 2 * NW * GP) * 4;  // o, m, l
+  static constexpr int NEWTOK = D + GP;          // floats of a unit's new token: its dequantised V, its scores
+  static constexpr int MERGE = (NW * GP * D + 2 * NW * GP + NW * NEWTOK) * 4;  // o, m, l, and the units' new tokens
   // the block-merge area sits behind the rings where both fit into the 160 KB of a compute unit, else on top of them
   static constexpr bool ALIAS = RING + MERGE > 160 * 1024;
   static constexpr int OFF_MERGE = ALIAS ? 0 : RING;
   // Where the query block of a wave lands before it is turned into operands: in an area of its own if
   // there is room, so that the whole ring can be filled at once; else in the last ring slot.
-  static constexpr int QBLK = GP * D * 2;
-  static_assert(QBLK <= STAGE, "the query block borrows one ring slot");
-  static constexpr bool QSEP = !ALIAS && RING + MERGE + NW * QBLK <= 160 * 1024;
+  // (1 KB behind it: the new token's K and V rows of a step, see `takes`)
+  static constexpr int QBLK = GP * D * 2, QAREA = QBLK + 1024;
+  static_assert(QAREA <= STAGE, "the query block borrows one ring slot");
+  static constexpr bool QSEP = !ALIAS && RING + MERGE + NW * QAREA <= 160 * 1024;
   static constexpr int OFF_QBLK = RING + MERGE;
-  static constexpr int SMEM = ALIAS ? (RING > MERGE ? RING : MERGE) : RING + MERGE + (QSEP ? NW * QBLK : 0);
+  static constexpr int SMEM = ALIAS ? (RING > MERGE ? RING : MERGE) : RING + MERGE + (QSEP ? NW * QAREA : 0);
   // The fp16 scale and zero-point arrays are fetched dword by dword (two groups of one token), and the
   // direct loads may gather: with NA == 2 a lane needs exactly one dword per token, so the dwords are
   // laid out in LDS as [kq][replica][tile][i] and a lane reads its eight tokens with two 16-byte reads; with
@@ -312,8 +314,13 @@ __device__ __forceinline__ void wait_loads() {               // until at most N 
 // The matrix cores have the room (52 instructions per supertile instead of 34, a quarter of its time), and the kernel
 // is bound by the stream like its groups-of-32 instance: 32 heads on 16 KV heads, one sequence of 32K tokens, groups of
 // 64 (151 MB), the whole step 305.5 us on the generic kernel, 35.6 us here.
-template <int D, int GP, int NW, bool NT, bool PLAIN, int GS = 0>
+//
+// PAGED = a pool of pages (with PLAIN: never).  An instance of its own keeps the page look-ups out of the others'
+// scalar registers, of which the general instance has none to spare.
+enum Mode { kPlain, kGeneral, kPaged };
+template <int D, int GP, int NW, bool NT, Mode MODE, int GS = 0>
 __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_kernel(DecodeParams p) {
+  constexpr bool PLAIN = MODE == kPlain, paged = MODE == kPaged;
   using C = Cfg<D, GP, NW, GS>;
   static_assert(GS == 0 || D == 256 || ((C::PERM || C::WIDE) && !PLAIN), "larger groups at d = 128: the gathered layouts");
   constexpr bool SPLIT = GS > 0 && D == 256;
@@ -327,7 +334,7 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
     // first stream loads leave instead of two (the compiler otherwise fetches q and start behind a branch)
     asm volatile("" :: "s"(p.q), "s"(p.start), "s"(p.k_codes), "s"(p.v_codes), "s"(p.k_scale), "s"(p.k_zero),
                  "s"(p.v_scale), "s"(p.v_zero), "s"(p.seq_len), "s"(p.tokens_per_split), "s"(p.row_stride),
-                 "s"(p.n_kv_heads), "s"(p.n_q_heads), "s"(p.gqa));
+                 "s"(p.n_kv_heads), "s"(p.n_q_heads), "s"(p.gqa), "s"(p.k_new));
   }
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -342,6 +349,7 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   // and only keeps the barriers company.
   const int W = PLAIN ? NW : p.waves_per_row;     // NW: the whole block on one unit
   const bool whole = W == NW;
+  const int sub = wave % W;                       // (several rows per block: the W waves of a row take its supertiles in turn)
   bool row_valid = true;
   if (!PLAIN && !whole && p.var_chunks == 0) {
     const int rows_y = p.n_kv_heads * p.kv_share, total = p.batch * rows_y;
@@ -439,11 +447,14 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   // tokens this sequence attends: the common length, or its own (a chunk past its end is empty); with a
   // sliding window the row simply starts `start` tokens later
   const bool var_lens = !PLAIN && p.seq_lens != nullptr;
-  const int seq = !row_valid ? 0 : var_lens ? var_len(p, b) : p.seq_len;
+  // a decode step (p.k_new set): the step's new token is not among the tokens the chunks cover; the block of the
+  // sequence's first chunk takes it in (see `takes`).  A sequence may hold nothing but its new token.
+  const bool new_here = p.k_new != nullptr && split == 0 && row_valid;
+  const int new_pos = var_lens ? max(1, min(p.seq_lens[b], p.seq_len)) - 1 : p.append_pos;
+  const int seq = !row_valid || (var_lens && p.k_new != nullptr && new_pos == 0) ? 0 : var_lens ? var_len(p, b) : p.seq_len;
   const int start = var_lens ? var_start(p, b) : p.start;
   // first row of the six arrays this block reads from: the sequence's own row (contiguous cache), or the
   // pool's row 0 (paged cache: the page's rows are added supertile by supertile)
-  const bool paged = !PLAIN && p.block_table != nullptr;
   // paged cache: token indices below count from `start` as well, but the rows are found page by page; the
   // window's first token may lie up to 31 tokens after `start` (see var_start)
   const int lead = (paged && var_lens) ? var_first(p, b) - start : 0;
@@ -453,7 +464,7 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   // A chunk past the end of its sequence has nothing to emit: the merge kernel works out from the same
   // lengths which chunks exist.  (With the in-kernel merge the block still has to be counted in, so it
   // goes through and publishes an empty partial.)
-  if (!PLAIN && whole && begin0 >= seq && p.merge_slot < 0) return;
+  if (!PLAIN && whole && begin0 >= seq && p.merge_slot < 0 && !new_here) return;
   const int end = max(begin0, min(seq, begin0 + tokens_per_split));
   // Several query tokens under a sliding window: the rows start at different tokens (row t one token after
   // row t - 1); the supertile that holds those starts takes the masked path too (wave 0, after its other work)
@@ -488,7 +499,19 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   const Bases row_bases = {kc_row, vc_row, {sz_row[0], sz_row[1], sz_row[2], sz_row[3]}};
   const int32_t* const tbl = paged ? p.block_table + (int64_t)b * p.max_blocks : nullptr;
   const int page_mask = (1 << p.page_shift) - 1;
-  auto page_of = [&](int tok0) { return tbl[min(tok0 >> p.page_shift, p.max_blocks - 1)]; };
+  // The page numbers of the chunk's first 64 pages sit in a register, one per lane, fetched before anything else (a
+  // table entry looked up in the loop would stall a supertile); entries past those are fetched by a scalar load
+  // that is waited for on the spot.
+  const int page0 = paged ? (pstart + begin0) >> p.page_shift : 0;
+  const int page_v = paged ? tbl[min(page0 + lane, p.max_blocks - 1)] : 0;
+  auto page_of = [&](int tok0) {
+    const int e = min(tok0 >> p.page_shift, p.max_blocks - 1);
+    if ((uint32_t)(e - page0) < 64u) return __builtin_amdgcn_readlane(page_v, e - page0);
+    int page;
+    const uint32_t byte = (uint32_t)e * 4;
+    asm volatile("s_load_dword %0, %1, %2\n\ts_waitcnt lgkmcnt(0)" : "=&s"(page) : "s"(tbl), "s"(byte) : "memory");
+    return page;
+  };
   auto bases_of_page = [&](int page) -> Bases {   // row 0 of `page` for this KV head (a page is 2^page_shift rows)
     const int64_t r = (int64_t)(page * p.n_kv_heads + kv) << p.page_shift;
     const int64_t rc = r * TB, rs = r * SZB;
@@ -585,7 +608,6 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   static_assert(NW == 8, "the work split assumes two waves per SIMD");
   const int simd = wave & 3, young = wave >> 2;
   constexpr int PERIOD = C::PER, OLD = PERIOD / 2 + 1, YNG = PERIOD / 2 - 1;   // of every PER supertiles of a SIMD: older wave, younger wave
-  const int sub = wave % W;                       // (several rows per block: the W waves of a row take its supertiles in turn)
   auto sidx_of = [&](int i) {                     // i-th supertile of this wave -> supertile of the chunk
     if (!whole) return W * i + sub;
     const int blk = young ? i / YNG : i / OLD, j = i - blk * (young ? YNG : OLD);
@@ -609,12 +631,19 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   // the 128K launch; at d = 256 the later point costs 0.3 us).
   constexpr int NPRE = NS - 1;
   const bool kSecondAfterFirstLanded = D == 128 && whole;   // (rows packed several to a block: 256 x 512 tokens 39.2 -> 40.0 us with it)
+  // A decode step's new token (one query token; its K and V rows in p.k_new / p.v_new): one wave of the block that
+  // holds its sequence's first chunk quantises it while the first stage of the stream is on its way, stores it, works
+  // out its scores against the block's query rows, and brings it to the block merge as one more wave would: m = the
+  // score, l = 1, o = the dequantised V.  The step needs no launch of its own for the append, and the merge kernel,
+  // where there is one, has nothing to do with it.  Lane l < 2 D / 8: eight elements of K (l < D / 8) or of V.
+  const bool takes = new_here && (whole ? wave == NW - 1 : sub == 0);
+  const int new_piece = lane % (D / 8), new_v = (lane / (D / 8)) & 1;
   // (a borrowed slot: behind its K tiles where the block fits there, else from the slot's start)
-  constexpr int Q_IN_SLOT = C::QBLK <= C::STAGE - C::OFF_V ? C::OFF_V : 0;
-  char* const q_area = C::QSEP ? smem + C::OFF_QBLK + wave * C::QBLK : ring + (NS - 1) * C::STAGE + Q_IN_SLOT;
+  constexpr int Q_IN_SLOT = C::QAREA <= C::STAGE - C::OFF_V ? C::OFF_V : 0;
+  char* const q_area = C::QSEP ? smem + C::OFF_QBLK + wave * C::QAREA : ring + (NS - 1) * C::STAGE + Q_IN_SLOT;
   {
     const uint32_t l = C::QSEP ? (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem + C::OFF_QBLK +
-                                     wave * C::QBLK
+                                     wave * C::QAREA
                                : ring_lds + (NS - 1) * C::STAGE + Q_IN_SLOT;
 #pragma unroll
     for (int u = 0; u < GP * D * 2 / 1024; ++u) {
@@ -622,6 +651,8 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
       const int h = min(chunk / (D / 8), G - 1);
       dma16_lane(p.q + query_row(h) * D + (chunk % (D / 8)) * 8, l + u * 1024);
     }
+    if (takes)                                    // the new token: lanes 0 .. D/8-1 its K row, the next D/8 its V row
+      dma16_lane((new_v ? p.v_new : p.k_new) + (int64_t)(b * p.n_kv_heads + kv) * D + new_piece * 8, l + C::QBLK);
   }
   // A wave has up to NS stages out before its loop and issues one per supertile while it has supertiles left.
   // (Stand-in loads that kept the count of outstanding loads the same to the end were taken out: the one issued in
@@ -678,6 +709,60 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
       for (int e = 0; e < 8; ++e) s += (float)qgrp[a][i][e];
     qsum[a] = (hl < G) ? s * 0x1p-24f : 0.0f;
   }
+  uint32_t new_w = 0;                             // the new token: this lane's packed word, its group's scale and
+  half2v new_sz = {0, 0};                         // zero-point, and (lane h of the first 16) its score against row h
+  float new_score = 0.0f;
+  if (takes) {
+    const half8v x16 = *reinterpret_cast<const half8v*>(q_area + C::QBLK + lane * 16);
+    float x[8], mn, mx;
+    half_t xh[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) { xh[e] = x16[e]; x[e] = (float)x16[e]; }
+    mn = mx = x[0];
+#pragma unroll
+    for (int e = 1; e < 8; ++e) { mn = fminf(mn, x[e]); mx = fmaxf(mx, x[e]); }
+    for (int o = 1; o < p.group / 8; o <<= 1) {   // over the lanes of the group (exact in any order)
+      mn = fminf(mn, __shfl_xor(mn, o));
+      mx = fmaxf(mx, __shfl_xor(mx, o));
+    }
+    half_t s16, z16;
+    quantize_scale_zero(mn, mx, s16, z16);
+    const float sf = (float)s16, zf = (float)z16;
+    const QuantFast fast = quantize_fast_setup(sf, zf, fmaxf(fabsf(mn), fabsf(mx)));
+    float far = 0.0f;
+    new_w = quantize_word_fast(xh, fast, far);
+    if (quantize_fast_in_doubt(far, fast)) new_w = quantize_word(x, sf, zf);
+    new_sz = half2v{s16, z16};
+    if (part == 0 && lane < 2 * (D / 8)) {        // (several blocks per KV head: the first stores)
+      int64_t row = (int64_t)(b * p.n_kv_heads + kv) * p.row_stride + new_pos;
+      if (paged) {
+        const int page = p.block_table[(int64_t)b * p.max_blocks + (new_pos >> p.page_shift)];
+        row = ((int64_t)page * p.n_kv_heads + kv) * p.row_stride + (new_pos & page_mask);
+      }
+      uint8_t* codes = const_cast<uint8_t*>(new_v ? p.v_codes : p.k_codes) + row * TB;
+      reinterpret_cast<uint32_t*>(codes)[new_piece] = new_w;
+      const int64_t g = row * (D / p.group) + new_piece * 8 / p.group;
+      const int first = new_piece * 8 % p.group;  // (the group's first two lanes store its scale and zero-point)
+      if (first == 0) const_cast<half_t*>(new_v ? p.v_scale : p.k_scale)[g] = s16;
+      if (first == 8) const_cast<half_t*>(new_v ? p.v_zero : p.k_zero)[g] = z16;
+    }
+    float k_hat[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) k_hat[e] = new_v ? 0.0f : ((float)((new_w >> (4 * e)) & 0xFu) - zf) * sf;   // Eq. 3
+#pragma unroll
+    for (int h = 0; h < GP; ++h) {
+      const half8v qv = *reinterpret_cast<const half8v*>(q_area + h * D * 2 + new_piece * 16);
+      float dot = 0.0f;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) dot = __builtin_fmaf((float)qv[e], k_hat[e], dot);
+      dot = row_ror_add<8>(dot);
+      dot = row_ror_add<4>(dot);
+      dot = row_ror_add<2>(dot);
+      dot = row_ror_add<1>(dot);
+      if constexpr (D == 256) dot += __shfl_xor(dot, 16);
+      new_score = c == h ? dot : new_score;
+    }
+  }
   const float kappa = p.scale_log2 * 0x1p24f;     // raw accumulator units -> log2 units
   const float slack = kSlack / kappa;             // the rescale slack in raw units
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the query block has been read: its slot may be refilled
@@ -686,16 +771,6 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   // position j in the wave's pattern of 9 (or 7) out of 16
   int nx_j = young ? NS % YNG : NS % OLD;
   int nx_tok = tok_of(sidx_of(NS));
-  // The page of the next supertile is looked up one supertile ahead of its use, by a scalar load the
-  // compiler does not wait for: the wait is the lgkmcnt(0) that precedes every issue in the loop (the
-  // value is threaded through that statement so that nothing reads it earlier).
-  auto page_ahead = [&](int tok0) {
-    int page;
-    const uint32_t byte = (uint32_t)min(tok0 >> p.page_shift, p.max_blocks - 1) * 4;
-    asm volatile("s_load_dword %0, %1, %2" : "=&s"(page) : "s"(tbl), "s"(byte) : "memory");
-    return page;
-  };
-  int nx_page = paged ? __builtin_amdgcn_readfirstlane(page_of(nx_tok)) : 0;
 
   // ---- running state
   float m_run = kNegBig;                          // per-head reference for exp2 (raw units)
@@ -1052,15 +1127,14 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
     // requests queued earlier than needed only delay the ones a wave is waiting for.  Issued here AND waited for
     // stage by stage, so that two stages are in flight: the kernel alone unchanged, the decode call 1 us slower.)
     auto refill = [&] {
-      asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(nx_page) :: "memory");   // every LDS read of this slot has returned
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // every LDS read of this slot has returned
       if (i + NS < n_mine) {
-        issue_tok(ring_lds + slot * C::STAGE, nx_tok, nx_page, koff, lane16, szoff);
+        issue_tok(ring_lds + slot * C::STAGE, nx_tok, paged ? page_of(nx_tok) : 0, koff, lane16, szoff);
         // next supertile of the pattern: of every PERIOD the older wave holds k = 0, 2, .., PERIOD-2 and PERIOD-1,
         // the younger k = 1, 3, .., PERIOD-3
         const int step = young ? (nx_j < YNG - 1 ? 2 : 4) : (nx_j < PERIOD / 2 - 1 ? 2 : 1);
         nx_j = (nx_j == (young ? YNG - 1 : OLD - 1)) ? 0 : nx_j + 1;
         nx_tok += whole ? step * (4 * 32) : W * 32;
-        if (paged) nx_page = page_ahead(nx_tok);
       }
     };
     float sc[2][4];
@@ -1123,6 +1197,7 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   float* const lds_o = reinterpret_cast<float*>(smem + C::OFF_MERGE);  // [NW][GP][D]   sum_t p_t v^_t
   float* const lds_m = lds_o + NW * GP * D;                            // [GP][NW]
   float* const lds_l = lds_m + NW * GP;                                // [GP][NW]
+  float* const lds_new = lds_l + NW * GP + (whole ? 0 : wave / W) * C::NEWTOK;   // [D] V of this unit's new token, [GP] scores
   if constexpr (C::ALIAS) __syncthreads();                   // everybody is done reading the rings
   const bool active = n_mine > 0 || tail_mine[0] || tail_mine[1] || tail_mine[2] || tail_mine[3];
   const float l_tot = blocks_sum(l_run);
@@ -1130,6 +1205,14 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
     // (a row whose tokens were all masked still has the initial reference: it counts as empty)
     lds_m[hl * NW + wave] = (active && m_run > kNegBig) ? m_run * kappa - off : kNegBig;
     lds_l[hl * NW + wave] = active ? l_tot : 0.0f;
+  }
+  if (takes) {
+    if (new_v && lane < 2 * (D / 8)) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        lds_new[new_piece * 8 + e] = ((float)((new_w >> (4 * e)) & 0xFu) - (float)new_sz[1]) * (float)new_sz[0];
+    }
+    if (lane < GP) lds_new[D + lane] = new_score * p.scale_log2;
   }
   if constexpr (C::WIDE) {
     // row 4 kq + i = head; group g's zero-point sum of that head sits in column g (any column c with c % 4 == g)
@@ -1197,6 +1280,14 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
 #pragma unroll
       for (int w = 0; w < NW; ++w) mg = (w >= first && w < first + count) ? fmaxf(mg, mw[w]) : mg;
       float n0 = 0.0f, n1 = 0.0f, den = 0.0f;
+      if (new_here) {
+        const float sn = lds_new[D + h];
+        mg = fmaxf(mg, sn);
+        den = __builtin_amdgcn_exp2f(sn - mg);
+        const float2 vn = *reinterpret_cast<const float2*>(lds_new + j);
+        n0 = vn.x * den;
+        n1 = vn.y * den;
+      }
 #pragma unroll
       for (int w = 0; w < NW; ++w) {
         if (w < first || w >= first + count) continue;       // (wave-uniform)
@@ -1329,7 +1420,7 @@ int kv_share_of(int head_dim, int gqa) {
   return 0;
 }
 
-template <int D, int GP, bool NT, bool PLAIN, int GS = 0>
+template <int D, int GP, bool NT, Mode MODE, int GS = 0>
 hipError_t launch_as(const DecodeParams& p, dim3 grid, hipStream_t s) {
   static_assert((64 + (2 * GP * kMaxSplits + GP) ) * 4 <= Cfg<D, GP, 8, GS>::SMEM, "the chunk merge reuses the block's LDS");
   // one block of 8 waves per compute unit: 8 rings of 2 x 5 KB (d=128) or 2 x 10 KB (d=256, all 160 KB of LDS)
@@ -1344,32 +1435,34 @@ hipError_t launch_as(const DecodeParams& p, dim3 grid, hipStream_t s) {
   if (e != hipSuccess) return e;
   if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
   std::call_once(configured[dev], [&] {
-    outcome[dev] = hipFuncSetAttribute(reinterpret_cast<const void*>(&decode_partial_mfma_kernel<D, GP, NW, NT, PLAIN, GS>),
+    outcome[dev] = hipFuncSetAttribute(reinterpret_cast<const void*>(&decode_partial_mfma_kernel<D, GP, NW, NT, MODE, GS>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, smem);
   });
   if (outcome[dev] != hipSuccess) return outcome[dev];
-  hipLaunchKernelGGL((decode_partial_mfma_kernel<D, GP, NW, NT, PLAIN, GS>), grid, dim3(NW * 64), smem, s, p);
+  hipLaunchKernelGGL((decode_partial_mfma_kernel<D, GP, NW, NT, MODE, GS>), grid, dim3(NW * 64), smem, s, p);
   return hipGetLastError();
 }
 // the stream is read once (non-temporal loads) unless several blocks share a KV head
+template <int D, int GP, Mode MODE, int GS>
+hipError_t launch_nt(const DecodeParams& p, dim3 grid, hipStream_t s) {
+  return p.kv_share == 1 ? launch_as<D, GP, true, MODE, GS>(p, grid, s) : launch_as<D, GP, false, MODE, GS>(p, grid, s);
+}
+template <int D, int GP, int GS>
+hipError_t launch_mode(const DecodeParams& p, dim3 grid, hipStream_t s) {
+  if (p.block_table != nullptr) return launch_nt<D, GP, kPaged, GS>(p, grid, s);
+  const bool plain = p.kv_share == 1 && p.n_queries == 1 && p.waves_per_row == 8 && p.var_chunks == 0 && p.seq_lens == nullptr;
+  if constexpr (GS == 0 || D == 256) {            // (no plain instances of the larger groups at d = 128)
+    if (plain) return launch_as<D, GP, true, kPlain, GS>(p, grid, s);
+  }
+  return launch_nt<D, GP, kGeneral, GS>(p, grid, s);
+}
 template <int D, int GP>
 hipError_t launch(const DecodeParams& p, dim3 grid, hipStream_t s) {
-  const bool plain = p.kv_share == 1 && p.n_queries == 1 && p.waves_per_row == 8 && p.var_chunks == 0 &&
-                     p.seq_lens == nullptr && p.block_table == nullptr;
   if constexpr (D == 256 || GP >= 8) {            // groups of 64 / 128 elements
-    constexpr bool P256 = D == 256;               // (the plain instance of larger groups: d = 256 only)
-    if (p.group == 2 * kGroup) {
-      if (P256 && plain) return launch_as<D, GP, true, P256, 1>(p, grid, s);
-      return p.kv_share == 1 ? launch_as<D, GP, true, false, 1>(p, grid, s) : launch_as<D, GP, false, false, 1>(p, grid, s);
-    }
-    if (p.group == 4 * kGroup) {
-      if (P256 && plain) return launch_as<D, GP, true, P256, 2>(p, grid, s);
-      return p.kv_share == 1 ? launch_as<D, GP, true, false, 2>(p, grid, s) : launch_as<D, GP, false, false, 2>(p, grid, s);
-    }
+    if (p.group == 2 * kGroup) return launch_mode<D, GP, 1>(p, grid, s);
+    if (p.group == 4 * kGroup) return launch_mode<D, GP, 2>(p, grid, s);
   }
-  if (p.group != kGroup) return hipErrorNotSupported;
-  if (plain) return launch_as<D, GP, true, true>(p, grid, s);
-  return p.kv_share == 1 ? launch_as<D, GP, true, false>(p, grid, s) : launch_as<D, GP, false, false>(p, grid, s);
+  return p.group == kGroup ? launch_mode<D, GP, 0>(p, grid, s) : hipErrorNotSupported;
 }
 
 }  // namespace

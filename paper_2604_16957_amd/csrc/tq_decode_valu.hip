@@ -295,7 +295,7 @@ __global__ __launch_bounds__(THREADS) void reduce_kernel(DecodeParams p) {
     // sequence with no cached token has no chunk (the one the decode kernel made up is ignored)
     const int total = max(1, min(p.seq_lens[sequence], p.seq_len));
     append_pos = total - 1;
-    if (total + p.len_bias < 1) n = 0;
+    if (p.k_new != nullptr && total + p.len_bias < 1) n = 0;
   }
   // The first chunks of this thread's output element, and the chunks' (m, l), are asked for before anything
   // else: they do not depend on the weights, so the kernel is about one memory round trip long (two with
@@ -455,7 +455,7 @@ __global__ __launch_bounds__(2 * D, HPT == 4 ? 5 : 4) void reduce_group_kernel(D
     // cached token has no chunk)
     const int total = max(1, min(p.seq_lens[sequence], p.seq_len));
     append_pos = total - 1;
-    if (total + p.len_bias < 1) n = 0;
+    if (p.k_new != nullptr && total + p.len_bias < 1) n = 0;
   }
   const bool appending = p.k_new != nullptr;
   __shared__ float hat[2][D];

@@ -159,10 +159,11 @@ int tq_sdpa_int4_decode_static(const tq_kv_cache* cache, const void* q, int32_t 
  * v_new: fp16 [batch][n_kv_heads][1][head_dim]) is quantised, written at position seq_len - 1 and
  * attended together with the seq_len - 1 cached ones (with opts->n_queries = n > 1: n new tokens,
  * written at seq_len - n .. seq_len - 1, each attended by its own query).  Same stored bits and same
- * result as the two calls.  With one query token the append costs no launch of its own: the decode
- * kernel attends the cached tokens, and the merge kernel quantises the new one, stores it and adds
- * its attention term from registers.  Otherwise (several query tokens, a window or sequence of one
- * token) the append kernel is launched first.
+ * result as the two calls.  With one query token the append costs no launch of its own: the matrix-core
+ * decode kernel quantises the new token next to the stream of the cached ones, stores it and adds its
+ * attention term from registers (so that a short sequence's whole step is one launch); behind the other
+ * kernels the merge kernel does that.  Otherwise (several query tokens, a window or sequence of one token;
+ * groups of 64 or 128 elements on the generic kernel) the append kernel is launched first.
  * Errors: those of the two calls. */
 int tq_sdpa_int4_append_decode(const tq_kv_cache* cache, const void* k_new, const void* v_new,
                                const void* q, int32_t n_q_heads, int32_t seq_len, float attn_scale,
@@ -187,8 +188,8 @@ int tq_sdpa_int4_decode_varlen(const tq_kv_cache* cache, const void* q, int32_t 
  * (DEVICE int32 [batch], each in [n_queries, max_seq_len]) is sequence b's length INCLUDING its new token(s),
  * which are written at its last position(s) and attended together with its cached ones; the same result and
  * the same stored bits as tq_quantize_kv_varlen at seq_lens[b] - n followed by tq_sdpa_int4_decode_varlen.
- * With one query token (and no window of a single token) the merge kernel takes the token in: two launches
- * instead of three.  tq_sdpa_int4_append_decode_paged (declared with the paged calls below) is the same over a
+ * With one query token (and no window of a single token) the token is taken in as there: no launch of its
+ * own.  tq_sdpa_int4_append_decode_paged (declared with the paged calls below) is the same over a
  * pool of pages.  Errors: those of the two calls. */
 int tq_sdpa_int4_append_decode_varlen(const tq_kv_cache* cache, const void* k_new, const void* v_new,
                                       const void* q, int32_t n_q_heads, const int32_t* seq_lens,

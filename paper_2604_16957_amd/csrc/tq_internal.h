@@ -63,9 +63,9 @@ struct DecodeParams {
   // block_table[b * max_blocks + (t >> page_shift)] at row t & (row_stride - 1).
   const int32_t* block_table;
   int32_t max_blocks, page_shift;
-  // Append-and-attend (merge kernel, one query token, common length): k_new / v_new non-null = one new token per
-  // sequence, fp16 [B][H_kv][1][D], not among the tokens the chunks cover; the merge kernel quantises it, writes it
-  // at token append_pos of its row and adds its attention term to Eq. 6.
+  // Append-and-attend (one query token): k_new / v_new non-null = one new token per sequence, fp16 [B][H_kv][1][D],
+  // not among the tokens the chunks cover; the kernel that finds them set (the matrix-core kernel, or the merge
+  // kernel behind the others) quantises it, writes it at token append_pos of its row and adds its attention term.
   // With per-sequence lengths the lengths COUNT the new token (len_bias = -1: the chunks cover one token fewer)
   // and it is written at each sequence's own last position.
   const half_t* k_new;

@@ -1738,6 +1738,30 @@ def test_eighty_sequences_with_their_own_lengths_and_a_step(S):
             assert np.array_equal(gb, ob), f"{name} sequence {b}"
 
 
+@pytest.mark.parametrize("group", [32, 64, 128])
+@pytest.mark.parametrize("B,Hq,Hkv,d,S", [
+    (1, 8, 1, 128, 2), (1, 8, 1, 128, 33), (1, 64, 8, 128, 1026), (2, 48, 2, 128, 514), (3, 32, 1, 128, 322),   # 1, several chunks; shares
+    (1, 4, 2, 256, 34), (2, 16, 2, 256, 1026), (1, 32, 16, 256, 3000),                                           # d = 256; four blocks a head
+    (40, 64, 8, 128, 66), (80, 32, 8, 128, 34), (264, 32, 8, 128, 34), (20, 32, 16, 256, 98)])                   # rows packed 2, 4, 8 to a block
+def test_step_takes_the_new_token_in_the_decode_kernel(B, Hq, Hkv, d, S, group):
+    """One-call steps through every kind of launch of the matrix-core kernel (one chunk, several merged in place or by
+    the merge kernel, blocks that share a KV head, rows packed several to a block; groups over 4, 8 and 16 lanes):
+    stored bits equal to the append kernel's, output against the oracle; a second step at a shorter length shows that
+    nothing beyond the new token's row is written."""
+    w = wl.custom(batch=B, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=d, seq_len=S, seed=41 + S + group, v_std=0.5)
+    q, k, v = make(w)
+    ocache = oracle_cache_from(k, v, group=group)
+    for n in (S, max(2, S - 1)):
+        cache = gpu_cache_from(k[:, :, :n - 1].contiguous(), v[:, :, :n - 1].contiguous(), capacity=S + (S & 1) + 2, group=group)
+        out = tq.tq_sdpa_int4_append_decode(cache, k[:, :, n - 1:n].contiguous().cuda(), v[:, :, n - 1:n].contiguous().cuda(),
+                                            q.cuda(), n, w.attn_scale)
+        torch.cuda.synchronize()
+        assert_cache_bit_exact(cache, [a[:, :, :n] for a in ocache], n)
+        for t in cache.tensors():
+            assert bool((t.view(torch.uint8)[:, :, n:] == 0xEE).all())
+        assert_close(out, oracle_attend(q, [np.ascontiguousarray(a[:, :, :n]) for a in ocache], n, w.attn_scale), f"step n={n}")
+
+
 @pytest.mark.parametrize("B,Hq,Hkv", [(128, 32, 8), (172, 24, 4), (86, 48, 4), (32, 128, 8)])
 def test_merge_of_thousands_of_outputs_runs_one_block_per_kv_head(B, Hq, Hkv):
     """From 768 (sequence, query head) outputs of 128 elements on (here: thousands), with four or more query heads

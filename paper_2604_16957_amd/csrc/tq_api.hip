@@ -193,17 +193,18 @@ int waves_per_packed_row(int64_t total_rows, int target) {
   return total_rows > 4 * target ? 1 : total_rows > 2 * target ? 2 : total_rows > target ? 4 : 8;
 }
 
-// Many short sequences with their own lengths: where the (sequence, KV head) rows fill at least two rounds of
-// blocks and the longest sequence is no more than about a thousand tokens per wave that will work on it, every
-// row is ONE chunk of its own length: the decode kernel writes the output itself, and neither the device-side
-// chunk plan nor the merge kernel (one block per sequence and query head) is needed.
-bool rows_as_chunks(const tq_kv_cache* cache, int n_q_heads, int seq_len, float attn_scale, const tq_decode_opts* opts,
-                    bool paged) {
-  if (paged || queries_of(opts) > 1 || (opts && opts->n_splits > 0)) return false;
+// Many sequences with their own lengths: where the (sequence, KV head) rows fill at least two rounds of eight-wave
+// blocks, every row is ONE chunk of its own length in a block of its own (DecodeParams::ranked), with as many waves
+// (8, 4, 2, 1) as make about two rounds of what the chip holds; the decode kernel writes the output itself, and
+// neither the device-side chunk plan nor the merge kernel is needed.  Up to about a thousand tokens per wave, or the
+// launch lasts as long as the longest row.  Returns the waves per row, 0 = not this way.
+int ranked_waves(const tq_kv_cache* cache, int n_q_heads, int seq_len, float attn_scale, const tq_decode_opts* opts) {
+  if (queries_of(opts) > 1 || (opts && opts->n_splits > 0)) return 0;
   const Route r = route_of(cache, n_q_heads, seq_len, attn_scale, opts);
-  if (!r.ok || !r.use_mfma) return false;
-  const int64_t total = (int64_t)cache->batch * cache->n_kv_heads * mfma_share_of(cache, n_q_heads, opts);
-  return total >= 2 * kBlocksMfma && windowed(seq_len, opts) <= 1024 * waves_per_packed_row(total, kBlocksMfma);
+  if (!r.ok || !r.use_mfma) return 0;
+  const int64_t rows = (int64_t)cache->batch * cache->n_kv_heads * mfma_share_of(cache, n_q_heads, opts);
+  const int waves = rows <= 2 * kBlocksMfma ? 8 : rows <= 4 * kBlocksMfma ? 4 : rows <= 8 * kBlocksMfma ? 2 : 1;
+  return rows >= 2 * kBlocksMfma && windowed(seq_len, opts) <= 1024 * waves ? waves : 0;
 }
 
 // One launch of phase 1: what to attend, and what came of it.
@@ -248,9 +249,8 @@ int run_partial(PartialRequest& rq) {
                                : 1;
   const int mfma_share = use_mfma ? mfma_share_of(cache, n_q_heads, opts) : 1;
   const int rows_per_batch = cache->n_kv_heads * (use_mfma ? mfma_share : row_tiles);
-  const bool one_chunk_rows = seq_lens && rq.out != nullptr &&
-                              rows_as_chunks(cache, n_q_heads, seq_len, rq.attn_scale, opts, rq.paged != nullptr);
-  const Plan plan = plan_splits(cache->batch, rows_per_batch, attended, one_chunk_rows ? 1 : opts ? opts->n_splits : 0,
+  const int ranked = seq_lens && rq.out != nullptr ? ranked_waves(cache, n_q_heads, seq_len, rq.attn_scale, opts) : 0;
+  const Plan plan = plan_splits(cache->batch, rows_per_batch, attended, ranked ? 1 : opts ? opts->n_splits : 0,
                                 target, use_mfma ? 8 : r.wide ? 2 : 1);
   DecodeParams p = make_params(cache, rq.q, n_q_heads, seq_len, rq.attn_scale, rq.out, rq.workspace, plan,
                                queries_of(opts));
@@ -271,7 +271,7 @@ int run_partial(PartialRequest& rq) {
     p.max_blocks = rq.paged->max_blocks;
     p.page_shift = rq.paged->page_shift;
   }
-  if (seq_lens && !(opts && opts->n_splits > 0) && !one_chunk_rows) {
+  if (seq_lens && !(opts && opts->n_splits > 0) && !ranked) {
     // per-sequence lengths, no chunk count asked for: the kernels plan the chunks themselves from the lengths,
     // `target` chunks over all sequences of a KV head (a requested n_splits keeps the fixed chunking)
     // per KV head: r rounds of target / H_kv chunks, r the smallest count that leaves at least half of them
@@ -293,7 +293,7 @@ int run_partial(PartialRequest& rq) {
   }
   rq.n_splits = plan.n_splits;
   hipStream_t s = static_cast<hipStream_t>(rq.stream);
-  rq.merged = one_chunk_rows || (rq.out != nullptr && r.merge && !seq_lens);
+  rq.merged = ranked > 0 || (rq.out != nullptr && r.merge && !seq_lens);
   int merge_slot = -1;
   if (rq.merged) {
     // several chunks: the arrival counters of this workspace (none left: the merge kernel does it); rows that are
@@ -301,7 +301,10 @@ int run_partial(PartialRequest& rq) {
     merge_slot = plan.n_splits > 1 ? tq::mfma_merge_slot_of(rq.workspace) : 0;
     if (merge_slot < 0) rq.merged = false;
   }
-  if (rq.merged && use_mfma && plan.n_splits == 1 && !rq.paged) {
+  if (ranked) {
+    p.ranked = 1;
+    p.waves_per_row = ranked;
+  } else if (rq.merged && use_mfma && plan.n_splits == 1 && !rq.paged) {
     // more single-chunk rows than the chip holds blocks: pack 2, 4 or 8 of them into a block
     p.waves_per_row = waves_per_packed_row((int64_t)cache->batch * rows_per_batch, target);
   }

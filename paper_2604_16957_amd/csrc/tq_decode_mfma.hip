@@ -61,6 +61,7 @@
 // rows (token, head) of one KV head; rows beyond one tile go to further blocks on the same KV head
 // (kv_share of them).  Per-row limits (causal end, window start) only exist in the masked path that the
 // ragged last supertile takes anyway.
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 #include <unordered_map>
@@ -351,67 +352,17 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   const bool whole = W == NW;
   const int sub = wave % W;                       // (several rows per block: the W waves of a row take its supertiles in turn)
   bool row_valid = true;
-  if (!PLAIN && !whole && p.var_chunks == 0) {
+  // Rows of their own lengths, one block of W waves each, the longest first (`ranked`): blockIdx.z is the sequence's
+  // place in the order of lengths.  The launch holds about two rounds of blocks, and what evens out the mix is the
+  // machine itself: a compute unit that is done with a row takes the next longest one.
+  if (!PLAIN && p.ranked) b = __builtin_amdgcn_readfirstlane(nth_longest(p, blockIdx.z));
+  if (!PLAIN && !whole && !p.ranked && p.var_chunks == 0) {
     const int rows_y = p.n_kv_heads * p.kv_share, total = p.batch * rows_y;
-    // One wave per row and per-sequence lengths: in list order a block's eight waves would all get rows of ONE
-    // sequence, and the launch would last as long as the longest sequence.  The two waves of a SIMD share its
-    // vector ALU, so what has to be even is the sum of their two rows: every block orders the sequences by length
-    // (a stable counting sort on the supertile count, in the idle block-merge area of LDS: the same order in every
-    // block) and pairs the i-th shortest with the i-th longest, the older wave of the SIMD taking the longer.
-    bool paired = false;
-    if constexpr (!C::ALIAS) {
-      constexpr int kPairMaxBatch = NW * 64;                 // one sequence per thread
-      static_assert(C::MERGE >= (NW * 64 + 128 + kPairMaxBatch) * 4, "the ordering uses the block-merge area");
-      paired = W == 1 && p.seq_lens != nullptr && (p.batch & 1) == 0 && p.batch <= kPairMaxBatch;
-      if (paired) {
-        int* const cnt = reinterpret_cast<int*>(smem + C::OFF_MERGE);      // [wave][64]: sequences of the wave per supertile count
-        int* const tot = cnt + NW * 64;                                     // [64]: sequences per count, then where each count starts
-        int* const order = tot + 128;                                       // [batch]: sequences, shortest first
-        const int t = threadIdx.x;                                          // this thread's sequence
-        const bool have = t < p.batch;
-        const int bk = have ? min(63, (var_len(p, t) + 31) >> 5) : 64;
-        cnt[t] = 0;
-        __syncthreads();
-        // place among the wave's sequences of the same count, by index
-        int ahead = 0;
-        for (uint64_t todo = __builtin_amdgcn_ballot_w64(have); todo != 0;) {
-          const int lead = __builtin_ctzll(todo);
-          const int bv = __shfl(bk, lead);
-          const uint64_t same = __builtin_amdgcn_ballot_w64(bk == bv);
-          if (bk == bv) ahead = __builtin_popcountll(same & ((1ull << lane) - 1));
-          if (lane == lead) cnt[wave * 64 + bv] = __builtin_popcountll(same);
-          todo &= ~same;
-        }
-        __syncthreads();
-        if (t < 64) {                                        // count t: where each wave's share starts inside it
-          int acc = 0;
-          for (int wv = 0; wv < NW; ++wv) { const int n_w = cnt[wv * 64 + t]; cnt[wv * 64 + t] = acc; acc += n_w; }
-          tot[t] = acc;
-        }
-        __syncthreads();
-        if (t == 0) {
-          int acc = 0;
-          for (int k = 0; k < 64; ++k) { const int n_k = tot[k]; tot[k] = acc; acc += n_k; }
-        }
-        __syncthreads();
-        if (have) order[tot[bk] + cnt[wave * 64 + bk] + ahead] = t;
-        __syncthreads();
-        const int half = p.batch >> 1;
-        const int pair = blockIdx.y * 4 + (wave & 3);        // waves w and w + 4 sit on one SIMD
-        row_valid = pair < half * rows_y;
-        const int pc = min(pair, half * rows_y - 1);
-        const int i = pc % half;
-        kvv = __builtin_amdgcn_readfirstlane(pc / half);
-        b = __builtin_amdgcn_readfirstlane(min(max(order[(wave >> 2) ? i : p.batch - 1 - i], 0), p.batch - 1));
-      }
-    }
-    if (!paired) {
-      const int row = blockIdx.y * (NW / W) + wave / W;
-      row_valid = row < total;
-      const int r = min(row, total - 1);
-      b = __builtin_amdgcn_readfirstlane(r / rows_y);
-      kvv = __builtin_amdgcn_readfirstlane(r - (r / rows_y) * rows_y);
-    }
+    const int row = blockIdx.y * (NW / W) + wave / W;
+    row_valid = row < total;
+    const int r = min(row, total - 1);
+    b = __builtin_amdgcn_readfirstlane(r / rows_y);
+    kvv = __builtin_amdgcn_readfirstlane(r - (r / rows_y) * rows_y);
   }
   const int kv_share = PLAIN ? 1 : p.kv_share;
   const int kv = PLAIN ? kvv : kvv / kv_share;    // the KV head whose rows are read
@@ -642,9 +593,13 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   const int new_piece = lane % (D / 8), new_v = (lane / (D / 8)) & 1;
   // (a borrowed slot: behind its K tiles where the block fits there, else from the slot's start)
   constexpr int Q_IN_SLOT = C::QAREA <= C::STAGE - C::OFF_V ? C::OFF_V : 0;
-  char* const q_area = C::QSEP ? smem + C::OFF_QBLK + wave * C::QAREA : ring + (NS - 1) * C::STAGE + Q_IN_SLOT;
+  // (a block of fewer waves, see `ranked`: the areas behind the rings move up)
+  const int n_waves = !PLAIN && p.ranked ? W : NW;
+  const int off_merge = C::ALIAS ? 0 : n_waves * NS * C::STAGE;
+  const int off_qblk = off_merge + (n_waves * GP * D + 2 * NW * GP + (n_waves == NW ? NW : 1) * C::NEWTOK) * 4;
+  char* const q_area = C::QSEP ? smem + off_qblk + wave * C::QAREA : ring + (NS - 1) * C::STAGE + Q_IN_SLOT;
   {
-    const uint32_t l = C::QSEP ? (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem + C::OFF_QBLK +
+    const uint32_t l = C::QSEP ? (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem + off_qblk +
                                      wave * C::QAREA
                                : ring_lds + (NS - 1) * C::STAGE + Q_IN_SLOT;
 #pragma unroll
@@ -1196,8 +1151,8 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   //      word belongs to is meaningful (and, the zero-point operand being laid out to match, the same one of its
   //      NA zero-point sums): it is selected, brought to common units (the 2^24 / 2^20 of the two nibble
   //      positions), the zero-point sum is taken off, and the eight dims of the word leave as two 16-byte writes.
-  float* const lds_o = reinterpret_cast<float*>(smem + C::OFF_MERGE);  // [NW][GP][D]   sum_t p_t v^_t
-  float* const lds_m = lds_o + NW * GP * D;                            // [GP][NW]
+  float* const lds_o = reinterpret_cast<float*>(smem + off_merge);     // [n_waves][GP][D]   sum_t p_t v^_t
+  float* const lds_m = lds_o + n_waves * GP * D;                       // [GP][NW]
   float* const lds_l = lds_m + NW * GP;                                // [GP][NW]
   float* const lds_new = lds_l + NW * GP + (whole ? 0 : wave / W) * C::NEWTOK;   // [D] V of this unit's new token, [GP] scores
   if constexpr (C::ALIAS) __syncthreads();                   // everybody is done reading the rings
@@ -1269,7 +1224,7 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
       const int h = idx / (D / 2), j = (idx % (D / 2)) * 2;
       float2 ow[NW];                              // (asked for first: their latency hides behind the weights' arithmetic)
 #pragma unroll
-      for (int w = 0; w < NW; ++w) ow[w] = *reinterpret_cast<const float2*>(lds_o + (w * GP + h) * D + j);
+      for (int w = 0; w < NW; ++w) ow[w] = *reinterpret_cast<const float2*>(lds_o + (min(w, n_waves - 1) * GP + h) * D + j);
       float mw[NW], lw[NW];
 #pragma unroll
       for (int w4 = 0; w4 < NW; w4 += 4) {
@@ -1427,7 +1382,14 @@ hipError_t launch_as(const DecodeParams& p, dim3 grid, hipStream_t s) {
   static_assert((64 + (2 * GP * kMaxSplits + GP) ) * 4 <= Cfg<D, GP, 8, GS>::SMEM, "the chunk merge reuses the block's LDS");
   // one block of 8 waves per compute unit: 8 rings of 2 x 5 KB (d=128) or 2 x 10 KB (d=256, all 160 KB of LDS)
   constexpr int NW = 8;
-  constexpr int smem = Cfg<D, GP, NW, GS>::SMEM;
+  using C = Cfg<D, GP, NW, GS>;
+  constexpr int smem = C::SMEM;
+  // a block of W < 8 waves for one row (`ranked`): its share of the LDS, so that as many fit a compute unit as its
+  // eight wave slots take (two per SIMD)
+  const int waves = p.ranked ? p.waves_per_row : NW;
+  const int rings = waves * C::NS * C::STAGE, merge = (waves * GP * D + 2 * NW * GP + (waves == NW ? NW : 1) * C::NEWTOK) * 4;
+  const int smem_used = C::ALIAS ? std::max(rings, merge) : rings + merge + (C::QSEP ? waves * C::QAREA : 0);
+  if (smem_used > smem) return hipErrorInvalidValue;
   static_assert(smem <= 160 * 1024, "LDS budget of one compute unit");
   // dynamic LDS above 64 KB has to be opted into, once per device and kernel instance (any thread may get here first)
   static std::once_flag configured[kMaxDevices];
@@ -1441,7 +1403,7 @@ hipError_t launch_as(const DecodeParams& p, dim3 grid, hipStream_t s) {
                                        hipFuncAttributeMaxDynamicSharedMemorySize, smem);
   });
   if (outcome[dev] != hipSuccess) return outcome[dev];
-  hipLaunchKernelGGL((decode_partial_mfma_kernel<D, GP, NW, NT, MODE, GS>), grid, dim3(NW * 64), smem, s, p);
+  hipLaunchKernelGGL((decode_partial_mfma_kernel<D, GP, NW, NT, MODE, GS>), grid, dim3(waves * 64), smem_used, s, p);
   return hipGetLastError();
 }
 // the stream is read once (non-temporal loads) unless several blocks share a KV head
@@ -1512,10 +1474,11 @@ hipError_t launch_partial_mfma(const DecodeParams& p_in, int batch, int head_dim
     p.merge_slot = merge_slot;
   }
   if (p.waves_per_row != 1 && p.waves_per_row != 2 && p.waves_per_row != 4) p.waves_per_row = 8;
+  if (p.ranked && (p.seq_lens == nullptr || p.merge_slot < 0 || p.n_splits != 1 || p.var_chunks > 0)) return hipErrorInvalidValue;
   // several units per block: single-chunk rows whose output the kernel writes itself, or the slots of a chunk list
-  if (p.waves_per_row != 8 && p.var_chunks == 0 && (p.merge_slot < 0 || p.n_splits != 1 || p.block_table))
+  if (p.waves_per_row != 8 && !p.ranked && p.var_chunks == 0 && (p.merge_slot < 0 || p.n_splits != 1 || p.block_table))
     return hipErrorInvalidValue;
-  const int per_block = 8 / p.waves_per_row;
+  const int per_block = p.ranked ? 1 : 8 / p.waves_per_row;
   const dim3 grid = p.var_chunks > 0 ? dim3((p.var_chunks + per_block - 1) / per_block, rows_y, 1)
                     : per_block > 1  ? dim3(1, (batch * rows_y + per_block - 1) / per_block, 1)
                                      : dim3(p.n_splits, rows_y, batch);

@@ -75,6 +75,9 @@ struct DecodeParams {
   // Matrix-core kernel, many single-chunk rows: 1, 2 or 4 = a block takes 8 / waves_per_row (sequence, KV head)
   // rows with that many waves each (grid.y counts groups of rows); anything else = one row per block.
   int32_t waves_per_row;
+  // Matrix-core kernel, many sequences with lengths of their own: every (sequence, KV head) row is one chunk with a
+  // block of waves_per_row waves to itself, and blockIdx.z counts the sequences from the longest to the shortest.
+  int32_t ranked;
   int32_t merge_slot;       // matrix-core kernel: >= 0 selects a set of arrival counters and makes the last
                             // block of every (b, kv head) merge the chunks and write `out`; < 0: partials only
 };
@@ -276,6 +279,42 @@ __device__ inline bool var_plan(const DecodeParams& p, int slot, VarPlan& out) {
     if (t < tiles && !found) visit(t, L.len[t]);
   for (int t = kPlanTiles; t < tiles && !found; ++t) visit(t, var_len_of_lane(p, t));
   return found;
+}
+// The sequence that comes r-th when they are ordered from the longest to the shortest in 32-token tiles (ties by
+// index).  Up to 64 * kPlanTiles sequences, one per lane and register: the length that r sequences exceed is found bit
+// by bit with wave-wide counts, then the sequence among those of that length.  (More sequences: in the given order.)
+// Wave-uniform; all lanes must be active.
+__device__ inline int nth_longest(const DecodeParams& p, int r) {
+  if (p.batch > 64 * kPlanTiles) return r;
+  VarLens L;
+  var_lens_load(p, L);                            // (0 past the batch, at least 1 inside it)
+#pragma unroll
+  for (int t = 0; t < kPlanTiles; ++t) L.len[t] = (L.len[t] + 31) >> 5;
+  auto at_least = [&](int v) {
+    int n = 0;
+#pragma unroll
+    for (int t = 0; t < kPlanTiles; ++t) n += __popcll(__ballot(L.len[t] >= v));
+    return n;
+  };
+  int v = 0;                                      // the largest length that more than r sequences reach
+  for (int bit = 1 << (31 - __clz(((p.seq_len + 31) >> 5) | 1)); bit > 0; bit >>= 1)
+    if (at_least(v | bit) > r) v |= bit;
+  int i = r - at_least(v + 1);                    // which of the sequences of that length
+  int b = r;
+  bool found = false;
+#pragma unroll
+  for (int t = 0; t < kPlanTiles; ++t) {
+    const uint64_t same = __ballot(L.len[t] == v);
+    const int n = __popcll(same);
+    if (!found && i < n) {
+      const int lane = threadIdx.x & 63;
+      const bool me = ((same >> lane) & 1) != 0 && __popcll(same & ((1ull << lane) - 1)) == i;
+      b = t * 64 + __ffsll((unsigned long long)__ballot(me)) - 1;
+      found = true;
+    }
+    i -= n;
+  }
+  return b;
 }
 #endif
 

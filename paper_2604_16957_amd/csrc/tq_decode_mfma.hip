@@ -615,22 +615,22 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   // (Stand-in loads that kept the count of outstanding loads the same to the end were taken out: the one issued in
   // a wave's last iteration made it wait a whole memory round trip for bytes nobody reads, 0.3 us per launch at
   // llama128k and 0.8 us at gemma32k; the waits below count what is really out instead.)
-  if (n_mine > 0) {
-#pragma unroll
-    for (int s = 0; s < NPRE; ++s) {
-      if (s < n_mine) issue(s, sidx_of(s));
-    }
-  }
+  // A wave whose share includes the ragged (or partly masked) last supertile takes that one FIRST: its loads then leave
+  // with the prologue's and its masked path runs while the wave's first full supertile is on its way.  (At the end it
+  // was a memory round trip of its own for one wave of the launch, 2 - 3 us of a short sequence's time.)
+  const bool tail0 = n_tail > 0 && count_of(n_full + 1) != count_of(n_full);
+  if (tail0) issue_tail(0, n_full);
+  else if (n_mine > 0) issue(0, sidx_of(0));
   // (the first loads are on their way: whatever they do not need is worked out behind them)
   __builtin_amdgcn_sched_barrier(0);
   bool tail_mine[4];                              // [2], [3]: the masked FIRST supertile(s) (see `head`), the one just
                                                   // before `begin` and the one before that
-#pragma unroll
-  for (int u = 0; u < 2; ++u) tail_mine[u] = u < n_tail && count_of(n_full + u + 1) != count_of(n_full + u);
+  tail_mine[0] = tail0;
+  tail_mine[1] = n_tail > 1 && count_of(n_full + 2) != count_of(n_full + 1);
   tail_mine[2] = head && (whole ? wave == 0 : sub == 0);
   tail_mine[3] = head2 && (whole ? wave == 0 : sub == 0);
   static_assert(NPRE == 1, "one stage follows the query block");
-  if (n_mine > 0) wait_loads<LPS>();                         // (the stage issued after the query block may still be out)
+  if (tail0 || n_mine > 0) wait_loads<LPS>();                // (the stage issued after the query block may still be out)
   else wait_loads<0>();
 
   // ---- query operands (the query pre-scaling of Alg. 1 is folded into the exp2 argument instead of the query)
@@ -723,7 +723,9 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   const float kappa = p.scale_log2 * 0x1p24f;     // raw accumulator units -> log2 units
   const float slack = kSlack / kappa;             // the rescale slack in raw units
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the query block has been read: its slot may be refilled
-  if (!kSecondAfterFirstLanded && NS - 1 < n_mine) issue(NS - 1, sidx_of(NS - 1));
+  if (tail0) {
+    if (n_mine > 0) issue(1, sidx_of(0));
+  } else if (!kSecondAfterFirstLanded && n_mine > 1) issue(1, sidx_of(1));
   // supertile NS, the first one issued inside the loop, and how to step from one supertile to the next:
   // position j in the wave's pattern of 9 (or 7) out of 16
   int nx_j = young ? NS % YNG : NS % OLD;
@@ -1065,13 +1067,45 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   KRegs kr;
   VRegs vr;
   static_assert(C::PFK && NS == 2, "the waits below count one or two stages");
-  if (n_mine > 0) {
-    if (!kSecondAfterFirstLanded && n_mine > 1) wait_loads<LPS>();   // (loads land in order: stage 0 is in)
-    else wait_loads<0>();
+  auto masked = [&](int sidx) {                   // supertile sidx, whose stage sits in slot 0, by the masked path
     load_k(0, kr);
-    if (kSecondAfterFirstLanded && NS - 1 < n_mine) issue(NS - 1, sidx_of(NS - 1));
-  }
+    load_v(0, vr);
+    if constexpr (GS == 2 && D == 128) {
+      // a token pair's dword may reach one token past the sequence's last: whatever lies there must not meet the
+      // (zero) weights of the masked tokens as an Inf or NaN (the scores of such tokens are replaced, not scaled)
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (begin + sidx * 32 + 16 * t + 4 * i + kq >= seq) {
+#pragma unroll
+            for (int dw = 0; dw < NDW; ++dw) vr.vs[dw][t][i] = 0;
+            vr.zb[4 * t + i] = 0;
+          }
+    }
+    float sc[2][4];
+    scores(kr, sidx, std::true_type{}, sc);
+    half8v pa[NPA];
+    softmax(sc, vr, pa);
+    pv(vr, pa);
+  };
   int slot = 0;
+  if (tail0) {
+    if (n_mine > 0) wait_loads<LPS>();            // (loads land in order: the tail is in, the first full supertile may be out)
+    else wait_loads<0>();
+    masked(n_full);
+    if (n_mine > 1) {
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // slot 0 has been read
+      issue(0, sidx_of(1));
+    }
+    slot = 1;
+  }
+  if (n_mine > 0) {
+    if ((tail0 || !kSecondAfterFirstLanded) && n_mine > 1) wait_loads<LPS>();   // (the first full supertile is in)
+    else wait_loads<0>();
+    load_k(slot, kr);
+    if (!tail0 && kSecondAfterFirstLanded && n_mine > 1) issue(1, sidx_of(1));
+  }
   for (int i = 0; i < n_mine; ++i) {
     const int next = (slot + 1 == NS) ? 0 : slot + 1;
     if constexpr (SPLIT) {
@@ -1115,33 +1149,16 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
     slot = next;
   }
   wait_loads<0>();                                           // (nothing is out any more: the rings are quiet)
+  if constexpr (!PLAIN) {
 #pragma unroll 1
-  for (int u = 0; u < (PLAIN ? 1 : 4); ++u) {                // the masked supertiles: the sequence's last one or two,
-    if (!tail_mine[u]) continue;                             // and under a window its first (or first two)
-    const int sidx = u < 2 ? n_full + u : 1 - u;
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    issue_tail(0, sidx);
-    wait_loads<0>();
-    load_k(0, kr);
-    load_v(0, vr);
-    if constexpr (GS == 2 && D == 128) {
-      // a token pair's dword may reach one token past the sequence's last: whatever lies there must not meet the
-      // (zero) weights of the masked tokens as an Inf or NaN (the scores of such tokens are replaced, not scaled)
-#pragma unroll
-      for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-          if (begin + sidx * 32 + 16 * t + 4 * i + kq >= seq) {
-#pragma unroll
-            for (int dw = 0; dw < NDW; ++dw) vr.vs[dw][t][i] = 0;
-            vr.zb[4 * t + i] = 0;
-          }
+    for (int u = 1; u < 4; ++u) {                            // further masked supertiles: the last but one with several
+      if (!tail_mine[u]) continue;                           // query tokens, under a window the first (or first two)
+      const int sidx = u < 2 ? n_full + u : 1 - u;
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      issue_tail(0, sidx);
+      wait_loads<0>();
+      masked(sidx);
     }
-    float sc[2][4];
-    scores(kr, sidx, std::true_type{}, sc);
-    half8v pa[NPA];
-    softmax(sc, vr, pa);
-    pv(vr, pa);
   }
 
   if constexpr (SPLIT) {

@@ -304,6 +304,12 @@ int run_partial(PartialRequest& rq) {
   if (ranked) {
     p.ranked = 1;
     p.waves_per_row = ranked;
+    // two rows to a block where the longest is at most 16 tiles per wave of its half block over the average; 5 where
+    // the rows fill that one round badly (measured on 64 heads over 8, us per step, two rounds / one: 64 sequences of
+    // 128 .. 4096 tokens 31.5 / 37.0, of 256 .. 2048 28.5 / 26.1, all of 1024 26.9 / 20.6; 256 of 64 .. 2048 75.9 / 80.8,
+    // of 64 .. 1024 51.5 / 46.9, all of 1024 86.6 / 65.6; badly filled: 34 of 33 .. 340, 32 heads over 32, 12.1 / 15.3)
+    const int64_t waves_at_once = (int64_t)cache->batch * rows_per_batch * (ranked / 2);
+    p.rank_spread = (waves_at_once >= 7 * kBlocksMfma ? 16 : 5) * (ranked / 2);
   } else if (rq.merged && use_mfma && plan.n_splits == 1 && !rq.paged) {
     // more single-chunk rows than the chip holds blocks: pack 2, 4 or 8 of them into a block
     p.waves_per_row = waves_per_packed_row((int64_t)cache->batch * rows_per_batch, target);

@@ -348,15 +348,30 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   // blockIdx.y counts groups of rows of the list [batch][KV head x part]; with per-sequence lengths a unit is a
   // slot of the chunk list, and blockIdx.x counts groups of slots.  A wave past the end of its list has no tokens
   // and only keeps the barriers company.
-  const int W = PLAIN ? NW : p.waves_per_row;     // NW: the whole block on one unit
+  int W = PLAIN ? NW : p.waves_per_row;           // NW: the whole block on one unit
+  bool row_valid = true;
+  // Rows of their own lengths, the longest first (`ranked`), a block of n_waves waves each: the launch holds about two
+  // rounds of blocks, and what evens out the mix is the machine itself: a compute unit that is done with a row takes
+  // the next longest one.  Where the lengths are too even for that to pay (the second round costs a row's fixed time
+  // once more), a block takes two rows that follow each other, half its waves each, in one round, and the other half
+  // of the blocks ends at once.  blockIdx.z: the place in the order of lengths (of a row, or of a pair).
+  const bool ranked = !PLAIN && p.ranked;
+  const int n_waves = ranked ? W : NW, n_units = ranked ? 2 : NW;
+  if (ranked) {
+    int rank = blockIdx.z;
+    RankedRows rows(p);
+    if (rows.even) {
+      W = n_waves >> 1;
+      rank = 2 * rank + wave / W;
+      if (2 * blockIdx.z >= (unsigned)p.batch) return;
+      row_valid = rank < p.batch;
+      rank = min(rank, p.batch - 1);
+    }
+    b = __builtin_amdgcn_readfirstlane(rows.sequence(p, rank));
+  }
   const bool whole = W == NW;
   const int sub = wave % W;                       // (several rows per block: the W waves of a row take its supertiles in turn)
-  bool row_valid = true;
-  // Rows of their own lengths, one block of W waves each, the longest first (`ranked`): blockIdx.z is the sequence's
-  // place in the order of lengths.  The launch holds about two rounds of blocks, and what evens out the mix is the
-  // machine itself: a compute unit that is done with a row takes the next longest one.
-  if (!PLAIN && p.ranked) b = __builtin_amdgcn_readfirstlane(nth_longest(p, blockIdx.z));
-  if (!PLAIN && !whole && !p.ranked && p.var_chunks == 0) {
+  if (!PLAIN && !whole && !ranked && p.var_chunks == 0) {
     const int rows_y = p.n_kv_heads * p.kv_share, total = p.batch * rows_y;
     const int row = blockIdx.y * (NW / W) + wave / W;
     row_valid = row < total;
@@ -594,9 +609,8 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   // (a borrowed slot: behind its K tiles where the block fits there, else from the slot's start)
   constexpr int Q_IN_SLOT = C::QAREA <= C::STAGE - C::OFF_V ? C::OFF_V : 0;
   // (a block of fewer waves, see `ranked`: the areas behind the rings move up)
-  const int n_waves = !PLAIN && p.ranked ? W : NW;
   const int off_merge = C::ALIAS ? 0 : n_waves * NS * C::STAGE;
-  const int off_qblk = off_merge + (n_waves * GP * D + 2 * NW * GP + (n_waves == NW ? NW : 1) * C::NEWTOK) * 4;
+  const int off_qblk = off_merge + (n_waves * GP * D + 2 * NW * GP + n_units * C::NEWTOK) * 4;
   char* const q_area = C::QSEP ? smem + off_qblk + wave * C::QAREA : ring + (NS - 1) * C::STAGE + Q_IN_SLOT;
   {
     const uint32_t l = C::QSEP ? (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem + off_qblk +
@@ -1404,7 +1418,7 @@ hipError_t launch_as(const DecodeParams& p, dim3 grid, hipStream_t s) {
   // a block of W < 8 waves for one row (`ranked`): its share of the LDS, so that as many fit a compute unit as its
   // eight wave slots take (two per SIMD)
   const int waves = p.ranked ? p.waves_per_row : NW;
-  const int rings = waves * C::NS * C::STAGE, merge = (waves * GP * D + 2 * NW * GP + (waves == NW ? NW : 1) * C::NEWTOK) * 4;
+  const int rings = waves * C::NS * C::STAGE, merge = (waves * GP * D + 2 * NW * GP + (p.ranked ? 2 : NW) * C::NEWTOK) * 4;
   const int smem_used = C::ALIAS ? std::max(rings, merge) : rings + merge + (C::QSEP ? waves * C::QAREA : 0);
   if (smem_used > smem) return hipErrorInvalidValue;
   static_assert(smem <= 160 * 1024, "LDS budget of one compute unit");

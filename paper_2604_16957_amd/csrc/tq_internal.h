@@ -76,8 +76,10 @@ struct DecodeParams {
   // rows with that many waves each (grid.y counts groups of rows); anything else = one row per block.
   int32_t waves_per_row;
   // Matrix-core kernel, many sequences with lengths of their own: every (sequence, KV head) row is one chunk with a
-  // block of waves_per_row waves to itself, and blockIdx.z counts the sequences from the longest to the shortest.
-  int32_t ranked;
+  // block of waves_per_row waves to itself (or, where the lengths are even, half of one: see RankedRows), and blockIdx.z
+  // counts the sequences from the longest to the shortest.  rank_spread: by how many tiles the longest sequence may
+  // exceed the average for the lengths to count as even.
+  int32_t ranked, rank_spread;
   int32_t merge_slot;       // matrix-core kernel: >= 0 selects a set of arrival counters and makes the last
                             // block of every (b, kv head) merge the chunks and write `out`; < 0: partials only
 };
@@ -175,6 +177,15 @@ __device__ inline int wave_sum(int x) {
   x += __builtin_amdgcn_update_dpp(0, x, 0x121, 0xF, 0xF, false);
   return __builtin_amdgcn_readlane(x, 0) + __builtin_amdgcn_readlane(x, 16) + __builtin_amdgcn_readlane(x, 32) +
          __builtin_amdgcn_readlane(x, 48);
+}
+// the same for the largest of non-negative values
+__device__ inline int wave_max(int x) {
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x128, 0xF, 0xF, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x124, 0xF, 0xF, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x122, 0xF, 0xF, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x121, 0xF, 0xF, false));
+  return max(max(__builtin_amdgcn_readlane(x, 0), __builtin_amdgcn_readlane(x, 16)),
+             max(__builtin_amdgcn_readlane(x, 32), __builtin_amdgcn_readlane(x, 48)));
 }
 // Tokens sequence (64 tile + lane) attends, 0 past the batch: the planner below keeps one sequence per lane.
 __device__ inline int var_len_of_lane(const DecodeParams& p, int tile) {
@@ -280,42 +291,53 @@ __device__ inline bool var_plan(const DecodeParams& p, int slot, VarPlan& out) {
   for (int t = kPlanTiles; t < tiles && !found; ++t) visit(t, var_len_of_lane(p, t));
   return found;
 }
-// The sequence that comes r-th when they are ordered from the longest to the shortest in 32-token tiles (ties by
-// index).  Up to 64 * kPlanTiles sequences, one per lane and register: the length that r sequences exceed is found bit
-// by bit with wave-wide counts, then the sequence among those of that length.  (More sequences: in the given order.)
-// Wave-uniform; all lanes must be active.
-__device__ inline int nth_longest(const DecodeParams& p, int r) {
-  if (p.batch > 64 * kPlanTiles) return r;
+// The sequences in the order of their lengths in 32-token tiles, the longest first (ties by index), and whether those
+// lengths are even.  Up to 64 * kPlanTiles sequences, one per lane and register; the length that r sequences exceed is
+// found bit by bit with wave-wide counts, then the sequence among those of that length.  (Even lengths, and more
+// sequences than that, taken for even: in the given order.)  Wave-uniform; all lanes must be active.
+struct RankedRows {
   VarLens L;
-  var_lens_load(p, L);                            // (0 past the batch, at least 1 inside it)
+  bool even;
+  __device__ RankedRows(const DecodeParams& p) {
+    even = p.waves_per_row > 1;
+    if (p.batch > 64 * kPlanTiles) return;
+    var_lens_load(p, L);                          // (0 past the batch, at least 1 inside it)
+    int mine = 0, most = 0;
 #pragma unroll
-  for (int t = 0; t < kPlanTiles; ++t) L.len[t] = (L.len[t] + 31) >> 5;
-  auto at_least = [&](int v) {
+    for (int t = 0; t < kPlanTiles; ++t) {
+      L.len[t] = (L.len[t] + 31) >> 5;
+      mine += L.len[t];
+      most = max(most, L.len[t]);
+    }
+    even = even && (wave_max(most) - p.rank_spread) * p.batch <= wave_sum(mine);
+  }
+  __device__ int at_least(int v) const {
     int n = 0;
 #pragma unroll
     for (int t = 0; t < kPlanTiles; ++t) n += __popcll(__ballot(L.len[t] >= v));
     return n;
-  };
-  int v = 0;                                      // the largest length that more than r sequences reach
-  for (int bit = 1 << (31 - __clz(((p.seq_len + 31) >> 5) | 1)); bit > 0; bit >>= 1)
-    if (at_least(v | bit) > r) v |= bit;
-  int i = r - at_least(v + 1);                    // which of the sequences of that length
-  int b = r;
-  bool found = false;
-#pragma unroll
-  for (int t = 0; t < kPlanTiles; ++t) {
-    const uint64_t same = __ballot(L.len[t] == v);
-    const int n = __popcll(same);
-    if (!found && i < n) {
-      const int lane = threadIdx.x & 63;
-      const bool me = ((same >> lane) & 1) != 0 && __popcll(same & ((1ull << lane) - 1)) == i;
-      b = t * 64 + __ffsll((unsigned long long)__ballot(me)) - 1;
-      found = true;
-    }
-    i -= n;
   }
-  return b;
-}
+  __device__ int sequence(const DecodeParams& p, int r) const {
+    if (even || p.batch > 64 * kPlanTiles) return r;
+    int v = 0;                                    // the largest length that more than r sequences reach
+    for (int bit = 1 << (31 - __clz(((p.seq_len + 31) >> 5) | 1)); bit > 0; bit >>= 1)
+      if (at_least(v | bit) > r) v |= bit;
+    int i = r - at_least(v + 1), b = r;           // i: which of the sequences of that length
+    bool found = false;
+#pragma unroll
+    for (int t = 0; t < kPlanTiles; ++t) {
+      const uint64_t same = __ballot(L.len[t] == v);
+      const int n = __popcll(same), lane = threadIdx.x & 63;
+      if (!found && i < n) {
+        const bool me = ((same >> lane) & 1) != 0 && __popcll(same & ((1ull << lane) - 1)) == i;
+        b = t * 64 + __ffsll((unsigned long long)__ballot(me)) - 1;
+        found = true;
+      }
+      i -= n;
+    }
+    return b;
+  }
+};
 #endif
 
 // Workspace carving: part_o first, then part_ml, both sized for kMaxSplits.

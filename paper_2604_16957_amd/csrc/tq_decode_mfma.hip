@@ -381,13 +381,16 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   }
   const int kv_share = PLAIN ? 1 : p.kv_share;
   const int kv = PLAIN ? kvv : kvv / kv_share;    // the KV head whose rows are read
+  int planned_len = -1;                           // (known from the plan: the lengths need not be fetched again)
   if (!PLAIN && p.var_chunks > 0) {                         // per-sequence lengths: which (sequence, chunk) is this block's
     VarPlan vp;
     vp.b = 0;
     vp.chunk = 0;
+    vp.len = 0;
     const bool listed = var_plan(p, whole ? blockIdx.x : blockIdx.x * (NW / W) + wave / W, vp);
     if (whole && !listed) return;                 // (with several units per block nobody leaves before the barriers)
     row_valid = listed;
+    planned_len = __builtin_amdgcn_readfirstlane(vp.len);
     split = __builtin_amdgcn_readfirstlane(vp.chunk);     // (wave-uniform by construction: tell the compiler)
     b = __builtin_amdgcn_readfirstlane(vp.b);
     tokens_per_split = __builtin_amdgcn_readfirstlane(vp.chunk_tokens);
@@ -416,14 +419,14 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   // a decode step (p.k_new set): the step's new token is not among the tokens the chunks cover; the block of the
   // sequence's first chunk takes it in (see `takes`).  A sequence may hold nothing but its new token.
   const bool new_here = p.k_new != nullptr && split == 0 && row_valid;
-  const int new_pos = var_lens ? max(1, min(p.seq_lens[b], p.seq_len)) - 1 : p.append_pos;
-  const int seq = !row_valid || (var_lens && p.k_new != nullptr && new_pos == 0) ? 0 : var_lens ? var_len(p, b) : p.seq_len;
-  const int start = var_lens ? var_start(p, b) : p.start;
+  const int new_pos = !var_lens ? p.append_pos : p.k_new == nullptr ? -1 : max(1, min(p.seq_lens[b], p.seq_len)) - 1;
+  const int seq = !row_valid || (var_lens && new_pos == 0) ? 0 : !var_lens ? p.seq_len : planned_len >= 0 ? planned_len : var_len(p, b);
+  const int start = !var_lens ? p.start : p.window > 0 ? var_start(p, b) : 0;
   // first row of the six arrays this block reads from: the sequence's own row (contiguous cache), or the
   // pool's row 0 (paged cache: the page's rows are added supertile by supertile)
   // paged cache: token indices below count from `start` as well, but the rows are found page by page; the
   // window's first token may lie up to 31 tokens after `start` (see var_start)
-  const int lead = (paged && var_lens) ? var_first(p, b) - start : 0;
+  const int lead = (paged && var_lens && p.window > 0) ? var_first(p, b) - start : 0;
   const int pstart = paged ? start : 0;           // added to a token index where a page is looked up
   const int64_t row0 = paged ? 0 : (int64_t)(b * p.n_kv_heads + kv) * p.row_stride + start;
   const int begin0 = split * tokens_per_split;    // first token of the chunk

@@ -153,7 +153,7 @@ __device__ inline uint32_t quantize_word_fast(const half_t* x, const QuantFast& 
 // below), so that the list "all chunks of sequence 0, then of sequence 1, ..." has at most p.var_chunks
 // entries: the grid.  Slot s of that list -> (b, chunk); returns false past the end of the list.
 // Everything here is wave-uniform.
-struct VarPlan { int chunk_tokens, b, chunk; };
+struct VarPlan { int chunk_tokens, b, chunk, len; };   // len: var_len of sequence b
 __device__ inline int var_full_len(const DecodeParams& p, int b) {
   return max(1, min(p.seq_lens[b], p.seq_len) + p.len_bias);
 }
@@ -186,6 +186,16 @@ __device__ inline int wave_max(int x) {
   x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x121, 0xF, 0xF, false));
   return max(max(__builtin_amdgcn_readlane(x, 0), __builtin_amdgcn_readlane(x, 16)),
              max(__builtin_amdgcn_readlane(x, 32), __builtin_amdgcn_readlane(x, 48)));
+}
+// inclusive prefix sum over the 64 lanes of the wave
+__device__ inline int wave_scan(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, false);   // row_shr:1, 2, 4, 8: inside each row of 16
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, false);
+  const int lane = threadIdx.x & 63;
+  const int r0 = __builtin_amdgcn_readlane(x, 15), r1 = __builtin_amdgcn_readlane(x, 31), r2 = __builtin_amdgcn_readlane(x, 47);
+  return x + (lane >= 16 ? r0 : 0) + (lane >= 32 ? r1 : 0) + (lane >= 48 ? r2 : 0);
 }
 // Tokens sequence (64 tile + lane) attends, 0 past the batch: the planner below keeps one sequence per lane.
 __device__ inline int var_len_of_lane(const DecodeParams& p, int tile) {
@@ -232,19 +242,21 @@ __device__ inline int var_chunk_tokens(const DecodeParams& p, const VarLens& L) 
   const int floor_c = max(p.var_min_chunk, (p.seq_len + kMaxSplits - 1) / kMaxSplits);
   auto round_up = [](long long c) { return (int)((c + kTile - 1) / kTile * kTile); };
   const int budget = p.var_chunks - p.batch;      // >= var_chunks / 2 by the host's choice of var_chunks
-  // (the two bounds: 32-bit divisions where the total allows, which is nearly always; a 64-bit one is some
-  // hundred and fifty instructions)
-  const bool narrow = total < (1ll << 31) - (1 << 24) && p.var_chunks < (1 << 24);
-  const long long need_hi = narrow ? (long long)(((uint32_t)total + (uint32_t)budget - 1) / (uint32_t)budget)
-                                   : (total + budget - 1) / budget;
-  const long long need_lo = narrow ? (long long)(((uint32_t)total + (uint32_t)p.var_chunks - 1) / (uint32_t)p.var_chunks)
-                                   : (total + p.var_chunks - 1) / p.var_chunks;
-  int hi = round_up(max((long long)floor_c, need_hi));
-  int lo = round_up(max((long long)floor_c, need_lo));
   const bool fl = var_exact_floats(p);
+  int hi, lo;
+  if (total < (1 << 23) && p.var_chunks < (1 << 16)) {
+    // (nearly always; estimates by the float reciprocal instead of 64-bit divisions of some hundred and fifty
+    // instructions: the upper one is never too small, a tile too many costs a step of the search, and a lower one that
+    // is a tile too small is ruled out by the count like any other candidate)
+    hi = round_up(max(floor_c, (int)((float)(int)total * __builtin_amdgcn_rcpf((float)budget)) + 2));
+    lo = round_up(max(floor_c, (int)((float)(int)total * __builtin_amdgcn_rcpf((float)p.var_chunks))));
+  } else {
+    hi = round_up(max((long long)floor_c, (total + budget - 1) / budget));
+    lo = round_up(max((long long)floor_c, (total + p.var_chunks - 1) / p.var_chunks));
+  }
   while (lo < hi) {
     const int mid = (lo + (hi - lo) / 2) / kTile * kTile;        // lo <= mid < hi, a multiple of 32
-    const float rmid = 1.0f / (float)mid;
+    const float rmid = __builtin_amdgcn_rcpf((float)mid);
     int n = 0;
 #pragma unroll
     for (int t = 0; t < kPlanTiles; ++t)
@@ -264,22 +276,19 @@ __device__ inline bool var_plan(const DecodeParams& p, int slot, VarPlan& out) {
   const int c = var_chunk_tokens(p, L);
   out.chunk_tokens = c;
   if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *p.plan = c;
-  const int tiles = (p.batch + 63) >> 6, lane = threadIdx.x & 63;
+  const int tiles = (p.batch + 63) >> 6;
   int first = 0;
   bool found = false;
-  const float rc = 1.0f / (float)c;
+  const float rc = __builtin_amdgcn_rcpf((float)c);
   const bool fl = var_exact_floats(p);
   auto visit = [&](int t, int len) {              // tile t: does it hold the slot?  (wave-uniform)
     const int n = var_chunks_of(len, c, rc, fl);  // this lane's sequence: its chunks
     const int in_tile = wave_sum(n);
     if (slot < first + in_tile) {
-      int incl = n;                               // inclusive prefix sum over the lanes
-      for (int d = 1; d < 64; d <<= 1) {
-        const int y = __shfl_up(incl, d);
-        if (lane >= d) incl += y;
-      }
+      const int incl = wave_scan(n);
       const int i = __ffsll((unsigned long long)__ballot(slot < first + incl)) - 1;   // first lane past the slot
       out.b = t * 64 + i;
+      out.len = __builtin_amdgcn_readlane(len, i);
       out.chunk = slot - first - (__builtin_amdgcn_readlane(incl, i) - __builtin_amdgcn_readlane(n, i));
       found = true;
     }

@@ -143,9 +143,18 @@ class KVCache:
         return sum(t.numel() * t.element_size() for t in self.tensors())
 
 
+# The current stream's handle without building a torch.cuda.Stream around it: 0.15 us instead of 2.7 us per call, of
+# the 10.4 us of host time a one-launch step took with it (7.7 us without).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device_of_thread = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream_ptr(stream) -> int:
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return s.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None or _device_of_thread is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_device_of_thread())
 
 
 def _opts(n_splits: int, variant: int, window: int = 0, n_queries: int = 1):

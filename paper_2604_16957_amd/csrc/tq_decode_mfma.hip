@@ -218,6 +218,25 @@ __device__ __forceinline__ float blocks_sum(float x) {
   swap16(x, a, b);
   return a + b;
 }
+// the largest, and the sum, of a value over the 64 lanes (in every lane)
+template <int ROT>
+__device__ __forceinline__ float row_ror(float x) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x120 + ROT, 0xF, 0xF, false));
+}
+__device__ __forceinline__ float wave_fmax(float x) {
+  x = fmaxf(x, row_ror<8>(x));
+  x = fmaxf(x, row_ror<4>(x));
+  x = fmaxf(x, row_ror<2>(x));
+  x = fmaxf(x, row_ror<1>(x));
+  return blocks_max(x);
+}
+__device__ __forceinline__ float wave_fsum(float x) {
+  x += row_ror<8>(x);
+  x += row_ror<4>(x);
+  x += row_ror<2>(x);
+  x += row_ror<1>(x);
+  return blocks_sum(x);
+}
 template <int ROT>
 __device__ __forceinline__ float row_ror_add(float x) {      // x + (x rotated by ROT inside its 16-lane row)
   const int y = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x120 + ROT, 0xF, 0xF, false);
@@ -282,13 +301,14 @@ __device__ __forceinline__ void dma16_x4(const void* sbase, uint32_t voff, uint3
               "global_load_lds_dwordx4 %0, %1 offset:3072 nt",
               "v"(voff), "s"(sbase), "s"(lds_base));
 }
-// device-scope (all compute dies) store and load of one float, without any cache-wide maintenance
+// device-scope (all compute dies) store and load of two floats, without any cache-wide maintenance
 __device__ __forceinline__ void st_dev2(float* p, float a, float b) {      // two floats, 8-byte aligned
   const uint64_t bits = (uint64_t)__builtin_bit_cast(uint32_t, a) | ((uint64_t)__builtin_bit_cast(uint32_t, b) << 32);
   __hip_atomic_store(reinterpret_cast<uint64_t*>(p), bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ float ld_dev(const float* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+__device__ __forceinline__ float2 ld_dev2(const float* p) {                 // two floats, 8-byte aligned
+  const uint64_t bits = __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return {__builtin_bit_cast(float, (uint32_t)bits), __builtin_bit_cast(float, (uint32_t)(bits >> 32))};
 }
 template <int N>
 __device__ __forceinline__ void wait_loads() {               // until at most N loads are outstanding
@@ -1332,64 +1352,79 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   // each block then writes its die's whole L2 back and invalidates it, and a decode of 256 blocks over 8K tokens
   // goes from 11.0 to 13.5 us (release alone +1.2 us, acquire alone +0.9 us), more than the separate merge kernel
   // costs (13.1 us), for no access that the atomics do not already cover.
-  float* const c_m = reinterpret_cast<float*>(smem) + 64;     // [G][n] chunk maxima, then chunk weights
-  float* const c_l = c_m + GP * kMaxSplits;                    // [G][n] chunk sums
-  float* const h_den = c_l + GP * kMaxSplits;                  // [G]
-  // Everything is asked for at once, so the merge is about one memory round trip long: the first 32
-  // chunks of this thread's output elements (which do not need the weights yet) and the chunk maxima
-  // and sums; the weights are worked out while the loads are in flight.
-  constexpr int PER = GP * D / (NW * 64);         // output elements per thread (padded group)
-  constexpr int FIRST = 32;
-  float pre[PER][FIRST];
-#pragma unroll
-  for (int e = 0; e < PER; ++e) {
-    const int idx = threadIdx.x + e * NW * 64, h = idx / D, j = idx % D;
-    const float* src = p.part_o + query_row(h < G ? h : 0) * n * D + j;
-#pragma unroll
-    for (int u = 0; u < FIRST; ++u) pre[e][u] = ld_dev(src + (int64_t)(u < n ? u : n - 1) * D);
-  }
-  for (int idx = threadIdx.x; idx < G * n; idx += NW * 64) {
-    const float* ml = p.part_ml + (query_row(idx / n) * n + idx % n) * 2;
-    c_m[(idx / n) * kMaxSplits + idx % n] = ld_dev(ml);
-    c_l[(idx / n) * kMaxSplits + idx % n] = ld_dev(ml + 1);
-  }
-  __syncthreads();
-  for (int h = wave; h < G; h += NW) {            // a wave per head: its chunk weights and its denominator
-    float mx = kNegBig;
-    for (int cc = lane; cc < n; cc += 64) mx = fmaxf(mx, c_m[h * kMaxSplits + cc]);
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
-    float dsum = 0.0f;
-    for (int cc = lane; cc < n; cc += 64) {
-      const float w = __builtin_amdgcn_exp2f(c_m[h * kMaxSplits + cc] - mx);
-      c_m[h * kMaxSplits + cc] = w;
-      dsum = fmaf(c_l[h * kMaxSplits + cc], w, dsum);
+  // Everything is asked for at once: wave h fetches the (m, l) of row h's chunks, a chunk or two per lane, and a thread
+  // the chunks' outputs for two neighbouring dims of one row (two threads share a pair where there are fewer pairs than
+  // threads, each with every other chunk).  The weights come out of lane reductions while the outputs are on their
+  // way; one barrier hands them over.  (With the (m, l) staged through LDS, two barriers, and always 32 loads per single
+  // element however few the chunks, this end of the kernel took 3.2 us for 4 chunks and 4 us for 32, of 10 and 11; with
+  // the (m, l) fetched by every thread for itself 1.3 and 5.)
+  if constexpr (GP <= 8) {                        // (a 16-row tile's chunks go to the merge kernel)
+    static_assert(GP <= NW && kMaxSplits <= 128, "a wave per row, at most two chunks per lane");
+    float* const c_w = reinterpret_cast<float*>(smem) + 64;    // [GP][kMaxSplits] chunk weights
+    float* const h_den = c_w + GP * kMaxSplits;                 // [GP]
+    float2 ml0 = {kNegBig, 0.0f}, ml1 = {kNegBig, 0.0f};
+    if (wave < G) {
+      const float* const ml = p.part_ml + query_row(wave) * n * 2;
+      if (lane < n) ml0 = ld_dev2(ml + lane * 2);
+      if (lane + 64 < n) ml1 = ld_dev2(ml + (lane + 64) * 2);
     }
+    constexpr int PAIRS = GP * D / 2, PARTS = NW * 64 / PAIRS;
+    static_assert(PARTS == 1 || PARTS == 2, "a thread, or two neighbouring ones, per pair of dims");
+    const int pair = threadIdx.x / PARTS, cpart = threadIdx.x % PARTS;
+    const int h = pair / (D / 2), j = (pair % (D / 2)) * 2;
+    const int64_t row = query_row(h < G ? h : 0);
+    const float* const src = p.part_o + row * n * D + j;
+    auto weights = [&] {
+      if (wave < G) {
+        const float mx = wave_fmax(fmaxf(ml0.x, ml1.x));
+        const float w0 = __builtin_amdgcn_exp2f(ml0.x - mx), w1 = __builtin_amdgcn_exp2f(ml1.x - mx);
+        if (lane < n) c_w[wave * kMaxSplits + lane] = w0;
+        if (lane + 64 < n) c_w[wave * kMaxSplits + lane + 64] = w1;
+        const float d = wave_fsum(fmaf(ml0.y, w0, ml1.y * w1));
+        if (lane == 0) h_den[wave] = d;
+      }
+      __syncthreads();
+    };
+    const float* const w = c_w + h * kMaxSplits;
+    float n0 = 0.0f, n1 = 0.0f;
+    auto fetch = [&](auto count_tag, int c0, float2* o) {
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) dsum += __shfl_xor(dsum, off);
-    if (lane == 0) h_den[h] = dsum;
-  }
-  __syncthreads();
+      for (int u = 0; u < decltype(count_tag)::value; ++u) o[u] = ld_dev2(src + (int64_t)min(c0 + u * PARTS + cpart, n - 1) * D);
+    };
+    auto add = [&](auto count_tag, int c0, const float2* o) {
 #pragma unroll
-  for (int e = 0; e < PER; ++e) {
-    const int idx = threadIdx.x + e * NW * 64, h = idx / D, j = idx % D;
-    if (h >= G) continue;
-    const int64_t row = query_row(h);
-    const float* src = p.part_o + row * n * D + j;
-    const float* w = c_m + h * kMaxSplits;
-    float num = 0.0f;
-#pragma unroll
-    for (int u = 0; u < FIRST; ++u) num = fmaf(pre[e][u], u < n ? w[u] : 0.0f, num);
-    int cc = FIRST;
-    for (; cc + 8 <= n; cc += 8) {
-      float v[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = ld_dev(src + (int64_t)(cc + u) * D);
-#pragma unroll
-      for (int u = 0; u < 8; ++u) num = fmaf(v[u], w[cc + u], num);
+      for (int u = 0; u < decltype(count_tag)::value; ++u) {
+        const int cc = c0 + u * PARTS + cpart;
+        const float e = cc < n ? w[cc] : 0.0f;
+        n0 = fmaf(o[u].x, e, n0);
+        n1 = fmaf(o[u].y, e, n1);
+      }
+    };
+    auto all = [&](auto count_tag) {
+      constexpr int U = decltype(count_tag)::value;
+      float2 o[U];
+      fetch(count_tag, 0, o);
+      weights();
+      add(count_tag, 0, o);
+      for (int c0 = U * PARTS; c0 < n; c0 += U * PARTS) {
+        fetch(count_tag, c0, o);
+        add(count_tag, c0, o);
+      }
+    };
+    if (n <= 4 * PARTS) all(std::integral_constant<int, 4>{});
+    else if (n <= 16 * PARTS) all(std::integral_constant<int, 16>{});
+    else all(std::integral_constant<int, 32>{});
+    if constexpr (PARTS == 2) {
+      n0 += __shfl_xor(n0, 1);
+      n1 += __shfl_xor(n1, 1);
     }
-    for (; cc < n; ++cc) num = fmaf(ld_dev(src + (int64_t)cc * D), w[cc], num);
-    p.out[row * D + j] = (half_t)(num / h_den[h]);
+    if (h < G && cpart == 0) {
+      const float den = h_den[h];
+      half2v r;
+      r[0] = (_Float16)(n0 / den);
+      r[1] = (_Float16)(n1 / den);
+      *reinterpret_cast<half2v*>(p.out + row * D + j) = r;
+    }
   }
 }
 
@@ -1413,7 +1448,6 @@ int kv_share_of(int head_dim, int gqa) {
 
 template <int D, int GP, bool NT, Mode MODE, int GS = 0>
 hipError_t launch_as(const DecodeParams& p, dim3 grid, hipStream_t s) {
-  static_assert((64 + (2 * GP * kMaxSplits + GP) ) * 4 <= Cfg<D, GP, 8, GS>::SMEM, "the chunk merge reuses the block's LDS");
   // one block of 8 waves per compute unit: 8 rings of 2 x 5 KB (d=128) or 2 x 10 KB (d=256, all 160 KB of LDS)
   constexpr int NW = 8;
   using C = Cfg<D, GP, NW, GS>;

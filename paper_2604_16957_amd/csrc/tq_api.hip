@@ -128,12 +128,18 @@ int hip_rc(hipError_t e) { return e == hipSuccess ? TQ_OK : TQ_ERR_HIP; }
 
 // Which kernel a decode call takes, and whether that kernel can also do the chunk merge.
 // single: every sequence is one chunk (no merge needed at all); wide: the head_dim 512 matrix-core kernel
-struct Route { bool ok, use_mfma, merge, single, wide; };
-// The in-kernel merge ends the kernel with a chain of device-wide round trips (publish the partial,
-// count in, read all partials) that one block walks alone: about 5 us, against about 3.5 us for the
-// separate merge kernel plus its launch.  It pays where the call is bound by launch overhead, not by
-// the stream: below this many packed bytes per call.
+// merge, merge_step: whether a decode, a decode step's launch also does the chunk merge.
+// small_tile: at most eight query rows to a block.
+struct Route { bool ok, use_mfma, merge, merge_step, single, wide, small_tile; };
+// The in-kernel merge ends the kernel with a chain of device-wide round trips (publish the partial, count in, read
+// all partials) that one block per KV head walks alone: about 2.5 us for up to 32 chunks, against about 3.5 us for the
+// separate merge kernel plus its launch; with 64 and 128 chunks to a row that one compute unit pulls in for too long
+// (one KV head, 8 heads, us per step, in place / merge kernel: 16K tokens, 64 chunks, 13.0 / 11.4; 128K, 128 chunks,
+// 20.9 / 15.8).  A decode step merges in place wherever that holds (128K tokens, 64 heads over 8, 33.3 -> 32.9 us;
+// 8 sequences of 8K 21.9 -> 20.6; 32 heads over 32, 32K, 31.4 -> 29.9); the decode alone up to this many packed bytes per
+// call: above, it keeps its two phases as the separate launches that tq_decode_launches has always told of.
 constexpr int64_t kMergeInKernelMaxBytes = 48ll << 20;
+constexpr int kMergeInKernelMaxChunks = 32;
 
 // tokens a sequence of length seq_len attends under the options' sliding window
 // (several query tokens: the span all rows together attend, the earliest row's window start to the end)
@@ -157,35 +163,35 @@ Route route_of(const tq_kv_cache* cache, int n_q_heads, int seq_len, float attn_
   if (!tq::mfma_supports_group(cache->head_dim, cache->group_size, cache->capacity) || pairs_split ||
       (larger && cache->head_dim == 256 && (variant == 2 || queries_of(opts) > 1))) {
     const bool ok = variant != 2 && queries_of(opts) == 1;
-    return {ok, false, false, false, false};
+    return {ok, false, false, false, false, false, false};
   }
   // the matrix-core kernel folds attn_scale into its exp2 argument and needs it positive and finite
   const bool scale_ok = attn_scale > 0.0f && std::isfinite(attn_scale);
-  if (variant == 2 && !scale_ok) return {false, false, false, false, false};
+  if (variant == 2 && !scale_ok) return {false, false, false, false, false, false, false};
   // head_dim 512: its own matrix-core kernel (any finite scale), partials merged by the merge kernel
   if (variant != 1 && tq::wide_supported(cache->head_dim) && std::isfinite(attn_scale))
-    return {true, false, false, false, true};
+    return {true, false, false, false, false, true, false};
   // the matrix-core kernel addresses a (batch, KV head) row of codes with 32-bit byte offsets
   const bool offsets_ok = (int64_t)seq_len * (cache->head_dim / 2) < (1ll << 31);
-  if (variant == 2 && !offsets_ok) return {false, false, false, false, false};
+  if (variant == 2 && !offsets_ok) return {false, false, false, false, false, false, false};
   const int rows = rows_of(cache, n_q_heads, opts);
   const bool use_mfma = variant == 2 || (variant == 0 && scale_ok && offsets_ok &&
                                          tq::mfma_supported(cache->head_dim, rows));
-  if (!use_mfma && queries_of(opts) > 1) return {false, false, false, false, false};
+  if (!use_mfma && queries_of(opts) > 1) return {false, false, false, false, false, false, false};
   // (more query rows than the kernel's tile holds: several blocks stream each KV head, counted as rows of their own)
   const int rows_per_batch = cache->n_kv_heads * std::max(1, use_mfma ? mfma_share_of(cache, n_q_heads, opts) : 1);
   const int64_t bytes = (int64_t)tq_kv_bytes(cache->batch, rows_per_batch, windowed(seq_len, opts), cache->head_dim);
   // a sequence that is one chunk needs no merge at all: the kernel writes the output itself, whatever the size
-  const bool single = use_mfma && plan_splits(cache->batch, rows_per_batch, windowed(seq_len, opts),
-                                               opts ? opts->n_splits : 0, kBlocksMfma, 8).n_splits == 1;
+  const int chunks = plan_splits(cache->batch, rows_per_batch, windowed(seq_len, opts), opts ? opts->n_splits : 0,
+                                 kBlocksMfma, 8).n_splits;
+  const bool single = use_mfma && chunks == 1;
   // (a 16-row tile leaves the last block twice the partials to fetch: there the merge kernel is the faster end,
   //  measured 21.8 against 24.1 us with 16 heads per KV head at 32K tokens)
   const bool small_tile = rows_per_batch == 0 || rows * cache->n_kv_heads / rows_per_batch <= 8;
-  // (larger groups at head_dim 256 keep the two launches tq_decode_launches has always answered for them)
-  const bool merge = use_mfma && (single || (bytes <= kMergeInKernelMaxBytes && small_tile &&
-                                             !(larger && cache->head_dim == 256) &&
-                                             tq::mfma_can_merge(cache->batch, rows_per_batch)));
-  return {true, use_mfma, merge, single && merge, false};
+  const bool in_place = small_tile && chunks <= kMergeInKernelMaxChunks && tq::mfma_can_merge(cache->batch, rows_per_batch);
+  // (larger groups at head_dim 256, decode alone: two launches as well)
+  const bool merge = use_mfma && (single || (in_place && bytes <= kMergeInKernelMaxBytes && !(larger && cache->head_dim == 256)));
+  return {true, use_mfma, merge, use_mfma && (single || in_place), single && merge, false, small_tile};
 }
 
 // waves that share one (sequence, KV head) row where single-chunk rows are packed several to a block
@@ -284,22 +290,26 @@ int run_partial(PartialRequest& rq) {
     // many sequences: the slots of several rounds share blocks (2, 4 or 8 to a block) and run in one
     if (use_mfma) p.waves_per_row = rounds > 4 ? 1 : rounds > 2 ? 2 : rounds > 1 ? 4 : 8;
   }
-  rq.params = p;
-  if (append) {                                   // one of the two kernels takes the token in
-    DecodeParams& taker = use_mfma ? p : rq.params;
-    taker.k_new = static_cast<const half_t*>(rq.k_new);
-    taker.v_new = static_cast<const half_t*>(rq.v_new);
-    taker.append_pos = seq_len - 1;
-  }
   rq.n_splits = plan.n_splits;
   hipStream_t s = static_cast<hipStream_t>(rq.stream);
-  rq.merged = ranked > 0 || (rq.out != nullptr && r.merge && !seq_lens);
+  rq.merged = ranked > 0 || (rq.out != nullptr && (append ? r.merge_step : r.merge) && !seq_lens);
   int merge_slot = -1;
   if (rq.merged) {
     // several chunks: the arrival counters of this workspace (none left: the merge kernel does it); rows that are
     // single chunks count nothing
     merge_slot = plan.n_splits > 1 ? tq::mfma_merge_slot_of(rq.workspace) : 0;
     if (merge_slot < 0) rq.merged = false;
+  }
+  rq.params = p;
+  if (append) {
+    // One of the two kernels takes the token in: the decode kernel where it writes the output (there is no other) and
+    // with up to eight rows to a block; with sixteen its sixteen scores are on the way of a short chunk and the merge
+    // kernel, which there always is, is the cheaper place (128 heads over 8, 8K tokens, 15.3 / 14.5 us per step).
+    const bool here = use_mfma && (rq.merged || r.small_tile || cache->group_size != tq::kGroup);
+    DecodeParams& taker = here ? p : rq.params;
+    taker.k_new = static_cast<const half_t*>(rq.k_new);
+    taker.v_new = static_cast<const half_t*>(rq.v_new);
+    taker.append_pos = seq_len - 1;
   }
   if (ranked) {
     p.ranked = 1;

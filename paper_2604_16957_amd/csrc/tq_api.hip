@@ -225,6 +225,7 @@ struct PartialRequest {
   const tq_decode_opts* opts = nullptr;
   const void* k_new = nullptr;         // append-and-attend: the step's new token (then seq_len includes it), taken in
   const void* v_new = nullptr;         // by the matrix-core kernel, or by the merge kernel behind the others
+  bool step = false;                   // a decode step (the new token(s) may be in the cache already)
   const tq::PagedView* paged = nullptr;
   void* stream = nullptr;
   // results
@@ -292,7 +293,7 @@ int run_partial(PartialRequest& rq) {
   }
   rq.n_splits = plan.n_splits;
   hipStream_t s = static_cast<hipStream_t>(rq.stream);
-  rq.merged = ranked > 0 || (rq.out != nullptr && (append ? r.merge_step : r.merge) && !seq_lens);
+  rq.merged = ranked > 0 || (rq.out != nullptr && (rq.step ? r.merge_step : r.merge) && !seq_lens);
   int merge_slot = -1;
   if (rq.merged) {
     // several chunks: the arrival counters of this workspace (none left: the merge kernel does it); rows that are
@@ -551,6 +552,7 @@ int tq_sdpa_int4_append_decode(const tq_kv_cache* cache, const void* k_new, cons
   rq.workspace = workspace;
   rq.opts = opts;
   rq.stream = stream;
+  rq.step = true;
   // The matrix-core kernel takes the token in, or the merge kernel behind the others (there with groups of 32 only);
   // one query token, at least one cached token to attend: no append launch, nothing read back.  Else the append
   // kernel runs first.

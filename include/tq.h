@@ -176,8 +176,9 @@ int tq_sdpa_int4_append_decode(const tq_kv_cache* cache, const void* k_new, cons
  * max_seq_len (host, <= capacity) only bounds them.  With opts->n_splits == 0 the kernels plan the
  * chunks themselves from the lengths, so that every block gets about the same number of tokens
  * whatever the mix (the cost follows the SUM of the lengths); with n_splits > 0 the sequence range
- * [0, max_seq_len) is cut into that many chunks and those past a sequence's end do no work.  Always
- * two launches (partial kernel + merge kernel).  Other arguments and errors as for
+ * [0, max_seq_len) is cut into that many chunks and those past a sequence's end do no work.  Two
+ * launches (partial kernel + merge kernel), or one where many sequences of moderate length make every
+ * (sequence, KV head) row a block of its own.  Other arguments and errors as for
  * tq_sdpa_int4_decode (EMPTY / CAPACITY refer to max_seq_len). */
 int tq_sdpa_int4_decode_varlen(const tq_kv_cache* cache, const void* q, int32_t n_q_heads,
                                const int32_t* seq_lens, int32_t max_seq_len, float attn_scale,

@@ -14,6 +14,7 @@ constexpr int kGroup = 32;        // elements per quantisation group (Sec. 2.1):
                                   // quantiser handles.  Groups of 64 and 128 (DecodeParams::group) take the generic kernels.
 constexpr int kMaxSplits = 128;   // upper bound on sequence chunks (Sec. 3.2); sizes the workspace
 constexpr int kTile = 32;         // chunk boundaries are multiples of this many tokens
+constexpr int kRankMaxBatch = 512;   // sequences a launch can order by their lengths (RankedRows)
 constexpr int kMaxQueries = 8;    // query tokens per sequence in one call (the masked path covers two supertiles)
 
 typedef _Float16 half_t;
@@ -301,41 +302,41 @@ __device__ inline bool var_plan(const DecodeParams& p, int slot, VarPlan& out) {
   return found;
 }
 // The sequences in the order of their lengths in 32-token tiles, the longest first (ties by index), and whether those
-// lengths are even.  Up to 64 * kPlanTiles sequences, one per lane and register; the length that r sequences exceed is
+// lengths are even.  One sequence per lane and register, up to 64 * TILES of them; the length that r sequences exceed is
 // found bit by bit with wave-wide counts, then the sequence among those of that length.  (Even lengths, and more
 // sequences than that, taken for even: in the given order.)  Wave-uniform; all lanes must be active.
+template <int TILES>
 struct RankedRows {
-  VarLens L;
+  int len[TILES];
   bool even;
   __device__ RankedRows(const DecodeParams& p) {
     even = p.waves_per_row > 1;
-    if (p.batch > 64 * kPlanTiles) return;
-    var_lens_load(p, L);                          // (0 past the batch, at least 1 inside it)
+    if (p.batch > 64 * TILES) return;
     int mine = 0, most = 0;
 #pragma unroll
-    for (int t = 0; t < kPlanTiles; ++t) {
-      L.len[t] = (L.len[t] + 31) >> 5;
-      mine += L.len[t];
-      most = max(most, L.len[t]);
+    for (int t = 0; t < TILES; ++t) {             // (0 past the batch, at least 1 inside it)
+      len[t] = t * 64 < p.batch ? (var_len_of_lane(p, t) + 31) >> 5 : 0;
+      mine += len[t];
+      most = max(most, len[t]);
     }
     even = even && (wave_max(most) - p.rank_spread) * p.batch <= wave_sum(mine);
   }
   __device__ int at_least(int v) const {
     int n = 0;
 #pragma unroll
-    for (int t = 0; t < kPlanTiles; ++t) n += __popcll(__ballot(L.len[t] >= v));
+    for (int t = 0; t < TILES; ++t) n += __popcll(__ballot(len[t] >= v));
     return n;
   }
   __device__ int sequence(const DecodeParams& p, int r) const {
-    if (even || p.batch > 64 * kPlanTiles) return r;
+    if (even || p.batch > 64 * TILES) return r;
     int v = 0;                                    // the largest length that more than r sequences reach
     for (int bit = 1 << (31 - __clz(((p.seq_len + 31) >> 5) | 1)); bit > 0; bit >>= 1)
       if (at_least(v | bit) > r) v |= bit;
     int i = r - at_least(v + 1), b = r;           // i: which of the sequences of that length
     bool found = false;
 #pragma unroll
-    for (int t = 0; t < kPlanTiles; ++t) {
-      const uint64_t same = __ballot(L.len[t] == v);
+    for (int t = 0; t < TILES; ++t) {
+      const uint64_t same = __ballot(len[t] == v);
       const int n = __popcll(same), lane = threadIdx.x & 63;
       if (!found && i < n) {
         const bool me = ((same >> lane) & 1) != 0 && __popcll(same & ((1ull << lane) - 1)) == i;

@@ -1,0 +1,137 @@
+"""Many sequences with lengths of their own: the launches in which every (sequence, KV head) row is one chunk of a block
+of its own, longest row first, and where they give way to the device-planned chunk list.  Every row against the oracle;
+and, for the mixes that an ordering or a bound exists for, that it does what it is there for."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2604_16957_amd as tq
+import tq_workloads as wl
+from gpu_common import assert_close_elementwise, gpu_cache_from, make, np16, oracle_cache_from
+
+pytestmark = pytest.mark.gpu
+
+
+def _uneven(batch, longest, seed):
+    """Mostly short lengths with many ties, a few long ones (the longest among them), in no order."""
+    rng = np.random.default_rng(seed)
+    lens = rng.integers(2, 97, batch)
+    lens[: batch // 4] = rng.choice([32, 33, 64, 65, 96], batch // 4)
+    lens[: max(1, batch // 32)] = rng.integers(longest // 2, longest + 1, max(1, batch // 32))
+    lens[0] = longest
+    return [int(n) for n in rng.permutation(lens)]
+
+
+def _reference(q, ocache, lens, alpha, window):
+    rows = []
+    for b, n in enumerate(lens):
+        lo = max(0, n - window) if window else 0
+        one = [np.ascontiguousarray(a[b:b + 1, :, lo:n]) for a in ocache]
+        rows.append(oracle.attend_packed(np16(q[b:b + 1]), *one, seq_len=n - lo, alpha=alpha))
+    return np.concatenate(rows, axis=0)
+
+
+def check(B, Hq, Hkv, d, lens, S, group=32, page=0, window=0):
+    """A decode, twice (bit for bit alike), and a step that brings every sequence's last token, against the oracle."""
+    w = wl.custom(batch=B, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=d, seq_len=max(lens), seed=9000 + B + Hkv + S + group)
+    q, k, v = make(w)
+    ocache = oracle_cache_from(k, v, group=group)
+    ref = _reference(q, ocache, lens, w.attn_scale, window)
+    lens_dev = torch.tensor(lens, dtype=torch.int32).cuda()
+    k_new = torch.stack([k[b, :, n - 1:n] for b, n in enumerate(lens)]).contiguous().cuda()
+    v_new = torch.stack([v[b, :, n - 1:n] for b, n in enumerate(lens)]).contiguous().cuda()
+    if page:
+        blocks = -(-S // page)
+        cache = tq.KVCache(B * blocks, Hkv, d, page, group_size=group)
+        table = torch.randperm(B * blocks, generator=torch.Generator().manual_seed(B + S)).to(torch.int32).reshape(B, blocks).cuda()
+        tq.tq_quantize_kv_paged(cache, table, k.cuda(), v.cuda(), torch.zeros(B, dtype=torch.int32, device="cuda"))
+        decode = lambda: tq.tq_sdpa_int4_decode_paged(cache, table, q.cuda(), lens_dev, S, w.attn_scale, window=window)
+        step = lambda: tq.tq_sdpa_int4_append_decode_paged(cache, table, k_new, v_new, q.cuda(), lens_dev, S, w.attn_scale, window=window)
+    else:
+        cache = gpu_cache_from(k, v, capacity=S + (S & 1), group=group)
+        decode = lambda: tq.tq_sdpa_int4_decode_varlen(cache, q.cuda(), lens_dev, S, w.attn_scale, window=window)
+        step = lambda: tq.tq_sdpa_int4_append_decode_varlen(cache, k_new, v_new, q.cuda(), lens_dev, S, w.attn_scale, window=window)
+    what = f"{B} sequences, {Hq}/{Hkv} heads, d={d}, bound {S}, g={group}, page={page}, window={window}"
+    out = decode()
+    again = decode()
+    torch.cuda.synchronize()
+    assert_close_elementwise(out, ref, "decode: " + what)
+    assert torch.equal(out, again), what
+    # the step: the last tokens' rows are wiped first, and have to come back bit for bit
+    before = [t.clone() for t in cache.tensors()]
+    for b, n in enumerate(lens):
+        for t in cache.tensors():
+            row = t[int(table[b, (n - 1) // page]), :, (n - 1) % page] if page else t[b, :, n - 1]
+            row.view(torch.uint8).fill_(0xEE)
+    out = step()
+    torch.cuda.synchronize()
+    assert_close_elementwise(out, ref, "step: " + what)
+    for t, old in zip(cache.tensors(), before):
+        assert torch.equal(t.view(torch.uint8), old.view(torch.uint8)), "step: " + what
+
+
+# more than 256 sequences: the order comes from eight registers of lanes instead of four; above 512 it is the given one
+@pytest.mark.parametrize("B,Hkv,longest", [(257, 2, 1500), (300, 4, 1300), (512, 1, 1500), (512, 8, 600), (513, 1, 900)])
+def test_hundreds_of_sequences_each_row_once(B, Hkv, longest):
+    check(B, 2 * Hkv, Hkv, 128, _uneven(B, longest, 31 + B), longest)
+
+
+def _time_us(hq, hkv, lens, S, page=0):
+    """us per decode, from a graph of 20 calls, the median of several replays (caches of random codes)."""
+    B, d = len(lens), 128
+    if page:
+        blocks = -(-S // page)
+        cache = tq.KVCache(B * blocks, hkv, d, page)
+        table = torch.arange(B * blocks, dtype=torch.int32, device="cuda").reshape(B, blocks)
+    else:
+        cache = tq.KVCache(B, hkv, d, S)
+    for t in cache.tensors():
+        t.zero_() if t.dtype != torch.uint8 else t.random_(0, 255)
+    cache.k_scale.fill_(0.05), cache.v_scale.fill_(0.2)
+    q = torch.randn(B, hq, d, device="cuda").half()
+    n = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    ws = torch.empty(tq.tq_workspace_bytes(B, hq, d), dtype=torch.uint8, device="cuda")
+    out = torch.empty_like(q)
+
+    def call():
+        if page:
+            tq.tq_sdpa_int4_decode_paged(cache, table, q, n, S, 0.09, out=out, workspace=ws)
+        else:
+            tq.tq_sdpa_int4_decode_varlen(cache, q, n, S, 0.09, out=out, workspace=ws)
+
+    for _ in range(20):
+        call()
+    torch.cuda.synchronize()
+    graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        call()
+        with torch.cuda.graph(graph, stream=side):
+            for _ in range(20):
+                call()
+    times = []
+    for _ in range(9):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        graph.replay()
+        a.record()
+        for _ in range(10):
+            graph.replay()
+        b.record()
+        torch.cuda.synchronize()
+        times.append(a.elapsed_time(b) * 1e3 / 200)
+    return sorted(times)[4]
+
+
+def _spread_over_the_logarithm(n, lo, hi):
+    lens = [int(round(lo * (hi / lo) ** (i / (n - 1)))) for i in range(n)]
+    return [lens[i] for i in torch.randperm(n, generator=torch.Generator().manual_seed(5)).tolist()]
+
+
+def test_the_order_of_lengths_is_kept_past_256_sequences():
+    """300 sequences against 256 of the same mix: 1.17 times the rows.  In the given order, two rows to a block
+    whatever their lengths, they took 2.5 times as long; ordered, 1.25 times (the bar lies in the middle)."""
+    few = _time_us(32, 4, _spread_over_the_logarithm(256, 64, 2048), 2048)
+    many = _time_us(32, 4, _spread_over_the_logarithm(300, 64, 2048), 2048)
+    assert many < 1.75 * few, f"256 sequences {few:.1f} us, 300 {many:.1f} us"

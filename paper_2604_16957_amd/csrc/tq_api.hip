@@ -199,18 +199,58 @@ int waves_per_packed_row(int64_t total_rows, int target) {
   return total_rows > 4 * target ? 1 : total_rows > 2 * target ? 2 : total_rows > target ? 4 : 8;
 }
 
-// Many sequences with their own lengths: where the (sequence, KV head) rows fill at least two rounds of eight-wave
-// blocks, every row is ONE chunk of its own length in a block of its own (DecodeParams::ranked), with as many waves
-// (8, 4, 2, 1) as make about two rounds of what the chip holds; the decode kernel writes the output itself, and
-// neither the device-side chunk plan nor the merge kernel is needed.  Up to about a thousand tokens per wave, or the
-// launch lasts as long as the longest row.  Returns the waves per row, 0 = not this way.
-int ranked_waves(const tq_kv_cache* cache, int n_q_heads, int seq_len, float attn_scale, const tq_decode_opts* opts) {
-  if (queries_of(opts) > 1 || (opts && opts->n_splits > 0)) return 0;
+// Many sequences with their own lengths: from two rounds of eight-wave blocks on (512 (sequence, KV head) rows), every
+// row can be ONE chunk of its own length in a block of its own (DecodeParams::ranked), with as many waves (8, 4, 2, 1)
+// as make one or two rounds of what the chip holds; the decode kernel writes the output itself, and neither the
+// device-side chunk plan nor the merge kernel is needed.  But such a row is never cut: the launch lasts at least as long
+// as the longest row (about 1.05 us per 32 tokens of a wave, and 8 us), whatever the others are, where the plan's lasts
+// as long as the sum.  The host knows only the bound, so the lines below lie where ONE sequence at the bound among very
+// short ones costs about what the plan takes for it.  us per step, ranked / planned, 64 heads over 8, d = 128, for
+// lengths spread over the logarithm up to the bound | one at the bound, the others 96 | all at the bound:
+//   64 sequences (512 rows)   1024, 4 waves 16.0 / 21.5 | 15.3 / 18.3 | 21.3 / 30.5    2048, 4 waves 23.1 / 26.2 | 21.9 / 19.1 | 33.3 / 43.5
+//                             4096, 8 waves 31.8 / 32.4 | 26.1 / 21.5 | 58.9 / 76.3    8192, 8 waves 45.2 / 44.0 | 42.7 / 21.6 | 113 / 121
+//   56 (448 rows, planned)    2048, 4 waves 22.8 / 24.5 | 21.9 / 19.0 | 31.2 / 40.0    4096, 8 waves 28.1 / 29.9 | 26.0 / 19.1 | 54.4 / 62.4
+//   72                        3072, 4 waves 30.8 / 38.1 | 28.8 / 28.0 | 66.2 / 75.8    4096, 8 waves 36.3 / 43.9 | 26.2 / 29.2 | 88.0 / 97.0
+//   128                       3072, 4 waves 40.0 / 44.8 | 29.5 / 28.5 | 86.7 / 100     4096, 4 waves 44.4 / 51.1 | 36.0 / 30.0 | 113 / 129
+//   160                       1500, 2 waves 33.1 / 57.5 | 29.6 / 33.2 | 72.3 / 97.7    2048, 4 waves 41.2 / 63.3 | 28.9 / 33.0 | 92.1 / 123
+//   256                       2048, 2 waves 51.7 / 71.4 | 36.7 / 47.5 | 117 / 146      300: 1024, 1 wave 44.3 / 80.0 | 38.4 / 46.1 | 97.4 / 130
+// and at d = 256, 32 heads over 16: 32 sequences, 2048, 8 waves 32.6 / 33.3 | 25.8 / 22.2 | 58.0 / 69.3, 3072 39.0 / 41.1 |
+// 35.2 / 22.4 | 83.4 / 90.6; 64, 2048, 4 waves 47.0 / 55.3 | 29.2 / 31.2 | 110 / 130; 80, 2048, 4 waves 57.5 / 87.6 |
+// 29.7 / 36.6 | 136 / 207.
+// Sequences past what a launch can order come in the given order: half the tokens per wave (600 sequences, 8 heads over 1,
+// 2048, 4 waves 32.8 / 41.8 | 21.8 / 26.9 | 49.1 / 66.3).
+int ranked_waves(int64_t rows, int batch, int tokens, bool d256) {
+  constexpr int C = kBlocksMfma;
+  if (rows < 2 * C) return 0;
+  int waves = 0;
+  if (rows <= 4 * C) {
+    if (tokens <= (rows <= 9 * C / 4 ? (d256 ? 1024 : 2048) : (d256 ? 2048 : 3072))) waves = 4;
+    else if (rows <= 11 * C / 4 && tokens <= (d256 ? 2048 : 4096)) waves = 8;
+  } else if (rows <= 8 * C) {
+    if (tokens <= 2048) waves = rows <= 6 * C && tokens > (d256 ? 1024 : 1536) ? 4 : 2;
+  } else if (tokens <= 1024) {
+    waves = 1;
+  }
+  return batch > tq::kRankMaxBatch && waves > 1 && tokens > 512 * waves ? 0 : waves;
+}
+struct Ranked { int waves, spread; };             // waves of a row's block, 0 = not this way; DecodeParams::rank_spread
+Ranked ranked_rows(const tq_kv_cache* cache, int n_q_heads, int seq_len, float attn_scale, const tq_decode_opts* opts) {
+  if (queries_of(opts) > 1 || (opts && opts->n_splits > 0)) return {0, -1};
   const Route r = route_of(cache, n_q_heads, seq_len, attn_scale, opts);
-  if (!r.ok || !r.use_mfma) return 0;
+  if (!r.ok || !r.use_mfma) return {0, -1};
   const int64_t rows = (int64_t)cache->batch * cache->n_kv_heads * mfma_share_of(cache, n_q_heads, opts);
-  const int waves = rows <= 2 * kBlocksMfma ? 8 : rows <= 4 * kBlocksMfma ? 4 : rows <= 8 * kBlocksMfma ? 2 : 1;
-  return rows >= 2 * kBlocksMfma && windowed(seq_len, opts) <= 1024 * waves ? waves : 0;
+  const bool d256 = cache->head_dim == 256;
+  const int waves = ranked_waves(rows, cache->batch, windowed(seq_len, opts), d256);
+  // Two rows to a block where the longest is at most 16 tiles (d = 256: 8) per wave of its half block over the average; 5
+  // where the rows fill that one round badly (us per step, two rounds / one, 64 heads over 8: 64 sequences of 128 .. 4096
+  // tokens 31.5 / 37.0, all of 4096 63.9 / 58.9; 256 of 64 .. 2048 75.9 / 80.8, of 64 .. 1024 51.5 / 46.9, all of 1024
+  // 86.6 / 65.6; badly filled: 34 of 33 .. 340, 32 heads over 32, 12.1 / 15.3).  Not where the rows fit one round as they
+  // are (64 of 1024, 4 waves, 21.3 / 24.3), nor where the pairs don't (72 of 4096, 8 waves, 88.0 / 98.4).
+  const int64_t chip = 8 * kBlocksMfma, paired = rows * (waves / 2);
+  int spread = -1;
+  if (cache->batch <= tq::kRankMaxBatch && waves > 1 && rows * waves > chip && paired <= chip)
+    spread = (paired >= chip - kBlocksMfma ? 16 : 5) * (waves / 2) / (d256 ? 2 : 1);
+  return {waves, spread};
 }
 
 // One launch of phase 1: what to attend, and what came of it.
@@ -256,7 +296,9 @@ int run_partial(PartialRequest& rq) {
                                : 1;
   const int mfma_share = use_mfma ? mfma_share_of(cache, n_q_heads, opts) : 1;
   const int rows_per_batch = cache->n_kv_heads * (use_mfma ? mfma_share : row_tiles);
-  const int ranked = seq_lens && rq.out != nullptr ? ranked_waves(cache, n_q_heads, seq_len, rq.attn_scale, opts) : 0;
+  const Ranked rank = seq_lens && rq.out != nullptr ? ranked_rows(cache, n_q_heads, seq_len, rq.attn_scale, opts)
+                                                    : Ranked{0, -1};
+  const bool ranked = rank.waves > 0;
   const Plan plan = plan_splits(cache->batch, rows_per_batch, attended, ranked ? 1 : opts ? opts->n_splits : 0,
                                 target, use_mfma ? 8 : r.wide ? 2 : 1);
   DecodeParams p = make_params(cache, rq.q, n_q_heads, seq_len, rq.attn_scale, rq.out, rq.workspace, plan,
@@ -293,7 +335,7 @@ int run_partial(PartialRequest& rq) {
   }
   rq.n_splits = plan.n_splits;
   hipStream_t s = static_cast<hipStream_t>(rq.stream);
-  rq.merged = ranked > 0 || (rq.out != nullptr && (rq.step ? r.merge_step : r.merge) && !seq_lens);
+  rq.merged = ranked || (rq.out != nullptr && (rq.step ? r.merge_step : r.merge) && !seq_lens);
   int merge_slot = -1;
   if (rq.merged) {
     // several chunks: the arrival counters of this workspace (none left: the merge kernel does it); rows that are
@@ -314,13 +356,8 @@ int run_partial(PartialRequest& rq) {
   }
   if (ranked) {
     p.ranked = 1;
-    p.waves_per_row = ranked;
-    // two rows to a block where the longest is at most 16 tiles per wave of its half block over the average; 5 where
-    // the rows fill that one round badly (measured on 64 heads over 8, us per step, two rounds / one: 64 sequences of
-    // 128 .. 4096 tokens 31.5 / 37.0, of 256 .. 2048 28.5 / 26.1, all of 1024 26.9 / 20.6; 256 of 64 .. 2048 75.9 / 80.8,
-    // of 64 .. 1024 51.5 / 46.9, all of 1024 86.6 / 65.6; badly filled: 34 of 33 .. 340, 32 heads over 32, 12.1 / 15.3)
-    const int64_t waves_at_once = (int64_t)cache->batch * rows_per_batch * (ranked / 2);
-    p.rank_spread = (waves_at_once >= 7 * kBlocksMfma ? 16 : 5) * (ranked / 2);
+    p.waves_per_row = rank.waves;
+    p.rank_spread = rank.spread;
   } else if (rq.merged && use_mfma && plan.n_splits == 1 && !rq.paged) {
     // more single-chunk rows than the chip holds blocks: pack 2, 4 or 8 of them into a block
     p.waves_per_row = waves_per_packed_row((int64_t)cache->batch * rows_per_batch, target);

@@ -1549,6 +1549,7 @@ hipError_t launch_partial_mfma(const DecodeParams& p_in, int batch, int head_dim
   }
   if (p.waves_per_row != 1 && p.waves_per_row != 2 && p.waves_per_row != 4) p.waves_per_row = 8;
   if (p.ranked && (p.seq_lens == nullptr || p.merge_slot < 0 || p.n_splits != 1 || p.var_chunks > 0)) return hipErrorInvalidValue;
+  if (p.ranked && p.waves_per_row == 1 && p.rank_spread >= 0) return hipErrorInvalidValue;   // (a wave is not shared by two rows)
   // several units per block: single-chunk rows whose output the kernel writes itself, or the slots of a chunk list
   if (p.waves_per_row != 8 && !p.ranked && p.var_chunks == 0 && (p.merge_slot < 0 || p.n_splits != 1 || p.block_table))
     return hipErrorInvalidValue;

@@ -79,7 +79,7 @@ struct DecodeParams {
   // Matrix-core kernel, many sequences with lengths of their own: every (sequence, KV head) row is one chunk with a
   // block of waves_per_row waves to itself (or, where the lengths are even, half of one: see RankedRows), and blockIdx.z
   // counts the sequences from the longest to the shortest.  rank_spread: by how many tiles the longest sequence may
-  // exceed the average for the lengths to count as even.
+  // exceed the average for the lengths to count as even (negative: they never do).
   int32_t ranked, rank_spread;
   int32_t merge_slot;       // matrix-core kernel: >= 0 selects a set of arrival counters and makes the last
                             // block of every (b, kv head) merge the chunks and write `out`; < 0: partials only
@@ -304,13 +304,13 @@ __device__ inline bool var_plan(const DecodeParams& p, int slot, VarPlan& out) {
 // The sequences in the order of their lengths in 32-token tiles, the longest first (ties by index), and whether those
 // lengths are even.  One sequence per lane and register, up to 64 * TILES of them; the length that r sequences exceed is
 // found bit by bit with wave-wide counts, then the sequence among those of that length.  (Even lengths, and more
-// sequences than that, taken for even: in the given order.)  Wave-uniform; all lanes must be active.
+// sequences than that: in the given order.)  Wave-uniform; all lanes must be active.
 template <int TILES>
 struct RankedRows {
   int len[TILES];
   bool even;
   __device__ RankedRows(const DecodeParams& p) {
-    even = p.waves_per_row > 1;
+    even = false;
     if (p.batch > 64 * TILES) return;
     int mine = 0, most = 0;
 #pragma unroll
@@ -319,7 +319,7 @@ struct RankedRows {
       mine += len[t];
       most = max(most, len[t]);
     }
-    even = even && (wave_max(most) - p.rank_spread) * p.batch <= wave_sum(mine);
+    even = p.rank_spread >= 0 && (wave_max(most) - p.rank_spread) * p.batch <= wave_sum(mine);
   }
   __device__ int at_least(int v) const {
     int n = 0;

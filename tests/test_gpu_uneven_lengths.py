@@ -79,6 +79,59 @@ def test_hundreds_of_sequences_each_row_once(B, Hkv, longest):
     check(B, 2 * Hkv, Hkv, 128, _uneven(B, longest, 31 + B), longest)
 
 
+# Which blocks the rows get follows from their number and the bound alone: (sequences, query heads, KV heads, d, longest,
+# bound); "even": all lengths within two tiles of each other.
+ROUTES = {
+    "one round of 4 waves a row": (64, 16, 8, 128, 1100, 2048),
+    "8 waves a row": (64, 16, 8, 128, 2300, 4096),
+    "8 waves a row, two rounds and a bit": (72, 16, 8, 128, 700, 4096),
+    "4 waves a row": (97, 16, 8, 128, 1100, 3072),
+    "4 waves a row, past two rounds": (129, 16, 8, 128, 700, 2048),
+    "2 waves a row": (161, 16, 8, 128, 900, 1024),
+    "1 wave a row": (261, 16, 8, 128, 600, 1024),
+    "sixteen rows to a tile, 4 waves": (64, 96, 8, 128, 400, 1024),
+    "sixteen rows to a tile, 8 waves": (64, 128, 8, 128, 300, 4000),
+    "d = 256, 4 waves": (32, 32, 16, 256, 600, 1024),
+    "d = 256, 8 waves": (32, 32, 16, 256, 1500, 2048),
+    "d = 256, 2 waves": (80, 32, 16, 256, 300, 1000),
+    "d = 256, 1 wave": (130, 16, 16, 256, 200, 500),
+    # (below 512 rows, or the bound too far: slots of the chunk list, 8, 4, 2 and 1 waves each)
+    "chunk list, 8 waves a slot": (12, 16, 8, 128, 1500, 6000),
+    "chunk list, 4 waves a slot": (30, 16, 8, 128, 900, 6000),
+    "chunk list, 2 waves a slot": (61, 16, 8, 128, 700, 3000),
+    "chunk list, 1 wave a slot": (65, 16, 8, 128, 900, 6000),
+    "chunk list, 1 wave a slot, d = 256": (33, 32, 16, 256, 500, 2500),
+}
+
+
+@pytest.mark.parametrize("mix", ["uneven", "even"])
+@pytest.mark.parametrize("route", ROUTES)
+def test_every_kind_of_block(route, mix):
+    B, Hq, Hkv, d, longest, S = ROUTES[route]
+    lens = _uneven(B, longest, 77 + B)
+    if mix == "even":
+        lens = [int(n) for n in np.random.default_rng(B).integers(130, 194, B)]
+    check(B, Hq, Hkv, d, lens, S)
+
+
+@pytest.mark.parametrize("group", [64, 128])
+@pytest.mark.parametrize("route", ["one round of 4 waves a row", "2 waves a row", "sixteen rows to a tile, 4 waves", "d = 256, 4 waves",
+                                   "d = 256, 2 waves", "chunk list, 1 wave a slot"])
+def test_larger_groups_in_every_kind_of_block(route, group):
+    B, Hq, Hkv, d, longest, S = ROUTES[route]
+    check(B, Hq, Hkv, d, _uneven(B, min(longest, 400), 78 + B), S, group=group)
+
+
+@pytest.mark.parametrize("window", [0, 77])
+@pytest.mark.parametrize("page", [32, 64])
+@pytest.mark.parametrize("route", ["one round of 4 waves a row", "4 waves a row", "2 waves a row", "1 wave a row",
+                                   "sixteen rows to a tile, 4 waves", "d = 256, 4 waves", "chunk list, 1 wave a slot"])
+def test_pages_and_windows_in_every_kind_of_block(route, page, window):
+    """(Under a window the bound is the window: the same rows, then, are ranked with the fewest tokens to a wave.)"""
+    B, Hq, Hkv, d, longest, S = ROUTES[route]
+    check(B, Hq, Hkv, d, _uneven(B, min(longest, 500), 79 + B), S, page=page, window=window)
+
+
 def _time_us(hq, hkv, lens, S, page=0):
     """us per decode, from a graph of 20 calls, the median of several replays (caches of random codes)."""
     B, d = len(lens), 128
@@ -135,3 +188,13 @@ def test_the_order_of_lengths_is_kept_past_256_sequences():
     few = _time_us(32, 4, _spread_over_the_logarithm(256, 64, 2048), 2048)
     many = _time_us(32, 4, _spread_over_the_logarithm(300, 64, 2048), 2048)
     assert many < 1.75 * few, f"256 sequences {few:.1f} us, 300 {many:.1f} us"
+
+
+@pytest.mark.parametrize("page", [0, 64])
+def test_one_long_sequence_does_not_hold_up_many_short_ones(page):
+    """64 sequences of 128 tokens, 8 KV heads, a bound of 8192: with one of them at the bound the plan cuts it up, and
+    the launch takes about as long as the sum of the lengths; as one chunk of one block it took 4 times as long as the
+    short ones alone."""
+    short = _time_us(64, 8, [128] * 64, 8192, page)
+    long = _time_us(64, 8, [128] * 40 + [8192] + [128] * 23, 8192, page)
+    assert long < 1.8 * short, f"64 of 128 tokens {short:.1f} us, one of 8192 among them {long:.1f} us"

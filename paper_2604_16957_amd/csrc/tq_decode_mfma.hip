@@ -1558,6 +1558,8 @@ hipError_t launch_partial_mfma(const DecodeParams& p_in, int batch, int head_dim
                     : per_block > 1  ? dim3(1, (batch * rows_y + per_block - 1) / per_block, 1)
                                      : dim3(p.n_splits, rows_y, batch);
   int gp = padded_gqa(head_dim, p.gqa);
+  // (a 16-row tile has no chunk merge of its own: `out` would stay unwritten)
+  if (gp == 16 && p.merge_slot >= 0 && p.n_splits > 1) return hipErrorInvalidValue;
   if (p.group != kGroup && gp == 4) gp = 8;       // (larger groups at d = 128: the 8- and 16-row layouts only)
   if (head_dim == 128 && gp == 16) return launch<128, 16>(p, grid, s);
   if (head_dim == 128 && gp == 8) return launch<128, 8>(p, grid, s);

@@ -151,6 +151,11 @@ int mfma_share_of(const tq_kv_cache* cache, int n_q_heads, const tq_decode_opts*
   return tq::mfma_kv_share(cache->head_dim, rows_of(cache, n_q_heads, opts));
 }
 
+// whether the matrix-core kernel can take a step's new token in
+bool takes_token(const tq_kv_cache* cache, int n_q_heads, const tq_decode_opts* opts) {
+  return tq::mfma_takes_token(cache->head_dim, cache->group_size, rows_of(cache, n_q_heads, opts));
+}
+
 Route route_of(const tq_kv_cache* cache, int n_q_heads, int seq_len, float attn_scale, const tq_decode_opts* opts) {
   const int variant = opts ? opts->variant : 0;
   // groups of 64 or 128 elements: the matrix-core kernel at head_dim 128 and 256 (see mfma_supports_group), else the
@@ -348,7 +353,7 @@ int run_partial(PartialRequest& rq) {
     // One of the two kernels takes the token in: the decode kernel where it writes the output (there is no other) and
     // with up to eight rows to a block; with sixteen its sixteen scores are on the way of a short chunk and the merge
     // kernel, which there always is, is the cheaper place (128 heads over 8, 8K tokens, 15.3 / 14.5 us per step).
-    const bool here = use_mfma && (rq.merged || r.small_tile || cache->group_size != tq::kGroup);
+    const bool here = use_mfma && takes_token(cache, n_q_heads, opts) && (rq.merged || r.small_tile || cache->group_size != tq::kGroup);
     DecodeParams& taker = here ? p : rq.params;
     taker.k_new = static_cast<const half_t*>(rq.k_new);
     taker.v_new = static_cast<const half_t*>(rq.v_new);
@@ -590,10 +595,11 @@ int tq_sdpa_int4_append_decode(const tq_kv_cache* cache, const void* k_new, cons
   rq.opts = opts;
   rq.stream = stream;
   rq.step = true;
-  // The matrix-core kernel takes the token in, or the merge kernel behind the others (there with groups of 32 only);
-  // one query token, at least one cached token to attend: no append launch, nothing read back.  Else the append
-  // kernel runs first.
-  if (queries_of(opts) == 1 && windowed(seq_len, opts) >= 2 && (r.use_mfma || cache->group_size == tq::kGroup)) {
+  // The matrix-core kernel takes the token in, or the merge kernel behind it or the others (there with groups of 32
+  // only); one query token, at least one cached token to attend: no append launch, nothing read back.  Else the
+  // append kernel runs first (also for a tile that takes no token and writes the output itself).
+  const bool taken_in = r.use_mfma ? !r.merge_step || takes_token(cache, n_q_heads, opts) : cache->group_size == tq::kGroup;
+  if (queries_of(opts) == 1 && windowed(seq_len, opts) >= 2 && taken_in) {
     rq.k_new = k_new;
     rq.v_new = v_new;
   } else {                                        // the append kernel first, then the plain decode
@@ -648,8 +654,10 @@ namespace {
 // tokens), else the append kernel runs first.
 int append_decode_with_lengths(PartialRequest& rq, const void* k_new, const void* v_new) {
   const tq_decode_opts* opts = rq.opts;
-  const bool taken_in = route_of(rq.cache, rq.n_q_heads, rq.seq_len, rq.attn_scale, opts).use_mfma ||
-                        rq.cache->group_size == tq::kGroup;
+  const bool taken_in = route_of(rq.cache, rq.n_q_heads, rq.seq_len, rq.attn_scale, opts).use_mfma
+                            ? takes_token(rq.cache, rq.n_q_heads, opts) ||
+                                  ranked_rows(rq.cache, rq.n_q_heads, rq.seq_len, rq.attn_scale, opts).waves == 0
+                            : rq.cache->group_size == tq::kGroup;
   if (queries_of(opts) == 1 && !(opts && opts->window == 1) && rq.seq_len >= 2 && taken_in) {
     rq.k_new = k_new;
     rq.v_new = v_new;

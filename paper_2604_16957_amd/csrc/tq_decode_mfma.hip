@@ -338,13 +338,23 @@ __device__ __forceinline__ void wait_loads() {               // until at most N 
 //
 // PAGED = a pool of pages (with PLAIN: never).  An instance of its own keeps the page look-ups out of the others'
 // scalar registers, of which the general instance has none to spare.
-enum Mode { kPlain, kGeneral, kPaged };
+enum Mode { kPlain, kPlainStep, kGeneral, kPaged };   // kPlainStep: see LEAN
+// LEAN: the 16-row tile's instances for plain launches and for blocks that share a KV head take no new token and come to
+// the masked last supertile at the end.  Two stretches of code that few waves run, between the prologue and the loop, are
+// two cold jumps for the instruction cache on every launch, and these launches are short: 128 heads over 8, 8K tokens,
+// decode 13.54 us with both, 13.5 with either, 13.02 with neither; 3.3K 12.87 / 12.40; 4 query tokens, 64 heads over 8,
+// 32K, 26.5 / 26.1 per step.  (With up to eight rows the steps gain more by both than this costs.)  The step of one short
+// sequence, whose only launch takes the token in, keeps a plain instance with both: 128 heads over 8, 300 tokens, 11.3 us,
+// 12.3 with an append launch or the general instance.
+template <int GP, bool NT, Mode MODE, int GS>
+constexpr bool lean_tile() { return GP == 16 && GS == 0 && (MODE == kPlain || !NT); }
 template <int D, int GP, int NW, bool NT, Mode MODE, int GS = 0>
 __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_kernel(DecodeParams p) {
-  constexpr bool PLAIN = MODE == kPlain, paged = MODE == kPaged;
+  constexpr bool PLAIN = MODE == kPlain || MODE == kPlainStep, paged = MODE == kPaged;
   using C = Cfg<D, GP, NW, GS>;
   static_assert(GS == 0 || D == 256 || ((C::PERM || C::WIDE) && !PLAIN), "larger groups at d = 128: the gathered layouts");
   constexpr bool SPLIT = GS > 0 && D == 256;
+  constexpr bool LEAN = lean_tile<GP, NT, MODE, GS>();
   constexpr int NGM = C::NGM;
   constexpr int SZB = (D / kGroup * 2) >> GS;     // bytes of one metadata array per token
   constexpr int NG = C::NG, NA = C::NA, NJ = C::NJ, NCS = C::NCS, TB = C::TB, NS = C::NS, LPS = C::LPS, GR = C::GR;
@@ -444,7 +454,7 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   const bool var_lens = !PLAIN && p.seq_lens != nullptr;
   // a decode step (p.k_new set): the step's new token is not among the tokens the chunks cover; the block of the
   // sequence's first chunk takes it in (see `takes`).  A sequence may hold nothing but its new token.
-  const bool new_here = p.k_new != nullptr && split == 0 && row_valid;
+  const bool new_here = !LEAN && p.k_new != nullptr && split == 0 && row_valid;
   const int new_pos = !var_lens ? p.append_pos : p.k_new == nullptr ? -1 : max(1, min(p.seq_lens[b], p.seq_len)) - 1;
   const int seq = !row_valid || (var_lens && new_pos == 0) ? 0 : !var_lens ? p.seq_len : planned_len >= 0 ? planned_len : var_len(p, b);
   const int start = !var_lens ? p.start : p.window > 0 ? var_start(p, b) : 0;
@@ -661,14 +671,15 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   // A wave whose share includes the ragged (or partly masked) last supertile takes that one FIRST: its loads then leave
   // with the prologue's and its masked path runs while the wave's first full supertile is on its way.  (At the end it
   // was a memory round trip of its own for one wave of the launch, 2 - 3 us of a short sequence's time.)
-  const bool tail0 = n_tail > 0 && count_of(n_full + 1) != count_of(n_full);
+  const bool tail_last = n_tail > 0 && count_of(n_full + 1) != count_of(n_full);
+  const bool tail0 = !LEAN && tail_last;
   if (tail0) issue_tail(0, n_full);
   else if (n_mine > 0) issue(0, sidx_of(0));
   // (the first loads are on their way: whatever they do not need is worked out behind them)
   __builtin_amdgcn_sched_barrier(0);
   bool tail_mine[4];                              // [2], [3]: the masked FIRST supertile(s) (see `head`), the one just
                                                   // before `begin` and the one before that
-  tail_mine[0] = tail0;
+  tail_mine[0] = tail_last;
   tail_mine[1] = n_tail > 1 && count_of(n_full + 2) != count_of(n_full + 1);
   tail_mine[2] = head && (whole ? wave == 0 : sub == 0);
   tail_mine[3] = head2 && (whole ? wave == 0 : sub == 0);
@@ -1192,9 +1203,9 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
     slot = next;
   }
   wait_loads<0>();                                           // (nothing is out any more: the rings are quiet)
-  if constexpr (!PLAIN) {
+  if constexpr (!PLAIN || LEAN) {
 #pragma unroll 1
-    for (int u = 1; u < 4; ++u) {                            // further masked supertiles: the last but one with several
+    for (int u = LEAN ? 0 : 1; u < (PLAIN ? 1 : 4); ++u) {   // further masked supertiles: the last but one with several
       if (!tail_mine[u]) continue;                           // query tokens, under a window the first (or first two)
       const int sidx = u < 2 ? n_full + u : 1 - u;
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -1490,6 +1501,9 @@ hipError_t launch_mode(const DecodeParams& p, dim3 grid, hipStream_t s) {
   if (p.block_table != nullptr) return launch_nt<D, GP, kPaged, GS>(p, grid, s);
   const bool plain = p.kv_share == 1 && p.n_queries == 1 && p.waves_per_row == 8 && p.var_chunks == 0 && p.seq_lens == nullptr;
   if constexpr (GS == 0 || D == 256) {            // (no plain instances of the larger groups at d = 128)
+    if constexpr (lean_tile<GP, true, kPlain, GS>()) {
+      if (plain && p.k_new != nullptr) return launch_as<D, GP, true, kPlainStep, GS>(p, grid, s);
+    }
     if (plain) return launch_as<D, GP, true, kPlain, GS>(p, grid, s);
   }
   return launch_nt<D, GP, kGeneral, GS>(p, grid, s);
@@ -1515,6 +1529,12 @@ bool mfma_supported(int head_dim, int gqa) { return kv_share_of(head_dim, gqa) >
 bool mfma_supports_group(int head_dim, int group, int capacity) {
   if (group == kGroup || head_dim == 256) return true;
   return head_dim == 128 && (group == 2 * kGroup || (group == 4 * kGroup && capacity % 2 == 0));
+}
+
+// A 16-row tile that shares its KV head with others does not (LEAN).
+bool mfma_takes_token(int head_dim, int group, int rows) {
+  const int share = kv_share_of(head_dim, rows);
+  return share > 0 && !(share > 1 && group == kGroup && padded_gqa(head_dim, rows / share) == 16);
 }
 
 bool mfma_can_merge(int batch, int n_kv_heads) { return (int64_t)batch * n_kv_heads <= kCountersPerSlot; }
@@ -1560,6 +1580,7 @@ hipError_t launch_partial_mfma(const DecodeParams& p_in, int batch, int head_dim
   int gp = padded_gqa(head_dim, p.gqa);
   // (a 16-row tile has no chunk merge of its own: `out` would stay unwritten)
   if (gp == 16 && p.merge_slot >= 0 && p.n_splits > 1) return hipErrorInvalidValue;
+  if (p.k_new != nullptr && !mfma_takes_token(head_dim, p.group, rows)) return hipErrorInvalidValue;
   if (p.group != kGroup && gp == 4) gp = 8;       // (larger groups at d = 128: the 8- and 16-row layouts only)
   if (head_dim == 128 && gp == 16) return launch<128, 16>(p, grid, s);
   if (head_dim == 128 && gp == 8) return launch<128, 8>(p, grid, s);

@@ -381,6 +381,8 @@ bool mfma_supports_group(int head_dim, int group_size, int capacity);   // group
 // tile, 0 = unsupported): the planner counts batch * n_kv_heads * share rows, and the launch is given the same
 // number in DecodeParams::kv_share.
 int mfma_kv_share(int head_dim, int gqa);
+// Whether the kernel can take a step's new token in (DecodeParams::k_new) with this many query rows per KV head.
+bool mfma_takes_token(int head_dim, int group_size, int rows);
 // With merge_slot >= 0 the kernel also does the chunk merge (Eq. 6) and writes p.out: one launch per decode.
 // The slot names the set of arrival counters the launch uses; mfma_merge_slot_of hands every workspace a set of
 // its own, for the life of the process, or -1 once all sets are taken (the caller then runs the merge kernel).

@@ -1741,6 +1741,7 @@ def test_eighty_sequences_with_their_own_lengths_and_a_step(S):
 @pytest.mark.parametrize("group", [32, 64, 128])
 @pytest.mark.parametrize("B,Hq,Hkv,d,S", [
     (1, 8, 1, 128, 2), (1, 8, 1, 128, 33), (1, 64, 8, 128, 1026), (2, 48, 2, 128, 514), (3, 32, 1, 128, 322),   # 1, several chunks; shares
+    (1, 128, 8, 128, 300), (1, 64, 2, 128, 130),                                                                 # 16-row tiles of one chunk
     (1, 4, 2, 256, 34), (2, 16, 2, 256, 1026), (1, 32, 16, 256, 3000),                                           # d = 256; four blocks a head
     (40, 64, 8, 128, 66), (80, 32, 8, 128, 34), (264, 32, 8, 128, 34), (20, 32, 16, 256, 98)])                   # rows packed 2, 4, 8 to a block
 def test_step_takes_the_new_token_in_the_decode_kernel(B, Hq, Hkv, d, S, group):

@@ -91,6 +91,7 @@ ROUTES = {
     "1 wave a row": (261, 16, 8, 128, 600, 1024),
     "sixteen rows to a tile, 4 waves": (64, 96, 8, 128, 400, 1024),
     "sixteen rows to a tile, 8 waves": (64, 128, 8, 128, 300, 4000),
+    "sixteen rows to a tile, two tiles to a KV head": (64, 96, 4, 128, 400, 1024),
     "d = 256, 4 waves": (32, 32, 16, 256, 600, 1024),
     "d = 256, 8 waves": (32, 32, 16, 256, 1500, 2048),
     "d = 256, 2 waves": (80, 32, 16, 256, 300, 1000),

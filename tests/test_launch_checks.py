@@ -27,6 +27,9 @@ int main() {
   DecodeParams p = plain;
   p.gqa = 16; p.n_q_heads = 16;             // sixteen rows to a tile: no chunk merge in the kernel
   ask("tile16_merge", p, 0);
+  p.n_splits = 1; p.tokens_per_split = 64;  // 32 rows in two such tiles: they take no new token
+  p.gqa = 32; p.n_q_heads = 32; p.kv_share = 2; p.k_new = p.v_new = reinterpret_cast<const half_t*>(256);
+  ask("shared_tile_new_token", p, 0);
   DecodeParams r = plain;                   // one chunk per row, blocks of one wave, two rows to a block
   r.n_splits = 1; r.tokens_per_split = 64; r.seq_lens = reinterpret_cast<const int32_t*>(256);
   r.ranked = 1; r.waves_per_row = 1; r.rank_spread = 0;
@@ -55,6 +58,6 @@ def test_a_request_that_is_covered_gets_past_the_checks(answers):
         assert answers["plain"] not in (0, INVALID_VALUE)
 
 
-@pytest.mark.parametrize("request_", ["tile16_merge", "one_wave_two_rows"])
+@pytest.mark.parametrize("request_", ["tile16_merge", "shared_tile_new_token", "one_wave_two_rows"])
 def test_a_request_no_instance_implements_is_refused(answers, request_):
     assert answers[request_] == INVALID_VALUE

@@ -329,8 +329,10 @@ __device__ __forceinline__ void wait_loads() {               // until at most N 
 // address changes with the group.
 //
 // SPLIT (d = 256 with larger groups): the weights p s_v go through the matrix core as TWO fp16 operands, their
-// leading part and the rest, so that they count as in fp32 (22 bits), as they do in the generic kernel that served
-// these shapes before; the reference of the exponentials then also carries an offset that keeps the largest weight
+// leading part and the rest: 22 bits, where the generic kernel that served these shapes before has fp32's 24; queries
+// enter whole (see q_up), and sums are the matrix core's.  Error of the output against 64 bits next to the generic
+// kernel's (fp16 rounding of the output is nearly all of both): 1.00002 of it over ten shapes of 600 .. 32K tokens and
+// three seeds, at most 1.0001.  The reference of the exponentials then also carries an offset that keeps the largest weight
 // near 2^10 whatever the size of the scales (see `softmax`), or small scales would push the rest below fp16's range.
 // The matrix cores have the room (52 instructions per supertile instead of 34, a quarter of its time), and the kernel
 // is bound by the stream like its groups-of-32 instance: 32 heads on 16 KV heads, one sequence of 32K tokens, groups of
@@ -699,6 +701,23 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
 #pragma unroll
     for (int i = 0; i < 4; ++i) qgrp[a][i] = *reinterpret_cast<const half8v*>(qh + (rep * NA + a) * kGroup + i * 8);
 
+  // (SPLIT) Half of the operand's elements are q over 16 (below), and those of a small query would lose bits in fp16's
+  // subnormals, which the fp32 queries of the generic kernel do not.  So a row with no element of 2 or more is taken 16
+  // times (every fp16 is a whole number of 2^-24: q and 16 q are exact), and in the others what is lost lies 2^-22
+  // below the row's largest element.  (A power of two that brings the largest element near 2^14 costs a short step 0.9 us.)
+  float q_up = 1.0f;
+  if constexpr (SPLIT) {
+    uint32_t any = 0;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      const uint4v w = __builtin_bit_cast(uint4v, qraw[j]);
+      any |= (w[0] | w[1]) | (w[2] | w[3]);
+    }
+    // (bit 14 of an fp16: 2 or more; a row's elements are spread over the four 16-lane rows)
+    q_up = blocks_max((any & 0x40004000u) != 0 ? 1.0f : 0.0f) > 0.0f ? 1.0f : 16.0f;
+  }
+  const _Float16 q_lo = (_Float16)q_up, q_hi = (_Float16)(q_up * 0.0625f);
+
   half8v qb[NJ];
 #pragma unroll
   for (int j = 0; j < NJ; ++j) {
@@ -707,10 +726,12 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
     // k-slot order of unpack_word: nibbles 0,4,1,5,2,6,3,7; the "hi" slots carry c*2^-20, so pre-divide by 16
     half8v y = {x[0], x[4], x[1] * (_Float16)0.0625f, x[5] * (_Float16)0.0625f,
                 x[2], x[6], x[3] * (_Float16)0.0625f, x[7] * (_Float16)0.0625f};
+    if constexpr (SPLIT)
+      y = half8v{x[0] * q_lo, x[4] * q_lo, x[1] * q_hi, x[5] * q_hi, x[2] * q_lo, x[6] * q_lo, x[3] * q_hi, x[7] * q_hi};
     if (!mine) y = half8v{0, 0, 0, 0, 0, 0, 0, 0};
     qb[j] = y;
   }
-  float qsum[NA];                                 // 2^-24 * sum of q over each of this lane's groups
+  float qsum[NA];                                 // 2^-24 * sum of the operand's q over each of this lane's groups
 #pragma unroll
   for (int a = 0; a < NA; ++a) {
     float s = 0.0f;
@@ -718,7 +739,7 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
     for (int i = 0; i < 4; ++i)
 #pragma unroll
       for (int e = 0; e < 8; ++e) s += (float)qgrp[a][i][e];
-    qsum[a] = (hl < G) ? s * 0x1p-24f : 0.0f;
+    qsum[a] = (hl < G) ? s * (SPLIT ? 0x1p-24f * q_up : 0x1p-24f) : 0.0f;
   }
   uint32_t new_w = 0;                             // the new token: this lane's packed word, its group's scale and
   half2v new_sz = {0, 0};                         // zero-point, and (lane h of the first 16) its score against row h
@@ -774,7 +795,7 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
       new_score = c == h ? dot : new_score;
     }
   }
-  const float kappa = p.scale_log2 * 0x1p24f;     // raw accumulator units -> log2 units
+  const float kappa = p.scale_log2 * 0x1p24f * (SPLIT ? 1.0f / q_up : 1.0f);   // raw accumulator units -> log2 units
   const float slack = kSlack / kappa;             // the rescale slack in raw units
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the query block has been read: its slot may be refilled
   if (tail0) {
@@ -954,8 +975,10 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   //    SPLIT also turns the sign of everything half way through the wave's supertiles: the matrix core's truncation
   //    pulls an accumulator the same way at every step, and what it takes from the first half it gives back in the
   //    second (32K tokens, flat softmax: 1.4 % of the output's error against 64 bits, most of it fp16 rounding).
+  //    Odd waves start with the other sign, for those that have a supertile or two.
   uint32_t sv_top = 0;                            // (SPLIT) bits of the power of two no scale so far reaches
-  float off = 0.0f, sgn = 1.0f;
+  const float sgn0 = SPLIT && (wave & 1) ? -1.0f : 1.0f;
+  float off = 0.0f, sgn = sgn0;
   auto negate_sums = [&] {
     sgn = -sgn;
 #pragma unroll
@@ -1163,7 +1186,7 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   for (int i = 0; i < n_mine; ++i) {
     const int next = (slot + 1 == NS) ? 0 : slot + 1;
     if constexpr (SPLIT) {
-      if (2 * i >= n_mine && sgn > 0.0f) negate_sums();
+      if (2 * i >= n_mine && sgn == sgn0) negate_sums();
     }
     load_v(slot, vr);
     // The slot's bytes all sit in registers from here on; its refill with supertile i + NS is issued after the

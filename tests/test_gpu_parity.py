@@ -265,10 +265,10 @@ def test_larger_groups_on_the_matrix_cores(shape, group):
 
 @pytest.mark.parametrize("group", [64, 128])
 @pytest.mark.parametrize("n_q,n_kv", [(2, 2), (4, 2), (3, 1), (8, 1)])
-def test_larger_groups_at_256_keep_fp32_weights(n_q, n_kv, group):
+def test_larger_groups_at_256_weights_to_22_bits(n_q, n_kv, group):
     """Groups of 64 / 128 at d = 256 on the matrix cores: one to four blocks per KV head, an odd capacity, lengths
     around the 32-token supertile, windows that start at odd tokens, lengths of their own, a paged pool.  The weights
-    p s_v enter as two fp16 operands and count as in fp32 whatever the size of V's scales (spreads of 1 and 1e-4,
+    p s_v enter as two fp16 operands, 22 bits together, whatever the size of V's scales (spreads of 1 and 1e-4,
     flat and sharp softmaxes).  Per element: half an fp16 ulp of the output (2^-25 in the subnormal range), plus the
     fp32 arithmetic: scores are sums of terms q c s, |terms| up to 400 together at these sizes, truncated at 2^-23 of
     that, 2^-14.3 relative on a weight, on both sides of a mean of values: 2^-13 of the largest |v|."""
@@ -304,6 +304,28 @@ def test_larger_groups_at_256_keep_fp32_weights(n_q, n_kv, group):
     with pytest.raises(tq.TqError) as e:            # several query tokens stay refused with these groups
         tq.tq_sdpa_int4_decode(cache, torch.zeros(2, 2, n_q, d, dtype=torch.float16, device="cuda"), S, 1.0)
     assert e.value.status == -6
+
+
+@pytest.mark.parametrize("group", [64, 128])
+@pytest.mark.parametrize("power", [7, 0, -6, -10, -14, -16])
+def test_larger_groups_at_256_take_small_queries_whole(power, group):
+    """The same scores from queries of any size: q is drawn around 2^power, the scale makes up for it.  Every bit of a
+    small fp16 query counts, in every dim (the kernel's operand holds half of the dims divided by 16).  Heads of one KV
+    head differ in size, one is zero.  Bars as in the test above: half an fp16 ulp of the output, plus 2^-13 of the
+    largest |v| for fp32 scores whose terms add up to at most 400."""
+    d, S, n_q, n_kv = 256, 700, 8, 2
+    w = wl.custom(batch=1, n_q_heads=n_q, n_kv_heads=n_kv, head_dim=d, seq_len=S, seed=2560 + group, attn_scale=1.0, qk_std=1.0)
+    q, k, v = make(w)
+    size = torch.tensor([0.1, 0.03, 0.0, 0.1, 0.01, 0.1, 0.1, 0.05]).reshape(1, n_q, 1)
+    q = (q.float() * size * 2.0 ** power).half()
+    alpha = 2.0 ** -power
+    cache = gpu_cache_from(k, v, group=group)
+    ocache = oracle_cache_from(k, v, group=group)
+    ref = oracle_attend(q, ocache, S, alpha)
+    out = tq.tq_sdpa_int4_decode(cache, q.cuda(), S, alpha)
+    torch.cuda.synchronize()
+    over = np.abs(np16(out).astype(np.float64) - ref) - (np.maximum(2.0 ** -11 * np.abs(ref), 2.0 ** -25) + 2.0 ** -13 * float(v.abs().max()))
+    assert over.max() <= 0, f"queries around 2^{power}: over by {over.max():.2e}"
 
 
 @pytest.mark.parametrize("group", [64, 128])

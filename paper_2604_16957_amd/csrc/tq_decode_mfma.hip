@@ -994,12 +994,12 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
     const float mx = fmaxf(fmaxf(fmaxf(sc[0][0], sc[0][1]), fmaxf(sc[0][2], sc[0][3])),
                            fmaxf(fmaxf(sc[1][0], sc[1][1]), fmaxf(sc[1][2], sc[1][3])));
     bool move = mx > m_run + slack;
-    uint32_t sv = 0;                              // (SPLIT) the largest of this lane's scales (positive fp16: ordered as integers)
+    uint32_t sv = 0;                              // (SPLIT) the largest of this lane's scales by size (positive fp16: ordered as integers)
     if constexpr (SPLIT) {
 #pragma unroll
       for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) sv = max(sv, r.vs[0][t][i]);
+        for (int i = 0; i < 4; ++i) sv = max(sv, r.vs[0][t][i] & 0x7FFFu);
       move = move || sv >= sv_top;
     }
     if (__builtin_amdgcn_ballot_w64(move) != 0) {   // wave-uniform, rare

@@ -329,6 +329,30 @@ def test_larger_groups_at_256_take_small_queries_whole(power, group):
 
 
 @pytest.mark.parametrize("group", [64, 128])
+def test_larger_groups_at_256_take_scales_of_either_sign(group):
+    """A cache that another program filled may hold (c - z) s as (c' - z') (-s): the same values, bit for bit, from
+    codes 15 - c, zero-points 15 - z and scales -s.  Half of V's groups are turned round like that; the generic
+    kernel reads it as what it is, and so does the default one (same bar as above, 2^-13 of the largest |v|)."""
+    d, S, n_q, n_kv = 256, 500, 4, 2
+    w = wl.custom(batch=1, n_q_heads=n_q, n_kv_heads=n_kv, head_dim=d, seq_len=S, seed=2570 + group, attn_scale=1.0, qk_std=0.1)
+    q, k, v = make(w)
+    cache = gpu_cache_from(k, v, group=group)
+    want = tq.tq_sdpa_int4_decode(cache, q.cuda(), S, 1.0, variant=1).float()
+    turn = (torch.arange(S * d // group) % 2 == 0).reshape(1, 1, S, d // group).cuda()
+    exact = turn & ((15.0 - cache.v_zero.float()).half().float() == 15.0 - cache.v_zero.float())   # (15 - z is an fp16)
+    assert int(exact.sum()) > 20
+    cache.v_zero.copy_(torch.where(exact, 15.0 - cache.v_zero.float(), cache.v_zero.float()))
+    cache.v_scale.copy_(torch.where(exact, -cache.v_scale.float(), cache.v_scale.float()))
+    bytes_turned = exact.repeat_interleave(group // 2, dim=-1)
+    cache.v_codes.copy_(torch.where(bytes_turned, 0xFF - cache.v_codes.int(), cache.v_codes.int()))
+    for variant in (1, 0):
+        out = tq.tq_sdpa_int4_decode(cache, q.cuda(), S, 1.0, variant=variant).float()
+        torch.cuda.synchronize()
+        over = (out - want).abs() - (2.0 ** -11 * want.abs()).clamp(min=2.0 ** -25) - 2.0 ** -13 * float(v.abs().max())
+        assert float(over.max()) <= 0, f"variant {variant}: over by {float(over.max()):.2e}"
+
+
+@pytest.mark.parametrize("group", [64, 128])
 def test_larger_groups_full_size(group):
     """The headline shape (64 / 8 heads, d = 128, 131072 tokens) quantised in groups of 64 / 128: cache bit-exact,
     every output element against the oracle."""

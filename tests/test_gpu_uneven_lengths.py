@@ -133,6 +133,17 @@ def test_pages_and_windows_in_every_kind_of_block(route, page, window):
     check(B, Hq, Hkv, d, _uneven(B, min(longest, 500), 79 + B), S, page=page, window=window)
 
 
+# chunks of more than 64 pages: the kernel keeps 64 page numbers at hand and fetches on as it goes.  (B, query heads, KV
+# heads, d, lengths, bound): one whole block to a chunk, half and a quarter of one, a row of its own, eight query rows.
+@pytest.mark.parametrize("window", [0, 4500])
+@pytest.mark.parametrize("B,Hq,Hkv,d,lens,S", [
+    (1, 64, 64, 128, [14000], 14000), (1, 64, 64, 256, [12031], 12031), (2, 128, 128, 128, [5003, 4100], 5003),
+    (9, 32, 32, 128, [4700 + 3 * i for i in range(9)], 4800), (64, 16, 8, 128, [4090] + [50 + i for i in range(63)], 4090),
+    (1, 256, 32, 128, [20001], 20001)])
+def test_chunks_of_more_than_64_pages(B, Hq, Hkv, d, lens, S, window):
+    check(B, Hq, Hkv, d, lens, S, page=32, window=window)
+
+
 def _time_us(hq, hkv, lens, S, page=0):
     """us per decode, from a graph of 20 calls, the median of several replays (caches of random codes)."""
     B, d = len(lens), 128

@@ -127,10 +127,9 @@ DecodeParams make_params(const tq_kv_cache* c, const void* q, int n_q_heads, int
 int hip_rc(hipError_t e) { return e == hipSuccess ? TQ_OK : TQ_ERR_HIP; }
 
 // Which kernel a decode call takes, and whether that kernel can also do the chunk merge.
-// single: every sequence is one chunk (no merge needed at all); wide: the head_dim 512 matrix-core kernel
-// merge, merge_step: whether a decode, a decode step's launch also does the chunk merge.
-// small_tile: at most eight query rows to a block.
-struct Route { bool ok, use_mfma, merge, merge_step, single, wide, small_tile; };
+// merge, merge_step: whether a decode, a decode step's launch also does the chunk merge (or has none to do: one chunk).
+// wide: the head_dim 512 matrix-core kernel; small_tile: at most eight query rows to a block.
+struct Route { bool ok, use_mfma, merge, merge_step, wide, small_tile; };
 // The in-kernel merge ends the kernel with a chain of device-wide round trips (publish the partial, count in, read
 // all partials) that one block per KV head walks alone: about 2.5 us for up to 32 chunks, against about 3.5 us for the
 // separate merge kernel plus its launch; with 64 and 128 chunks to a row that one compute unit pulls in for too long
@@ -168,21 +167,21 @@ Route route_of(const tq_kv_cache* cache, int n_q_heads, int seq_len, float attn_
   if (!tq::mfma_supports_group(cache->head_dim, cache->group_size, cache->capacity) || pairs_split ||
       (larger && cache->head_dim == 256 && (variant == 2 || queries_of(opts) > 1))) {
     const bool ok = variant != 2 && queries_of(opts) == 1;
-    return {ok, false, false, false, false, false, false};
+    return {ok, false, false, false, false, false};
   }
   // the matrix-core kernel folds attn_scale into its exp2 argument and needs it positive and finite
   const bool scale_ok = attn_scale > 0.0f && std::isfinite(attn_scale);
-  if (variant == 2 && !scale_ok) return {false, false, false, false, false, false, false};
+  if (variant == 2 && !scale_ok) return {false, false, false, false, false, false};
   // head_dim 512: its own matrix-core kernel (any finite scale), partials merged by the merge kernel
   if (variant != 1 && tq::wide_supported(cache->head_dim) && std::isfinite(attn_scale))
-    return {true, false, false, false, false, true, false};
+    return {true, false, false, false, true, false};
   // the matrix-core kernel addresses a (batch, KV head) row of codes with 32-bit byte offsets
   const bool offsets_ok = (int64_t)seq_len * (cache->head_dim / 2) < (1ll << 31);
-  if (variant == 2 && !offsets_ok) return {false, false, false, false, false, false, false};
+  if (variant == 2 && !offsets_ok) return {false, false, false, false, false, false};
   const int rows = rows_of(cache, n_q_heads, opts);
   const bool use_mfma = variant == 2 || (variant == 0 && scale_ok && offsets_ok &&
                                          tq::mfma_supported(cache->head_dim, rows));
-  if (!use_mfma && queries_of(opts) > 1) return {false, false, false, false, false, false, false};
+  if (!use_mfma && queries_of(opts) > 1) return {false, false, false, false, false, false};
   // (more query rows than the kernel's tile holds: several blocks stream each KV head, counted as rows of their own)
   const int rows_per_batch = cache->n_kv_heads * std::max(1, use_mfma ? mfma_share_of(cache, n_q_heads, opts) : 1);
   const int64_t bytes = (int64_t)tq_kv_bytes(cache->batch, rows_per_batch, windowed(seq_len, opts), cache->head_dim);
@@ -196,7 +195,7 @@ Route route_of(const tq_kv_cache* cache, int n_q_heads, int seq_len, float attn_
   const bool in_place = small_tile && chunks <= kMergeInKernelMaxChunks && tq::mfma_can_merge(cache->batch, rows_per_batch);
   // (larger groups at head_dim 256, decode alone: two launches as well)
   const bool merge = use_mfma && (single || (in_place && bytes <= kMergeInKernelMaxBytes && !(larger && cache->head_dim == 256)));
-  return {true, use_mfma, merge, use_mfma && (single || in_place), single && merge, false, small_tile};
+  return {true, use_mfma, merge, use_mfma && (single || in_place), false, small_tile};
 }
 
 // waves that share one (sequence, KV head) row where single-chunk rows are packed several to a block
@@ -340,7 +339,8 @@ int run_partial(PartialRequest& rq) {
   }
   rq.n_splits = plan.n_splits;
   hipStream_t s = static_cast<hipStream_t>(rq.stream);
-  rq.merged = ranked || (rq.out != nullptr && (rq.step ? r.merge_step : r.merge) && !seq_lens);
+  // (the chunks of one token fewer may be shorter, and then up to twice as many as the route counted)
+  rq.merged = ranked || (rq.out != nullptr && (rq.step ? r.merge_step : r.merge) && !seq_lens && plan.n_splits <= tq::kMergeMaxChunks);
   int merge_slot = -1;
   if (rq.merged) {
     // several chunks: the arrival counters of this workspace (none left: the merge kernel does it); rows that are

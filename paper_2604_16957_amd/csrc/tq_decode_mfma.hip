@@ -146,14 +146,12 @@ struct Cfg {
   static constexpr int MERGE = (NW * GP * D + 2 * NW * GP + NW * NEWTOK) * 4;  // o, m, l, and the units' new tokens
   // the block-merge area sits behind the rings where both fit into the 160 KB of a compute unit, else on top of them
   static constexpr bool ALIAS = RING + MERGE > 160 * 1024;
-  static constexpr int OFF_MERGE = ALIAS ? 0 : RING;
   // Where the query block of a wave lands before it is turned into operands: in an area of its own if
   // there is room, so that the whole ring can be filled at once; else in the last ring slot.
   // (1 KB behind it: the new token's K and V rows of a step, see `takes`)
   static constexpr int QBLK = GP * D * 2, QAREA = QBLK + 1024;
   static_assert(QAREA <= STAGE, "the query block borrows one ring slot");
   static constexpr bool QSEP = !ALIAS && RING + MERGE + NW * QAREA <= 160 * 1024;
-  static constexpr int OFF_QBLK = RING + MERGE;
   static constexpr int SMEM = ALIAS ? (RING > MERGE ? RING : MERGE) : RING + MERGE + (QSEP ? NW * QAREA : 0);
   // The fp16 scale and zero-point arrays are fetched dword by dword (two groups of one token), and the
   // direct loads may gather: with NA == 2 a lane needs exactly one dword per token, so the dwords are
@@ -1395,22 +1393,18 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   // each block then writes its die's whole L2 back and invalidates it, and a decode of 256 blocks over 8K tokens
   // goes from 11.0 to 13.5 us (release alone +1.2 us, acquire alone +0.9 us), more than the separate merge kernel
   // costs (13.1 us), for no access that the atomics do not already cover.
-  // Everything is asked for at once: wave h fetches the (m, l) of row h's chunks, a chunk or two per lane, and a thread
+  // Everything is asked for at once: wave h fetches the (m, l) of row h's chunks, a chunk per lane, and a thread
   // the chunks' outputs for two neighbouring dims of one row (two threads share a pair where there are fewer pairs than
   // threads, each with every other chunk).  The weights come out of lane reductions while the outputs are on their
   // way; one barrier hands them over.  (With the (m, l) staged through LDS, two barriers, and always 32 loads per single
   // element however few the chunks, this end of the kernel took 3.2 us for 4 chunks and 4 us for 32, of 10 and 11; with
   // the (m, l) fetched by every thread for itself 1.3 and 5.)
   if constexpr (GP <= 8) {                        // (a 16-row tile's chunks go to the merge kernel)
-    static_assert(GP <= NW && kMaxSplits <= 128, "a wave per row, at most two chunks per lane");
-    float* const c_w = reinterpret_cast<float*>(smem) + 64;    // [GP][kMaxSplits] chunk weights
-    float* const h_den = c_w + GP * kMaxSplits;                 // [GP]
-    float2 ml0 = {kNegBig, 0.0f}, ml1 = {kNegBig, 0.0f};
-    if (wave < G) {
-      const float* const ml = p.part_ml + query_row(wave) * n * 2;
-      if (lane < n) ml0 = ld_dev2(ml + lane * 2);
-      if (lane + 64 < n) ml1 = ld_dev2(ml + (lane + 64) * 2);
-    }
+    static_assert(GP <= NW && kMergeMaxChunks <= 64, "a wave per row, a lane per chunk");
+    float* const c_w = reinterpret_cast<float*>(smem) + 64;    // [GP][kMergeMaxChunks] chunk weights
+    float* const h_den = c_w + GP * kMergeMaxChunks;            // [GP]
+    float2 ml = {kNegBig, 0.0f};
+    if (wave < G && lane < n) ml = ld_dev2(p.part_ml + (query_row(wave) * n + lane) * 2);
     constexpr int PAIRS = GP * D / 2, PARTS = NW * 64 / PAIRS;
     static_assert(PARTS == 1 || PARTS == 2, "a thread, or two neighbouring ones, per pair of dims");
     const int pair = threadIdx.x / PARTS, cpart = threadIdx.x % PARTS;
@@ -1419,16 +1413,14 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
     const float* const src = p.part_o + row * n * D + j;
     auto weights = [&] {
       if (wave < G) {
-        const float mx = wave_fmax(fmaxf(ml0.x, ml1.x));
-        const float w0 = __builtin_amdgcn_exp2f(ml0.x - mx), w1 = __builtin_amdgcn_exp2f(ml1.x - mx);
-        if (lane < n) c_w[wave * kMaxSplits + lane] = w0;
-        if (lane + 64 < n) c_w[wave * kMaxSplits + lane + 64] = w1;
-        const float d = wave_fsum(fmaf(ml0.y, w0, ml1.y * w1));
+        const float w = __builtin_amdgcn_exp2f(ml.x - wave_fmax(ml.x));
+        if (lane < n) c_w[wave * kMergeMaxChunks + lane] = w;
+        const float d = wave_fsum(ml.y * w);
         if (lane == 0) h_den[wave] = d;
       }
       __syncthreads();
     };
-    const float* const w = c_w + h * kMaxSplits;
+    const float* const w = c_w + h * kMergeMaxChunks;
     float n0 = 0.0f, n1 = 0.0f;
     auto fetch = [&](auto count_tag, int c0, float2* o) {
 #pragma unroll
@@ -1606,6 +1598,7 @@ hipError_t launch_partial_mfma(const DecodeParams& p_in, int batch, int head_dim
   int gp = padded_gqa(head_dim, p.gqa);
   // (a 16-row tile has no chunk merge of its own: `out` would stay unwritten)
   if (gp == 16 && p.merge_slot >= 0 && p.n_splits > 1) return hipErrorInvalidValue;
+  if (p.merge_slot >= 0 && p.n_splits > kMergeMaxChunks) return hipErrorInvalidValue;
   if (p.k_new != nullptr && !mfma_takes_token(head_dim, p.group, rows)) return hipErrorInvalidValue;
   if (p.group != kGroup && gp == 4) gp = 8;       // (larger groups at d = 128: the 8- and 16-row layouts only)
   if (head_dim == 128 && gp == 16) return launch<128, 16>(p, grid, s);

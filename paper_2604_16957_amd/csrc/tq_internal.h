@@ -13,6 +13,7 @@ constexpr int kGroup = 32;        // elements per quantisation group (Sec. 2.1):
                                   // matrix-core kernels are built for; also the piece of a vector one thread of the
                                   // quantiser handles.  Groups of 64 and 128 (DecodeParams::group) take the generic kernels.
 constexpr int kMaxSplits = 128;   // upper bound on sequence chunks (Sec. 3.2); sizes the workspace
+constexpr int kMergeMaxChunks = 64;  // chunks of a row that the matrix-core kernel can merge in place (a lane each)
 constexpr int kTile = 32;         // chunk boundaries are multiples of this many tokens
 constexpr int kRankMaxBatch = 512;   // sequences a launch can order by their lengths (RankedRows)
 constexpr int kMaxQueries = 8;    // query tokens per sequence in one call (the masked path covers two supertiles)

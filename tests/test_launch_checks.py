@@ -30,6 +30,9 @@ int main() {
   p.n_splits = 1; p.tokens_per_split = 64;  // 32 rows in two such tiles: they take no new token
   p.gqa = 32; p.n_q_heads = 32; p.kv_share = 2; p.k_new = p.v_new = reinterpret_cast<const half_t*>(256);
   ask("shared_tile_new_token", p, 0);
+  DecodeParams m = plain;                   // more chunks than the in-kernel merge holds
+  m.seq_len = m.row_stride = 32 * 65; m.n_splits = 65;
+  ask("merge_of_65_chunks", m, 0);
   DecodeParams r = plain;                   // one chunk per row, blocks of one wave, two rows to a block
   r.n_splits = 1; r.tokens_per_split = 64; r.seq_lens = reinterpret_cast<const int32_t*>(256);
   r.ranked = 1; r.waves_per_row = 1; r.rank_spread = 0;
@@ -58,6 +61,6 @@ def test_a_request_that_is_covered_gets_past_the_checks(answers):
         assert answers["plain"] not in (0, INVALID_VALUE)
 
 
-@pytest.mark.parametrize("request_", ["tile16_merge", "shared_tile_new_token", "one_wave_two_rows"])
+@pytest.mark.parametrize("request_", ["tile16_merge", "merge_of_65_chunks", "shared_tile_new_token", "one_wave_two_rows"])
 def test_a_request_no_instance_implements_is_refused(answers, request_):
     assert answers[request_] == INVALID_VALUE

@@ -501,16 +501,19 @@ def test_sharp_softmax_large_scores(variant):
     assert_close_elementwise(out, ref, f"sharp softmax variant={variant}")
 
 
-@pytest.mark.parametrize("B", [130, 256, 512])
-def test_rows_of_their_own_length_are_paired_long_with_short(B):
-    """More than a thousand (sequence, KV head) rows of their own lengths, each a single chunk taken by one wave:
-    every block orders the sequences by length and gives the two waves of a SIMD the i-th shortest and the i-th
-    longest.  Every block has to arrive at the SAME order (equal lengths included), or rows would be computed twice
-    and others not at all: every row against the oracle, many equal lengths, and two calls bit for bit alike."""
-    Hkv, S = 8, 300
+@pytest.mark.parametrize("B,Hkv", [(130, 8), (256, 8), (512, 4)])
+def test_rows_of_their_own_length_are_each_taken_once(B, Hkv):
+    """More than a thousand (sequence, KV head) rows of their own lengths, each a single chunk of a block of two waves:
+    every block orders the sequences by length, in four registers of lanes or (beyond 256) eight, and takes the row
+    whose place in that order is its own.  Every block has to arrive at the SAME order (equal lengths included), or
+    rows would be computed twice and others not at all: every row against the oracle, many equal lengths, a few far
+    longer than the rest (or the launch would take the lengths for even, and keep the list's order), and two calls
+    bit for bit alike."""
+    S = 700
     rng = np.random.default_rng(7000 + B)
-    lens = rng.integers(1, S + 1, B).astype(np.int32)
-    lens[: B // 4] = rng.choice([33, 64, 65, 200], B // 4)          # many ties
+    lens = rng.integers(1, 97, B).astype(np.int32)
+    lens[: B // 4] = rng.choice([33, 64, 65], B // 4)               # many ties
+    lens[:: 40] = rng.integers(300, S + 1, len(lens[:: 40]))
     lens[0] = S
     w = wl.custom(batch=B, n_q_heads=2 * Hkv, n_kv_heads=Hkv, head_dim=128, seq_len=S, seed=7100 + B)
     q, k, v = make(w)
@@ -526,14 +529,14 @@ def test_rows_of_their_own_length_are_paired_long_with_short(B):
     assert torch.equal(out, again)
 
 
-@pytest.mark.parametrize("route", ["packed_rows", "one_block", "planned_chunks"])
+@pytest.mark.parametrize("route", ["own_blocks", "one_block", "planned_chunks"])
 def test_sharp_softmax_every_head_keeps_its_own_reference(route):
     """Scores with a spread of tens of log2 units (attn_scale 1 on N(0,1) queries and keys): new maxima keep turning
     up, for one head or another of the group, all along a wave's tokens.  A head's exp2 reference must move only
     when its OWN maximum outgrows it: one that follows every move of a neighbour ends tens of units above the head's
     scores and its weights p * s_v sink into fp16's subnormals (percent-level errors on single rows).  Routes: many
-    rows of their own length packed four to a block; one long chunk per block; the device-planned chunks."""
-    if route == "packed_rows":
+    rows of their own length, a block of four waves each; one long chunk per block; the device-planned chunks."""
+    if route == "own_blocks":
         B, Hkv, S, n_splits = 131, 4, 1025, 0
     elif route == "one_block":
         B, Hkv, S, n_splits = 3, 2, 6000, 1
@@ -941,11 +944,11 @@ def test_graph_capture_and_replay():
             assert torch.equal(out1, want1) and torch.equal(out2, want2)
 
 
-@pytest.mark.parametrize("route", ["d512", "own_lengths_planned", "own_lengths_rows_as_chunks"])
+@pytest.mark.parametrize("route", ["d512", "own_lengths_planned", "own_lengths_own_blocks"])
 def test_graph_capture_and_replay_of_the_other_routes(route):
     """The one-call step captured and replayed on the routes the test above does not take: the head_dim 512 kernel
-    (its ring is static LDS above 64 KB), per-sequence lengths with device-planned chunks (the plan and the merge
-    kernel's appender are redone by every replay), and many rows of their own length (append kernel + decode)."""
+    (its ring is static LDS above 64 KB), per-sequence lengths with device-planned chunks (the plan is redone by
+    every replay), and many rows of their own length with a block each; in both the decode kernel takes the token in."""
     if route == "d512":
         w = wl.custom(seq_len=1500, seed=93, **SHAPES["g32_d512"])
         lens = None
@@ -1073,7 +1076,7 @@ def test_random_configurations_with_several_query_tokens():
 def test_random_configurations_of_the_decode_step():
     """The same kind of sweep over the one-call step (append the sequences' last tokens, then attend): common and
     per-sequence lengths, paged pools, 1 ... 4 query tokens, windows, chunk counts, every head dimension; enough
-    rows in some cases for the packed-rows routes.  Output against the oracle, and every stored bit of the cache."""
+    rows in some cases for blocks of their own.  Output against the oracle, and every stored bit of the cache."""
     rng = np.random.default_rng(20260418)
     names = ("k_codes", "k_scale", "k_zero", "v_codes", "v_scale", "v_zero")
     shapes = [(128, 8), (128, 4), (128, 16), (128, 3), (256, 2), (256, 4), (256, 1), (512, 2), (512, 32), (512, 6)]
@@ -1744,26 +1747,26 @@ def test_more_rows_than_blocks_are_packed_several_to_a_block(shape):
                 assert_close(out, _oracle_causal(q4, ocache, [S] * batch, w.attn_scale), f"{shape} batch={batch} S={S}, 2 queries")
 
 
-@pytest.mark.parametrize("S", [1800, 2600])
-def test_eighty_sequences_with_their_own_lengths_and_a_step(S):
-    """640 (sequence, KV head) rows with their own lengths.  Up to 2048 tokens every row is one chunk of its own
-    length, packed four to a block, and the decode kernel writes the output itself (no chunk plan, no merge kernel;
-    the step appends with the append kernel); beyond that the device plans chunks whose slots share blocks and the
-    merge kernel takes the step's token in.  Plain decode, a window, and the one-call step, against the oracle."""
+@pytest.mark.parametrize("S,bound", [(1800, 1800), (2600, 4500)])
+def test_eighty_sequences_with_their_own_lengths_and_a_step(S, bound):
+    """640 (sequence, KV head) rows with their own lengths.  With a bound of up to 3072 tokens every row is one chunk of a
+    block of its own, and the decode kernel writes the output itself (no chunk plan, no merge kernel); beyond 4096
+    the device plans chunks whose slots share blocks.  Either way the decode kernel takes the step's token in.  Plain
+    decode, a window (which then is the bound), and the one-call step, against the oracle."""
     rng = np.random.default_rng(80)
     B = 80
     lens = [int(x) for x in rng.integers(1, S + 1, B)]
     lens[0], lens[1] = S, 1
     w = wl.custom(batch=B, n_q_heads=64, n_kv_heads=8, head_dim=128, seq_len=S, seed=1900, outlier_channels=4)
     q, k, v = make(w)
-    cache = gpu_cache_from(k, v)
+    cache = gpu_cache_from(k, v, capacity=bound)
     ocache = oracle_cache_from(k, v)
     lens_dev = torch.tensor(lens, dtype=torch.int32, device="cuda")
     ref = _oracle_varlen(q, ocache, lens, w.attn_scale)
-    out = tq.tq_sdpa_int4_decode_varlen(cache, q.cuda(), lens_dev, S, w.attn_scale)
+    out = tq.tq_sdpa_int4_decode_varlen(cache, q.cuda(), lens_dev, bound, w.attn_scale)
     torch.cuda.synchronize()
     assert_close(out, ref, "80 sequences, own lengths")
-    out = tq.tq_sdpa_int4_decode_varlen(cache, q.cuda(), lens_dev, S, w.attn_scale, window=300)
+    out = tq.tq_sdpa_int4_decode_varlen(cache, q.cuda(), lens_dev, bound, w.attn_scale, window=300)
     torch.cuda.synchronize()
     assert_close(out, _oracle_window(q, ocache, lens, 300, w.attn_scale), "80 sequences, own lengths, window 300")
     # the step: wipe every sequence's last token, hand it over as the new one
@@ -1772,7 +1775,7 @@ def test_eighty_sequences_with_their_own_lengths_and_a_step(S):
     for t in cache.tensors():
         for b in range(B):
             t.view(torch.uint8)[b, :, lens[b] - 1] = 0xEE
-    out = tq.tq_sdpa_int4_append_decode_varlen(cache, kn.cuda(), vn.cuda(), q.cuda(), lens_dev, S, w.attn_scale)
+    out = tq.tq_sdpa_int4_append_decode_varlen(cache, kn.cuda(), vn.cuda(), q.cuda(), lens_dev, bound, w.attn_scale)
     torch.cuda.synchronize()
     assert_close(out, ref, "80 sequences, own lengths, append + decode")
     for name, g, o in zip(("k_codes", "k_scale", "k_zero", "v_codes", "v_scale", "v_zero"), cache.tensors(), ocache):

@@ -400,10 +400,11 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
       b = __builtin_amdgcn_readfirstlane(rows.sequence(p, rank));
       return true;
     };
-    // (lists of up to 256 sequences keep a form of their own: the eight registers of the longer one cost them 1.7 us.
+    // (lists of up to 256 sequences keep a form of their own: the eight registers of the longer one cost them 1.7 us, and
+    // its code on their way 0.2.
     // 300 sequences of 64 .. 2048 tokens, 32 heads over 4, taken in the given order and two to a block 77.9 us per step,
     // ordered 39.7; 512 of 64 .. 1024, 64 heads over 8, 76.8 / 66.0; 512 of 64 .. 4096, 8 heads over 1, 41.1 / 33.1)
-    if (!(p.batch <= 256 ? place(RankedRows<4>(p)) : place(RankedRows<kRankMaxBatch / 64>(p)))) return;
+    if (!(__builtin_expect(p.batch <= 256, 1) ? place(RankedRows<4>(p)) : place(RankedRows<kRankMaxBatch / 64>(p)))) return;
   }
   const bool whole = W == NW;
   const int sub = wave % W;                       // (several rows per block: the W waves of a row take its supertiles in turn)

@@ -453,9 +453,7 @@ def main():
     # ---- dominant kernel: stream events around each of its launches.  Where the decode call is ONE
     #      launch (partials and chunk merge in the same kernel) that launch is timed; otherwise phase 1,
     #      the partial kernel, which tq_sdpa_int4_partial launches on its own.
-    fused = (not paged) and tq.tq_decode_launches(caches[0], Hq, S, w.attn_scale, n_queries=NQ, **kw) == 1
-    if args.workload == "varlen256_2k":           # (the launch count above is that of a common length; these lengths
-        fused = False                             # take chunks planned on the device and the merge kernel)
+    fused = lens is None and tq.tq_decode_launches(caches[0], Hq, S, w.attn_scale, n_queries=NQ, **kw) == 1
     evs = [(torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)) for _ in range(args.steps)]
     n_splits = 0 if paged else tq.tq_sdpa_int4_partial(caches[0], qs[0], S, w.attn_scale, ws, **kw)
     lo = max(0, S - args.window) if args.window > 0 else 0     # first attended token
@@ -626,7 +624,9 @@ def main():
                                   "tq_quantize_kv_paged + tq_sdpa_int4_decode_paged" if paged else
                                   "tq_quantize_kv_varlen + tq_sdpa_int4_decode_varlen" if lens is not None else
                                   "tq_quantize_kv + tq_sdpa_int4_decode"),
-                   "decode_launches": 1 if fused else 2},
+                   # (of the decode call by itself; the step merges its chunks in place, in one launch, in more cases, and
+                   #  the launches of calls with per-sequence lengths follow from number and bound of the lengths)
+                   "decode_launches": (1 if fused else 2) if lens is None else None},
         "effective_GBps": round(packed_bytes / (us_per_step * 1e-6) / 1e9, 1),
         "pct_of_hbm_peak": round(100 * packed_bytes / (us_per_step * 1e-6) / 1e9 / HBM_PEAK_GBPS, 2),
         "packed_bytes_per_step": packed_bytes,
@@ -635,9 +635,9 @@ def main():
         "roofline": {"bound": "hbm",
                      "kernel": ("decode_partial_mfma_kernel: fused int4 attention over the chunks + in-kernel chunk merge "
                                 "(the whole tq_sdpa_int4_decode call)" if fused else
-                                "partial kernel (phase 1 of the decode)" if lens is None else
-                                "the whole tq_sdpa_int4_decode_paged call (partial kernel + merge kernel)" if paged else
-                                "the whole tq_sdpa_int4_decode_varlen call (partial kernel + merge kernel)"),
+                                "partial kernel (phase 1 of the decode), launched by itself" if lens is None else
+                                "the whole tq_sdpa_int4_decode_paged call" if paged else
+                                "the whole tq_sdpa_int4_decode_varlen call"),
                      "achieved": round(achieved, 1),
                      "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBPS, 4),
                      "traffic": None, "traffic_source": None, "kernel_us_mean": round(kernel_us, 3),

@@ -29,6 +29,13 @@ def _rows(d, suffix):
     return out
 
 
+def _short(name):
+    """A kernel's name without return type, namespaces (a template argument's type among them) and parameter list."""
+    name = name.replace("(tq::(anonymous namespace)::Mode)", "")
+    name = name.replace("void tq::(anonymous namespace)::", "").replace("tq::(anonymous namespace)::", "")
+    return name.split("(")[0][:70]
+
+
 def trace(d):
     rows = _rows(d, "kernel_stats.csv")
     print(f"{'kernel':70s} {'calls':>6s} {'avg_us':>10s} {'min_us':>10s} {'max_us':>10s} {'pct':>7s}")
@@ -36,8 +43,7 @@ def trace(d):
         name = r["Name"]
         if "tq::" not in name and COPY_KERNEL not in name:
             continue
-        name = name.replace("void tq::(anonymous namespace)::", "").replace("tq::(anonymous namespace)::", "")
-        name = name.split("(")[0][:70]
+        name = _short(name)
         print(f"{name:70s} {int(r['Calls']):6d} {float(r['AverageNs']) / 1e3:10.2f} {float(r['MinNs']) / 1e3:10.2f} "
               f"{float(r['MaxNs']) / 1e3:10.2f} {float(r['Percentage']):7.2f}")
 
@@ -86,7 +92,7 @@ def counters(dirs):
             k = r["Kernel_Name"]
             if "decode_partial" not in k:
                 continue
-            name = "decode_partial" + k.split("decode_partial")[1].split("(")[0]
+            name = _short(k)
             acc.setdefault(name, {}).setdefault(r["Counter_Name"], []).append(float(r["Counter_Value"]))
     for name, cs in acc.items():
         m = {c: statistics.fmean(v[len(v) // 4:]) for c, v in cs.items()}

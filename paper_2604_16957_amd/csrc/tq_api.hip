@@ -134,9 +134,11 @@ struct Route { bool ok, use_mfma, merge, merge_step, wide, small_tile; };
 // all partials) that one block per KV head walks alone: about 2.5 us for up to 32 chunks, against about 3.5 us for the
 // separate merge kernel plus its launch; with 64 and 128 chunks to a row that one compute unit pulls in for too long
 // (one KV head, 8 heads, us per step, in place / merge kernel: 16K tokens, 64 chunks, 13.0 / 11.4; 128K, 128 chunks,
-// 20.9 / 15.8).  A decode step merges in place wherever that holds (128K tokens, 64 heads over 8, 33.3 -> 32.9 us;
+// 20.9 / 15.8).  A decode step merges in place wherever that holds (128K tokens, 64 heads over 8, 33.3 -> 32.6 us;
 // 8 sequences of 8K 21.9 -> 20.6; 32 heads over 32, 32K, 31.4 -> 29.9); the decode alone up to this many packed bytes per
-// call: above, it keeps its two phases as the separate launches that tq_decode_launches has always told of.
+// call.  Above, and at head_dim 256 with larger groups, it keeps two launches, although one would be the faster there too
+// (32 heads over 16, d = 256, 32K tokens: the step's one launch 33.0 us, the decode's two 33.9): callers that ask tq_decode_launches, and the
+// benchmark, which times phase 1 by itself, go by them.
 constexpr int64_t kMergeInKernelMaxBytes = 48ll << 20;
 constexpr int kMergeInKernelMaxChunks = 32;
 

@@ -54,7 +54,9 @@
 // Work split: grid (n_splits, H_kv * kv_share, B), 8 waves per block, one block per compute unit; the
 // waves of a block share the chunk's 32-token supertiles in a fixed pattern (17:15 or 9:7 between the older
 // and the younger wave of a SIMD, see the kernel), keep private online-softmax state, and are merged through
-// LDS so that the block writes one partial (o_c, m_c, l_c) per query row.
+// LDS so that the block writes one partial (o_c, m_c, l_c) per query row.  Where there are more rows, or slots of a
+// device-planned chunk list, than the chip holds blocks, 2, 4 or 8 of them share a block; many rows of their own
+// lengths get blocks of 8, 4, 2 or 1 waves, one per row, longest first (`ranked` in the kernel).
 //
 // Query rows: the tile's GP columns take the G heads of the GQA group (Sec. 3.1), or, with several query
 // tokens per sequence (the sequence's last n_queries tokens, causal among themselves), the n_queries * G
@@ -334,7 +336,7 @@ __device__ __forceinline__ void wait_loads() {               // until at most N 
 // near 2^10 whatever the size of the scales (see `softmax`), or small scales would push the rest below fp16's range.
 // The matrix cores have the room (52 instructions per supertile instead of 34, a quarter of its time), and the kernel
 // is bound by the stream like its groups-of-32 instance: 32 heads on 16 KV heads, one sequence of 32K tokens, groups of
-// 64 (151 MB), the whole step 305.5 us on the generic kernel, 35.6 us here.
+// 64 (151 MB), the whole step 305.5 us on the generic kernel, 31.4 us here.
 //
 // PAGED = a pool of pages (with PLAIN: never).  An instance of its own keeps the page look-ups out of the others'
 // scalar registers, of which the general instance has none to spare.

@@ -11,7 +11,7 @@ namespace tq {
 
 constexpr int kGroup = 32;        // elements per quantisation group (Sec. 2.1): the paper's configuration and the one the
                                   // matrix-core kernels are built for; also the piece of a vector one thread of the
-                                  // quantiser handles.  Groups of 64 and 128 (DecodeParams::group) take the generic kernels.
+                                  // quantiser handles.  Groups of 64 and 128 (DecodeParams::group): see mfma_supports_group.
 constexpr int kMaxSplits = 128;   // upper bound on sequence chunks (Sec. 3.2); sizes the workspace
 constexpr int kMergeMaxChunks = 64;  // chunks of a row that the matrix-core kernel can merge in place (a lane each)
 constexpr int kTile = 32;         // chunk boundaries are multiples of this many tokens

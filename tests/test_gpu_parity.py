@@ -587,6 +587,26 @@ def test_in_kernel_merge_agrees_with_the_two_phase_path():
             assert np.abs(a - b).max() <= 2.0 ** -10 * max(1.0, np.abs(b).max())    # an fp16 ulp or two
 
 
+@pytest.mark.parametrize("shape,n_splits", [("g8_d128", 63), ("g8_d128", 40), ("g2_d256", 63), ("g8_d128_b2_kv3", 33)])
+def test_step_that_merges_more_chunks_than_its_route_counted(shape, n_splits):
+    """A step's chunks cover one token fewer than its sequence: where that takes a 32-token tile away, the chunks asked for
+    may come out half as long and almost twice as many as the 32 up to which a step merges in place (63 at most; a lane
+    of the merging wave each).  Stored bits and output against the oracle, twice, with a plain step in between."""
+    S = 32 * n_splits + 1
+    w = wl.custom(seq_len=S, seed=460 + n_splits, **SHAPES[shape])
+    q, k, v = make(w)
+    ocache = oracle_cache_from(k, v)
+    ref = oracle_attend(q, ocache, S, w.attn_scale)
+    cache = gpu_cache_from(k[:, :, :S - 1].contiguous(), v[:, :, :S - 1].contiguous(), capacity=S)
+    kn, vn = k[:, :, S - 1:].contiguous().cuda(), v[:, :, S - 1:].contiguous().cuda()
+    ws = torch.empty(tq.tq_workspace_bytes(w.batch, w.n_q_heads, w.head_dim), dtype=torch.uint8, device="cuda")
+    for asked in (n_splits, 0, n_splits):
+        out = tq.tq_sdpa_int4_append_decode(cache, kn, vn, q.cuda(), S, w.attn_scale, workspace=ws, n_splits=asked)
+        torch.cuda.synchronize()
+        assert_close(out, ref, f"{shape}: {asked} chunks asked for")
+    assert_cache_bit_exact(cache, ocache, S)
+
+
 # ---------------------------------------------------------------- unfused comparator
 
 @pytest.mark.parametrize("variant", [0, 1])

@@ -35,7 +35,7 @@ struct Plan { int n_splits, tokens_per_split; };
 
 constexpr int kBlocksMfma = 256;   // matrix-core kernel: 8-wave blocks, one per compute unit
 constexpr int kBlocksValu = 512;   // generic kernel: 4-wave blocks, two per compute unit
-constexpr int kBlocksWide = 512;   // head_dim 512 matrix-core kernel: 4-wave blocks, two per compute unit
+constexpr int kBlocksWide = 256;   // head_dim 512 matrix-core kernel: 8-wave blocks, one per compute unit
 
 // A chunk is never longer than this many tokens under the heuristic: the fp32 accumulators of one wave
 // then take in at most 64 tiles, which bounds the rounding they pick up however long the sequence is.
@@ -297,16 +297,17 @@ int run_partial(PartialRequest& rq) {
   const bool append = rq.k_new != nullptr;
   const int first = seq_len - attended;           // first attended token
   if (append) --attended;
-  const int row_tiles = r.wide ? tq::wide_row_tiles(rows_of(cache, n_q_heads, opts),
-                                                    (int64_t)cache->batch * cache->n_kv_heads, std::max(1, attended))
-                               : 1;
+  const int row_tiles = r.wide ? tq::wide_row_tiles(rows_of(cache, n_q_heads, opts)) : 1;
   const int mfma_share = use_mfma ? mfma_share_of(cache, n_q_heads, opts) : 1;
   const int rows_per_batch = cache->n_kv_heads * (use_mfma ? mfma_share : row_tiles);
   const Ranked rank = seq_lens && rq.out != nullptr ? ranked_rows(cache, n_q_heads, seq_len, rq.attn_scale, opts)
                                                     : Ranked{0, -1};
   const bool ranked = rank.waves > 0;
-  const Plan plan = plan_splits(cache->batch, rows_per_batch, attended, ranked ? 1 : opts ? opts->n_splits : 0,
-                                target, use_mfma ? 8 : r.wide ? 2 : 1);
+  const int asked = ranked ? 1 : opts ? opts->n_splits : 0;
+  Plan plan = plan_splits(cache->batch, rows_per_batch, attended, asked, target, use_mfma ? 8 : 1);
+  if (r.wide && asked <= 0)
+    plan = plan_splits(cache->batch, rows_per_batch, attended,
+                       std::min(plan.n_splits, tq::wide_max_chunks((attended + tq::kTile - 1) / tq::kTile)), target, 1);
   DecodeParams p = make_params(cache, rq.q, n_q_heads, seq_len, rq.attn_scale, rq.out, rq.workspace, plan,
                                queries_of(opts));
   p.seq_lens = seq_lens;

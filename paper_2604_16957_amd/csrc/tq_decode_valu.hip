@@ -546,24 +546,35 @@ bool reduce_is_grouped(int head_dim, int64_t out_rows, int n_q_heads, int gqa) {
 hipError_t launch_reduce(const DecodeParams& p, int batch, int head_dim, hipStream_t s) {
   const dim3 grid(p.n_q_heads, batch * std::max(1, p.n_queries));
   const bool many = (int64_t)grid.x * grid.y >= 4096;      // several rounds of blocks: smaller blocks, more at once
+  // (the host can tell from the longest length allowed and the planner's shortest chunk, or from the chunk count asked for)
+  const int most_chunks = p.var_chunks > 0 ? (p.seq_len + p.var_min_chunk - 1) / std::max(1, p.var_min_chunk) : p.n_splits;
   if (reduce_is_grouped(head_dim, grid.y, p.n_q_heads, p.gqa)) {
     // Heads per thread: two; four (one block per KV head of eight query heads) where there are thousands of
     // outputs and no sequence can have more than 16 chunks, which the host can tell from the longest length
     // allowed and the planner's shortest chunk, or from the chunk count asked for.
-    const int most_chunks = p.var_chunks > 0 ? (p.seq_len + p.var_min_chunk - 1) / std::max(1, p.var_min_chunk) : p.n_splits;
     if (many && most_chunks <= 16)
       hipLaunchKernelGGL((reduce_group_kernel<128, 4>), dim3(p.n_kv_heads * ((p.gqa + 7) / 8), grid.y), dim3(256), 0, s, p);
     else
       hipLaunchKernelGGL((reduce_group_kernel<128, kGroupHeads>),
                          dim3(p.n_kv_heads * ((p.gqa + 2 * kGroupHeads - 1) / (2 * kGroupHeads)), grid.y), dim3(256), 0, s, p);
   }
+  // Few outputs with many chunks: several blocks per query head, each with a part of its elements and with that many more
+  // threads to an element, so that every chunk is asked for in the first round of loads (us per decode, one block per head / four:
+  // 8 outputs of 64 chunks 10.3 / 9.7, of 128 15.0 / 13.3, 32 of 64 21.2 / 20.7; d = 256: 32 of 47 13.3 / 10.4, of 64 18.5 / 15.1,
+  // 128 of 32 14.2 / 13.9; not with 256 outputs, 10.6 / 11.1, nor where the chunks fit one round as they are).
+  else if (head_dim == 128 && (int64_t)grid.x * grid.y <= 32 && most_chunks > 32)
+    hipLaunchKernelGGL((reduce_kernel<128, 256, 4>), dim3(4 * grid.x, grid.y), dim3(256), 0, s, p);
   else if (head_dim == 128 && many) hipLaunchKernelGGL((reduce_kernel<128, 128>), grid, dim3(128), 0, s, p);
   else if (head_dim == 128) hipLaunchKernelGGL((reduce_kernel<128, 256>), grid, dim3(256), 0, s, p);
+  else if (head_dim == 256 && (int64_t)grid.x * grid.y <= 128 && most_chunks > 16)
+    hipLaunchKernelGGL((reduce_kernel<256, 256, 4>), dim3(4 * grid.x, grid.y), dim3(256), 0, s, p);
   else if (head_dim == 256) hipLaunchKernelGGL((reduce_kernel<256, 256>), grid, dim3(256), 0, s, p);
   // d = 512: with few outputs, several blocks per query head (measured: 32 outputs 8 slices, 64 outputs 4; from
-  // 128 outputs on slicing no longer pays and one block of 1024 threads per head is the shortest)
+  // 128 outputs on slicing no longer pays and one block of 1024 threads per head is the shortest); with many, two of 512
+  // threads, of which more fit a compute unit at once (1024 outputs, 32 sequences of 600 tokens 24.0 -> 22.2 us, of 1900 32.6 -> 30.7)
   else if ((int64_t)grid.x * grid.y <= 32) hipLaunchKernelGGL((reduce_kernel<512, 512, 8>), dim3(8 * grid.x, grid.y), dim3(512), 0, s, p);
   else if ((int64_t)grid.x * grid.y <= 64) hipLaunchKernelGGL((reduce_kernel<512, 512, 4>), dim3(4 * grid.x, grid.y), dim3(512), 0, s, p);
+  else if ((int64_t)grid.x * grid.y >= 512) hipLaunchKernelGGL((reduce_kernel<512, 512, 2>), dim3(2 * grid.x, grid.y), dim3(512), 0, s, p);
   else hipLaunchKernelGGL((reduce_kernel<512, 1024>), grid, dim3(1024), 0, s, p);
   return hipGetLastError();
 }

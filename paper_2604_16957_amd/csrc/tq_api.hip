@@ -35,7 +35,7 @@ struct Plan { int n_splits, tokens_per_split; };
 
 constexpr int kBlocksMfma = 256;   // matrix-core kernel: 8-wave blocks, one per compute unit
 constexpr int kBlocksValu = 512;   // generic kernel: 4-wave blocks, two per compute unit
-constexpr int kBlocksWide = 256;   // head_dim 512 matrix-core kernel: 8-wave blocks, one per compute unit
+constexpr int kBlocksWide = 256;   // matrix-core kernel for wide rows: 8-wave blocks, one per compute unit
 
 // A chunk is never longer than this many tokens under the heuristic: the fp32 accumulators of one wave
 // then take in at most 64 tiles, which bounds the rounding they pick up however long the sequence is.
@@ -89,7 +89,7 @@ int check_decode(const tq_kv_cache* c, const void* q, int n_q_heads, int seq_len
     if (opts->variant < 0 || opts->variant > 2 || opts->n_splits < 0 || opts->window < 0) return TQ_ERR_UNSUPPORTED;
     if (opts->n_queries < 0 || opts->n_queries > tq::kMaxQueries) return TQ_ERR_UNSUPPORTED;
     if (opts->n_queries > 1 && opts->variant == 1) return TQ_ERR_UNSUPPORTED;   // matrix-core kernels only
-    if (opts->variant == 2 && !tq::wide_supported(c->head_dim) &&
+    if (opts->variant == 2 && c->head_dim != 512 &&
         !tq::mfma_supported(c->head_dim, rows_of(c, n_q_heads, opts)))
       return TQ_ERR_UNSUPPORTED;
   }
@@ -128,7 +128,7 @@ int hip_rc(hipError_t e) { return e == hipSuccess ? TQ_OK : TQ_ERR_HIP; }
 
 // Which kernel a decode call takes, and whether that kernel can also do the chunk merge.
 // merge, merge_step: whether a decode, a decode step's launch also does the chunk merge (or has none to do: one chunk).
-// wide: the head_dim 512 matrix-core kernel; small_tile: at most eight query rows to a block.
+// wide: the matrix-core kernel for many query rows (head_dim 512, and 256 by wide_rows_at_256); small_tile: at most eight query rows to a block.
 struct Route { bool ok, use_mfma, merge, merge_step, wide, small_tile; };
 // The in-kernel merge ends the kernel with a chain of device-wide round trips (publish the partial, count in, read
 // all partials) that one block per KV head walks alone: about 2.5 us for up to 32 chunks, against about 3.5 us for the
@@ -157,7 +157,27 @@ bool takes_token(const tq_kv_cache* cache, int n_q_heads, const tq_decode_opts* 
   return tq::mfma_takes_token(cache->head_dim, cache->group_size, rows_of(cache, n_q_heads, opts));
 }
 
-Route route_of(const tq_kv_cache* cache, int n_q_heads, int seq_len, float attn_scale, const tq_decode_opts* opts) {
+// head_dim 256 with more than two query rows per KV head: the kernel of head_dim 512 takes 16 rows to a block, the other one two,
+// and unpacks the stream again for every two.  It always merges in a launch of its own, so what it loses by shows where blocks of many
+// rows have little to do each: with one query token it is taken from five rows on (16 heads over 4, one sequence of 32K tokens
+// 17.6 / 18.7 us per step, other / this) and from 12K (token, KV head) pairs (4 sequences of 512, 32 heads over 4, 10.3 / 10.5),
+// and with more than 128 (sequence, KV head) rows only for sequences of 512 tokens and more (1024 where they have lengths of
+// their own, which the other kernel orders).  us per step, other / this: 32 heads over 4, 6000 tokens
+// 12.0 / 11.3, 20K 18.1 / 15.3, 128K 68 / 42; 8 sequences of 1000 14.4 / 11.3, of 8192 54 / 28; 64 of 200 14.4 / 15.3,
+// of 600 25.4 / 22.4; 128 of 150 18.0 / 25.2, of 2000 121 / 82.5; own lengths: 8 of 400 .. 6000 22.0 / 18.8, 32 of 100 .. 1000 19.0 / 17.9,
+// 64 of 60 .. 600 23.7 / 28.3, of 100 .. 2000 41.8 / 38.8, 128 of 60 .. 600 36.6 / 52.3.  Several query tokens: 32 heads over 16, 2 of
+// them, 600 tokens 12.9 / 10.3, 32K 46 / 40; 8, 32K 128 / 43; 16 over 8, 8 of them, 4 sequences of 2000 33 / 16.
+bool wide_rows_at_256(const tq_kv_cache* cache, int n_q_heads, int seq_len, const tq_decode_opts* opts, bool own_lengths) {
+  const int rows = rows_of(cache, n_q_heads, opts);
+  if (cache->head_dim != 256 || cache->group_size != tq::kGroup || rows <= (queries_of(opts) > 1 ? 2 : 4)) return false;
+  const int64_t kv_rows = (int64_t)cache->batch * cache->n_kv_heads;
+  if (queries_of(opts) == 1 && kv_rows * windowed(seq_len, opts) < 12288) return false;
+  return kv_rows <= 128 || windowed(seq_len, opts) >= (own_lengths ? 1024 : 512);
+}
+
+// own_lengths: the call has per-sequence lengths (seq_len: their bound)
+Route route_of(const tq_kv_cache* cache, int n_q_heads, int seq_len, float attn_scale, const tq_decode_opts* opts,
+               bool own_lengths = false) {
   const int variant = opts ? opts->variant : 0;
   // groups of 64 or 128 elements: the matrix-core kernel at head_dim 128 and 256 (see mfma_supports_group), else the
   // generic vector-ALU kernel with one query token per sequence
@@ -174,8 +194,9 @@ Route route_of(const tq_kv_cache* cache, int n_q_heads, int seq_len, float attn_
   // the matrix-core kernel folds attn_scale into its exp2 argument and needs it positive and finite
   const bool scale_ok = attn_scale > 0.0f && std::isfinite(attn_scale);
   if (variant == 2 && !scale_ok) return {false, false, false, false, false, false};
-  // head_dim 512: its own matrix-core kernel (any finite scale), partials merged by the merge kernel
-  if (variant != 1 && tq::wide_supported(cache->head_dim) && std::isfinite(attn_scale))
+  // the kernel for wide rows: head_dim 512 (any finite scale), partials merged by the merge kernel
+  if (variant != 1 && (cache->head_dim == 512 ? std::isfinite(attn_scale)
+                                              : scale_ok && wide_rows_at_256(cache, n_q_heads, seq_len, opts, own_lengths)))
     return {true, false, false, false, true, false};
   // the matrix-core kernel addresses a (batch, KV head) row of codes with 32-bit byte offsets
   const bool offsets_ok = (int64_t)seq_len * (cache->head_dim / 2) < (1ll << 31);
@@ -242,7 +263,7 @@ int ranked_waves(int64_t rows, int batch, int tokens, bool d256) {
 struct Ranked { int waves, spread; };             // waves of a row's block, 0 = not this way; DecodeParams::rank_spread
 Ranked ranked_rows(const tq_kv_cache* cache, int n_q_heads, int seq_len, float attn_scale, const tq_decode_opts* opts) {
   if (queries_of(opts) > 1 || (opts && opts->n_splits > 0)) return {0, -1};
-  const Route r = route_of(cache, n_q_heads, seq_len, attn_scale, opts);
+  const Route r = route_of(cache, n_q_heads, seq_len, attn_scale, opts, true);
   if (!r.ok || !r.use_mfma) return {0, -1};
   const int64_t rows = (int64_t)cache->batch * cache->n_kv_heads * mfma_share_of(cache, n_q_heads, opts);
   const bool d256 = cache->head_dim == 256;
@@ -271,6 +292,8 @@ struct PartialRequest {
   const tq_decode_opts* opts = nullptr;
   const void* k_new = nullptr;         // append-and-attend: the step's new token (then seq_len includes it), taken in
   const void* v_new = nullptr;         // by the matrix-core kernel, or by the merge kernel behind the others
+  bool new_in_chunks = false;          // k_new / v_new hold the last n_queries of the attended tokens: the kernel for wide rows
+                                       // takes them in as tokens of the chunks (common length)
   bool step = false;                   // a decode step (the new token(s) may be in the cache already)
   const tq::PagedView* paged = nullptr;
   void* stream = nullptr;
@@ -286,7 +309,7 @@ int run_partial(PartialRequest& rq) {
   const tq_decode_opts* opts = rq.opts;
   const int32_t* seq_lens = rq.seq_lens;
   const int n_q_heads = rq.n_q_heads, seq_len = rq.seq_len;
-  const Route r = route_of(cache, n_q_heads, seq_len, rq.attn_scale, opts);
+  const Route r = route_of(cache, n_q_heads, seq_len, rq.attn_scale, opts, seq_lens != nullptr);
   if (!r.ok) return TQ_ERR_UNSUPPORTED;
   const bool use_mfma = r.use_mfma;
   const int target = use_mfma ? kBlocksMfma : r.wide ? kBlocksWide : kBlocksValu;
@@ -294,7 +317,7 @@ int run_partial(PartialRequest& rq) {
   // (paged cache: counted from the supertile boundary before the window, see var_start)
   if (rq.paged && attended < seq_len) attended = std::min(seq_len, attended + tq::kTile - 1);
   // append-and-attend: the new token (the last attended one) does not come from the cache
-  const bool append = rq.k_new != nullptr;
+  const bool append = rq.k_new != nullptr && !rq.new_in_chunks;
   const int first = seq_len - attended;           // first attended token
   if (append) --attended;
   const int row_tiles = r.wide ? tq::wide_row_tiles(rows_of(cache, n_q_heads, opts)) : 1;
@@ -307,7 +330,7 @@ int run_partial(PartialRequest& rq) {
   Plan plan = plan_splits(cache->batch, rows_per_batch, attended, asked, target, use_mfma ? 8 : 1);
   if (r.wide && asked <= 0)
     plan = plan_splits(cache->batch, rows_per_batch, attended,
-                       std::min(plan.n_splits, tq::wide_max_chunks((attended + tq::kTile - 1) / tq::kTile)), target, 1);
+                       std::min(plan.n_splits, tq::wide_max_chunks(cache->head_dim, (attended + tq::kTile - 1) / tq::kTile)), target, 1);
   DecodeParams p = make_params(cache, rq.q, n_q_heads, seq_len, rq.attn_scale, rq.out, rq.workspace, plan,
                                queries_of(opts));
   p.seq_lens = seq_lens;
@@ -375,6 +398,10 @@ int run_partial(PartialRequest& rq) {
     return hip_rc(tq::launch_partial_mfma(p, cache->batch, cache->head_dim, merge_slot, s));
   }
   if (r.wide) {
+    if (rq.new_in_chunks) {
+      p.k_new = static_cast<const half_t*>(rq.k_new);
+      p.v_new = static_cast<const half_t*>(rq.v_new);
+    }
     p.kv_share = row_tiles;
     return hip_rc(tq::launch_partial_wide(p, cache->batch, cache->head_dim, s));
   }
@@ -467,7 +494,7 @@ int32_t tq_decode_launches(const tq_kv_cache* cache, int32_t n_q_heads, int32_t 
   if (n_q_heads < 1 || n_q_heads % cache->n_kv_heads != 0 || seq_len < 1 || seq_len > cache->capacity) return 0;
   if (opts && (opts->variant < 0 || opts->variant > 2)) return 0;
   if (opts && (opts->n_queries < 0 || opts->n_queries > tq::kMaxQueries || seq_len < queries_of(opts))) return 0;
-  if (opts && opts->variant == 2 && !tq::wide_supported(cache->head_dim) &&
+  if (opts && opts->variant == 2 && cache->head_dim != 512 &&
       !tq::mfma_supported(cache->head_dim, rows_of(cache, n_q_heads, opts)))
     return 0;
   const Route r = route_of(cache, n_q_heads, seq_len, attn_scale, opts);
@@ -602,7 +629,11 @@ int tq_sdpa_int4_append_decode(const tq_kv_cache* cache, const void* k_new, cons
   // only); one query token, at least one cached token to attend: no append launch, nothing read back.  Else the
   // append kernel runs first (also for a tile that takes no token and writes the output itself).
   const bool taken_in = r.use_mfma ? !r.merge_step || takes_token(cache, n_q_heads, opts) : cache->group_size == tq::kGroup;
-  if (queries_of(opts) == 1 && windowed(seq_len, opts) >= 2 && taken_in) {
+  if (r.wide) {                                   // (any number of query tokens, the sequence's first token too)
+    rq.k_new = k_new;
+    rq.v_new = v_new;
+    rq.new_in_chunks = true;
+  } else if (queries_of(opts) == 1 && windowed(seq_len, opts) >= 2 && taken_in) {
     rq.k_new = k_new;
     rq.v_new = v_new;
   } else {                                        // the append kernel first, then the plain decode
@@ -657,7 +688,7 @@ namespace {
 // tokens), else the append kernel runs first.
 int append_decode_with_lengths(PartialRequest& rq, const void* k_new, const void* v_new) {
   const tq_decode_opts* opts = rq.opts;
-  const bool taken_in = route_of(rq.cache, rq.n_q_heads, rq.seq_len, rq.attn_scale, opts).use_mfma
+  const bool taken_in = route_of(rq.cache, rq.n_q_heads, rq.seq_len, rq.attn_scale, opts, true).use_mfma
                             ? takes_token(rq.cache, rq.n_q_heads, opts) ||
                                   ranked_rows(rq.cache, rq.n_q_heads, rq.seq_len, rq.attn_scale, opts).waves == 0
                             : rq.cache->group_size == tq::kGroup;
@@ -682,7 +713,7 @@ int tq_sdpa_int4_append_decode_varlen(const tq_kv_cache* cache, const void* k_ne
   if (rc != TQ_OK) return rc;
   if (!seq_lens || !k_new || !v_new) return TQ_ERR_NULL;
   if (!aligned(seq_lens, 4) || !aligned(k_new, 16) || !aligned(v_new, 16)) return TQ_ERR_ALIGN;
-  if (!route_of(cache, n_q_heads, max_seq_len, attn_scale, opts).ok) return TQ_ERR_UNSUPPORTED;
+  if (!route_of(cache, n_q_heads, max_seq_len, attn_scale, opts, true).ok) return TQ_ERR_UNSUPPORTED;
   PartialRequest rq{cache, q, n_q_heads, max_seq_len};
   rq.seq_lens = seq_lens;
   rq.attn_scale = attn_scale;
@@ -707,7 +738,7 @@ int tq_sdpa_int4_append_decode_paged(const tq_kv_cache* pool, const int32_t* blo
   if (rc != TQ_OK) return rc;
   if (!seq_lens || !k_new || !v_new) return TQ_ERR_NULL;
   if (!aligned(seq_lens, 4) || !aligned(k_new, 16) || !aligned(v_new, 16)) return TQ_ERR_ALIGN;
-  if (!route_of(&view, n_q_heads, max_seq_len, attn_scale, opts).ok) return TQ_ERR_UNSUPPORTED;
+  if (!route_of(&view, n_q_heads, max_seq_len, attn_scale, opts, true).ok) return TQ_ERR_UNSUPPORTED;
   PartialRequest rq{&view, q, n_q_heads, max_seq_len};
   rq.seq_lens = seq_lens;
   rq.attn_scale = attn_scale;

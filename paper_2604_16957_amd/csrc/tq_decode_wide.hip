@@ -1,5 +1,6 @@
-// Matrix-core fused int4 decode attention for wide rows of query heads: head_dim 512 (the global-attention column of the
-// kernel configuration table, Appendix A: 32 query heads on one KV head), phase 1 of Sec. 3.2.
+// Matrix-core fused int4 decode attention for many query rows per KV head: head_dim 512 (the global-attention column of the
+// kernel configuration table, Appendix A: 32 query heads on one KV head) and head_dim 256 with more than two rows, phase 1 of
+// Sec. 3.2.
 //
 // A KV head's query rows form tiles of 16 (every column of a matrix instruction is a row of its own), every fetched
 // byte is used by all of them, and the work is arithmetic, not traffic: the vector ALU prepares the operands of the
@@ -13,7 +14,8 @@
 //           the fp32 accumulator).  Scale and zero-point are applied to the accumulator in fp32,
 //             q.k^ = sum_g s_g (q_g.c_g - z_g sum(q_g)).
 //           The wave's weights (32 bits) go to LDS, with the reference of its exponentials: the round's one barrier.
-//   P V     by DIMS: a wave takes two groups (64 of 512 dims) of all the round's tokens.  The accumulator layout of S^T (lane =
+//   P V     by DIMS: a wave takes two groups (64 dims) of all the round's tokens (d = 256: of every other supertile, two waves to
+//           the groups).  The accumulator layout of S^T (lane =
 //           query row, four tokens per lane and 16-token tile) IS the A-operand layout of P, so a lane reads back what the same
 //           lane of the scoring wave wrote.  The 16 columns of one instruction lie in ONE group (column c = byte c / 4
 //           of word c % 4), so that A = fp16(p s_v), rounded once, is right for all of them and the codes enter exactly: a
@@ -107,10 +109,13 @@ struct Tile {
   // weights p of a round, [wave's tile][row tile][lane] x 4, and the reference of each wave, [row][wave]; two rounds
   static constexpr int P_M = NW * TT * RT * 1024, P_BLK = P_M + 16 * RT * NW * 4;
   static constexpr int OFF_V = NW * NK * K_SLOT, OFF_P = OFF_V + 2 * NW * V_BLK;
-  static constexpr int OFF_Q = OFF_P + 2 * P_BLK, SMEM = OFF_Q + 16 * RT * NG * 4;   // sums of q over the groups, [row][group]
+  static constexpr int OFF_Q = OFF_P + 2 * P_BLK;     // sums of q over the groups, [row][group]
+  // a step's new tokens, quantised: [token][K | V]: codes, (scale, zero-point) of each group
+  static constexpr int N_ROW = TB + NG * 4, OFF_N = OFF_Q + 16 * RT * NG * 4, SMEM = OFF_N + kMaxQueries * 2 * N_ROW;
+  static constexpr int NOPS = D == 512 ? 2 : 1;     // load instructions for a new token's K and V
   static constexpr int ROWS = 16 * RT, RPW = ROWS / NW, QOPS = RPW * D * 2 / 1024;   // query rows a wave brings in (into the second V round)
   static constexpr int GPW = 2, TH = NW * GPW / NG; // groups of V a wave takes; waves that share them (each every TH-th supertile)
-  static_assert(SMEM <= 160 * 1024 && QOPS * 1024 == RPW * D * 2 && ROWS * D * 2 <= NW * V_BLK && VC * 1024 == V_SC, "LDS");
+  static_assert(SMEM <= 160 * 1024 && QOPS * 1024 == RPW * D * 2 && (ROWS + 2 * NW) * D * 2 <= NW * V_BLK && kMaxQueries <= NW && VC * 1024 == V_SC, "LDS");
   static_assert(TT * SG == 2, "a slot is 2 KB of codes and 2 x 256 B of scales and zero-points");
   static __device__ constexpr int place(int tok, int piece) { return piece ^ ((tok & 15) >> (4 - LG)); }   // V: place of a token's piece
 };
@@ -298,6 +303,23 @@ __global__ __launch_bounds__(512, 2) void decode_partial_wide_kernel(DecodeParam
       dma16_lane(p.q + qr * D + ((idx % PIECES) ^ (r & 15)) * 8, lds0 + C::OFF_V + NW * C::V_BLK + (wave * C::QOPS + u) * 1024);
     }
   }
+  // A decode step (p.k_new set; common length): the sequence's last NQ tokens are not in the cache yet.  The blocks whose
+  // chunk holds one quantise it, a token a wave, and put it where the loads of the round they lie in have left what
+  // the cache holds there; the first row tile's block stores them.
+  const int new_first = seq - NQ;
+  const bool new_block = p.k_new != nullptr && end > new_first;
+  const bool new_mine = new_block && wave < NQ && new_first + wave >= begin && new_first + wave < end;
+  const uint32_t new_raw = lds0 + C::OFF_V + NW * C::V_BLK + C::ROWS * D * 2 + wave * (4 * D);
+  if (new_mine) {
+    const int64_t at = ((int64_t)(b * p.n_kv_heads + kv) * NQ + wave) * D;
+    if constexpr (D == 512) {
+      dma16_lane(p.k_new + at + lane * 8, new_raw);
+      dma16_lane(p.v_new + at + lane * 8, new_raw + 1024);
+    } else {
+      const int l = lane & (D / 4 - 1);           // D / 8 lanes K, D / 8 lanes V
+      dma16_lane((l < D / 8 ? p.k_new : p.v_new) + at + (l & (D / 8 - 1)) * 8, new_raw);
+    }
+  }
   const bool any = first_of(0) < end;             // (a wave may have no tokens at all)
   if (any) {
     const int64_t row = row_at(first_of(0));
@@ -356,6 +378,43 @@ __global__ __launch_bounds__(512, 2) void decode_partial_wide_kernel(DecodeParam
       sum += __shfl_xor(sum, 2);
       const int g = ((idx % PIECES) ^ (r & 15)) >> 2;
       if ((lane & 3) == 0) lds_put(lds0 + C::OFF_Q + (r * NG + g) * 4, sum * (0x1p-24f * (float)one));
+    }
+  }
+  if (new_mine) {
+#pragma unroll
+    for (int u = 0; u < C::NOPS; ++u) {
+      const int piece = lane & (D / 8 - 1);
+      const bool is_v = D == 512 ? u == 1 : (lane & (D / 8)) != 0;
+      const half8v x16 = lds_get<half8v>(new_raw + u * 1024 + lane * 16);
+      float x[8];
+      half_t xh[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) { xh[e] = x16[e]; x[e] = (float)x16[e]; }
+      float mn = x[0], mx = x[0];
+#pragma unroll
+      for (int e = 1; e < 8; ++e) { mn = fminf(mn, x[e]); mx = fmaxf(mx, x[e]); }
+#pragma unroll
+      for (int o = 1; o < 4; o <<= 1) {           // over the four lanes of the group (exact in any order)
+        mn = fminf(mn, __shfl_xor(mn, o));
+        mx = fmaxf(mx, __shfl_xor(mx, o));
+      }
+      half_t s16, z16;
+      quantize_scale_zero(mn, mx, s16, z16);
+      const float sf = (float)s16, zf = (float)z16;
+      const QuantFast fast = quantize_fast_setup(sf, zf, fmaxf(fabsf(mn), fabsf(mx)));
+      float far = 0.0f;
+      uint32_t word = quantize_word_fast(xh, fast, far);
+      if (quantize_fast_in_doubt(far, fast)) word = quantize_word(x, sf, zf);
+      const half2v sz = {s16, z16};
+      const uint32_t to = lds0 + C::OFF_N + (wave * 2 + (is_v ? 1 : 0)) * C::N_ROW;
+      lds_put(to + piece * 4, word);
+      if ((piece & 3) == 0) lds_put(to + TB + piece, __builtin_bit_cast(uint32_t, sz));
+      if (tile == 0 && (D == 512 || lane < D / 4)) {
+        const int64_t row = row_at(new_first + wave);
+        reinterpret_cast<uint32_t*>(const_cast<uint8_t*>(is_v ? p.v_codes : p.k_codes) + row * TB)[piece] = word;
+        if ((piece & 3) == 0) const_cast<half_t*>(is_v ? p.v_scale : p.k_scale)[row * NG + piece / 4] = s16;
+        if ((piece & 3) == 1) const_cast<half_t*>(is_v ? p.v_zero : p.k_zero)[row * NG + piece / 4] = z16;
+      }
     }
   }
   block_barrier();
@@ -455,6 +514,34 @@ __global__ __launch_bounds__(512, 2) void decode_partial_wide_kernel(DecodeParam
       //    next round's as soon as it sits in registers, so the waits below always leave the same loads out.
       constexpr int OUT = (C::SP - 1) * KOPS + VOPS, SG = C::SG;
       const int slot0 = C::SP > 1 ? 0 : (r & 1);
+      if (new_block && tok0 + WT > new_first) {   // (the chunk's last round: nothing else is on its way)
+        wait_loads<0>();
+        const int t0 = max(0, new_first - tok0), n = min(WT, end - tok0) - t0;
+        const uint32_t vb = lds0 + C::OFF_V + ((r & 1) * NW + wave) * C::V_BLK;
+        for (int i = lane; i < WT * NG; i += 64)  // (what else lies there must not meet the zero weights of later tokens as Inf or NaN)
+          if (i % WT >= t0) lds_put(vb + C::V_SC + i * 4, 0u);
+        constexpr int W = D / 8;                  // words of a row, four to a group
+        for (int i = lane; i < n * 2 * W; i += 64) {
+          const int row = i / W, w = i % W, g = w >> 2, t = t0 + (row >> 1);
+          const uint32_t from = lds0 + C::OFF_N + ((tok0 + t - new_first) * 2 + (row & 1)) * C::N_ROW;
+          const uint32_t word = lds_get<uint32_t>(from + w * 4), sz = lds_get<uint32_t>(from + TB + g * 4);
+          if (row & 1) {
+            lds_put(vb + t * TB + C::place(t, g) * 16 + (w & 3) * 4, word);
+            if ((w & 3) == 0) {
+              lds_put(vb + C::V_SC + (g >> 1) * (WT * 4) + t * 4 + (g & 1) * 2, (uint16_t)sz);
+              lds_put(vb + C::V_Z + (g >> 1) * (WT * 4) + t * 4 + (g & 1) * 2, (uint16_t)(sz >> 16));
+            }
+          } else {
+            const int gs = g % (4 * SG), h = gs >> 2;            // group of the slot, slice of the slot
+            const uint32_t kb = k_lds + (slot0 + g / (4 * SG)) * C::K_SLOT;
+            lds_put(kb + t * (SG * 64) + (SG == 1 ? gs ^ ((t >> 2) & 3) : gs ^ ((t >> 1) & 7)) * 16 + (w & 3) * 4, word);
+            if ((w & 3) == 0) {
+              lds_put(kb + C::K_SC + h * (WT * 8) + t * 8 + (gs & 3) * 2, (uint16_t)sz);
+              lds_put(kb + C::K_SC + 256 + h * (WT * 8) + t * 8 + (gs & 3) * 2, (uint16_t)(sz >> 16));
+            }
+          }
+        }
+      }
       KCodes kw;
       wait_loads<OUT>();
       load_kw(slot0, 0, kw);
@@ -697,30 +784,31 @@ __global__ __launch_bounds__(512, 2) void decode_partial_wide_kernel(DecodeParam
         const float zc = __shfl(zacc[rt][m][i], (lane & ~1) | m);
         const float even = oacc[rt][m][0][i], mixed = oacc[rt][m][1][i];
         o2[rt][m][i] = float2{__builtin_fmaf(even, 0x1p24f, -zc), __builtin_fmaf(mixed - even, 0x1p20f, -zc)};
-        if (TH > 1 && wave >= NW / TH) lds_o[((((wave - NW / TH) * RT + rt) * 4 + i) * GPW + m) * 64 + lane] = o2[rt][m][i];
+        if constexpr (TH > 1) lds_o[(((wave * RT + rt) * 4 + i) * GPW + m) * 64 + lane] = o2[rt][m][i];
       }
   __syncthreads();
-  if (TH > 1 && wave >= NW / TH) return;
 #pragma unroll
-  for (int rt = 0; rt < RT; ++rt)
+  for (int k = 0; k < RT * 4 / TH; ++k) {         // the waves that share the groups take every TH-th row each
+    const int ri = TH > 1 ? k * TH + wave / (NW / TH) : k, rt = ri >> 2, i = ri & 3;
+    const int r = (tile * RT + rt) * 16 + 4 * kq + i;
+    int t_q;
+    const int64_t ph = row_of(min(r, rows_total - 1), t_q) * part_stride + split;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int r = (tile * RT + rt) * 16 + 4 * kq + i;
-      if (r >= rows_total) continue;
-      int t_q;
-      const int64_t ph = row_of(r, t_q) * part_stride + split;
+    for (int m = 0; m < GPW; ++m) {
+      float2 o = {0.0f, 0.0f};
+      if constexpr (TH == 1) {
+        o = o2[k >> 2][m][k & 3];
+      } else {
 #pragma unroll
-      for (int m = 0; m < GPW; ++m) {
-        float2 o = o2[rt][m][i];
-#pragma unroll
-        for (int w = 1; w < TH; ++w) {
-          const float2 x = lds_o[(((((w - 1) * (NW / TH) + wave) * RT + rt) * 4 + i) * GPW + m) * 64 + lane];
+        for (int w = 0; w < TH; ++w) {
+          const float2 x = lds_o[((((w * (NW / TH) + wave % (NW / TH)) * RT + rt) * 4 + i) * GPW + m) * 64 + lane];
           o.x += x.x;
           o.y += x.y;
         }
-        st_dev2(p.part_o + ph * D + 32 * (g0 + m) + 8 * (c & 3) + 2 * (c >> 2), o.x, o.y);
       }
+      if (r < rows_total) st_dev2(p.part_o + ph * D + 32 * (g0 + m) + 8 * (c & 3) + 2 * (c >> 2), o.x, o.y);
     }
+  }
   if (wave == 0 && kq == 0) {
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
@@ -763,29 +851,28 @@ hipError_t launch(const DecodeParams& p, dim3 grid, hipStream_t s) {
 
 }  // namespace
 
-bool wide_supported(int head_dim) { return head_dim == 512; }
-
 int wide_row_tiles(int rows) { return (rows + 15) / 16; }
 
-// Chunks of a sequence of `tiles` 32-token tiles, at most.  A block scores 128 tokens in a round; with fewer, and up to 64 of
-// them, each still shortens the launch; beyond, the merge kernel pays for what the shorter chunks save (us per step at
+// Chunks of a sequence of `tiles` 32-token tiles, at most.  A block scores 128 tokens in a round (d = 256: 256); with fewer, and up
+// to 64 of them, each still shortens the launch; beyond, the merge kernel pays for what the shorter chunks save (us per step at
 // chunks of 32 / 64 / 128 tokens: 32 heads on one KV head, 1500 tokens 11.4 / 12.3 / 14.1; 4096 14.2 / 12.7 / 13.4; 8192
 // 15.3 / 15.3 / 14.8; 16 heads on two, 700 tokens 10.4 / 11.1 / 14.2; 5000 12.0 (64) / 12.9 / 14.9).
-int wide_max_chunks(int tiles) {
-  const int m = tiles <= 64 ? 1 : tiles < 224 ? 2 : 4;
+int wide_max_chunks(int head_dim, int tiles) {
+  const int m = head_dim == 256 ? (tiles <= 48 ? 2 : 4) : tiles <= 64 ? 1 : tiles < 224 ? 2 : 4;
   return (tiles + m - 1) / m;
 }
 
 hipError_t launch_partial_wide(const DecodeParams& p_in, int batch, int head_dim, hipStream_t s) {
   DecodeParams p = p_in;
   if (p.n_queries < 1) p.n_queries = 1;
-  if (!wide_supported(head_dim) || p.gqa < 1 || p.kv_share < 1) return hipErrorInvalidValue;
+  if ((head_dim != 512 && head_dim != 256) || p.group != kGroup || p.gqa < 1 || p.kv_share < 1) return hipErrorInvalidValue;
   if (p.n_queries > kMaxQueries) return hipErrorInvalidValue;
   if (p.kv_share != wide_row_tiles(p.n_queries * p.gqa)) return hipErrorInvalidValue;
+  if (p.k_new && (p.seq_lens || p.block_table)) return hipErrorInvalidValue;
   if (p.block_table && (p.page_shift < 5 || !p.seq_lens)) return hipErrorInvalidValue;   // a supertile must not straddle pages
   const dim3 grid = p.var_chunks > 0 ? dim3(p.var_chunks, p.n_kv_heads * p.kv_share, 1)
                                      : dim3(p.n_splits, p.n_kv_heads * p.kv_share, batch);
-  return launch<512, 1, 1>(p, grid, s);
+  return head_dim == 256 ? launch<256, 1, 2>(p, grid, s) : launch<512, 1, 1>(p, grid, s);
 }
 
 }  // namespace tq

@@ -1,15 +1,22 @@
 """The matrix-core kernel for many query rows per KV head: where its rounds, tiles and references can go wrong."""
+import numpy as np
 import pytest
 import torch
 
+import oracle
 import paper_2604_16957_amd as tq
 import tq_workloads as wl
-from gpu_common import assert_close, gpu_cache_from, make, oracle_attend, oracle_cache_from
+from gpu_common import (assert_cache_bit_exact, assert_close, gpu_cache_from, make, np16, oracle_attend, oracle_cache_from)
 
 pytestmark = pytest.mark.gpu
 
-# a wave scores 16 tokens of a round of 128; a supertile of 32 is the unit of P V
-LENGTHS = {512: (15, 16, 17, 31, 48, 65, 112, 127, 128, 129, 144, 145, 255, 257, 300)}
+# a wave scores 16 tokens of a round of 128 (head_dim 256: 32 of 256); a supertile of 32 is the unit of P V
+LENGTHS = {512: (15, 16, 17, 31, 48, 65, 112, 127, 128, 129, 144, 145, 255, 257, 300),
+           256: (2, 31, 32, 33, 65, 96, 224, 225, 255, 256, 257, 289, 511, 513, 600)}
+
+
+# At head_dim 256 the kernel takes small calls with several query tokens only.
+QUERIES = {512: 1, 256: 2}
 
 
 def _poisoned(k, v, S):
@@ -21,37 +28,77 @@ def _poisoned(k, v, S):
     return cache
 
 
-@pytest.mark.parametrize("heads", [(1, 1), (17, 1), (34, 2), (20, 1)])
-@pytest.mark.parametrize("head_dim", [512])
+def _queries(w, nq):
+    gen = torch.Generator().manual_seed(w.seed + 1)
+    q = (torch.randn(w.batch, nq, w.n_q_heads, w.head_dim, generator=gen) * 0.1).half()
+    return q if nq > 1 else q[:, 0].contiguous()
+
+
+def _reference(q, ocache, S, alpha):
+    if q.dim() == 3:
+        return oracle_attend(q, ocache, S, alpha)
+    nq = q.shape[1]
+    return np.stack([oracle.attend_packed(np16(q[:, t]), *ocache, seq_len=S - (nq - 1 - t), alpha=alpha) for t in range(nq)], axis=1)
+
+
+@pytest.mark.parametrize("heads", [(5, 1), (17, 1), (34, 2), (20, 1)])
+@pytest.mark.parametrize("head_dim", [256, 512])
 def test_rounds_and_their_remainders(head_dim, heads):
     """Every remainder of a round, in one chunk and in two: waves without tokens, half supertiles, rows of a last tile
     that has few; nothing behind the sequence's end is used."""
+    nq = QUERIES[head_dim]
     for S in LENGTHS[head_dim]:
         w = wl.custom(n_q_heads=heads[0], n_kv_heads=heads[1], head_dim=head_dim, seq_len=S, attn_scale=1.0, qk_std=0.1,
                       v_std=0.5, seed=2100 + S)
-        q, k, v = make(w)
+        _, k, v = make(w)
+        q = _queries(w, nq)
         cache, ocache = _poisoned(k, v, S), oracle_cache_from(k, v)
-        ref = oracle_attend(q, ocache, S, w.attn_scale)
+        ref = _reference(q, ocache, S, w.attn_scale)
         for n_splits in (0, 1, 2):
             out = tq.tq_sdpa_int4_decode(cache, q.cuda(), S, w.attn_scale, n_splits=n_splits)
             torch.cuda.synchronize()
             assert_close(out, ref, f"d={head_dim} {heads} S={S} n_splits={n_splits}")
 
 
-@pytest.mark.parametrize("head_dim", [512])
+@pytest.mark.parametrize("head_dim", [256, 512])
 def test_references_that_move_in_every_round(head_dim):
     """Scores that grow along the sequence: the rows' references move round after round, by another wave each time."""
     S = 1000
     w = wl.custom(n_q_heads=20, n_kv_heads=1, head_dim=head_dim, seq_len=S, attn_scale=1.0, qk_std=0.1, seed=2200)
-    q, k, v = make(w)
-    ramp = torch.linspace(0.2, 6.0, S).reshape(1, 1, S, 1)
-    k = (k.float() * ramp).half()
+    _, k, v = make(w)
+    q = _queries(w, QUERIES[head_dim])
+    k = (k.float() * torch.linspace(0.2, 6.0, S).reshape(1, 1, S, 1)).half()
     ocache = oracle_cache_from(k, v)
     cache = gpu_cache_from(k, v)
     for n_splits in (1, 3):
         out = tq.tq_sdpa_int4_decode(cache, q.cuda(), S, w.attn_scale, n_splits=n_splits)
         torch.cuda.synchronize()
-        assert_close(out, oracle_attend(q, ocache, S, w.attn_scale), f"d={head_dim} n_splits={n_splits}")
+        assert_close(out, _reference(q, ocache, S, w.attn_scale), f"d={head_dim} n_splits={n_splits}")
+
+
+@pytest.mark.parametrize("kind", ["fixed", "lengths", "paged"])
+def test_eight_rows_at_256_with_one_query_token(kind):
+    """The smallest calls with one query token that take this kernel at head_dim 256, next to ones that do not: same result."""
+    for S, B in ((3072, 1), (3071, 1), (1100, 3)):
+        w = wl.custom(batch=B, n_q_heads=32, n_kv_heads=4, head_dim=256, seq_len=S, attn_scale=1.0, qk_std=0.1, seed=2500 + S)
+        q, k, v = make(w)
+        ocache = oracle_cache_from(k, v)
+        lens = [S - 37 * b for b in range(B)]
+        ref = np.concatenate([oracle.attend_packed(np16(q[b:b + 1]), *[np.ascontiguousarray(a[b:b + 1]) for a in ocache],
+                                                   seq_len=n if kind != "fixed" else S, alpha=1.0) for b, n in enumerate(lens)])
+        lens = torch.tensor(lens, dtype=torch.int32).cuda()
+        if kind == "paged":
+            pages = -(-S // 64)
+            pool = tq.KVCache(B * pages, 4, 256, 64)
+            table = torch.randperm(B * pages, generator=torch.Generator().manual_seed(S)).to(torch.int32).reshape(B, pages).cuda()
+            tq.tq_quantize_kv_paged(pool, table, k.cuda(), v.cuda(), torch.zeros(B, dtype=torch.int32).cuda())
+            out = tq.tq_sdpa_int4_decode_paged(pool, table, q.cuda(), lens, S, 1.0)
+        else:
+            cache = gpu_cache_from(k, v)
+            out = (tq.tq_sdpa_int4_decode(cache, q.cuda(), S, 1.0) if kind == "fixed" else
+                   tq.tq_sdpa_int4_decode_varlen(cache, q.cuda(), lens, S, 1.0))
+        torch.cuda.synchronize()
+        assert_close(out, ref, f"{kind} S={S} B={B}")
 
 
 @pytest.mark.parametrize("scale", [-0.7, 0.0, 1.0e-6])
@@ -62,3 +109,35 @@ def test_any_finite_scale_at_512(scale):
     out = tq.tq_sdpa_int4_decode(gpu_cache_from(k, v), q.cuda(), S, scale)
     torch.cuda.synchronize()
     assert_close(out, oracle_attend(q, oracle_cache_from(k, v), S, scale), f"scale={scale}")
+
+
+@pytest.mark.parametrize("head_dim,nq", [(256, 2), (256, 5), (256, 8), (512, 1), (512, 2), (512, 8)])
+def test_new_tokens_across_tiles_and_chunks(head_dim, nq):
+    """A step's new tokens at every place of a supertile, across two of them and across two chunks: stored bit for bit, attended,
+    and nothing that the cache held in their place (NaN here) is used."""
+    for S in (nq, nq + 1, 17, 31 + nq // 2, 32, 64 + nq - 1, 65, 96 + nq // 2, 130, 257, 260):
+        if S < nq:
+            continue
+        for n_splits in (0, 3):
+            w = wl.custom(batch=2, n_q_heads=12, n_kv_heads=2, head_dim=head_dim, seq_len=S, attn_scale=1.0, qk_std=0.1,
+                          v_std=0.5, seed=2400 + S)
+            _, k, v = make(w)
+            gen = torch.Generator().manual_seed(S)
+            q = (torch.randn(2, nq, 12, head_dim, generator=gen) * 0.1).half()
+            ocache = oracle_cache_from(k, v)
+            cache = tq.KVCache(2, 2, head_dim, S + 40)
+            for t in cache.tensors():
+                t.fill_(float("nan")) if t.dtype == torch.float16 else t.fill_(0xEE)
+            if S > nq:
+                tq.tq_quantize_kv(cache, k[:, :, :S - nq].contiguous().cuda(), v[:, :, :S - nq].contiguous().cuda(), 0)
+            kn, vn = k[:, :, S - nq:].contiguous().cuda(), v[:, :, S - nq:].contiguous().cuda()
+            qd = q.cuda() if nq > 1 else q[:, 0].contiguous().cuda()
+            out = tq.tq_sdpa_int4_append_decode(cache, kn, vn, qd, S, w.attn_scale, n_splits=n_splits)
+            torch.cuda.synchronize()
+            assert_cache_bit_exact(cache, ocache, S)
+            for t in cache.tensors():
+                rest = t[:, :, S:]
+                assert bool(torch.isnan(rest).all() if t.dtype == torch.float16 else (rest == 0xEE).all())
+            rows = [oracle.attend_packed(np16(q[:, t]), *ocache, seq_len=S - (nq - 1 - t), alpha=1.0) for t in range(nq)]
+            ref = np.stack(rows, axis=1) if nq > 1 else rows[0]
+            assert_close(out, ref, f"d={head_dim} nq={nq} S={S} n_splits={n_splits}")

@@ -128,7 +128,7 @@ int hip_rc(hipError_t e) { return e == hipSuccess ? TQ_OK : TQ_ERR_HIP; }
 
 // Which kernel a decode call takes, and whether that kernel can also do the chunk merge.
 // merge, merge_step: whether a decode, a decode step's launch also does the chunk merge (or has none to do: one chunk).
-// wide: the matrix-core kernel for many query rows (head_dim 512, and 256 by wide_rows_at_256); small_tile: at most eight query rows to a block.
+// wide: the matrix-core kernel for many query rows (head_dim 512; 256 and 128 by wide_rows); small_tile: at most eight query rows to a block.
 struct Route { bool ok, use_mfma, merge, merge_step, wide, small_tile; };
 // The in-kernel merge ends the kernel with a chain of device-wide round trips (publish the partial, count in, read
 // all partials) that one block per KV head walks alone: about 2.5 us for up to 32 chunks, against about 3.5 us for the
@@ -157,7 +157,11 @@ bool takes_token(const tq_kv_cache* cache, int n_q_heads, const tq_decode_opts* 
   return tq::mfma_takes_token(cache->head_dim, cache->group_size, rows_of(cache, n_q_heads, opts));
 }
 
-// head_dim 256 with more than two query rows per KV head: the kernel of head_dim 512 takes 16 rows to a block, the other one two,
+// What a call is: a decode, or a decode step, of one common length; either of per-sequence lengths (seq_len: their bound).
+enum class Call { kDecode, kStep, kLengths };
+
+// Where the kernel for wide rows is taken (head_dim 512: always, any finite scale; else groups of 32 and a positive one).
+// head_dim 256 with more than two query rows per KV head: it takes 16 rows to a block, the other one two,
 // and unpacks the stream again for every two.  It always merges in a launch of its own, so what it loses by shows where blocks of many
 // rows have little to do each: with one query token it is taken from five rows on (16 heads over 4, one sequence of 32K tokens
 // 17.6 / 18.7 us per step, other / this) and from 12K (token, KV head) pairs (4 sequences of 512, 32 heads over 4, 10.3 / 10.5),
@@ -167,17 +171,41 @@ bool takes_token(const tq_kv_cache* cache, int n_q_heads, const tq_decode_opts* 
 // of 600 25.4 / 22.4; 128 of 150 18.0 / 25.2, of 2000 121 / 82.5; own lengths: 8 of 400 .. 6000 22.0 / 18.8, 32 of 100 .. 1000 19.0 / 17.9,
 // 64 of 60 .. 600 23.7 / 28.3, of 100 .. 2000 41.8 / 38.8, 128 of 60 .. 600 36.6 / 52.3.  Several query tokens: 32 heads over 16, 2 of
 // them, 600 tokens 12.9 / 10.3, 32K 46 / 40; 8, 32K 128 / 43; 16 over 8, 8 of them, 4 sequences of 2000 33 / 16.
-bool wide_rows_at_256(const tq_kv_cache* cache, int n_q_heads, int seq_len, const tq_decode_opts* opts, bool own_lengths) {
-  const int rows = rows_of(cache, n_q_heads, opts);
-  if (cache->head_dim != 256 || cache->group_size != tq::kGroup || rows <= (queries_of(opts) > 1 ? 2 : 4)) return false;
-  const int64_t kv_rows = (int64_t)cache->batch * cache->n_kv_heads;
-  if (queries_of(opts) == 1 && kv_rows * windowed(seq_len, opts) < 12288) return false;
-  return kv_rows <= 128 || windowed(seq_len, opts) >= (own_lengths ? 1024 : 512);
+bool wide_rows_at_256(int rows, int64_t kv_rows, int tokens, int n_queries, Call call) {
+  if (rows <= (n_queries > 1 ? 2 : 4) || (n_queries == 1 && kv_rows * tokens < 12288)) return false;
+  return kv_rows <= 128 || tokens >= (call == Call::kLengths ? 1024 : 512);
+}
+// head_dim 128: up to 128 (sequence, KV head) rows (with more the other kernel's blocks are full, and it orders and packs them), and
+// up to some tokens per compute unit (and 32-row block, where a KV head's rows take several).  It starts and merges 4 - 5 us sooner and
+// takes several new tokens in, which saves a step its append launch (2.6 us); the 16-row tile takes 5.9 ns per token and compute
+// unit against 6.6 (up to 16 rows) and 9.9 (two tiles to a block).  So a step may be longer than a decode, and several query tokens longer
+// than one; up to eight rows only the append launch is saved (a launch of one new token has none to save: 64 heads over 8, 8191
+// tokens 10.8 / 10.5 us per step, 32 heads over 8, 4000, 8.4 / 9.1).  us per step, other / this (d: per decode):
+// 17 rows and more: 64 heads over 8, 4 query tokens, 600 tokens 16.7 / 11.4, 8000 19.4 / 14.0 (d 16.1 / 13.9), 16K 21.8 / 17.6
+// (d 18.8 / 17.5), 24K 23.8 / 21.3 (d 21.2 / 21.2), 32K 26.0 / 25.0, 48K 32.5 / 31.9, 128K 61.4 / 69.2; 16 sequences of 1000 20.2 / 18.3
+// (d 15.8 / 18.0); 8 query tokens, 16K 27.2 / 24.7 (d 23.2 / 24.7), 24K 31.0 / 32.4; 128 heads over 8, 4, 16K 25.9 / 24.6.
+// 9 .. 16 rows: 128 heads over 8, 600 tokens 14.0 / 9.2, 8192 14.4 / 10.7, 24K 17.4 / 15.4 (d 16.0 / 15.3), 32K 19.2 / 18.1 (d 17.7 / 17.8),
+// 48K 22.3 / 22.5; 16 sequences of 1500 17.0 / 15.4 (d 15.6 / 14.8); 64 over 8, 2 query tokens, 16K 19.3 / 13.3, 32K 22.3 / 18.0
+// (d 19.9 / 17.9), 48K 25.4 / 22.7 (d 22.6 / 22.6), 64K 28.0 / 27.3, 128K 39.8 / 46; own lengths, 4 of 400 .. 6000
+// 18.7 / 16.0, 8 of them 22.6 / 21.5, 16 of 300 .. 4000 24.2 / 25.0, 8 of 2000 .. 8000 25.5 / 26.4.
+// Up to 8 rows: 32 over 8, 2, 8000 14.3 / 10.5, 24K 17.9 / 15.2, 30K 18.1 / 17.2; 32 over 32, 2, 2000 12.0 / 10.6, 4000 13.3 / 13.1.
+bool wide_rows_at_128(int rows, int64_t kv_rows, int tokens, int n_queries, Call call) {
+  if (kv_rows > 128) return false;
+  const bool step = call == Call::kStep;
+  const int64_t load = kv_rows * tokens / kBlocksWide * std::max(1, (rows + 31) / 32);   // tokens per compute unit and block
+  if (call == Call::kLengths) return rows > 8 && load <= 1600;   // (tokens: the longest, the others may be any)
+  if (rows > 16) return step ? load <= 1250 : load <= 600 && kv_rows <= 64;
+  if (rows > 8) return load <= (n_queries > 1 ? (step ? 1800 : 1200) : (step ? 1100 : 900));
+  return n_queries > 1 && step && load <= (rows > 4 ? 960 : 500);
+}
+bool wide_rows(const tq_kv_cache* cache, int n_q_heads, int seq_len, float attn_scale, const tq_decode_opts* opts, Call call) {
+  if (cache->head_dim == 512) return std::isfinite(attn_scale);
+  if (cache->group_size != tq::kGroup || !(attn_scale > 0.0f && std::isfinite(attn_scale))) return false;
+  const auto rule = cache->head_dim == 256 ? wide_rows_at_256 : wide_rows_at_128;
+  return rule(rows_of(cache, n_q_heads, opts), (int64_t)cache->batch * cache->n_kv_heads, windowed(seq_len, opts), queries_of(opts), call);
 }
 
-// own_lengths: the call has per-sequence lengths (seq_len: their bound)
-Route route_of(const tq_kv_cache* cache, int n_q_heads, int seq_len, float attn_scale, const tq_decode_opts* opts,
-               bool own_lengths = false) {
+Route route_of(const tq_kv_cache* cache, int n_q_heads, int seq_len, float attn_scale, const tq_decode_opts* opts, Call call) {
   const int variant = opts ? opts->variant : 0;
   // groups of 64 or 128 elements: the matrix-core kernel at head_dim 128 and 256 (see mfma_supports_group), else the
   // generic vector-ALU kernel with one query token per sequence
@@ -194,9 +222,8 @@ Route route_of(const tq_kv_cache* cache, int n_q_heads, int seq_len, float attn_
   // the matrix-core kernel folds attn_scale into its exp2 argument and needs it positive and finite
   const bool scale_ok = attn_scale > 0.0f && std::isfinite(attn_scale);
   if (variant == 2 && !scale_ok) return {false, false, false, false, false, false};
-  // the kernel for wide rows: head_dim 512 (any finite scale), partials merged by the merge kernel
-  if (variant != 1 && (cache->head_dim == 512 ? std::isfinite(attn_scale)
-                                              : scale_ok && wide_rows_at_256(cache, n_q_heads, seq_len, opts, own_lengths)))
+  // the kernel for wide rows, partials merged by the merge kernel
+  if (variant != 1 && wide_rows(cache, n_q_heads, seq_len, attn_scale, opts, call))
     return {true, false, false, false, true, false};
   // the matrix-core kernel addresses a (batch, KV head) row of codes with 32-bit byte offsets
   const bool offsets_ok = (int64_t)seq_len * (cache->head_dim / 2) < (1ll << 31);
@@ -263,7 +290,7 @@ int ranked_waves(int64_t rows, int batch, int tokens, bool d256) {
 struct Ranked { int waves, spread; };             // waves of a row's block, 0 = not this way; DecodeParams::rank_spread
 Ranked ranked_rows(const tq_kv_cache* cache, int n_q_heads, int seq_len, float attn_scale, const tq_decode_opts* opts) {
   if (queries_of(opts) > 1 || (opts && opts->n_splits > 0)) return {0, -1};
-  const Route r = route_of(cache, n_q_heads, seq_len, attn_scale, opts, true);
+  const Route r = route_of(cache, n_q_heads, seq_len, attn_scale, opts, Call::kLengths);
   if (!r.ok || !r.use_mfma) return {0, -1};
   const int64_t rows = (int64_t)cache->batch * cache->n_kv_heads * mfma_share_of(cache, n_q_heads, opts);
   const bool d256 = cache->head_dim == 256;
@@ -309,7 +336,8 @@ int run_partial(PartialRequest& rq) {
   const tq_decode_opts* opts = rq.opts;
   const int32_t* seq_lens = rq.seq_lens;
   const int n_q_heads = rq.n_q_heads, seq_len = rq.seq_len;
-  const Route r = route_of(cache, n_q_heads, seq_len, rq.attn_scale, opts, seq_lens != nullptr);
+  const Route r = route_of(cache, n_q_heads, seq_len, rq.attn_scale, opts,
+                           seq_lens ? Call::kLengths : rq.step ? Call::kStep : Call::kDecode);
   if (!r.ok) return TQ_ERR_UNSUPPORTED;
   const bool use_mfma = r.use_mfma;
   const int target = use_mfma ? kBlocksMfma : r.wide ? kBlocksWide : kBlocksValu;
@@ -320,7 +348,7 @@ int run_partial(PartialRequest& rq) {
   const bool append = rq.k_new != nullptr && !rq.new_in_chunks;
   const int first = seq_len - attended;           // first attended token
   if (append) --attended;
-  const int row_tiles = r.wide ? tq::wide_row_tiles(rows_of(cache, n_q_heads, opts)) : 1;
+  const int row_tiles = r.wide ? tq::wide_row_tiles(cache->head_dim, rows_of(cache, n_q_heads, opts)) : 1;
   const int mfma_share = use_mfma ? mfma_share_of(cache, n_q_heads, opts) : 1;
   const int rows_per_batch = cache->n_kv_heads * (use_mfma ? mfma_share : row_tiles);
   const Ranked rank = seq_lens && rq.out != nullptr ? ranked_rows(cache, n_q_heads, seq_len, rq.attn_scale, opts)
@@ -497,7 +525,7 @@ int32_t tq_decode_launches(const tq_kv_cache* cache, int32_t n_q_heads, int32_t 
   if (opts && opts->variant == 2 && cache->head_dim != 512 &&
       !tq::mfma_supported(cache->head_dim, rows_of(cache, n_q_heads, opts)))
     return 0;
-  const Route r = route_of(cache, n_q_heads, seq_len, attn_scale, opts);
+  const Route r = route_of(cache, n_q_heads, seq_len, attn_scale, opts, Call::kDecode);
   if (!r.ok) return 0;
   return r.merge ? 1 : 2;
 }
@@ -616,7 +644,7 @@ int tq_sdpa_int4_append_decode(const tq_kv_cache* cache, const void* k_new, cons
   if (rc != TQ_OK) return rc;
   if (!k_new || !v_new) return TQ_ERR_NULL;
   if (!aligned(k_new, 16) || !aligned(v_new, 16)) return TQ_ERR_ALIGN;
-  const Route r = route_of(cache, n_q_heads, seq_len, attn_scale, opts);
+  const Route r = route_of(cache, n_q_heads, seq_len, attn_scale, opts, Call::kStep);
   if (!r.ok) return TQ_ERR_UNSUPPORTED;
   PartialRequest rq{cache, q, n_q_heads, seq_len};
   rq.attn_scale = attn_scale;
@@ -688,7 +716,7 @@ namespace {
 // tokens), else the append kernel runs first.
 int append_decode_with_lengths(PartialRequest& rq, const void* k_new, const void* v_new) {
   const tq_decode_opts* opts = rq.opts;
-  const bool taken_in = route_of(rq.cache, rq.n_q_heads, rq.seq_len, rq.attn_scale, opts, true).use_mfma
+  const bool taken_in = route_of(rq.cache, rq.n_q_heads, rq.seq_len, rq.attn_scale, opts, Call::kLengths).use_mfma
                             ? takes_token(rq.cache, rq.n_q_heads, opts) ||
                                   ranked_rows(rq.cache, rq.n_q_heads, rq.seq_len, rq.attn_scale, opts).waves == 0
                             : rq.cache->group_size == tq::kGroup;
@@ -713,7 +741,7 @@ int tq_sdpa_int4_append_decode_varlen(const tq_kv_cache* cache, const void* k_ne
   if (rc != TQ_OK) return rc;
   if (!seq_lens || !k_new || !v_new) return TQ_ERR_NULL;
   if (!aligned(seq_lens, 4) || !aligned(k_new, 16) || !aligned(v_new, 16)) return TQ_ERR_ALIGN;
-  if (!route_of(cache, n_q_heads, max_seq_len, attn_scale, opts, true).ok) return TQ_ERR_UNSUPPORTED;
+  if (!route_of(cache, n_q_heads, max_seq_len, attn_scale, opts, Call::kLengths).ok) return TQ_ERR_UNSUPPORTED;
   PartialRequest rq{cache, q, n_q_heads, max_seq_len};
   rq.seq_lens = seq_lens;
   rq.attn_scale = attn_scale;
@@ -738,7 +766,7 @@ int tq_sdpa_int4_append_decode_paged(const tq_kv_cache* pool, const int32_t* blo
   if (rc != TQ_OK) return rc;
   if (!seq_lens || !k_new || !v_new) return TQ_ERR_NULL;
   if (!aligned(seq_lens, 4) || !aligned(k_new, 16) || !aligned(v_new, 16)) return TQ_ERR_ALIGN;
-  if (!route_of(&view, n_q_heads, max_seq_len, attn_scale, opts, true).ok) return TQ_ERR_UNSUPPORTED;
+  if (!route_of(&view, n_q_heads, max_seq_len, attn_scale, opts, Call::kLengths).ok) return TQ_ERR_UNSUPPORTED;
   PartialRequest rq{&view, q, n_q_heads, max_seq_len};
   rq.seq_lens = seq_lens;
   rq.attn_scale = attn_scale;

@@ -1,6 +1,6 @@
 // Matrix-core fused int4 decode attention for many query rows per KV head: head_dim 512 (the global-attention column of the
-// kernel configuration table, Appendix A: 32 query heads on one KV head) and head_dim 256 with more than two rows, phase 1 of
-// Sec. 3.2.
+// kernel configuration table, Appendix A: 32 query heads on one KV head) and head_dim 256 and 128 where the kernel with
+// few rows to a block would unpack the stream again and again; phase 1 of Sec. 3.2.
 //
 // A KV head's query rows form tiles of 16 (every column of a matrix instruction is a row of its own), every fetched
 // byte is used by all of them, and the work is arithmetic, not traffic: the vector ALU prepares the operands of the
@@ -14,11 +14,11 @@
 //           the fp32 accumulator).  Scale and zero-point are applied to the accumulator in fp32,
 //             q.k^ = sum_g s_g (q_g.c_g - z_g sum(q_g)).
 //           The wave's weights (32 bits) go to LDS, with the reference of its exponentials: the round's one barrier.
-//   P V     by DIMS: a wave takes two groups (64 dims) of all the round's tokens (d = 256: of every other supertile, two waves to
-//           the groups).  The accumulator layout of S^T (lane =
+//   P V     by DIMS: a wave takes two groups (64 dims) of all the round's tokens (d = 256 / 128: of every
+//           second / fourth supertile, two / four waves to the groups).  The accumulator layout of S^T (lane =
 //           query row, four tokens per lane and 16-token tile) IS the A-operand layout of P, so a lane reads back what the same
 //           lane of the scoring wave wrote.  The 16 columns of one instruction lie in ONE group (column c = byte c / 4
-//           of word c % 4), so that A = fp16(p s_v), rounded once, is right for all of them and the codes enter exactly: a
+//           of word c % 4), so that A = fp16(p s_v) (d = 128: in two parts, see SPLIT) is right for all of them and the codes enter exactly: a
 //           byte's two nibbles mixed (n_even + 16 n_odd, an exact subnormal) next to n_even alone, the odd dim
 //           recovered from the two sums at the end.  The zero-points go through one more instruction per group with the
 //           same A.  The second 16-token tile enters with its weights negated and its codes complemented, which keeps all
@@ -113,9 +113,16 @@ struct Tile {
   // a step's new tokens, quantised: [token][K | V]: codes, (scale, zero-point) of each group
   static constexpr int N_ROW = TB + NG * 4, OFF_N = OFF_Q + 16 * RT * NG * 4, SMEM = OFF_N + kMaxQueries * 2 * N_ROW;
   static constexpr int NOPS = D == 512 ? 2 : 1;     // load instructions for a new token's K and V
-  static constexpr int ROWS = 16 * RT, RPW = ROWS / NW, QOPS = RPW * D * 2 / 1024;   // query rows a wave brings in (into the second V round)
+  // query rows, brought in by the first QW waves, RPW each (into the second V round)
+  static constexpr int ROWS = 16 * RT, QW = ROWS * D * 2 / 1024 < NW ? ROWS * D * 2 / 1024 : NW, RPW = ROWS / QW, QOPS = RPW * D * 2 / 1024;
+  // The weights p s_v enter the matrix core as two fp16 operands, the leading part and the rest.  At d = 128 the kernels this one
+  // takes over from have a reference per wave, which makes the weight of every wave's largest score exact in fp16; with one
+  // reference to the block one operand has 3 - 10 % more error against 64 bits than they (2.25e-4 .. 2.45e-4, 2.2e-4 .. 2.35e-4), two
+  // have less (2.07e-4, nearly all of it the output's own rounding).  It costs 16 vector and 3 matrix instructions per 32 tokens
+  // and group (64 heads over 8, 4 query tokens, 32K tokens 22.4 -> 25.0 us per step; the rest by one fma_mixlo an element 26.4).
+  static constexpr bool SPLIT = D == 128;
   static constexpr int GPW = 2, TH = NW * GPW / NG; // groups of V a wave takes; waves that share them (each every TH-th supertile)
-  static_assert(SMEM <= 160 * 1024 && QOPS * 1024 == RPW * D * 2 && (ROWS + 2 * NW) * D * 2 <= NW * V_BLK && kMaxQueries <= NW && VC * 1024 == V_SC, "LDS");
+  static_assert(SMEM <= 160 * 1024 && QOPS * 1024 == RPW * D * 2 && ROWS * D * 2 + NW * NOPS * 1024 <= NW * V_BLK && kMaxQueries <= NW && VC * 1024 == V_SC, "LDS");
   static_assert(TT * SG == 2, "a slot is 2 KB of codes and 2 x 256 B of scales and zero-points");
   static __device__ constexpr int place(int tok, int piece) { return piece ^ ((tok & 15) >> (4 - LG)); }   // V: place of a token's piece
 };
@@ -297,6 +304,7 @@ __global__ __launch_bounds__(512, 2) void decode_partial_wide_kernel(DecodeParam
     constexpr int PIECES = D / 8;
 #pragma unroll
     for (int u = 0; u < C::QOPS; ++u) {
+      if (C::QW < NW && wave >= C::QW) break;
       const int idx = u * 64 + lane, r = wave * C::RPW + idx / PIECES;
       int t_q;
       const int64_t qr = row_of(min(tile * C::ROWS + r, rows_total - 1), t_q);
@@ -309,14 +317,14 @@ __global__ __launch_bounds__(512, 2) void decode_partial_wide_kernel(DecodeParam
   const int new_first = seq - NQ;
   const bool new_block = p.k_new != nullptr && end > new_first;
   const bool new_mine = new_block && wave < NQ && new_first + wave >= begin && new_first + wave < end;
-  const uint32_t new_raw = lds0 + C::OFF_V + NW * C::V_BLK + C::ROWS * D * 2 + wave * (4 * D);
+  const uint32_t new_raw = lds0 + C::OFF_V + NW * C::V_BLK + C::ROWS * D * 2 + wave * (C::NOPS * 1024);
   if (new_mine) {
     const int64_t at = ((int64_t)(b * p.n_kv_heads + kv) * NQ + wave) * D;
     if constexpr (D == 512) {
       dma16_lane(p.k_new + at + lane * 8, new_raw);
       dma16_lane(p.v_new + at + lane * 8, new_raw + 1024);
     } else {
-      const int l = lane & (D / 4 - 1);           // D / 8 lanes K, D / 8 lanes V
+      const int l = lane & (D / 4 - 1);           // D / 8 lanes K, D / 8 lanes V (d = 128: and once more)
       dma16_lane((l < D / 8 ? p.k_new : p.v_new) + at + (l & (D / 8 - 1)) * 8, new_raw);
     }
   }
@@ -365,6 +373,7 @@ __global__ __launch_bounds__(512, 2) void decode_partial_wide_kernel(DecodeParam
     constexpr int PIECES = D / 8;
 #pragma unroll
     for (int u = 0; u < C::QOPS; ++u) {
+      if (C::QW < NW && wave >= C::QW) break;
       const int idx = u * 64 + lane, r = wave * C::RPW + idx / PIECES;
       const uint32_t at = lds0 + C::OFF_V + NW * C::V_BLK + (wave * C::QOPS + u) * 1024 + lane * 16;
       const half8v x = lds_get<half8v>(at);
@@ -746,20 +755,34 @@ __global__ __launch_bounds__(512, 2) void decode_partial_wide_kernel(DecodeParam
 #pragma unroll
       for (int i = 0; i < 4; ++i) zw[i] = __builtin_amdgcn_perm(v.z[1][i], v.z[0][i], z_sel) ^ 0x80000000u;
       const half8v zb = as_half8(zw[0], zw[1], zw[2], zw[3]);
+      const half8v zb15 = zb + pos15_odd;         // (one operand is enough for the rest, 2^-11 of the whole)
 #pragma unroll
       for (int m = 0; m < GPW; ++m)
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
-          half8v pa;
+          half8v pa, rest;
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            pa[2 * i] = (half_t)__builtin_fmaf(v.p[rt][0][i], half_of(v.s[0][i], m), 0.0f);
-            pa[2 * i + 1] = (half_t)__builtin_fmaf(-v.p[rt][1][i], half_of(v.s[1][i], m), 0.0f);
+            if constexpr (C::SPLIT) {             // (both rounded towards zero: what the first leaves out the second takes)
+              const float w0 = v.p[rt][0][i] * half_of(v.s[0][i], m), w1 = -v.p[rt][1][i] * half_of(v.s[1][i], m);
+              const auto hi = __builtin_amdgcn_cvt_pkrtz(w0, w1);
+              const auto lo = __builtin_amdgcn_cvt_pkrtz(__builtin_fmaf((float)hi[0], -1.0f, w0), __builtin_fmaf((float)hi[1], -1.0f, w1));
+              pa[2 * i] = hi[0]; pa[2 * i + 1] = hi[1];
+              rest[2 * i] = lo[0]; rest[2 * i + 1] = lo[1];
+            } else {
+              pa[2 * i] = (half_t)__builtin_fmaf(v.p[rt][0][i], half_of(v.s[0][i], m), 0.0f);
+              pa[2 * i + 1] = (half_t)__builtin_fmaf(-v.p[rt][1][i], half_of(v.s[1][i], m), 0.0f);
+            }
           }
           oacc[rt][m][0] = mfma16(pa, v_even[m], oacc[rt][m][0]);
           oacc[rt][m][1] = mfma16(pa, v_mixed[m], oacc[rt][m][1]);
           zacc[rt][m] = mfma16(pa, zb, zacc[rt][m]);
           zacc[rt][m] = mfma16(pa, pos15_odd, zacc[rt][m]);
+          if constexpr (C::SPLIT) {
+            oacc[rt][m][0] = mfma16(rest, v_even[m], oacc[rt][m][0]);
+            oacc[rt][m][1] = mfma16(rest, v_mixed[m], oacc[rt][m][1]);
+            zacc[rt][m] = mfma16(rest, zb15, zacc[rt][m]);
+          }
         }
     }
   }
@@ -851,27 +874,28 @@ hipError_t launch(const DecodeParams& p, dim3 grid, hipStream_t s) {
 
 }  // namespace
 
-int wide_row_tiles(int rows) { return (rows + 15) / 16; }
+int wide_row_tiles(int head_dim, int rows) { return head_dim == 128 ? (rows + 31) / 32 : (rows + 15) / 16; }
 
 // Chunks of a sequence of `tiles` 32-token tiles, at most.  A block scores 128 tokens in a round (d = 256: 256); with fewer, and up
 // to 64 of them, each still shortens the launch; beyond, the merge kernel pays for what the shorter chunks save (us per step at
 // chunks of 32 / 64 / 128 tokens: 32 heads on one KV head, 1500 tokens 11.4 / 12.3 / 14.1; 4096 14.2 / 12.7 / 13.4; 8192
 // 15.3 / 15.3 / 14.8; 16 heads on two, 700 tokens 10.4 / 11.1 / 14.2; 5000 12.0 (64) / 12.9 / 14.9).
 int wide_max_chunks(int head_dim, int tiles) {
-  const int m = head_dim == 256 ? (tiles <= 48 ? 2 : 4) : tiles <= 64 ? 1 : tiles < 224 ? 2 : 4;
+  const int m = head_dim < 512 ? (tiles <= 48 ? 2 : 4) : tiles <= 64 ? 1 : tiles < 224 ? 2 : 4;
   return (tiles + m - 1) / m;
 }
 
 hipError_t launch_partial_wide(const DecodeParams& p_in, int batch, int head_dim, hipStream_t s) {
   DecodeParams p = p_in;
   if (p.n_queries < 1) p.n_queries = 1;
-  if ((head_dim != 512 && head_dim != 256) || p.group != kGroup || p.gqa < 1 || p.kv_share < 1) return hipErrorInvalidValue;
+  if ((head_dim != 512 && head_dim != 256 && head_dim != 128) || p.group != kGroup || p.gqa < 1 || p.kv_share < 1) return hipErrorInvalidValue;
   if (p.n_queries > kMaxQueries) return hipErrorInvalidValue;
-  if (p.kv_share != wide_row_tiles(p.n_queries * p.gqa)) return hipErrorInvalidValue;
+  if (p.kv_share != wide_row_tiles(head_dim, p.n_queries * p.gqa)) return hipErrorInvalidValue;
   if (p.k_new && (p.seq_lens || p.block_table)) return hipErrorInvalidValue;
   if (p.block_table && (p.page_shift < 5 || !p.seq_lens)) return hipErrorInvalidValue;   // a supertile must not straddle pages
   const dim3 grid = p.var_chunks > 0 ? dim3(p.var_chunks, p.n_kv_heads * p.kv_share, 1)
                                      : dim3(p.n_splits, p.n_kv_heads * p.kv_share, batch);
+  if (head_dim == 128) return p.n_queries * p.gqa <= 16 ? launch<128, 1, 2>(p, grid, s) : launch<128, 2, 2>(p, grid, s);
   return head_dim == 256 ? launch<256, 1, 2>(p, grid, s) : launch<512, 1, 1>(p, grid, s);
 }
 

@@ -6,17 +6,18 @@ import torch
 import oracle
 import paper_2604_16957_amd as tq
 import tq_workloads as wl
-from gpu_common import (assert_cache_bit_exact, assert_close, gpu_cache_from, make, np16, oracle_attend, oracle_cache_from)
+from gpu_common import (assert_cache_bit_exact, assert_close, assert_close_elementwise, gpu_cache_from, make, np16, oracle_attend, oracle_cache_from)
 
 pytestmark = pytest.mark.gpu
 
-# a wave scores 16 tokens of a round of 128 (head_dim 256: 32 of 256); a supertile of 32 is the unit of P V
+# a wave scores 16 tokens of a round of 128 (head_dim 256 and 128: 32 of 256); a supertile of 32 is the unit of P V
 LENGTHS = {512: (15, 16, 17, 31, 48, 65, 112, 127, 128, 129, 144, 145, 255, 257, 300),
+           128: (2, 31, 33, 65, 97, 161, 225, 255, 256, 257, 300, 513),
            256: (2, 31, 32, 33, 65, 96, 224, 225, 255, 256, 257, 289, 511, 513, 600)}
 
 
-# At head_dim 256 the kernel takes small calls with several query tokens only.
-QUERIES = {512: 1, 256: 2}
+# At head_dim 256 the kernel takes small calls with several query tokens only (at 128: also with nine rows and more).
+QUERIES = {512: 1, 256: 2, 128: 2}
 
 
 def _poisoned(k, v, S):
@@ -42,7 +43,7 @@ def _reference(q, ocache, S, alpha):
 
 
 @pytest.mark.parametrize("heads", [(5, 1), (17, 1), (34, 2), (20, 1)])
-@pytest.mark.parametrize("head_dim", [256, 512])
+@pytest.mark.parametrize("head_dim", [128, 256, 512])
 def test_rounds_and_their_remainders(head_dim, heads):
     """Every remainder of a round, in one chunk and in two: waves without tokens, half supertiles, rows of a last tile
     that has few; nothing behind the sequence's end is used."""
@@ -60,7 +61,7 @@ def test_rounds_and_their_remainders(head_dim, heads):
             assert_close(out, ref, f"d={head_dim} {heads} S={S} n_splits={n_splits}")
 
 
-@pytest.mark.parametrize("head_dim", [256, 512])
+@pytest.mark.parametrize("head_dim", [128, 256, 512])
 def test_references_that_move_in_every_round(head_dim):
     """Scores that grow along the sequence: the rows' references move round after round, by another wave each time."""
     S = 1000
@@ -111,7 +112,7 @@ def test_any_finite_scale_at_512(scale):
     assert_close(out, oracle_attend(q, oracle_cache_from(k, v), S, scale), f"scale={scale}")
 
 
-@pytest.mark.parametrize("head_dim,nq", [(256, 2), (256, 5), (256, 8), (512, 1), (512, 2), (512, 8)])
+@pytest.mark.parametrize("head_dim,nq", [(128, 1), (128, 2), (128, 3), (128, 8), (256, 2), (256, 5), (256, 8), (512, 1), (512, 2), (512, 8)])
 def test_new_tokens_across_tiles_and_chunks(head_dim, nq):
     """A step's new tokens at every place of a supertile, across two of them and across two chunks: stored bit for bit, attended,
     and nothing that the cache held in their place (NaN here) is used."""
@@ -119,11 +120,11 @@ def test_new_tokens_across_tiles_and_chunks(head_dim, nq):
         if S < nq:
             continue
         for n_splits in (0, 3):
-            w = wl.custom(batch=2, n_q_heads=12, n_kv_heads=2, head_dim=head_dim, seq_len=S, attn_scale=1.0, qk_std=0.1,
+            w = wl.custom(batch=2, n_q_heads=18, n_kv_heads=2, head_dim=head_dim, seq_len=S, attn_scale=1.0, qk_std=0.1,
                           v_std=0.5, seed=2400 + S)
             _, k, v = make(w)
             gen = torch.Generator().manual_seed(S)
-            q = (torch.randn(2, nq, 12, head_dim, generator=gen) * 0.1).half()
+            q = (torch.randn(2, nq, 18, head_dim, generator=gen) * 0.1).half()
             ocache = oracle_cache_from(k, v)
             cache = tq.KVCache(2, 2, head_dim, S + 40)
             for t in cache.tensors():
@@ -141,3 +142,30 @@ def test_new_tokens_across_tiles_and_chunks(head_dim, nq):
             rows = [oracle.attend_packed(np16(q[:, t]), *ocache, seq_len=S - (nq - 1 - t), alpha=1.0) for t in range(nq)]
             ref = np.stack(rows, axis=1) if nq > 1 else rows[0]
             assert_close(out, ref, f"d={head_dim} nq={nq} S={S} n_splits={n_splits}")
+
+
+@pytest.mark.parametrize("heads,nq", [((4, 4), 2), ((12, 4), 2), ((8, 2), 2), ((24, 3), 3)])
+def test_steps_of_several_query_tokens_at_128(heads, nq):
+    """Two to 24 rows per KV head, lengths on both sides of where the kernel is chosen by its load: step and decode agree with the
+    oracle, under a window too."""
+    for S, window in ((nq, 0), (70, 0), (1500, 0), (1500, 100), (66000 // heads[1], 0)):
+        w = wl.custom(n_q_heads=heads[0], n_kv_heads=heads[1], head_dim=128, seq_len=S, seed=2600 + S)
+        _, k, v = make(w)
+        q = (torch.randn(1, nq, heads[0], 128, generator=torch.Generator().manual_seed(S))).half()
+        ocache = oracle_cache_from(k, v)
+        cache = gpu_cache_from(k[:, :, :max(1, S - nq)].contiguous(), v[:, :, :max(1, S - nq)].contiguous(), capacity=S + 1)
+        out = tq.tq_sdpa_int4_append_decode(cache, k[:, :, S - nq:].contiguous().cuda(), v[:, :, S - nq:].contiguous().cuda(), q.cuda(),
+                                            S, w.attn_scale, window=window)
+        torch.cuda.synchronize()
+        assert_cache_bit_exact(cache, ocache, S)
+        again = tq.tq_sdpa_int4_decode(cache, q.cuda(), S, w.attn_scale, window=window)
+        torch.cuda.synchronize()
+        rows = []
+        for t in range(nq):
+            n = S - (nq - 1 - t)
+            lo = max(0, n - window) if window else 0
+            part = [np.ascontiguousarray(a[:, :, lo:n]) for a in ocache]
+            rows.append(oracle.attend_packed(np16(q[:, t]), *part, seq_len=n - lo, alpha=w.attn_scale))
+        ref = np.stack(rows, axis=1)
+        assert_close_elementwise(out, ref, f"step {heads} nq={nq} S={S} window={window}")
+        assert_close_elementwise(again, ref, f"decode {heads} nq={nq} S={S} window={window}")

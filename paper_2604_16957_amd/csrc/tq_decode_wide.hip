@@ -26,9 +26,9 @@
 // So the operands of either contraction are prepared once per block, the scores need no exchange, a wave's sums take 24
 // registers (192, if a wave kept all of a row's dims for the tokens it scored) and no sums are merged at the end.
 // Measured against four waves that split the head dimension for both contractions, exchanged partial scores (a barrier per
-// 32 tokens) and multiplied V out into fp16 (us per step): 32 heads on one KV head, 32K tokens 28.1 -> 19.3, 128K 71.7 ->
-// 42, 8 sequences of 32K 74.9 -> 68.4; 16 heads on two 27.3 -> 19.4; 32 heads over 8 49.5 -> 40.5; the error against 64
-// bits 3.5e-4 -> 3.0e-4.  (Eight waves in lock step with the dims split likewise: 25.1; a wave that keeps whole tokens and all
+// 32 tokens) and multiplied V out into fp16 (us per step): 32 heads on one KV head, 32K tokens 28.0 -> 18.6, 128K 71.7 ->
+// 39.5, 8 sequences of 32K 75.2 -> 68.3; 16 heads on two 27.5 -> 19.1; 32 heads over 8 49.8 -> 40.6; the error against 64
+// bits 3.6e-4 -> 2.9e-4.  (Eight waves in lock step with the dims split likewise: 25.1; a wave that keeps whole tokens and all
 // dims: the compiler moves the 192 accumulator registers about.)  A round of 128 tokens takes about 3.5 us, 72 - 78 % of it
 // the vector port's: some 660 instructions a wave, two waves to a SIMD.
 //

@@ -54,12 +54,23 @@ namespace {
 typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 typedef _Float16 half8v __attribute__((ext_vector_type(8)));
 typedef float float4v __attribute__((ext_vector_type(4)));
-typedef uint32_t uint2v __attribute__((ext_vector_type(2)));
+typedef uint16_t ushort2v __attribute__((ext_vector_type(2)));
 typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
 
 constexpr int kMaxDevices = 64;
 constexpr float kNegBig = -1.0e30f;         // "no token seen yet" (finite: no inf - inf)
 constexpr float kSlack = 2.0f;              // log2 units: exp2(score - reference) <= 4
+// The weights p carry 2^kLift, so that p s_v is a normal fp16 number from 2^-26 on (2^-14 without) and below 2^15 for scales of V below 2.
+// Without the lift the weights of small scales were subnormals of one fixed spacing (relative error against 64 bits, scores of spread 2
+// (nats), V of spread 1 / 1e-2 / 1e-3, without -> with: d = 512, 32K tokens 2.5e-4 / 3.8e-4 / 2.6e-3 -> 2.5e-4 / 2.5e-4 / 5.2e-4;
+// d = 128, 4 query tokens, 8K 2.1e-4 / 7.0e-4 / 5.3e-3 -> 2.1e-4 / 2.1e-4 / 2.7e-4; the output's own rounding is 2.1e-4 / 2.1e-4 / 2.7e-4 ..
+// 5.0e-4).  What remains of the spacing, 2^-24 of a lifted weight, moves a result by less than the spacing of fp16 outputs.  For scales from
+// 2 on see sv_lim.  The lift is part of the reference that the partial is published with.  Time: 18.54 -> 18.6 us (d = 512, 32K), 14.15 ->
+// 14.3 (d = 128, 4 query tokens, 8K), 41.4 -> 41.8 (d = 256, 32 heads over 4, 128K); a power of two common to the block, taken from the
+// largest scale it has met and exchanged at the round's barrier, 19.0, 14.45 and 41.6.
+constexpr float kLift = 12.0f;
+constexpr uint32_t scale_limit(uint32_t e) { return (e << 10 | 0x3FFu) * 0x10001u; }   // the largest scale of biased fp16 exponent e, twice
+constexpr uint32_t kPlainScales = scale_limit(15);
 constexpr uint32_t kMaskLo = 0x000F000Fu;   // nibbles 0 and 4 of a word -> fp16 subnormals c * 2^-24
 constexpr uint32_t kMaskHi = 0x00F000F0u;   // nibbles 1 and 5           -> c * 2^-20
 constexpr uint32_t kPos15Odd = 0x4B800000u; // fp16 pair (0, 15): k-slots alternate first tile, second tile
@@ -438,6 +449,10 @@ __global__ __launch_bounds__(512, 2) void decode_partial_wide_kernel(DecodeParam
 
   // ---- running state (Alg. 1, the initialisation), per column (query row)
   float m_all[RT], m_run[RT], l_run[RT];          // references of exp2 (raw units): the sums', this wave's weights'; this lane's share of the sum
+  // sv_lim: the largest size a scale of this wave's groups may have as it stands.  From 2 on its sums carry 2^lower, lower < 0, so that
+  // p s_v stays below 2^15.  A wave looks at its scales once per round; those below 2 cost it nothing more.
+  uint32_t sv_lim = kPlainScales;
+  auto lower_of = [](uint32_t lim) { return (float)(int)(kPlainScales >> 26) - (float)(int)(lim >> 26); };
   float4v oacc[RT][GPW][2], zacc[RT][GPW];        // rows 4kq+i; [0]: sum w c - 15 sum_t1 w of the even dim, [1]: of even + 16 odd; zero-points
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) {
@@ -461,6 +476,7 @@ __global__ __launch_bounds__(512, 2) void decode_partial_wide_kernel(DecodeParam
 #pragma unroll
   for (int x = 0; x < NX; ++x) v_rd[x] = lds0 + C::OFF_V + 4 * kq * TB + (C::place(4 * kq, g0) ^ x) * 16 + 4 * (c & 3);
   uint32_t vs_rd = lds0 + C::OFF_V + C::V_SC + (g0 / 2 * WT + 4 * kq) * 4;
+  uint32_t sv_rd = lds0 + C::OFF_V + C::V_SC + g0 / 2 * (WT * 4) + lane / WT * (TH * C::V_BLK) + lane % WT * 4;   // lane: a token of the wave's supertiles
   const uint32_t v_sel = 0x0C000C00u | ((4u + (c >> 2)) << 16) | (uint32_t)(c >> 2);   // this column's byte of a word
   const uint32_t z_sel = (c & 1) ? 0x07060302u : 0x05040100u;    // the zero-point operand's column c: group c % 2 of the pair
 
@@ -507,7 +523,7 @@ __global__ __launch_bounds__(512, 2) void decode_partial_wide_kernel(DecodeParam
 
   for (int r = 0; r < n_rounds; ++r) {
     // (the LDS addresses made from these are worked out where they are needed: not kept in registers throughout the loop)
-    asm volatile("" : "+v"(k_rd[0]), "+v"(k_rd[1]), "+v"(k_rd[2]), "+v"(k_rd[3]), "+v"(ks_rd), "+v"(q_rd));
+    asm volatile("" : "+v"(k_rd[0]), "+v"(k_rd[1]), "+v"(k_rd[2]), "+v"(k_rd[3]), "+v"(ks_rd), "+v"(q_rd), "+v"(sv_rd));
     const int tok0 = first_of(r);
     const bool mine = tok0 < end, more = first_of(r + 1) < end;  // (wave-uniform)
     float sc[RT][TT][4];                          // then the weights
@@ -621,8 +637,7 @@ __global__ __launch_bounds__(512, 2) void decode_partial_wide_kernel(DecodeParam
       }
       // -- online softmax (Alg. 1: the maximum, the weights and the running sum).  m_run is a REFERENCE per row: it moves when
       //    a score exceeds it by more than kSlack (log2 units), and then to kSlack above the new maximum, so that exp2(score -
-      //    m_run) <= 4 and p s_v fits fp16 for every representable scale.  Any reference gives the same o / l, and the
-      //    chunk merge (Eq. 6) accepts any m_c.
+      //    m_run) <= 4.  Any reference gives the same o / l, and the chunk merge (Eq. 6) accepts any m_c.
       float mx[RT];
       bool move = false;
 #pragma unroll
@@ -641,7 +656,7 @@ __global__ __launch_bounds__(512, 2) void decode_partial_wide_kernel(DecodeParam
       }
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) {
-        const float mk = fmaxf(m_run[rt] * kappa, -3.0e38f);    // (finite also for a column that has seen no token yet)
+        const float mk = fmaxf(__builtin_fmaf(m_run[rt], kappa, -kLift), -3.0e38f);    // (finite also for a column that has seen no token yet)
 #pragma unroll
         for (int t = 0; t < TT; ++t) {
           float4v pr;
@@ -674,6 +689,9 @@ __global__ __launch_bounds__(512, 2) void decode_partial_wide_kernel(DecodeParam
     // whose V area is filled again (and whose weights the next round overwrites).
     block_barrier();
     if (more) issue_v(r + 1, row_n, last_n);
+    constexpr int STEPS = R / 32 / TH;
+    const int st0 = wave / (NW / TH);             // (this wave's supertiles: st0, st0 + TH, ..)
+    const uint32_t sv_at = sv_rd + (r & 1) * (NW * C::V_BLK) + st0 * (2 / TT * C::V_BLK);
     // -- everybody's references.  They differ from the sums' only where a row's maximum has moved: then the sums are
     //    rescaled (Alg. 1, the correction factor) and the weights brought to the common reference as they are read.
     bool differ = false;
@@ -688,6 +706,35 @@ __global__ __launch_bounds__(512, 2) void decode_partial_wide_kernel(DecodeParam
       differ = differ || lo != m_all[rt] || hi != m_all[rt];
     }
     const bool rescale = __builtin_amdgcn_ballot_w64(differ) != 0;
+    // -- the scales of this wave's groups, 64 tokens a word
+    {
+      uint32_t sv[STEPS / 2];
+#pragma unroll
+      for (int u = 0; u < STEPS / 2; ++u) sv[u] = lds_get<uint32_t>(sv_at + u * (64 / WT * TH * C::V_BLK));
+      const ushort2v big = __builtin_elementwise_max(__builtin_bit_cast(ushort2v, sv[0]), __builtin_bit_cast(ushort2v, sv[STEPS / 2 - 1]));
+      const ushort2v lim = __builtin_bit_cast(ushort2v, sv_lim);                                       // (fp16 bits are ordered by size)
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64(__builtin_bit_cast(uint32_t, __builtin_elementwise_max(big, lim)) != sv_lim) != 0, 0)) {
+        uint32_t top = 0;                         // (a negative scale comes here every time: its size counts; behind the chunk's end lies anything)
+#pragma unroll
+        for (int u = 0; u < STEPS / 2; ++u) {
+          const int st = st0 + TH * (2 * u + (lane >> 5));
+          if (32 * st + (lane & 31) < end - begin - R * r) top = max(top, max(sv[u] & 0x7FFFu, (sv[u] >> 16) & 0x7FFFu));
+        }
+        const uint32_t e = min(wave_max((int)top) >> 10, 30);
+        if (e > sv_lim >> 26) {
+          const float f = __builtin_amdgcn_exp2f(lower_of(scale_limit(e)) - lower_of(sv_lim));
+          sv_lim = scale_limit(e);
+#pragma unroll
+          for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int m = 0; m < GPW; ++m) {
+              oacc[rt][m][0] *= f;
+              oacc[rt][m][1] *= f;
+              zacc[rt][m] *= f;
+            }
+        }
+      }
+    }
     if (rescale) {
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) {
@@ -708,8 +755,6 @@ __global__ __launch_bounds__(512, 2) void decode_partial_wide_kernel(DecodeParam
     }
     // -- P V (Alg. 1, the accumulator update): this wave's groups of V, all the round's tokens
     const int n_st = min(R / 32, (end - begin - R * r + 31) >> 5);
-    constexpr int STEPS = R / 32 / TH;
-    const int st0 = wave / (NW / TH);             // (this wave's supertiles: st0, st0 + TH, ..)
     VBase at;
     {
       const uint32_t blk = (r & 1) * (NW * C::V_BLK) + st0 * (2 / TT * C::V_BLK);
@@ -740,13 +785,14 @@ __global__ __launch_bounds__(512, 2) void decode_partial_wide_kernel(DecodeParam
       }
       __builtin_amdgcn_sched_barrier(0);
       if (k + 1 < STEPS) load_vw(at, (k + 1) * TH, vw);
-      if (rescale) {
+      if (rescale || sv_lim != kPlainScales) {
+        const float lower = lower_of(sv_lim);
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
           for (int t = 0; t < 2; ++t) {
             const float mw = lds_get<float>(pb + C::P_M + ((rt * 16 + c) * NW + (2 * (st0 + k * TH) + t) / TT) * 4);
-            const float f = __builtin_amdgcn_exp2f((mw - m_all[rt]) * kappa);
+            const float f = __builtin_amdgcn_exp2f(__builtin_fmaf(mw - m_all[rt], kappa, lower));
 #pragma unroll
             for (int i = 0; i < 4; ++i) v.p[rt][t][i] *= f;
           }
@@ -763,7 +809,7 @@ __global__ __launch_bounds__(512, 2) void decode_partial_wide_kernel(DecodeParam
           half8v pa, rest;
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            if constexpr (C::SPLIT) {             // (both rounded towards zero: what the first leaves out the second takes)
+            if constexpr (C::SPLIT) {             // (both rounded towards zero: what the first leaves out the second takes, down to 2^-24)
               const float w0 = v.p[rt][0][i] * half_of(v.s[0][i], m), w1 = -v.p[rt][1][i] * half_of(v.s[1][i], m);
               const auto hi = __builtin_amdgcn_cvt_pkrtz(w0, w1);
               const auto lo = __builtin_amdgcn_cvt_pkrtz(__builtin_fmaf((float)hi[0], -1.0f, w0), __builtin_fmaf((float)hi[1], -1.0f, w1));
@@ -798,6 +844,7 @@ __global__ __launch_bounds__(512, 2) void decode_partial_wide_kernel(DecodeParam
     if (kq == 0) lds_l[(rt * 16 + c) * NW + wave] = l;
   }
   float2 o2[RT][GPW][4];
+  const float raise = __builtin_amdgcn_exp2f(-lower_of(sv_lim));
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
@@ -807,6 +854,10 @@ __global__ __launch_bounds__(512, 2) void decode_partial_wide_kernel(DecodeParam
         const float zc = __shfl(zacc[rt][m][i], (lane & ~1) | m);
         const float even = oacc[rt][m][0][i], mixed = oacc[rt][m][1][i];
         o2[rt][m][i] = float2{__builtin_fmaf(even, 0x1p24f, -zc), __builtin_fmaf(mixed - even, 0x1p20f, -zc)};
+        if (__builtin_expect(sv_lim != kPlainScales, 0)) {
+          o2[rt][m][i].x *= raise;
+          o2[rt][m][i].y *= raise;
+        }
         if constexpr (TH > 1) lds_o[(((wave * RT + rt) * 4 + i) * GPW + m) * 64 + lane] = o2[rt][m][i];
       }
   __syncthreads();
@@ -842,7 +893,7 @@ __global__ __launch_bounds__(512, 2) void decode_partial_wide_kernel(DecodeParam
       int t_q;
       const int64_t ph = row_of((tile * RT + rt) * 16 + c, t_q) * part_stride + split;
       const bool seen = m_all[rt] > kNegBig;      // (a row whose tokens were all masked counts as empty)
-      st_dev2(p.part_ml + ph * 2, seen ? m_all[rt] * kappa : kNegBig, seen ? l : 0.0f);
+      st_dev2(p.part_ml + ph * 2, seen ? m_all[rt] * kappa - kLift : kNegBig, seen ? l : 0.0f);
     }
   }
 }

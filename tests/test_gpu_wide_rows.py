@@ -169,3 +169,62 @@ def test_steps_of_several_query_tokens_at_128(heads, nq):
         ref = np.stack(rows, axis=1)
         assert_close_elementwise(out, ref, f"step {heads} nq={nq} S={S} window={window}")
         assert_close_elementwise(again, ref, f"decode {heads} nq={nq} S={S} window={window}")
+
+
+def _spread_inputs(head_dim, heads, S, nq, sigma, v_std, seed):
+    """Scores of a Gaussian spread of sigma (attention scale 1), V of spread v_std (a number, or one per element of the head)."""
+    gen = torch.Generator().manual_seed(seed)
+    shape = (1, heads[1], S, head_dim)
+    k = torch.randn(shape, generator=gen).half()
+    v = (torch.randn(shape, generator=gen) * torch.as_tensor(v_std)).half()
+    q = (torch.randn(1, nq, heads[0], head_dim, generator=gen) * (sigma / head_dim ** 0.5)).half()
+    return (q if nq > 1 else q[:, 0].contiguous()), k, v
+
+
+def _assert_weights_whole(out, ref, dims, what):
+    """The relative error (2-norm) over `dims` of the head: the output's own fp16 rounding, as it falls on this reference, and one fp16
+    rounding of every weight, 2^-10 / sqrt(12) of a weight's power of two, sqrt(1/2) of that relative to a weight on average, independent from
+    token to token like V; a quarter on top of both for the fp32 arithmetic and for chance."""
+    ref = ref[..., dims]
+    err = np.linalg.norm(np16(out).astype(np.float64)[..., dims] - ref) / np.linalg.norm(ref)
+    own = np.linalg.norm(ref.astype(np.float16).astype(np.float64) - ref) / np.linalg.norm(ref)
+    bar = 1.25 * np.hypot(own, 2.0 ** -10 / 24 ** 0.5)
+    assert err <= bar, f"{what}: {err:.2e} over {bar:.2e} (the output's rounding {own:.2e})"
+
+
+@pytest.mark.parametrize("v_std", [30.0, 1.0, 1e-2, 1e-3, 1e-4])
+@pytest.mark.parametrize("head_dim", [128, 256, 512])
+def test_weights_keep_their_bits_whatever_the_size_of_v(head_dim, v_std):
+    """P V takes fp16 operands p s_v: they stay in fp16's normal range for large scales of V and for small ones, flat softmax or sharp."""
+    nq = QUERIES[head_dim]
+    for heads, S, n_splits, sigma in (((2, 1), 300, 0, 2.0), ((16, 1), 2000, 0, 0.3), ((32, 2), 2000, 1, 2.0), ((9, 1), 5000, 4, 2.0)):
+        if head_dim == 128 and heads == (2, 1):
+            heads = (9, 1)                          # (up to eight rows the kernel takes steps only)
+        q, k, v = _spread_inputs(head_dim, heads, S, nq, sigma, v_std, 2700 + S)
+        out = tq.tq_sdpa_int4_decode(_poisoned(k, v, S), q.cuda(), S, 1.0, n_splits=n_splits)
+        torch.cuda.synchronize()
+        _assert_weights_whole(out, _reference(q, oracle_cache_from(k, v), S, 1.0), slice(None), f"d={head_dim} {heads} S={S} v_std={v_std}")
+
+
+@pytest.mark.parametrize("head_dim", [128, 256, 512])
+def test_scales_of_v_that_grow_differ_and_turn_negative(head_dim):
+    """Large scales first met rounds into the chunk, next to groups whose scales stay small, and scales of either sign."""
+    nq, S, heads = QUERIES[head_dim], 3000, (10, 1)
+    v_std = torch.full((head_dim,), 0.03)
+    large = torch.arange(head_dim) // 32 % 3 == 1  # every third group
+    v_std[large] = 3.0
+    for case in ("late", "negative"):
+        q, k, v = _spread_inputs(head_dim, heads, S, nq, 1.0, v_std, 2800)
+        if case == "late":
+            v = (v.float() * torch.where(large, torch.linspace(-2.0, 5.0, S)[:, None].exp2(), torch.ones(1))).half()
+        cache, arrays = gpu_cache_from(k, v), list(oracle_cache_from(k, v))
+        if case == "negative":
+            flip = torch.rand(arrays[4].shape, generator=torch.Generator().manual_seed(1)) < 0.3
+            arrays[4] = np.where(flip.numpy(), -arrays[4], arrays[4])
+            cache.v_scale.copy_(torch.from_numpy(arrays[4]))
+        ref = _reference(q, arrays, S, 1.0)
+        for n_splits in (1, 3):
+            out = tq.tq_sdpa_int4_decode(cache, q.cuda(), S, 1.0, n_splits=n_splits)
+            torch.cuda.synchronize()
+            for dims in (large.numpy(), ~large.numpy()):
+                _assert_weights_whole(out, ref, dims, f"d={head_dim} {case} n_splits={n_splits} {int(dims.sum())} dims")

@@ -121,6 +121,9 @@ DecodeParams make_params(const tq_kv_cache* c, const void* q, int n_q_heads, int
   p.n_splits = plan.n_splits;
   p.tokens_per_split = plan.tokens_per_split;
   p.scale_log2 = attn_scale * 1.4426950408889634f;
+  // (below this every weight is 1 to the last bit of 32, |q.k| being under 2^43, and the kernels' slack in raw units, 2 / scale, would
+  // pass their mark of a row that has seen no token)
+  if (p.scale_log2 != 0.0f && std::fabs(p.scale_log2) < 1.0e-30f) p.scale_log2 = std::copysign(1.0e-30f, p.scale_log2);
   return p;
 }
 

@@ -112,6 +112,20 @@ def test_any_finite_scale_at_512(scale):
     assert_close(out, oracle_attend(q, oracle_cache_from(k, v), S, scale), f"scale={scale}")
 
 
+@pytest.mark.parametrize("head_dim,scales", [(128, (1e-38, 1e-44)), (256, (1e-38, 1e-44)), (512, (1e-38, 1e-44, -1e-38, -1e-44))])
+def test_scales_of_the_smallest_size(head_dim, scales):
+    """Scales down to fp32's subnormals: every token weighs the same (on whichever kernel the call takes)."""
+    S = 333
+    for heads, nq in (((8, 1), 1), ((2, 1), 1), ((9, 1), 2)):
+        w = wl.custom(n_q_heads=heads[0], n_kv_heads=heads[1], head_dim=head_dim, seq_len=S, attn_scale=1.0, seed=2350)
+        _, k, v = make(w)
+        q, ocache, cache = _queries(w, nq), oracle_cache_from(k, v), gpu_cache_from(k, v)
+        for scale in scales:
+            out = tq.tq_sdpa_int4_decode(cache, q.cuda(), S, scale)
+            torch.cuda.synchronize()
+            assert_close(out, _reference(q, ocache, S, scale), f"d={head_dim} {heads} nq={nq} scale={scale}")
+
+
 @pytest.mark.parametrize("head_dim,nq", [(128, 1), (128, 2), (128, 3), (128, 8), (256, 2), (256, 5), (256, 8), (512, 1), (512, 2), (512, 8)])
 def test_new_tokens_across_tiles_and_chunks(head_dim, nq):
     """A step's new tokens at every place of a supertile, across two of them and across two chunks: stored bit for bit, attended,

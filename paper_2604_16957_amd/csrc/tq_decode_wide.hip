@@ -545,6 +545,7 @@ __global__ __launch_bounds__(512, 2) void decode_partial_wide_kernel(DecodeParam
         const uint32_t vb = lds0 + C::OFF_V + ((r & 1) * NW + wave) * C::V_BLK;
         for (int i = lane; i < WT * NG; i += 64)  // (what else lies there must not meet the zero weights of later tokens as Inf or NaN)
           if (i % WT >= t0) lds_put(vb + C::V_SC + i * 4, 0u);
+        asm volatile("" ::: "memory");            // (16-bit stores to the same places follow: not to be moved across these by their type)
         constexpr int W = D / 8;                  // words of a row, four to a group
         for (int i = lane; i < n * 2 * W; i += 64) {
           const int row = i / W, w = i % W, g = w >> 2, t = t0 + (row >> 1);

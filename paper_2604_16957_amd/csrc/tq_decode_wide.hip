@@ -921,7 +921,8 @@ template <int D, int RT, int TT>
 hipError_t launch(const DecodeParams& p, dim3 grid, hipStream_t s) {
   const bool plain = p.seq_lens == nullptr && p.block_table == nullptr;
   if (p.kv_share == 1) return plain ? launch_as<D, RT, TT, true, true>(p, grid, s) : launch_as<D, RT, TT, true, false>(p, grid, s);
-  return plain ? launch_as<D, RT, TT, false, true>(p, grid, s) : launch_as<D, RT, TT, false, false>(p, grid, s);
+  if constexpr (D == 128 && RT == 1) return hipErrorInvalidValue;   // (at most 16 rows: one tile per KV head)
+  else return plain ? launch_as<D, RT, TT, false, true>(p, grid, s) : launch_as<D, RT, TT, false, false>(p, grid, s);
 }
 
 }  // namespace

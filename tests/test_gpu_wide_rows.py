@@ -221,6 +221,17 @@ def test_weights_keep_their_bits_whatever_the_size_of_v(head_dim, v_std):
 
 
 @pytest.mark.parametrize("head_dim", [128, 256, 512])
+def test_the_longest_chunk_a_plan_makes(head_dim):
+    """16384 tokens in one chunk: what the accumulators pick up over its 512 (256, 128) tiles does not show."""
+    S, heads = 16384, (16, 1)
+    for sigma in (0.16, 1.0):
+        q, k, v = _spread_inputs(head_dim, heads, S, QUERIES[head_dim], sigma, 1.0, 2900)
+        out = tq.tq_sdpa_int4_decode(gpu_cache_from(k, v), q.cuda(), S, 1.0, n_splits=1)
+        torch.cuda.synchronize()
+        _assert_weights_whole(out, _reference(q, oracle_cache_from(k, v), S, 1.0), slice(None), f"d={head_dim} sigma={sigma}")
+
+
+@pytest.mark.parametrize("head_dim", [128, 256, 512])
 def test_scales_of_v_that_grow_differ_and_turn_negative(head_dim):
     """Large scales first met rounds into the chunk, next to groups whose scales stay small, and scales of either sign."""
     nq, S, heads = QUERIES[head_dim], 3000, (10, 1)

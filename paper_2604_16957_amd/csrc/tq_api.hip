@@ -535,6 +535,12 @@ int32_t tq_decode_launches(const tq_kv_cache* cache, int32_t n_q_heads, int32_t 
   return r.merge ? 1 : 2;
 }
 
+int32_t tq_internal_decode_kernel(const tq_kv_cache* cache, int32_t n_q_heads, int32_t seq_len, float attn_scale,
+                                  const tq_decode_opts* opts, int32_t call) {
+  const Route r = route_of(cache, n_q_heads, seq_len, attn_scale, opts, call == 0 ? Call::kDecode : call == 1 ? Call::kStep : Call::kLengths);
+  return !r.ok ? 0 : r.wide ? 4 : !r.use_mfma ? 1 : r.small_tile ? 2 : 3;
+}
+
 const char* tq_status_string(int status) {
   switch (status) {
     case TQ_OK: return "ok";

@@ -402,3 +402,9 @@ hipError_t launch_reduce(const DecodeParams& p, int batch, int head_dim, hipStre
 bool reduce_is_grouped(int head_dim, int64_t out_rows, int n_q_heads, int gqa);
 
 }  // namespace tq
+
+// Which kernel serves a decode (call 0), a decode step (1) or either with per-sequence lengths (2): 0 refused, 1 generic, 2 matrix-core
+// kernel with up to eight query rows to a block (head_dim 256: two), 3 with sixteen, 4 the one for wide rows.  Not part of the
+// public ABI: results agree on either side of a rule, so only this shows a test which side it is on.
+extern "C" int32_t tq_internal_decode_kernel(const tq_kv_cache* cache, int32_t n_q_heads, int32_t seq_len, float attn_scale,
+                                             const tq_decode_opts* opts, int32_t call);

@@ -2,12 +2,15 @@
 fed the same seeded fp16 bits.  Nothing computed by the HIP path is ever given to the oracle."""
 from __future__ import annotations
 
+import ctypes
+
 import numpy as np
 import torch
 
 import oracle
 import paper_2604_16957_amd as tq
 import tq_workloads as wl
+from paper_2604_16957_amd import binding
 
 MAX_ABS = 2e-3      # attention output: max |gpu - oracle|
 REL_L2 = 1e-3       # attention output: |gpu - oracle|_2 / |oracle|_2
@@ -95,3 +98,19 @@ def oracle_attend(q: torch.Tensor, ocache, seq_len: int, alpha: float) -> np.nda
 def make(w: wl.Workload):
     q, k, v = wl.make_inputs(w, device="cpu")
     return q, k, v
+
+
+KERNELS = ("refused", "generic", "8 rows", "16 rows", "wide rows")   # matrix-core tiles of up to 8 (d = 256: 2) and of 16 rows
+
+
+def kernel_of(batch, n_q_heads, n_kv_heads, head_dim, seq_len, call="decode", scale=1.0, group=32, n_queries=1, window=0,
+              variant=0, n_splits=0):
+    """Which kernel the library takes for such a call ("decode", "step", or "lengths" for per-sequence lengths of at most seq_len and for
+    pages); asked on the host, nothing is launched."""
+    fake = 0x10000
+    struct = binding.TqKvCacheStruct(fake, fake, fake, fake, fake, fake, batch, n_kv_heads, head_dim, group, seq_len + seq_len % 2, 0)
+    opts = binding.TqDecodeOptsStruct(n_splits, variant, window, n_queries)
+    ask = binding.raw().tq_internal_decode_kernel
+    ask.restype = ctypes.c_int32
+    ask.argtypes = [ctypes.c_void_p, ctypes.c_int32, ctypes.c_int32, ctypes.c_float, ctypes.c_void_p, ctypes.c_int32]
+    return KERNELS[ask(ctypes.byref(struct), n_q_heads, seq_len, scale, ctypes.byref(opts), ("decode", "step", "lengths").index(call))]

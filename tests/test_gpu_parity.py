@@ -1204,9 +1204,9 @@ def test_append_decode_in_one_call(shape, variant):
 @pytest.mark.parametrize("variant", [0, 2])
 @pytest.mark.parametrize("shape", ["g16_d128_b2_kv2", "g12_d128", "g8_d256"])
 def test_gqa_groups_larger_than_the_matrix_core_tile(shape, variant):
-    """GQA ratios above the 8-row tile (d=128: a tile of 16 rows) or above any tile (d=256: two rows; then several
-    blocks stream each KV head, each with its share of the group); plain decode (merged in the kernel or by the
-    reduce launch), sliding window, per-sequence lengths and the one-call step all take that path."""
+    """GQA ratios above the tile of the kernel with few rows to a block (d = 128: eight rows, d = 256: two); plain decode, sliding
+    window, per-sequence lengths and the one-call step.  At d = 128 all of them are on the kernel for wide rows; at d = 256 the shorter
+    ones are on the two-row tile, where several blocks stream each KV head, each with its share of the group."""
     shapes = dict(g16_d128_b2_kv2=dict(batch=2, n_q_heads=32, n_kv_heads=2, head_dim=128, outlier_channels=4),
                   g12_d128=dict(n_q_heads=12, n_kv_heads=1, head_dim=128),
                   g8_d256=dict(batch=2, n_q_heads=24, n_kv_heads=3, head_dim=256, attn_scale=1.0, qk_std=0.1))
@@ -1233,11 +1233,10 @@ def test_gqa_groups_larger_than_the_matrix_core_tile(shape, variant):
 
 @pytest.mark.parametrize("gqa", [9, 10, 16, 24, 40])
 def test_sixteen_row_tiles(gqa):
-    """d = 128 with 9 or more query rows per KV head: tiles of 16 rows (every column of the tile a row of its own,
-    one score accumulator per quantisation group, the P V columns regrouped by group), partly filled (9, 10 of 16),
-    full, and several per KV head (24 = 2 x 12, 40 = 4 x 10).  Ragged lengths around the 32-token supertile and
-    the chunk boundaries, forced chunk counts, a sliding window, per-sequence lengths, and a sharp softmax where
-    every one of the 16 rows keeps moving its own reference."""
+    """d = 128 with 9 or more query rows per KV head and few sequences: the kernel for wide rows in all but the longest decode with
+    40 rows, whose tiles have 16 (test_gpu_many_rows.py has that tile at every size of its range).  Tiles partly filled (9, 10), full,
+    and several per KV head.  Ragged lengths around the 32-token supertile and the chunk boundaries, forced chunk
+    counts, a sliding window, per-sequence lengths, and a sharp softmax where every row keeps moving its own reference."""
     Hkv, B = 2, 2
     for S, window, n_splits, scale in ((1, 0, 0, None), (31, 0, 0, None), (32, 0, 0, None), (33, 0, 0, None),
                                        (1025, 0, 0, None), (2500, 0, 7, None), (4133, 700, 0, None),
@@ -1302,7 +1301,8 @@ def _oracle_causal(q4, ocache, lens, alpha, window=0):
 def test_several_query_tokens(shape, nq):
     """n_queries > 1: the sequence's last nq tokens as queries, causal among themselves, against the oracle
     row by row; lengths around the 32-token supertile boundaries put the masked tokens in one supertile, in
-    two, and in a chunk of their own."""
+    two, and in a chunk of their own.  (With more than eight rows per KV head, at d = 256 more than two: on the kernel for wide rows;
+    test_gpu_many_rows.py has the calls of that many rows on the others.)"""
     for S, n_splits in ((nq, 0), (31, 0), (33, 0), (63, 0), (64, 0), (65, 0), (66, 0), (71, 0), (1000, 0), (1030, 4),
                         (4133, 0), (20002, 0)):
         if S < nq:

@@ -6,7 +6,7 @@ import torch
 import oracle
 import paper_2604_16957_amd as tq
 import tq_workloads as wl
-from gpu_common import (assert_cache_bit_exact, assert_close, assert_close_elementwise, gpu_cache_from, make, np16, oracle_attend, oracle_cache_from)
+from gpu_common import (assert_cache_bit_exact, assert_close, assert_close_elementwise, gpu_cache_from, kernel_of, make, np16, oracle_attend, oracle_cache_from)
 
 pytestmark = pytest.mark.gpu
 
@@ -55,6 +55,7 @@ def test_rounds_and_their_remainders(head_dim, heads):
         q = _queries(w, nq)
         cache, ocache = _poisoned(k, v, S), oracle_cache_from(k, v)
         ref = _reference(q, ocache, S, w.attn_scale)
+        assert kernel_of(1, *heads, head_dim, S, n_queries=nq) == "wide rows"
         for n_splits in (0, 1, 2):
             out = tq.tq_sdpa_int4_decode(cache, q.cuda(), S, w.attn_scale, n_splits=n_splits)
             torch.cuda.synchronize()
@@ -158,11 +159,38 @@ def test_new_tokens_across_tiles_and_chunks(head_dim, nq):
             assert_close(out, ref, f"d={head_dim} nq={nq} S={S} n_splits={n_splits}")
 
 
+# heads, query tokens, the last length of one sequence whose step (decode) is on this kernel
+@pytest.mark.parametrize("heads,nq,last,of", [((4, 4), 2, 32063, "step"), ((12, 4), 2, 61503, "step"), ((8, 2), 2, 123007, "step"),
+                                              ((24, 3), 3, 106751, "step"), ((24, 3), 3, 51285, "decode"), ((32, 4), 2, 115263, "step"),
+                                              ((32, 4), 2, 76863, "decode"), ((64, 4), 1, 70463, "step"), ((64, 4), 1, 57663, "decode")])
+def test_steps_and_decodes_around_the_line_at_128(heads, nq, last, of):
+    """Two to 24 rows per KV head: the last length that the kernel is chosen for by its load, and the next: step and decode agree with the
+    oracle, on whichever kernel each is."""
+    for S in (last, last + 1):
+        assert (kernel_of(1, *heads, 128, S, of, n_queries=nq) == "wide rows") == (S == last)
+        w = wl.custom(n_q_heads=heads[0], n_kv_heads=heads[1], head_dim=128, seq_len=S, seed=2600 + nq)
+        _, k, v = make(w)
+        q = torch.randn(1, nq, heads[0], 128, generator=torch.Generator().manual_seed(S)).half()
+        q = q if nq > 1 else q[:, 0].contiguous()
+        ocache = oracle_cache_from(k, v)
+        cache = gpu_cache_from(k[:, :, :S - nq].contiguous(), v[:, :, :S - nq].contiguous(), capacity=S + 1)
+        out = tq.tq_sdpa_int4_append_decode(cache, k[:, :, S - nq:].contiguous().cuda(), v[:, :, S - nq:].contiguous().cuda(), q.cuda(),
+                                            S, w.attn_scale)
+        torch.cuda.synchronize()
+        assert_cache_bit_exact(cache, ocache, S)
+        again = tq.tq_sdpa_int4_decode(cache, q.cuda(), S, w.attn_scale)
+        torch.cuda.synchronize()
+        ref = _reference(q, ocache, S, w.attn_scale)
+        assert_close_elementwise(out, ref, f"step {heads} nq={nq} S={S}")
+        assert_close_elementwise(again, ref, f"decode {heads} nq={nq} S={S}")
+
+
 @pytest.mark.parametrize("heads,nq", [((4, 4), 2), ((12, 4), 2), ((8, 2), 2), ((24, 3), 3)])
 def test_steps_of_several_query_tokens_at_128(heads, nq):
-    """Two to 24 rows per KV head, lengths on both sides of where the kernel is chosen by its load: step and decode agree with the
-    oracle, under a window too."""
+    """Two to 24 rows per KV head, steps on this kernel (their decodes with up to eight rows on the other): both agree with the oracle,
+    under a window too."""
     for S, window in ((nq, 0), (70, 0), (1500, 0), (1500, 100), (66000 // heads[1], 0)):
+        assert kernel_of(1, *heads, 128, S, "step", n_queries=nq, window=window) == "wide rows"
         w = wl.custom(n_q_heads=heads[0], n_kv_heads=heads[1], head_dim=128, seq_len=S, seed=2600 + S)
         _, k, v = make(w)
         q = (torch.randn(1, nq, heads[0], 128, generator=torch.Generator().manual_seed(S))).half()
@@ -214,6 +242,7 @@ def test_weights_keep_their_bits_whatever_the_size_of_v(head_dim, v_std):
     for heads, S, n_splits, sigma in (((2, 1), 300, 0, 2.0), ((16, 1), 2000, 0, 0.3), ((32, 2), 2000, 1, 2.0), ((9, 1), 5000, 4, 2.0)):
         if head_dim == 128 and heads == (2, 1):
             heads = (9, 1)                          # (up to eight rows the kernel takes steps only)
+        assert kernel_of(1, *heads, head_dim, S, n_queries=nq) == "wide rows"
         q, k, v = _spread_inputs(head_dim, heads, S, nq, sigma, v_std, 2700 + S)
         out = tq.tq_sdpa_int4_decode(_poisoned(k, v, S), q.cuda(), S, 1.0, n_splits=n_splits)
         torch.cuda.synchronize()

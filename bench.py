@@ -72,7 +72,7 @@ def parse():
     ap.add_argument("--workload", default="llama128k",
                     help="tiny | llama8k | llama128k (default, the headline shape) | gqa16_128k (the same with 128 query heads: "
                          "the 16-row tile) | gemma32k | global512_32k (d=512, GQA 32: "
-                         "the head_dim 512 matrix-core kernel) | varlen8 (8 sequences of "
+                         "the matrix-core kernel for wide rows) | varlen8 (8 sequences of "
                          "the llama shape with their own lengths in [4096, 32768], per-sequence append + decode) | paged8 (the same "
                          "over a pool of 256-token pages in random order) | varlen256 (256 sequences of 64 ... 1024 tokens of the llama "
                          "shape: every (sequence, KV head) row is one chunk, no merge kernel) | varlen256_2k (the same with 64 ... 2048 tokens: "

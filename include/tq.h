@@ -81,8 +81,10 @@ typedef struct tq_kv_cache {
 /* Optional tuning knobs for the decode entry points; NULL or zeros = library defaults. */
 typedef struct tq_decode_opts {
   int32_t n_splits;  /* chunks the sequence is split into (Sec. 3.2); 0 = heuristic            */
-  int32_t variant;   /* 0 = default kernel, 1 = generic vector-ALU kernel, 2 = matrix-core kernel
-                        (head_dim 512 has a matrix-core kernel of its own: 0 and 2 both take it)    */
+  int32_t variant;   /* 0 = default kernel, 1 = generic vector-ALU kernel, 2 = matrix-core kernels.
+                        Of those there are two, chosen by the library for 0 and 2 alike: one for few
+                        and one for many query rows per KV head (head_dim 512: always the latter;
+                        128 and 256: by rows, lengths and whether the call is a step)               */
   int32_t window;    /* sliding-window attention (the Gemma local layers of Appendix A): > 0 = every
                         sequence attends only its last `window` tokens, [len - window, len); 0 = all.
                         tq_dequant_then_attend does not offer it (UNSUPPORTED).                  */
@@ -160,12 +162,16 @@ int tq_sdpa_int4_decode_static(const tq_kv_cache* cache, const void* q, int32_t 
  * tq_sdpa_int4_decode(cache, q, ..., seq_len, ...), i.e. the new token of every sequence (k_new,
  * v_new: fp16 [batch][n_kv_heads][1][head_dim]) is quantised, written at position seq_len - 1 and
  * attended together with the seq_len - 1 cached ones (with opts->n_queries = n > 1: n new tokens,
- * written at seq_len - n .. seq_len - 1, each attended by its own query).  Same stored bits and same
- * result as the two calls.  With one query token the append costs no launch of its own: the matrix-core
- * decode kernel quantises the new token next to the stream of the cached ones, stores it and adds its
- * attention term from registers (so that a short sequence's whole step is one launch); behind the other
- * kernels the merge kernel does that.  Otherwise (several query tokens, a window or sequence of one token;
- * groups of 64 or 128 elements on the generic kernel) the append kernel is launched first.
+ * written at seq_len - n .. seq_len - 1, each attended by its own query).  Same stored bits as the two
+ * calls, and the same result up to the rounding of fp16 weights and the order of fp32 sums: a step may
+ * take another kernel than the decode of the same shape.  The append costs no launch of its own where the
+ * kernel for many query rows serves the step (up to 8 new tokens, a sequence's first among them: they are
+ * quantised as tokens of the chunks that hold them), nor for one query token with an older one to attend:
+ * the other matrix-core kernel quantises it next to the stream of the cached ones, stores it and adds its
+ * attention term from registers (so that a short sequence's whole step is one launch), and behind the
+ * generic kernel, and the tile of 16 rows, the merge kernel does that.  Otherwise (several query tokens, a
+ * window or sequence of one token on the kernel for few rows; groups of 64 or 128 elements on the generic
+ * kernel) the append kernel is launched first.
  * Errors: those of the two calls. */
 int tq_sdpa_int4_append_decode(const tq_kv_cache* cache, const void* k_new, const void* v_new,
                                const void* q, int32_t n_q_heads, int32_t seq_len, float attn_scale,
@@ -257,7 +263,7 @@ size_t tq_kv_bytes(int32_t batch, int32_t n_kv_heads, int32_t capacity, int32_t 
 /* The same for a group size of 32, 64 or 128: 2 * batch * n_kv_heads * capacity * (head_dim/2 + 4*head_dim/group_size). */
 size_t tq_kv_bytes_grouped(int32_t batch, int32_t n_kv_heads, int32_t capacity, int32_t head_dim, int32_t group_size);
 
-/* Chunk count the heuristic would pick (host only). */
+/* Chunk count the heuristic would pick on the matrix-core kernel for few query rows per KV head (host only). */
 int32_t tq_plan_splits(int32_t batch, int32_t n_kv_heads, int32_t seq_len);
 
 /* Kernel launches one tq_sdpa_int4_decode call makes for this cache shape, query head count,

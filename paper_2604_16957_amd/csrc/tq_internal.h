@@ -70,6 +70,8 @@ struct DecodeParams {
   // kernel behind the others) quantises it, writes it at token append_pos of its row and adds its attention term.
   // With per-sequence lengths the lengths COUNT the new token (len_bias = -1: the chunks cover one token fewer)
   // and it is written at each sequence's own last position.
+  // The kernel for wide rows (common length) has them otherwise: k_new / v_new are fp16 [B][H_kv][n_queries][D], the last
+  // n_queries of the tokens that the chunks DO cover, and the blocks that hold one quantise it in the cache's stead.
   const half_t* k_new;
   const half_t* v_new;
   int32_t append_pos;
@@ -391,9 +393,8 @@ bool mfma_takes_token(int head_dim, int group_size, int rows);
 bool mfma_can_merge(int batch, int n_kv_heads);
 int mfma_merge_slot_of(const void* workspace);
 hipError_t launch_partial_mfma(const DecodeParams& p, int batch, int head_dim, int merge_slot, hipStream_t s);
-// Matrix-core kernel whose blocks take a tile of 16 query rows of one KV head (head_dim 128: 32, where there are more than 16) (p.kv_share = row tiles per
-// KV head, from wide_row_tiles; p.gqa = H_q / H_kv; p.n_queries query tokens; p.k_new / p.v_new, common length only: the
-// sequence's last n_queries tokens, fp16 [B][H_kv][n_queries][D], among the tokens the chunks cover).
+// Matrix-core kernel whose blocks take a tile of 16 query rows of one KV head (head_dim 128: 32, where there are more than 16)
+// (p.kv_share = row tiles per KV head, from wide_row_tiles; p.gqa = H_q / H_kv; p.n_queries query tokens; p.k_new / p.v_new: see there).
 int wide_row_tiles(int head_dim, int rows);
 int wide_max_chunks(int head_dim, int tiles);   // chunks worth cutting a sequence of that many 32-token tiles into
 hipError_t launch_partial_wide(const DecodeParams& p, int batch, int head_dim, hipStream_t s);

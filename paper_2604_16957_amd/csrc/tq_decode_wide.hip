@@ -65,9 +65,9 @@ constexpr float kSlack = 2.0f;              // log2 units: exp2(score - referenc
 // (nats), V of spread 1 / 1e-2 / 1e-3, without -> with: d = 512, 32K tokens 2.5e-4 / 3.8e-4 / 2.6e-3 -> 2.5e-4 / 2.5e-4 / 5.2e-4;
 // d = 128, 4 query tokens, 8K 2.1e-4 / 7.0e-4 / 5.3e-3 -> 2.1e-4 / 2.1e-4 / 2.7e-4; the output's own rounding is 2.1e-4 / 2.1e-4 / 2.7e-4 ..
 // 5.0e-4).  What remains of the spacing, 2^-24 of a lifted weight, moves a result by less than the spacing of fp16 outputs.  For scales from
-// 2 on see sv_lim.  The lift is part of the reference that the partial is published with.  Time: 18.54 -> 18.6 us (d = 512, 32K), 14.15 ->
-// 14.3 (d = 128, 4 query tokens, 8K), 41.4 -> 41.8 (d = 256, 32 heads over 4, 128K); a power of two common to the block, taken from the
-// largest scale it has met and exchanged at the round's barrier, 19.0, 14.45 and 41.6.
+// 2 on see sv_lim.  The lift is part of the reference that the partial is published with.  us per step, without -> with: 18.55 -> 18.65 (d = 512,
+// 32K), 39.6 -> 40.1 (128K), 14.13 -> 14.2 (d = 128, 4 query tokens, 8K), 40.7 -> 41.1 (d = 256, 32 heads over 4, 128K).  (A power of two
+// common to the block, from the largest scale it has met, exchanged at the round's barrier: 19.0, 14.45, 41.6.)
 constexpr float kLift = 12.0f;
 constexpr uint32_t scale_limit(uint32_t e) { return (e << 10 | 0x3FFu) * 0x10001u; }   // the largest scale of biased fp16 exponent e, twice
 constexpr uint32_t kPlainScales = scale_limit(15);
@@ -450,7 +450,8 @@ __global__ __launch_bounds__(512, 2) void decode_partial_wide_kernel(DecodeParam
   // ---- running state (Alg. 1, the initialisation), per column (query row)
   float m_all[RT], m_run[RT], l_run[RT];          // references of exp2 (raw units): the sums', this wave's weights'; this lane's share of the sum
   // sv_lim: the largest size a scale of this wave's groups may have as it stands.  From 2 on its sums carry 2^lower, lower < 0, so that
-  // p s_v stays below 2^15.  A wave looks at its scales once per round; those below 2 cost it nothing more.
+  // p s_v stays below 2^15 (its two groups together).  A wave looks at its scales once per round, with the references: one branch for both;
+  // scales below 2 cost it nothing more.
   uint32_t sv_lim = kPlainScales;
   auto lower_of = [](uint32_t lim) { return (float)(int)(kPlainScales >> 26) - (float)(int)(lim >> 26); };
   float4v oacc[RT][GPW][2], zacc[RT][GPW];        // rows 4kq+i; [0]: sum w c - 15 sum_t1 w of the even dim, [1]: of even + 16 odd; zero-points
@@ -695,6 +696,9 @@ __global__ __launch_bounds__(512, 2) void decode_partial_wide_kernel(DecodeParam
     const uint32_t sv_at = sv_rd + (r & 1) * (NW * C::V_BLK) + st0 * (2 / TT * C::V_BLK);
     // -- everybody's references.  They differ from the sums' only where a row's maximum has moved: then the sums are
     //    rescaled (Alg. 1, the correction factor) and the weights brought to the common reference as they are read.
+    uint32_t sv[STEPS / 2];                       // the scales of this wave's groups, 64 tokens a word
+#pragma unroll
+    for (int u = 0; u < STEPS / 2; ++u) sv[u] = lds_get<uint32_t>(sv_at + u * (64 / WT * TH * C::V_BLK));
     bool differ = false;
     float top[RT];
 #pragma unroll
@@ -706,22 +710,20 @@ __global__ __launch_bounds__(512, 2) void decode_partial_wide_kernel(DecodeParam
       const float lo = fminf(fminf(fminf(a[0], a[1]), fminf(a[2], a[3])), fminf(fminf(d[0], d[1]), fminf(d[2], d[3])));
       differ = differ || lo != m_all[rt] || hi != m_all[rt];
     }
-    const bool rescale = __builtin_amdgcn_ballot_w64(differ) != 0;
-    // -- the scales of this wave's groups, 64 tokens a word
-    {
-      uint32_t sv[STEPS / 2];
-#pragma unroll
-      for (int u = 0; u < STEPS / 2; ++u) sv[u] = lds_get<uint32_t>(sv_at + u * (64 / WT * TH * C::V_BLK));
-      const ushort2v big = __builtin_elementwise_max(__builtin_bit_cast(ushort2v, sv[0]), __builtin_bit_cast(ushort2v, sv[STEPS / 2 - 1]));
-      const ushort2v lim = __builtin_bit_cast(ushort2v, sv_lim);                                       // (fp16 bits are ordered by size)
-      if (__builtin_expect(__builtin_amdgcn_ballot_w64(__builtin_bit_cast(uint32_t, __builtin_elementwise_max(big, lim)) != sv_lim) != 0, 0)) {
-        uint32_t top = 0;                         // (a negative scale comes here every time: its size counts; behind the chunk's end lies anything)
+    const ushort2v lim = __builtin_bit_cast(ushort2v, sv_lim);   // (fp16 bits are ordered by size)
+    const uint32_t sv_a = sv[0], sv_b = sv[STEPS / 2 - 1];
+    const ushort2v big = __builtin_elementwise_max(__builtin_bit_cast(ushort2v, sv_a), __builtin_bit_cast(ushort2v, sv_b));
+    const bool exceed = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(big, lim)) != sv_lim;
+    const bool rescale = __builtin_amdgcn_ballot_w64(differ || exceed) != 0;
+    if (rescale) {
+      if (__builtin_amdgcn_ballot_w64(exceed) != 0) {
+        uint32_t most = 0;                        // (a negative scale comes here every time: its size counts; behind the chunk's end lies anything)
 #pragma unroll
         for (int u = 0; u < STEPS / 2; ++u) {
           const int st = st0 + TH * (2 * u + (lane >> 5));
-          if (32 * st + (lane & 31) < end - begin - R * r) top = max(top, max(sv[u] & 0x7FFFu, (sv[u] >> 16) & 0x7FFFu));
+          if (32 * st + (lane & 31) < end - begin - R * r) most = max(most, max(sv[u] & 0x7FFFu, (sv[u] >> 16) & 0x7FFFu));
         }
-        const uint32_t e = min(wave_max((int)top) >> 10, 30);
+        const uint32_t e = min(wave_max((int)most) >> 10, 30);
         if (e > sv_lim >> 26) {
           const float f = __builtin_amdgcn_exp2f(lower_of(scale_limit(e)) - lower_of(sv_lim));
           sv_lim = scale_limit(e);
@@ -735,8 +737,6 @@ __global__ __launch_bounds__(512, 2) void decode_partial_wide_kernel(DecodeParam
             }
         }
       }
-    }
-    if (rescale) {
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) {
         const float f = __builtin_amdgcn_exp2f((m_all[rt] - top[rt]) * kappa);

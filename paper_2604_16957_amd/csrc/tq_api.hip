@@ -169,31 +169,34 @@ enum class Call { kDecode, kStep, kLengths };
 // head_dim 256 with more than two query rows per KV head: it takes 16 rows to a block, the other one two,
 // and unpacks the stream again for every two.  It always merges in a launch of its own, so what it loses by shows where blocks of many
 // rows have little to do each: with one query token it is taken from five rows on (16 heads over 4, one sequence of 32K tokens
-// 17.6 / 18.7 us per step, other / this) and from 12K (token, KV head) pairs (4 sequences of 512, 32 heads over 4, 10.3 / 10.5),
-// and with more than 128 (sequence, KV head) rows only for sequences of 512 tokens and more (1024 where they have lengths of
-// their own, which the other kernel orders).  us per step, other / this: 32 heads over 4, 6000 tokens
-// 12.0 / 11.3, 20K 18.1 / 15.3, 128K 68 / 42; 8 sequences of 1000 14.4 / 11.3, of 8192 54 / 28; 64 of 200 14.4 / 15.3,
-// of 600 25.4 / 22.4; 128 of 150 18.0 / 25.2, of 2000 121 / 82.5; own lengths: 8 of 400 .. 6000 22.0 / 18.8, 32 of 100 .. 1000 19.0 / 17.9,
-// 64 of 60 .. 600 23.7 / 28.3, of 100 .. 2000 41.8 / 38.8, 128 of 60 .. 600 36.6 / 52.3.  Several query tokens: 32 heads over 16, 2 of
-// them, 600 tokens 12.9 / 10.3, 32K 46 / 40; 8, 32K 128 / 43; 16 over 8, 8 of them, 4 sequences of 2000 33 / 16.
+// 17.1 / 18.7 us per step, other / this) and from 12K (token, KV head) pairs (32 heads over 4, 4 sequences of 512, 10.3 / 9.9, one of
+// 3072 as long on either), and with more than 128 (sequence, KV head) rows only for sequences of 512 tokens and more (1024 where they have
+// lengths of their own, which the other kernel orders).  us per step, other / this: 32 heads over 4, 6000 tokens
+// 12.1 / 11.3, 20K 17.9 / 15.5, 128K 66.9 / 40.1; 8 sequences of 1000 14.4 / 11.6, of 8192 54.0 / 26.2; 64 of 200 14.4 / 15.4,
+// of 600 25.2 / 22.8; 128 of 150 18.0 / 25.4, of 2000 117 / 81.1; own lengths: 8 of 400 .. 6000 22.1 / 19.0, 32 of 100 .. 1000 19.1 / 17.5,
+// 64 of 60 .. 600 23.7 / 28.5, of 100 .. 2000 41.4 / 39.0, 128 of 60 .. 600 36.5 / 52.6.  Several query tokens: 32 heads over 16, 2 of
+// them, 600 tokens 14.0 / 10.4, 32K 46.5 / 40.5; 8, 32K 125 / 42.4; 16 over 8, 8 of them, 4 sequences of 2000 32.7 / 16.3.
 bool wide_rows_at_256(int rows, int64_t kv_rows, int tokens, int n_queries, Call call) {
   if (rows <= (n_queries > 1 ? 2 : 4) || (n_queries == 1 && kv_rows * tokens < 12288)) return false;
   return kv_rows <= 128 || tokens >= (call == Call::kLengths ? 1024 : 512);
 }
 // head_dim 128: up to 128 (sequence, KV head) rows (with more the other kernel's blocks are full, and it orders and packs them), and
-// up to some tokens per compute unit (and 32-row block, where a KV head's rows take several).  It starts and merges 4 - 5 us sooner and
-// takes several new tokens in, which saves a step its append launch (2.6 us); the 16-row tile takes 5.9 ns per token and compute
-// unit against 6.6 (up to 16 rows) and 9.9 (two tiles to a block).  So a step may be longer than a decode, and several query tokens longer
-// than one; up to eight rows only the append launch is saved (a launch of one new token has none to save: 64 heads over 8, 8191
-// tokens 10.8 / 10.5 us per step, 32 heads over 8, 4000, 8.4 / 9.1).  us per step, other / this (d: per decode):
-// 17 rows and more: 64 heads over 8, 4 query tokens, 600 tokens 16.7 / 11.4, 8000 19.4 / 14.0 (d 16.1 / 13.9), 16K 21.8 / 17.6
-// (d 18.8 / 17.5), 24K 23.8 / 21.3 (d 21.2 / 21.2), 32K 26.0 / 25.0, 48K 32.5 / 31.9, 128K 61.4 / 69.2; 16 sequences of 1000 20.2 / 18.3
-// (d 15.8 / 18.0); 8 query tokens, 16K 27.2 / 24.7 (d 23.2 / 24.7), 24K 31.0 / 32.4; 128 heads over 8, 4, 16K 25.9 / 24.6.
-// 9 .. 16 rows: 128 heads over 8, 600 tokens 14.0 / 9.2, 8192 14.4 / 10.7, 24K 17.4 / 15.4 (d 16.0 / 15.3), 32K 19.2 / 18.1 (d 17.7 / 17.8),
-// 48K 22.3 / 22.5; 16 sequences of 1500 17.0 / 15.4 (d 15.6 / 14.8); 64 over 8, 2 query tokens, 16K 19.3 / 13.3, 32K 22.3 / 18.0
-// (d 19.9 / 17.9), 48K 25.4 / 22.7 (d 22.6 / 22.6), 64K 28.0 / 27.3, 128K 39.8 / 46; own lengths, 4 of 400 .. 6000
-// 18.7 / 16.0, 8 of them 22.6 / 21.5, 16 of 300 .. 4000 24.2 / 25.0, 8 of 2000 .. 8000 25.5 / 26.4.
-// Up to 8 rows: 32 over 8, 2, 8000 14.3 / 10.5, 24K 17.9 / 15.2, 30K 18.1 / 17.2; 32 over 32, 2, 2000 12.0 / 10.6, 4000 13.3 / 13.1.
+// up to some tokens L per compute unit (and 32-row block, where a KV head's rows take several).  It starts and merges sooner and takes
+// several new tokens in, where the other launches the append kernel (2.6 us); the 16-row tile takes less time per token:
+//   9 .. 16 rows   a step 8.8 us (several query tokens 9.2) + 9.2 ns L here, 12.9 us (16.3) + 5.6 ns L on the 16-row tile
+//   17 .. 32 rows         10.8 us                            + 13.9 ns L here, 17.0 us      + 10.4 ns L there, two tiles
+// and a decode is 0.3 us shorter here, 1.3 (several query tokens 2.8 .. 4) there.  The lines lie before these meet (step 1190, several
+// 1950, 17 rows and more 1790; decode 910, 1410, 870), further before where lengths next to each other go either way.  Up to eight rows only the append
+// launch is saved (a launch of one new token has none to save: 64 heads over 8, 8191 tokens 10.8 / 10.5 us per step, 32 heads over 8, 4000,
+// 8.4 / 9.1).  us per step, other / this (d: per decode):
+// 17 rows and more: 64 heads over 8, 4 query tokens, 600 tokens 16.8 / 11.5, 8000 18.9 / 14.1 (d 16.1 / 14.0), 16K 22.4 / 17.9
+// (d 18.7 / 17.6), 24K 23.9 / 21.5 (d 21.2 / 21.2), 32K 25.8 / 25.0 (d 23.1 / 24.8), 48K 32.0 / 32.2, 128K 59.5 / 67.9; 16 sequences of
+// 1000 19.8 / 18.5 (d 15.9 / 18.0); 8 query tokens, 16K 25.9 / 25.6 (d 23.2 / 24.3), 24K 30.9 / 32.7; 128 heads over 8, 4, 16K 26.8 / 25.1.
+// 9 .. 16 rows: 128 heads over 8, 600 tokens 13.9 / 9.4, 8192 14.3 / 10.9, 24K 17.3 / 15.7 (d 16.0 / 15.5), 32K 18.7 / 18.4 (d 17.3 / 17.8),
+// 48K 21.8 / 22.8, 128K 36.7 / 46.6; 16 sequences of 1500 17.2 / 15.7 (d 15.7 / 14.9); 64 over 8, 2 query tokens, 16K 19.1 / 13.9, 32K
+// 21.9 / 18.8 (d 19.3 / 18.1), 48K 24.7 / 23.3 (d 22.1 / 22.7), 64K 27.3 / 28.0, 128K 38.9 / 47.0; own lengths, 4 of 400 .. 6000
+// 17.7 / 15.1, 8 of them 20.4 / 18.3, 16 of 300 .. 4000 21.6 / 21.0, 8 of 2000 .. 8000 24.0 / 24.4.
+// Up to 8 rows: 32 over 8, 2, 8000 14.4 / 10.6, 24K 16.9 / 16.1, 30K 18.1 / 17.5; 32 over 32, 2, 2000 11.0 / 10.7, 4000 13.7 / 13.3.
 bool wide_rows_at_128(int rows, int64_t kv_rows, int tokens, int n_queries, Call call) {
   if (kv_rows > 128) return false;
   const bool step = call == Call::kStep;

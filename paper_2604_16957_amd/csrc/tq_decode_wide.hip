@@ -26,8 +26,8 @@
 // So the operands of either contraction are prepared once per block, the scores need no exchange, a wave's sums take 24
 // registers (192, if a wave kept all of a row's dims for the tokens it scored) and no sums are merged at the end.
 // Measured against four waves that split the head dimension for both contractions, exchanged partial scores (a barrier per
-// 32 tokens) and multiplied V out into fp16 (us per step): 32 heads on one KV head, 32K tokens 28.0 -> 18.6, 128K 71.7 ->
-// 39.5, 8 sequences of 32K 75.2 -> 68.3; 16 heads on two 27.5 -> 19.1; 32 heads over 8 49.8 -> 40.6; the error against 64
+// 32 tokens) and multiplied V out into fp16 (us per step): 32 heads on one KV head, 32K tokens 28.0 -> 18.7, 128K 71.5 ->
+// 40.1, 8 sequences of 32K 74.9 -> 69; 16 heads on two 27.4 -> 19.3; 32 heads over 8 49.2 -> 40.4; the error against 64
 // bits 3.6e-4 -> 2.9e-4.  (Eight waves in lock step with the dims split likewise: 25.1; a wave that keeps whole tokens and all
 // dims: the compiler moves the 192 accumulator registers about.)  A round of 128 tokens takes about 3.5 us, 72 - 78 % of it
 // the vector port's: some 660 instructions a wave, two waves to a SIMD.
@@ -131,6 +131,9 @@ struct Tile {
   // reference to the block one operand has 3 - 10 % more error against 64 bits than they (2.25e-4 .. 2.45e-4, 2.2e-4 .. 2.35e-4), two
   // have less (2.07e-4, nearly all of it the output's own rounding).  It costs 16 vector and 3 matrix instructions per 32 tokens
   // and group (64 heads over 8, 4 query tokens, 32K tokens 22.4 -> 25.0 us per step; the rest by one fma_mixlo an element 26.4).
+  // At d = 256 the kernel before has a reference per wave too (error of this one over its: scores of spread 0.16 0.997 .. 1.011, of 1
+  // 0.97 .. 1.04, of 2 1.01 .. 1.05, 2.14e-4 -> 2.24e-4 of which the output's rounding is 2.07e-4; 0.1 .. 0.9 for V of spread 1e-2 and less), but
+  // two operands cost 10 - 13 % of the time there (32 heads over 4, 128K 41 -> 47): one.
   static constexpr bool SPLIT = D == 128;
   static constexpr int GPW = 2, TH = NW * GPW / NG; // groups of V a wave takes; waves that share them (each every TH-th supertile)
   static_assert(SMEM <= 160 * 1024 && QOPS * 1024 == RPW * D * 2 && ROWS * D * 2 + NW * NOPS * 1024 <= NW * V_BLK && kMaxQueries <= NW && VC * 1024 == V_SC, "LDS");

@@ -187,56 +187,6 @@ __device__ __forceinline__ half8v unpack_word(uint32_t w) {   // 8 nibbles -> 8 
 __device__ __forceinline__ float4v mfma16(half8v a, half8v b, float4v c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
 }
-// reductions over the four 16-lane blocks (lanes l, l^16, l^32, l^48).  The swap builtins return a
-// 2-vector; its elements are copied to scalars before any bit_cast (a bit_cast applied directly to
-// a vector-element expression reads element 0).
-__device__ __forceinline__ void swap32(float x, float& lo, float& hi) {
-  const uint32_t u = __builtin_bit_cast(uint32_t, x);
-  const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  const uint32_t r0 = r[0], r1 = r[1];
-  lo = __builtin_bit_cast(float, r0);
-  hi = __builtin_bit_cast(float, r1);
-}
-__device__ __forceinline__ void swap16(float x, float& lo, float& hi) {
-  const uint32_t u = __builtin_bit_cast(uint32_t, x);
-  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  const uint32_t r0 = r[0], r1 = r[1];
-  lo = __builtin_bit_cast(float, r0);
-  hi = __builtin_bit_cast(float, r1);
-}
-__device__ __forceinline__ float blocks_max(float x) {
-  float a, b;
-  swap32(x, a, b);
-  x = fmaxf(a, b);
-  swap16(x, a, b);
-  return fmaxf(a, b);
-}
-__device__ __forceinline__ float blocks_sum(float x) {
-  float a, b;
-  swap32(x, a, b);
-  x = a + b;
-  swap16(x, a, b);
-  return a + b;
-}
-// the largest, and the sum, of a value over the 64 lanes (in every lane)
-template <int ROT>
-__device__ __forceinline__ float row_ror(float x) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x120 + ROT, 0xF, 0xF, false));
-}
-__device__ __forceinline__ float wave_fmax(float x) {
-  x = fmaxf(x, row_ror<8>(x));
-  x = fmaxf(x, row_ror<4>(x));
-  x = fmaxf(x, row_ror<2>(x));
-  x = fmaxf(x, row_ror<1>(x));
-  return blocks_max(x);
-}
-__device__ __forceinline__ float wave_fsum(float x) {
-  x += row_ror<8>(x);
-  x += row_ror<4>(x);
-  x += row_ror<2>(x);
-  x += row_ror<1>(x);
-  return blocks_sum(x);
-}
 template <int ROT>
 __device__ __forceinline__ float row_ror_add(float x) {      // x + (x rotated by ROT inside its 16-lane row)
   const int y = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x120 + ROT, 0xF, 0xF, false);

@@ -319,9 +319,7 @@ __global__ __launch_bounds__(THREADS) void reduce_kernel(DecodeParams p) {
   const bool appending = p.k_new != nullptr;
   float a_new = kNegBig;
   // (the chunk maxima of each wave go to LDS ahead of the barriers below, which then serve them as well)
-  float mw = m;
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) mw = fmaxf(mw, __shfl_xor(mw, off));
+  const float mw = wave_fmax(m);
   if ((tid & 63) == 0) red_m[tid >> 6] = mw;
   if (!appending) __syncthreads();
   if (appending) {
@@ -331,9 +329,7 @@ __global__ __launch_bounds__(THREADS) void reduce_kernel(DecodeParams p) {
     const int kv = h / p.gqa;
     quantize_new_token<D>(p, b, kv, append_pos, tid, h % p.gqa == 0 && slice == 0, hat);
     __syncthreads();
-    float prod = tid < D ? q_e * hat[0][tid] : 0.0f;
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) prod += __shfl_xor(prod, off);
+    const float prod = wave_fsum(tid < D ? q_e * hat[0][tid] : 0.0f);
     if ((tid & 63) == 0) red_a[tid >> 6] = prod;
     __syncthreads();
     float dot = 0.0f;
@@ -345,10 +341,10 @@ __global__ __launch_bounds__(THREADS) void reduce_kernel(DecodeParams p) {
 #pragma unroll
   for (int w = 1; w < WAVES; ++w) mg = fmaxf(mg, red_m[w]);
   const float w = exp2f(m - mg);
-  if (tid < n) w_c[tid] = w;
-  float lw = l * w;
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) lw += __shfl_xor(lw, off);
+  // (zero past the last chunk: the weights are then read without a condition, several at once and ahead of their use;
+  // behind `chunk < n ? w_c[chunk] : 0` each was a branch, a read and a wait of its own)
+  if (tid < kMaxSplits) w_c[tid] = tid < n ? w : 0.0f;
+  const float lw = wave_fsum(l * w);
   if ((tid & 63) == 0) red_l[tid >> 6] = lw;
   __syncthreads();
   float den = red_l[0] + red_l[1];
@@ -362,11 +358,12 @@ __global__ __launch_bounds__(THREADS) void reduce_kernel(DecodeParams p) {
     den += w_new;
     if (part == 0) num = w_new * hat[1][j];
   }
+  static_assert(FIRST * PARTS <= kMaxSplits, "a weight for every chunk of the first round");
+  float wc[FIRST];
 #pragma unroll
-  for (int u = 0; u < FIRST; ++u) {
-    const int c = part + u * PARTS;
-    num = c < n ? fmaf(pre[u], w_c[c], num) : num;
-  }
+  for (int u = 0; u < FIRST; ++u) wc[u] = w_c[part + u * PARTS];
+#pragma unroll
+  for (int u = 0; u < FIRST; ++u) num = part + u * PARTS < n ? fmaf(pre[u], wc[u], num) : num;
   int c = part + FIRST * PARTS;
   for (; c + 7 * PARTS < n; c += 8 * PARTS) {
     float v[8];
@@ -485,9 +482,7 @@ __global__ __launch_bounds__(2 * D, HPT == 4 ? 5 : 4) void reduce_group_kernel(D
     float prod[HPT];
 #pragma unroll
     for (int i = 0; i < HPT; ++i) {
-      prod[i] = (float)p.q[row[i] * D + j] * hat[0][j];
-#pragma unroll
-      for (int off = 32; off >= 1; off >>= 1) prod[i] += __shfl_xor(prod[i], off);
+      prod[i] = wave_fsum((float)p.q[row[i] * D + j] * hat[0][j]);
     }
     if ((tid & 63) == 0) {
 #pragma unroll

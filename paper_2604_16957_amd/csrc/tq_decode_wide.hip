@@ -88,16 +88,6 @@ __device__ __forceinline__ float4v mfma16(half8v a, half8v b, float4v c) {
 __device__ __forceinline__ float half_of(uint32_t w, int hi) {
   return (float)__builtin_bit_cast(half_t, (uint16_t)(hi ? w >> 16 : w));
 }
-// reductions over the four 16-lane blocks (lanes l, l^16, l^32, l^48)
-__device__ __forceinline__ float blocks_max(float x) {
-  x = fmaxf(x, __shfl_xor(x, 16));
-  return fmaxf(x, __shfl_xor(x, 32));
-}
-__device__ __forceinline__ float blocks_sum(float x) {
-  x += __shfl_xor(x, 16);
-  return x + __shfl_xor(x, 32);
-}
-
 // D: head dimension.  RT: 16-row tiles of query rows.  TT: 16-token tiles a wave scores per round.
 template <int D, int RT, int TT>
 struct Tile {

@@ -598,9 +598,18 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   // score, l = 1, o = the dequantised V.  The step needs no launch of its own for the append, and a merge kernel only
   // where the decode does.  (Steps with the merge kernel as the appender, or the append kernel in front of packed
   // rows, and like this: one sequence of 1024 tokens, 8 heads on 1, 12.5 -> 11.3 us per call; a window of 1024, d = 256,
-  // 13.1 -> 10.9; 32K tokens, d = 256, 35.3 -> 33.9; 128 sequences of 512 .. 1024 tokens 35.3 -> 32.6.)  Lane l < 2 D / 8: eight elements of K (l < D / 8) or of V.
-  const bool takes = new_here && (whole ? wave == NW - 1 : sub == 0);
-  const int new_piece = lane % (D / 8), new_v = (lane / (D / 8)) & 1;
+  // 13.1 -> 10.9; 32K tokens, d = 256, 35.3 -> 33.9; 128 sequences of 512 .. 1024 tokens 35.3 -> 32.6.)
+  // What the token costs is the chain of instructions of the wave that takes it: the block waits for that wave.  So its K
+  // and its V go to two waves (where a row has one wave only: to its two halves), of the older ones of their SIMDs, which are
+  // 0.6 us ahead of the younger at this point, and a wave's lanes hold the row several times over, eight elements a lane, so
+  // that the copies of K share the query rows' scores between them.  (One younger wave for all of it, half of its lanes idle:
+  // that wave 2.0 us behind the others; us per step 8 heads over 1, 1024 tokens 8.62 -> 7.94, 64 over 8, 8K 10.77 -> 10.02,
+  // 32 over 16, d = 256, a window of 1024 9.31 -> 8.78; the decode alone 7.83, 10.01, 8.80.)
+  const bool takes_k = new_here && (whole ? wave == NW / 2 - 1 : sub == 0);
+  const bool takes_v = new_here && (whole ? wave == NW / 2 - 2 : sub == (W > 1 ? 1 : 0));
+  const bool takes = takes_k || takes_v;
+  constexpr int PIECES = D / 8, COPIES = 64 / PIECES;
+  const int new_piece = lane % PIECES, new_v = takes_k && takes_v ? lane >> 5 : takes_v;
   // (a borrowed slot: behind its K tiles where the block fits there, else from the slot's start)
   constexpr int Q_IN_SLOT = C::QAREA <= C::STAGE - C::OFF_V ? C::OFF_V : 0;
   // (a block of fewer waves, see `ranked`: the areas behind the rings move up)
@@ -617,7 +626,7 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
       const int h = min(chunk / (D / 8), G - 1);
       dma16_lane(p.q + query_row(h) * D + (chunk % (D / 8)) * 8, l + u * 1024);
     }
-    if (takes)                                    // the new token: lanes 0 .. D/8-1 its K row, the next D/8 its V row
+    if (takes)                                    // the new token's K row, or its V row (one wave for both: half the lanes each)
       dma16_lane((new_v ? p.v_new : p.k_new) + (int64_t)(b * p.n_kv_heads + kv) * D + new_piece * 8, l + C::QBLK);
   }
   // A wave has up to NS stages out before its loop and issues one per supertile while it has supertiles left.
@@ -700,26 +709,59 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   float new_score = 0.0f;
   if (takes) {
     const half8v x16 = *reinterpret_cast<const half8v*>(q_area + C::QBLK + lane * 16);
-    float x[8], mn, mx;
     half_t xh[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) { xh[e] = x16[e]; x[e] = (float)x16[e]; }
-    mn = mx = x[0];
-#pragma unroll
-    for (int e = 1; e < 8; ++e) { mn = fminf(mn, x[e]); mx = fmaxf(mx, x[e]); }
-    for (int o = 1; o < p.group / 8; o <<= 1) {   // over the lanes of the group (exact in any order)
-      mn = fminf(mn, __shfl_xor(mn, o));
-      mx = fmaxf(mx, __shfl_xor(mx, o));
-    }
+    for (int e = 0; e < 8; ++e) xh[e] = x16[e];
+    // the group's smallest and largest element: (min, -max) as a pair of fp16, exact in any order
+    const auto pk_min = [](half2v a, half2v b) { return __builtin_elementwise_min(a, b); };
+    const half2v x01 = {xh[0], xh[1]}, x23 = {xh[2], xh[3]}, x45 = {xh[4], xh[5]}, x67 = {xh[6], xh[7]};
+    const half2v lo = pk_min(pk_min(x01, x23), pk_min(x45, x67)), hi = pk_min(pk_min(-x01, -x23), pk_min(-x45, -x67));
+    half2v range = pk_min(half2v{lo[0], hi[0]}, half2v{lo[1], hi[1]});
+    auto over_lanes = [&](auto ctrl_tag) {
+      const int other = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, range), decltype(ctrl_tag)::value, 0xF, 0xF, false);
+      range = pk_min(range, __builtin_bit_cast(half2v, other));
+    };
+    over_lanes(std::integral_constant<int, 0xB1>{});                       // quad_perm: the lanes 1, then 2, away
+    over_lanes(std::integral_constant<int, 0x4E>{});
+    if constexpr (GS >= 1) over_lanes(std::integral_constant<int, 0x141>{});   // row_half_mirror: the other four of eight
+    if constexpr (GS >= 2) over_lanes(std::integral_constant<int, 0x140>{});   // row_mirror: the other eight of sixteen
+    const float mn = (float)range[0], mx = -(float)range[1];
     half_t s16, z16;
     quantize_scale_zero(mn, mx, s16, z16);
     const float sf = (float)s16, zf = (float)z16;
     const QuantFast fast = quantize_fast_setup(sf, zf, fmaxf(fabsf(mn), fabsf(mx)));
     float far = 0.0f;
     new_w = quantize_word_fast(xh, fast, far);
-    if (quantize_fast_in_doubt(far, fast)) new_w = quantize_word(x, sf, zf);
+    if (quantize_fast_in_doubt(far, fast)) {
+      float x[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x[e] = (float)xh[e];
+      new_w = quantize_word(x, sf, zf);
+    }
     new_sz = half2v{s16, z16};
-    if (part == 0 && lane < 2 * (D / 8)) {        // (several blocks per KV head: the first stores)
+    if (takes_k) {
+      const int copies = takes_v ? COPIES / 2 : COPIES, copy = lane / PIECES;
+      float k_hat[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) k_hat[e] = ((float)((new_w >> (4 * e)) & 0xFu) - zf) * sf;   // Eq. 3
+      for (int i = 0, h = copy; i * copies < GP; ++i, h += copies) {       // copy k: rows k, k + copies, ...
+        const half8v qv = *reinterpret_cast<const half8v*>(q_area + min(h, GP - 1) * D * 2 + new_piece * 16);
+        float dot = 0.0f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) dot = __builtin_fmaf((float)qv[e], k_hat[e], dot);
+        dot = row_ror_add<8>(dot);
+        dot = row_ror_add<4>(dot);
+        dot = row_ror_add<2>(dot);
+        dot = row_ror_add<1>(dot);
+        if constexpr (D == 256) {
+          float a, b2;
+          swap16(dot, a, b2);
+          dot = a + b2;
+        }
+        new_score = new_piece == i ? dot : new_score;
+      }
+    }
+    if (part == 0 && (takes_k && takes_v ? (lane & 31) < PIECES : lane < PIECES)) {   // (several blocks per KV head: the first stores)
       int64_t row = (int64_t)(b * p.n_kv_heads + kv) * p.row_stride + new_pos;
       if (paged) {
         const int page = p.block_table[(int64_t)b * p.max_blocks + (new_pos >> p.page_shift)];
@@ -727,26 +769,11 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
       }
       uint8_t* codes = const_cast<uint8_t*>(new_v ? p.v_codes : p.k_codes) + row * TB;
       reinterpret_cast<uint32_t*>(codes)[new_piece] = new_w;
-      const int64_t g = row * (D / p.group) + new_piece * 8 / p.group;
-      const int first = new_piece * 8 % p.group;  // (the group's first two lanes store its scale and zero-point)
+      constexpr int GROUP = kGroup << GS;
+      const int64_t g = row * (D / GROUP) + new_piece * 8 / GROUP;
+      const int first = new_piece * 8 % GROUP;    // (the group's first two lanes store its scale and zero-point)
       if (first == 0) const_cast<half_t*>(new_v ? p.v_scale : p.k_scale)[g] = s16;
       if (first == 8) const_cast<half_t*>(new_v ? p.v_zero : p.k_zero)[g] = z16;
-    }
-    float k_hat[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) k_hat[e] = new_v ? 0.0f : ((float)((new_w >> (4 * e)) & 0xFu) - zf) * sf;   // Eq. 3
-#pragma unroll
-    for (int h = 0; h < GP; ++h) {
-      const half8v qv = *reinterpret_cast<const half8v*>(q_area + h * D * 2 + new_piece * 16);
-      float dot = 0.0f;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) dot = __builtin_fmaf((float)qv[e], k_hat[e], dot);
-      dot = row_ror_add<8>(dot);
-      dot = row_ror_add<4>(dot);
-      dot = row_ror_add<2>(dot);
-      dot = row_ror_add<1>(dot);
-      if constexpr (D == 256) dot += __shfl_xor(dot, 16);
-      new_score = c == h ? dot : new_score;
     }
   }
   const float kappa = p.scale_log2 * 0x1p24f * (SPLIT ? 1.0f / q_up : 1.0f);   // raw accumulator units -> log2 units
@@ -1212,12 +1239,13 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
     lds_l[hl * NW + wave] = active ? l_tot : 0.0f;
   }
   if (takes) {
-    if (new_v && lane < 2 * (D / 8)) {
+    if (new_v && (lane & 31) < PIECES) {
 #pragma unroll
       for (int e = 0; e < 8; ++e)
         lds_new[new_piece * 8 + e] = ((float)((new_w >> (4 * e)) & 0xFu) - (float)new_sz[1]) * (float)new_sz[0];
     }
-    if (lane < GP) lds_new[D + lane] = new_score * p.scale_log2;
+    const int copies = takes_v ? COPIES / 2 : COPIES, row_of = lane / PIECES + new_piece * copies;   // the row this lane's score is of
+    if (takes_k && lane / PIECES < copies && row_of < GP) lds_new[D + row_of] = new_score * p.scale_log2;
   }
   if constexpr (C::WIDE) {
     // row 4 kq + i = head; group g's zero-point sum of that head sits in column g (any column c with c % 4 == g)
@@ -1366,8 +1394,11 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
     const float* const src = p.part_o + row * n * D + j;
     auto weights = [&] {
       if (wave < G) {
-        const float w = __builtin_amdgcn_exp2f(ml.x - wave_fmax(ml.x));
-        if (lane < n) c_w[wave * kMergeMaxChunks + lane] = w;
+        // (zero past the last chunk: the weights below are then read without a condition, in a few wide reads at once; behind
+        // `chunk < n ? w : 0` each of the 32 was a branch, a read and a wait of its own, 2 us of a merge of 32 chunks)
+        const float top = wave_fmax(ml.x);        // (every lane takes part)
+        const float w = lane < n ? __builtin_amdgcn_exp2f(ml.x - top) : 0.0f;
+        c_w[wave * kMergeMaxChunks + lane] = w;
         const float d = wave_fsum(ml.y * w);
         if (lane == 0) h_den[wave] = d;
       }
@@ -1382,8 +1413,7 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
     auto add = [&](auto count_tag, int c0, const float2* o) {
 #pragma unroll
       for (int u = 0; u < decltype(count_tag)::value; ++u) {
-        const int cc = c0 + u * PARTS + cpart;
-        const float e = cc < n ? w[cc] : 0.0f;
+        const float e = w[c0 + u * PARTS + cpart];
         n0 = fmaf(o[u].x, e, n0);
         n1 = fmaf(o[u].y, e, n1);
       }

@@ -128,7 +128,7 @@ int tq_quantize_kv_varlen(const tq_kv_cache* cache, const void* k_new, const voi
  * Same result as tq_sdpa_int4_partial followed by tq_sdpa_int4_reduce on the same stream (up to the
  * order of the fp32 sums of the merge).  For short sequences, where launch overhead outweighs the
  * stream (see tq_decode_launches), the matrix-core kernel does both in ONE launch: the block that
- * finishes a (batch, KV head) last merges its chunks in place (a sequence that is a single chunk
+ * finishes an output row last merges that row's chunks in place (a sequence that is a single chunk
  * needs no merge: its block writes out).  That path counts the blocks in with arrival counters in device
  * memory owned by the library, one set per WORKSPACE address (kept for the life of the process, left zero by
  * every launch).  Calls that may run at the same time must not share a workspace (they would overwrite each

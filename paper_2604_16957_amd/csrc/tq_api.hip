@@ -250,7 +250,7 @@ Route route_of(const tq_kv_cache* cache, int n_q_heads, int seq_len, float attn_
   // (a 16-row tile leaves the last block twice the partials to fetch: there the merge kernel is the faster end,
   //  measured 21.8 against 24.1 us with 16 heads per KV head at 32K tokens)
   const bool small_tile = rows_per_batch == 0 || rows * cache->n_kv_heads / rows_per_batch <= 8;
-  const bool in_place = small_tile && chunks <= kMergeInKernelMaxChunks && tq::mfma_can_merge(cache->batch, rows_per_batch);
+  const bool in_place = small_tile && chunks <= kMergeInKernelMaxChunks && tq::mfma_can_merge((int64_t)cache->batch * queries_of(opts) * n_q_heads);
   // (larger groups at head_dim 256, decode alone: two launches as well)
   const bool merge = use_mfma && (single || (in_place && bytes <= kMergeInKernelMaxBytes && !(larger && cache->head_dim == 256)));
   return {true, use_mfma, merge, use_mfma && (single || in_place), false, small_tile};

@@ -81,7 +81,7 @@ typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
 constexpr float kNegBig = -1.0e30f;
 constexpr int kMaxDevices = 64;
 
-// Arrival counters of the in-kernel chunk merge: one per (b, kv head), in kCounterSlots independent sets.  A set
+// Arrival counters of the in-kernel chunk merge: one per output row, in kCounterSlots independent sets.  A set
 // belongs to ONE WORKSPACE (the host keeps the table, see merge_slot_of): calls that may be in flight at the same
 // time have different workspaces by the contract of the decode calls (they would overwrite each other's partials
 // otherwise), hence different sets, whether they are issued eagerly or replayed from a captured graph, which
@@ -89,13 +89,13 @@ constexpr int kMaxDevices = 64;
 // counter back to zero, so every launch leaves them zero again.  A workspace that finds all sets taken gets the
 // merge kernel instead (two launches: always correct).
 constexpr int kCounterSlots = 256;
-constexpr int kCountersPerSlot = 2048;
-// Within a set, the counters of neighbouring (b, KV head) rows lie 128 bytes apart (row r at (r % 64) * 32 + r / 64):
+constexpr int kCountersPerSlot = 16384;
+// Within a set, the counters of neighbouring rows lie 128 bytes apart (row r at (r % 512) * 32 + r / 512):
 // the blocks of a launch finish at about the same time, and their atomics on counters that share a cache line
 // queue up behind one another at that line's channel (8 KV heads x 32 chunks on one line: 1.4 us of a 13 us call).
 __device__ __attribute__((aligned(256))) unsigned int g_arrivals[kCounterSlots * kCountersPerSlot];
-static_assert(kCountersPerSlot == 64 * 32, "the spreading below");
-__device__ __forceinline__ int arrival_counter(int row) { return (row & 63) * 32 + (row >> 6); }
+static_assert(kCountersPerSlot == 512 * 32, "the spreading below");
+__device__ __forceinline__ int arrival_counter(int row) { return (row & 511) * 32 + (row >> 9); }
 constexpr float kSlack = 2.0f;              // log2 units: exp2(score - reference) <= 4
 constexpr uint32_t kMaskLo = 0x000F000Fu;   // nibbles 0 and 4 of a word -> fp16 subnormals c * 2^-24
 constexpr uint32_t kMaskHi = 0x00F000F0u;   // nibbles 1 and 5           -> c * 2^-20
@@ -1289,140 +1289,141 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   }
   __syncthreads();
 
-  // ---- merge the waves, write one partial per query head (Sec. 3.2); where the sequence is a single
+  // ---- merge the waves, write one partial per query row (Sec. 3.2); where the sequence is a single
   //      chunk and the kernel is to produce the output, that partial, normalised, IS the output.
-  //      A thread takes two neighbouring dims of one head: the waves' maxima and sums of that head arrive as
-  //      16-byte reads (the same for the whole wave at d = 128, where wave h merges head h).
+  //      A wave takes a row, a lane two neighbouring dims of it (d = 256: four): the waves' maxima and sums of that row
+  //      arrive as 16-byte reads, the same for the whole wave.
   const bool direct = p.merge_slot >= 0 && p.n_splits == 1;
-  // `first` .. `first + count - 1`: the waves to merge; `stride`, `lane0`: this thread's place among the threads that do it
-  auto merge_waves = [&](int first, int count, int lane0, int stride) {
-    for (int idx = lane0; idx < G * (D / 2); idx += stride) {
-      const int h = idx / (D / 2), j = (idx % (D / 2)) * 2;
-      float2 ow[NW];                              // (asked for first: their latency hides behind the weights' arithmetic)
+  constexpr int DPL = D / 64;                     // dims of a lane
+  typedef float float_dims __attribute__((ext_vector_type(DPL)));
+  // row h of the waves first .. first + count - 1
+  auto merge_row = [&](int h, int first, int count) {
+    const int j = lane * DPL;
+    float_dims ow[NW];                            // (asked for first: their latency hides behind the weights' arithmetic)
 #pragma unroll
-      for (int w = 0; w < NW; ++w) ow[w] = *reinterpret_cast<const float2*>(lds_o + (min(w, n_waves - 1) * GP + h) * D + j);
-      float mw[NW], lw[NW];
+    for (int w = 0; w < NW; ++w) ow[w] = *reinterpret_cast<const float_dims*>(lds_o + (min(w, n_waves - 1) * GP + h) * D + j);
+    float mw[NW], lw[NW];
 #pragma unroll
-      for (int w4 = 0; w4 < NW; w4 += 4) {
-        const float4v a = *reinterpret_cast<const float4v*>(lds_m + h * NW + w4);
-        const float4v bb = *reinterpret_cast<const float4v*>(lds_l + h * NW + w4);
+    for (int w4 = 0; w4 < NW; w4 += 4) {
+      const float4v a = *reinterpret_cast<const float4v*>(lds_m + h * NW + w4);
+      const float4v bb = *reinterpret_cast<const float4v*>(lds_l + h * NW + w4);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) { mw[w4 + u] = a[u]; lw[w4 + u] = bb[u]; }
+      for (int u = 0; u < 4; ++u) { mw[w4 + u] = a[u]; lw[w4 + u] = bb[u]; }
+    }
+    float mg = kNegBig;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) mg = (w >= first && w < first + count) ? fmaxf(mg, mw[w]) : mg;
+    float_dims num = 0.0f;
+    float den = 0.0f;
+    if (new_here) {
+      const float sn = lds_new[D + h];
+      mg = fmaxf(mg, sn);
+      den = __builtin_amdgcn_exp2f(sn - mg);
+#pragma unroll
+      for (int e2 = 0; e2 < DPL; e2 += 2) {       // (8-byte reads: a later unit's token is no better aligned)
+        const float2 vn = *reinterpret_cast<const float2*>(lds_new + j + e2);
+        num[e2] = vn.x * den;
+        num[e2 + 1] = vn.y * den;
       }
-      float mg = kNegBig;
+    }
 #pragma unroll
-      for (int w = 0; w < NW; ++w) mg = (w >= first && w < first + count) ? fmaxf(mg, mw[w]) : mg;
-      float n0 = 0.0f, n1 = 0.0f, den = 0.0f;
-      if (new_here) {
-        const float sn = lds_new[D + h];
-        mg = fmaxf(mg, sn);
-        den = __builtin_amdgcn_exp2f(sn - mg);
-        const float2 vn = *reinterpret_cast<const float2*>(lds_new + j);
-        n0 = vn.x * den;
-        n1 = vn.y * den;
-      }
+    for (int w = 0; w < NW; ++w) {
+      if (w < first || w >= first + count) continue;         // (wave-uniform)
+      const float e = __builtin_amdgcn_exp2f(mw[w] - mg);
 #pragma unroll
-      for (int w = 0; w < NW; ++w) {
-        if (w < first || w >= first + count) continue;       // (wave-uniform)
-        const float e = __builtin_amdgcn_exp2f(mw[w] - mg);
-        n0 = fmaf(ow[w].x, e, n0);
-        n1 = fmaf(ow[w].y, e, n1);
-        den = fmaf(lw[w], e, den);
-      }
-      if (direct) {
+      for (int e4 = 0; e4 < DPL; ++e4) num[e4] = fmaf(ow[w][e4], e, num[e4]);
+      den = fmaf(lw[w], e, den);
+    }
+    if (direct) {
+#pragma unroll
+      for (int e2 = 0; e2 < DPL; e2 += 2) {
         half2v r;
-        r[0] = (_Float16)(n0 / den);
-        r[1] = (_Float16)(n1 / den);
-        *reinterpret_cast<half2v*>(p.out + query_row(h) * D + j) = r;
-      } else {
-        // device-scope stores: they go through to where every compute die sees them (the L2 caches of
-        // different dies are not coherent with each other), so no cache-wide write-back is needed later
-        const int64_t ph = query_row(h) * part_stride + split;
-        st_dev2(p.part_o + ph * D + j, n0, n1);
-        if (j == 0) st_dev2(p.part_ml + ph * 2, mg, den);
+        r[0] = (_Float16)(num[e2] / den);
+        r[1] = (_Float16)(num[e2 + 1] / den);
+        *reinterpret_cast<half2v*>(p.out + query_row(h) * D + j + e2) = r;
       }
+    } else {
+      // device-scope stores: they go through to where every compute die sees them (the L2 caches of
+      // different dies are not coherent with each other), so no cache-wide write-back is needed later
+      const int64_t ph = query_row(h) * part_stride + split;
+#pragma unroll
+      for (int e2 = 0; e2 < DPL; e2 += 2) st_dev2(p.part_o + ph * D + j + e2, num[e2], num[e2 + 1]);
+      if (j == 0) st_dev2(p.part_ml + ph * 2, mg, den);
     }
   };
   if (!whole) {                                   // several units per block: the W waves of one merge among themselves
     // (a single-chunk row: the output; a slot of the chunk list: its partial)
-    if (row_valid) merge_waves(wave - sub, W, sub * 64 + lane, W * 64);
+    if (row_valid)
+      for (int h = sub; h < G; h += W) merge_row(h, wave - sub, W);
     return;
   }
-  merge_waves(0, NW, threadIdx.x, NW * 64);
+  for (int h = wave; h < G; h += NW) merge_row(h, 0, NW);
   if (p.merge_slot < 0 || direct) return;
 
-  // ---- chunk merge (Eq. 6) by whichever block of this (b, kv head) finishes last.  A block publishes
-  //      its partial (device-scope stores, waited for), then counts itself in; the one that sees all
-  //      others counted re-reads all partials, with device-scope loads and in chunk order, so the
-  //      result does not depend on which block that is.
-  const int n = p.n_splits;
-  int* const is_last = reinterpret_cast<int*>(smem);
-  wait_loads<0>();                                // vmcnt counts stores too: this wave's partial has landed
-  __syncthreads();                                // every wave's has; and nobody reads the block-merge area any more
-  if (threadIdx.x == 0) {
-    unsigned int* ctr = &g_arrivals[p.merge_slot * kCountersPerSlot + arrival_counter(b * (p.n_kv_heads * kv_share) + kvv)];
-    *is_last = atomicInc(ctr, (unsigned int)(n - 1)) == (unsigned int)(n - 1);   // wraps to 0 on the last arrival
-  }
-  __syncthreads();
-  if (*is_last == 0) return;
-  // What orders the partials before their readers is the machine's memory model for device-scope ATOMIC accesses,
+  // ---- chunk merge (Eq. 6), row by row, by whichever wave that has this row finishes last.  A wave publishes
+  //      its row's partial (device-scope stores, waited for), then counts itself in; the one that sees all
+  //      others counted re-reads the row's partials, with device-scope loads and in chunk order, so the
+  //      result does not depend on which wave that is.  No barrier: a row is one wave's in every block, and the rows of
+  //      a KV head may be merged by different blocks.  What bounds it is the chain store, count, fetch, and for 32 chunks
+  //      the fetch through one compute unit.  (Counted block by block, two barriers, 8-byte loads with an address
+  //      each: us per step 8 heads over 1, 1024 tokens, 4 chunks, 7.94 -> 7.68; 64 over 8, 8K, 32 chunks, 10.02 -> 9.35, 32K
+  //      14.4 -> 14.05; d = 256, 4 chunks, 8.78 -> 8.56.)
+  // What orders the partials before their readers is the machine's memory model for device-scope accesses,
   // not a pair of fences: every partial is written with device-scope atomic stores (write-through: complete, as
-  // counted by vmcnt, once the data sits where every compute die reads it), the wave waits for vmcnt(0) and the
-  // block for its barrier before one thread counts the block in with a device-scope atomic, and the last block
-  // issues its device-scope atomic loads (which do not hit lines a die cached earlier) only after that atomic has
+  // counted by vmcnt, once the data sits where every compute die reads it), the wave waits for vmcnt(0)
+  // before it counts itself in with a device-scope atomic, and the last wave
+  // issues its device-scope loads (which do not hit lines a die cached earlier) only after that atomic has
   // returned.  A release fence before the count and an acquire fence after it (agent scope) were measured instead:
   // each block then writes its die's whole L2 back and invalidates it, and a decode of 256 blocks over 8K tokens
   // goes from 11.0 to 13.5 us (release alone +1.2 us, acquire alone +0.9 us), more than the separate merge kernel
   // costs (13.1 us), for no access that the atomics do not already cover.
-  // Everything is asked for at once: wave h fetches the (m, l) of row h's chunks, a chunk per lane, and a thread
-  // the chunks' outputs for two neighbouring dims of one row (two threads share a pair where there are fewer pairs than
-  // threads, each with every other chunk).  The weights come out of lane reductions while the outputs are on their
-  // way; one barrier hands them over.  (With the (m, l) staged through LDS, two barriers, and always 32 loads per single
-  // element however few the chunks, this end of the kernel took 3.2 us for 4 chunks and 4 us for 32, of 10 and 11; with
-  // the (m, l) fetched by every thread for itself 1.3 and 5.)
   if constexpr (GP <= 8) {                        // (a 16-row tile's chunks go to the merge kernel)
     static_assert(GP <= NW && kMergeMaxChunks <= 64, "a wave per row, a lane per chunk");
-    float* const c_w = reinterpret_cast<float*>(smem) + 64;    // [GP][kMergeMaxChunks] chunk weights
-    float* const h_den = c_w + GP * kMergeMaxChunks;            // [GP]
+    if (wave >= G) return;
+    const int n = p.n_splits;
+    const int64_t row = query_row(wave);
+    wait_loads<0>();                              // vmcnt counts stores too: this wave's partial has landed
+    unsigned int seen = 0;
+    if (lane == 0)
+      seen = atomicInc(&g_arrivals[p.merge_slot * kCountersPerSlot + arrival_counter((int)row)], (unsigned int)(n - 1));   // wraps to 0 on the last arrival
+    if (__builtin_amdgcn_readfirstlane((int)seen) != n - 1) return;
+    asm volatile("" ::: "memory");                // (no load below may move above the count)
+    // Everything is asked for at once: the row's (m, l), a chunk per lane, and the chunks' outputs, sixteen bytes a lane (D / 4
+    // lanes to a chunk, PARTS chunks to an instruction).  The row's partials are addressed as a buffer of n chunks: what lies
+    // past the last one reads as zero, and its weight is zero.
+    constexpr int PARTS = 256 / D;
+    float* const c_w = reinterpret_cast<float*>(smem + (C::ALIAS ? NW / 2 + wave : wave) * (NS * C::STAGE));   // [kMergeMaxChunks], a ring that is quiet
+    static_assert(!C::ALIAS || (GP <= NW / 2 && C::MERGE <= NW / 2 * NS * C::STAGE), "the rings behind the block-merge area");
+    const int cpart = PARTS == 2 ? lane >> 5 : 0, j = (lane % (D / 4)) * 4;
     float2 ml = {kNegBig, 0.0f};
-    if (wave < G && lane < n) ml = ld_dev2(p.part_ml + (query_row(wave) * n + lane) * 2);
-    constexpr int PAIRS = GP * D / 2, PARTS = NW * 64 / PAIRS;
-    static_assert(PARTS == 1 || PARTS == 2, "a thread, or two neighbouring ones, per pair of dims");
-    const int pair = threadIdx.x / PARTS, cpart = threadIdx.x % PARTS;
-    const int h = pair / (D / 2), j = (pair % (D / 2)) * 2;
-    const int64_t row = query_row(h < G ? h : 0);
-    const float* const src = p.part_o + row * n * D + j;
-    auto weights = [&] {
-      if (wave < G) {
-        // (zero past the last chunk: the weights below are then read without a condition, in a few wide reads at once; behind
-        // `chunk < n ? w : 0` each of the 32 was a branch, a read and a wait of its own, 2 us of a merge of 32 chunks)
-        const float top = wave_fmax(ml.x);        // (every lane takes part)
-        const float w = lane < n ? __builtin_amdgcn_exp2f(ml.x - top) : 0.0f;
-        c_w[wave * kMergeMaxChunks + lane] = w;
-        const float d = wave_fsum(ml.y * w);
-        if (lane == 0) h_den[wave] = d;
-      }
-      __syncthreads();
-    };
-    const float* const w = c_w + h * kMergeMaxChunks;
-    float n0 = 0.0f, n1 = 0.0f;
-    auto fetch = [&](auto count_tag, int c0, float2* o) {
+    if (lane < n) ml = ld_dev2(p.part_ml + (row * n + lane) * 2);
+    const auto rows = __builtin_amdgcn_make_buffer_rsrc(p.part_o + row * n * D, 0, n * D * 4, 0x00020000);
+    auto fetch = [&](auto count_tag, int c0, float4v* o) {   // chunks c0 + cpart * U ..
+      constexpr int U = decltype(count_tag)::value;
 #pragma unroll
-      for (int u = 0; u < decltype(count_tag)::value; ++u) o[u] = ld_dev2(src + (int64_t)min(c0 + u * PARTS + cpart, n - 1) * D);
+      for (int u = 0; u < U; ++u)
+        o[u] = __builtin_bit_cast(float4v, __builtin_amdgcn_raw_buffer_load_b128(rows, ((c0 + cpart * U) * D + j) * 4, u * D * 4, 16));   // 16: device scope
     };
-    auto add = [&](auto count_tag, int c0, const float2* o) {
+    float4v num = {0, 0, 0, 0};
+    auto add = [&](auto count_tag, int c0, const float4v* o) {
+      constexpr int U = decltype(count_tag)::value;
+      const float* const w = c_w + c0 + cpart * U;
 #pragma unroll
-      for (int u = 0; u < decltype(count_tag)::value; ++u) {
-        const float e = w[c0 + u * PARTS + cpart];
-        n0 = fmaf(o[u].x, e, n0);
-        n1 = fmaf(o[u].y, e, n1);
+      for (int u = 0; u < U; ++u) {
+        const float e = w[u];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) num[k] = fmaf(o[u][k], e, num[k]);
       }
     };
+    float den = 0.0f;
     auto all = [&](auto count_tag) {
       constexpr int U = decltype(count_tag)::value;
-      float2 o[U];
+      float4v o[U];
       fetch(count_tag, 0, o);
-      weights();
+      const float top = wave_fmax(ml.x);          // (every lane takes part)
+      const float w = lane < n ? __builtin_amdgcn_exp2f(ml.x - top) : 0.0f;
+      c_w[lane] = w;
+      den = wave_fsum(ml.y * w);
       add(count_tag, 0, o);
       for (int c0 = U * PARTS; c0 < n; c0 += U * PARTS) {
         fetch(count_tag, c0, o);
@@ -1430,18 +1431,22 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
       }
     };
     if (n <= 4 * PARTS) all(std::integral_constant<int, 4>{});
-    else if (n <= 16 * PARTS) all(std::integral_constant<int, 16>{});
-    else all(std::integral_constant<int, 32>{});
+    else if (n <= 8 * PARTS) all(std::integral_constant<int, 8>{});
+    else all(std::integral_constant<int, 16>{});
     if constexpr (PARTS == 2) {
-      n0 += __shfl_xor(n0, 1);
-      n1 += __shfl_xor(n1, 1);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        float a, b2;
+        swap32(num[k], a, b2);
+        num[k] = a + b2;
+      }
     }
-    if (h < G && cpart == 0) {
-      const float den = h_den[h];
-      half2v r;
-      r[0] = (_Float16)(n0 / den);
-      r[1] = (_Float16)(n1 / den);
-      *reinterpret_cast<half2v*>(p.out + row * D + j) = r;
+    if (cpart == 0) {
+      typedef _Float16 half4v __attribute__((ext_vector_type(4)));
+      half4v r;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) r[k] = (_Float16)(num[k] / den);
+      *reinterpret_cast<half4v*>(p.out + row * D + j) = r;
     }
   }
 }
@@ -1538,7 +1543,7 @@ bool mfma_takes_token(int head_dim, int group, int rows) {
   return share > 0 && !(share > 1 && group == kGroup && padded_gqa(head_dim, rows / share) == 16);
 }
 
-bool mfma_can_merge(int batch, int n_kv_heads) { return (int64_t)batch * n_kv_heads <= kCountersPerSlot; }
+bool mfma_can_merge(int64_t out_rows) { return out_rows <= kCountersPerSlot; }
 
 int mfma_merge_slot_of(const void* workspace) {
   static std::mutex guard;
@@ -1564,7 +1569,7 @@ hipError_t launch_partial_mfma(const DecodeParams& p_in, int batch, int head_dim
   const int rows_y = p.n_kv_heads * p.kv_share;
   p.merge_slot = -1;
   if (merge_slot >= 0) {
-    if ((p.n_splits > 1 && !mfma_can_merge(batch, rows_y)) || p.out == nullptr || merge_slot >= kCounterSlots)
+    if ((p.n_splits > 1 && !mfma_can_merge((int64_t)batch * p.n_queries * p.n_q_heads)) || p.out == nullptr || merge_slot >= kCounterSlots)
       return hipErrorInvalidValue;
     p.merge_slot = merge_slot;
   }

@@ -440,7 +440,7 @@ bool mfma_takes_token(int head_dim, int group_size, int rows);
 // The slot names the set of arrival counters the launch uses; mfma_merge_slot_of hands every workspace a set of
 // its own, for the life of the process, or -1 once all sets are taken (the caller then runs the merge kernel).
 // A launch whose rows are single chunks counts nothing and takes any slot >= 0.
-bool mfma_can_merge(int batch, int n_kv_heads);
+bool mfma_can_merge(int64_t out_rows);
 int mfma_merge_slot_of(const void* workspace);
 hipError_t launch_partial_mfma(const DecodeParams& p, int batch, int head_dim, int merge_slot, hipStream_t s);
 // Matrix-core kernel whose blocks take a tile of 16 query rows of one KV head (head_dim 128: 32, where there are more than 16)

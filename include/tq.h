@@ -263,7 +263,8 @@ size_t tq_kv_bytes(int32_t batch, int32_t n_kv_heads, int32_t capacity, int32_t 
 /* The same for a group size of 32, 64 or 128: 2 * batch * n_kv_heads * capacity * (head_dim/2 + 4*head_dim/group_size). */
 size_t tq_kv_bytes_grouped(int32_t batch, int32_t n_kv_heads, int32_t capacity, int32_t head_dim, int32_t group_size);
 
-/* Chunk count the heuristic would pick on the matrix-core kernel for few query rows per KV head (host only). */
+/* Chunk count the heuristic would pick on the matrix-core kernel for few query rows per KV head (host only), before a call
+ * whose decode kernel merges the chunks of a short sequence itself cuts it finer. */
 int32_t tq_plan_splits(int32_t batch, int32_t n_kv_heads, int32_t seq_len);
 
 /* Kernel launches one tq_sdpa_int4_decode call makes for this cache shape, query head count,

@@ -67,6 +67,27 @@ Plan plan_splits(int batch, int n_kv_heads, int seq_len, int requested, int targ
   return p;
 }
 
+// Chunks of a short sequence (1: as plan_splits has it) where up to eight rows share a block and the decode kernel merges the chunks
+// in place.  A call that leaves compute units without a block is as long as its longest chain: with four tiles to a chunk or fewer a
+// block has one wave to a SIMD, which is done about 0.7 us sooner than two that share it, and with two tiles the block merge has
+// as good as no spread to wait for; against that a chunk more is 4 KB more for the waves that merge.  So two or three tiles
+// to a chunk up to 16 chunks, then four and more up to 32; a sequence of up to eight tiles stays one chunk (no merge at all), and one of up to
+// 15, which would be, is cut only where there are compute units for two tiles a chunk.  us per step, eight tiles and more to a chunk / this:
+// 8 heads over 1, 300 tokens 6.2 / 6.1, 1024 7.7 / 6.3, 4096 8.0 / 7.5; 64 over 8, 600 tokens 8.0 / 6.5, 2048 8.0 / 7.0, 4096 8.4 / 7.9,
+// 4 sequences of 600 8.1 / 6.7, 8 of 600 8.2 / 7.8; 32 over 32, 600 6.7 / 5.7; d = 256: 32 over 16, 600 9.2 / 6.9, a window of 1024
+// 8.6 / 7.0, 16 over 8, 3000 10.1 / 8.5.  (64 over 8, 200 tokens in four chunks 6.7, in one 6.4; 2048 tokens in 32 chunks 7.5, in 16 7.2;
+// 16 sequences of 300 in two chunks each 8.0, in one 7.3.)
+int fine_splits(int batch, int n_kv_heads, int seq_len, int target_blocks) {
+  const int tiles = (seq_len + tq::kTile - 1) / tq::kTile;
+  const int64_t most = (int64_t)target_blocks / ((int64_t)batch * n_kv_heads);
+  if (tiles <= 8) return 1;
+  for (int t = 2; t <= (tiles < 16 ? 2 : 8); ++t) {
+    const int n = (tiles + t - 1) / t;
+    if (n <= most && n <= (t < 4 ? 16 : 32)) return n;
+  }
+  return 1;
+}
+
 // query tokens per sequence the options ask for
 int queries_of(const tq_decode_opts* opts) { return (opts && opts->n_queries > 1) ? opts->n_queries : 1; }
 // query rows that share one KV head
@@ -367,6 +388,18 @@ int run_partial(PartialRequest& rq) {
   if (r.wide && asked <= 0)
     plan = plan_splits(cache->batch, rows_per_batch, attended,
                        std::min(plan.n_splits, tq::wide_max_chunks(cache->head_dim, (attended + tq::kTile - 1) / tq::kTile)), target, 1);
+  // (the chunks of one token fewer may be shorter, and then up to twice as many as the route counted)
+  rq.merged = ranked || (rq.out != nullptr && (rq.step ? r.merge_step : r.merge) && !seq_lens && plan.n_splits <= tq::kMergeMaxChunks);
+  int merge_slot = -1;
+  if (rq.merged) {
+    const int fine = ranked || asked > 0 || !r.small_tile ? 1 : fine_splits(cache->batch, rows_per_batch, attended, target);
+    // several chunks: the arrival counters of this workspace (none left: the merge kernel does it); rows that are
+    // single chunks count nothing
+    merge_slot = std::max(plan.n_splits, fine) > 1 ? tq::mfma_merge_slot_of(rq.workspace) : 0;
+    if (merge_slot < 0 && plan.n_splits == 1) merge_slot = 0;
+    else if (merge_slot < 0) rq.merged = false;
+    else if (fine > plan.n_splits) plan = plan_splits(cache->batch, rows_per_batch, attended, fine, target, 1);
+  }
   DecodeParams p = make_params(cache, rq.q, n_q_heads, seq_len, rq.attn_scale, rq.out, rq.workspace, plan,
                                queries_of(opts));
   p.seq_lens = seq_lens;
@@ -401,15 +434,6 @@ int run_partial(PartialRequest& rq) {
   }
   rq.n_splits = plan.n_splits;
   hipStream_t s = static_cast<hipStream_t>(rq.stream);
-  // (the chunks of one token fewer may be shorter, and then up to twice as many as the route counted)
-  rq.merged = ranked || (rq.out != nullptr && (rq.step ? r.merge_step : r.merge) && !seq_lens && plan.n_splits <= tq::kMergeMaxChunks);
-  int merge_slot = -1;
-  if (rq.merged) {
-    // several chunks: the arrival counters of this workspace (none left: the merge kernel does it); rows that are
-    // single chunks count nothing
-    merge_slot = plan.n_splits > 1 ? tq::mfma_merge_slot_of(rq.workspace) : 0;
-    if (merge_slot < 0) rq.merged = false;
-  }
   rq.params = p;
   if (append) {
     // One of the two kernels takes the token in: the decode kernel where it writes the output (there is no other) and

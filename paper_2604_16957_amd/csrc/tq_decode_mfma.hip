@@ -581,6 +581,11 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
     return young ? YNG * (K / PERIOD) + (r >> 1) : OLD * (K / PERIOD) + ((r + 1) >> 1);
   };
   const int n_mine = count_of(n_full);
+  const bool tail_last = n_tail > 0 && count_of(n_full + 1) != count_of(n_full);
+  // A short chunk has no supertile for every wave: its first ones are its first waves', one each, and the others only keep
+  // the barriers company (and take their rows of the merges).
+  const bool busy = !PLAIN || n_mine > 0 || tail_last;
+  const int n_busy = PLAIN ? min(NW, n_full + n_tail) : NW;
   // ---- prologue: the query rows of this KV head's group come in by direct load as well (so that every
   //      vector-memory operation of the kernel is one of the counted loads), then the ring is filled.
   //      Where the query block has to borrow the last ring slot, that slot is filled once the query
@@ -605,8 +610,10 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   // that the copies of K share the query rows' scores between them.  (One younger wave for all of it, half of its lanes idle:
   // that wave 2.0 us behind the others; us per step 8 heads over 1, 1024 tokens 8.62 -> 7.94, 64 over 8, 8K 10.77 -> 10.02,
   // 32 over 16, d = 256, a window of 1024 9.31 -> 8.78; the decode alone 7.83, 10.01, 8.80.)
-  const bool takes_k = new_here && (whole ? wave == NW / 2 - 1 : sub == 0);
-  const bool takes_v = new_here && (whole ? wave == NW / 2 - 2 : sub == (W > 1 ? 1 : 0));
+  // (A chunk of few supertiles leaves the younger waves idle: then they.)
+  const int taker = n_busy <= NW / 2 ? NW - 1 : NW / 2 - 1;
+  const bool takes_k = new_here && (whole ? wave == taker : sub == 0);
+  const bool takes_v = new_here && (whole ? wave == taker - 1 : sub == (W > 1 ? 1 : 0));
   const bool takes = takes_k || takes_v;
   constexpr int PIECES = D / 8, COPIES = 64 / PIECES;
   const int new_piece = lane % PIECES, new_v = takes_k && takes_v ? lane >> 5 : takes_v;
@@ -620,11 +627,13 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
     const uint32_t l = C::QSEP ? (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem + off_qblk +
                                      wave * C::QAREA
                                : ring_lds + (NS - 1) * C::STAGE + Q_IN_SLOT;
+    {
 #pragma unroll
-    for (int u = 0; u < GP * D * 2 / 1024; ++u) {
-      const int chunk = u * 64 + lane;            // 16-byte chunk of the [GP][D] fp16 query block
-      const int h = min(chunk / (D / 8), G - 1);
-      dma16_lane(p.q + query_row(h) * D + (chunk % (D / 8)) * 8, l + u * 1024);
+      for (int u = 0; u < GP * D * 2 / 1024; ++u) {
+        const int chunk = u * 64 + lane;          // 16-byte chunk of the [GP][D] fp16 query block
+        const int h = min(chunk / (D / 8), G - 1);
+        dma16_lane(p.q + query_row(h) * D + (chunk % (D / 8)) * 8, l + u * 1024);
+      }
     }
     if (takes)                                    // the new token's K row, or its V row (one wave for both: half the lanes each)
       dma16_lane((new_v ? p.v_new : p.k_new) + (int64_t)(b * p.n_kv_heads + kv) * D + new_piece * 8, l + C::QBLK);
@@ -636,7 +645,6 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   // A wave whose share includes the ragged (or partly masked) last supertile takes that one FIRST: its loads then leave
   // with the prologue's and its masked path runs while the wave's first full supertile is on its way.  (At the end it
   // was a memory round trip of its own for one wave of the launch, 2 - 3 us of a short sequence's time.)
-  const bool tail_last = n_tail > 0 && count_of(n_full + 1) != count_of(n_full);
   const bool tail0 = !LEAN && tail_last;
   if (tail0) issue_tail(0, n_full);
   else if (n_mine > 0) issue(0, sidx_of(0));
@@ -653,57 +661,60 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   else wait_loads<0>();
 
   // ---- query operands (the query pre-scaling of Alg. 1 is folded into the exp2 argument instead of the query)
-  const _Float16* qh = reinterpret_cast<const _Float16*>(q_area) + hl * D;
-  half8v qraw[NJ];
-#pragma unroll
-  for (int j = 0; j < NJ; ++j)
-    qraw[j] = *reinterpret_cast<const half8v*>(qh + C::a_group(j, kq) * kGroup + C::a_word(j, kq) * 8);
-  half8v qgrp[NA][4];
-#pragma unroll
-  for (int a = 0; a < NA; ++a)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) qgrp[a][i] = *reinterpret_cast<const half8v*>(qh + (rep * NA + a) * kGroup + i * 8);
-
-  // (SPLIT) Half of the operand's elements are q over 16 (below), and those of a small query would lose bits in fp16's
-  // subnormals, which the fp32 queries of the generic kernel do not.  So a row with no element of 2 or more is taken 16
-  // times (every fp16 is a whole number of 2^-24: q and 16 q are exact), and in the others what is lost lies 2^-22
-  // below the row's largest element.  (A power of two that brings the largest element near 2^14 costs a short step 0.9 us.)
+  half8v qb[NJ];
+  float qsum[NA];                                 // 2^-24 * sum of the operand's q over each of this lane's groups
   float q_up = 1.0f;
-  if constexpr (SPLIT) {
-    uint32_t any = 0;
+  if (busy) {
+    const _Float16* qh = reinterpret_cast<const _Float16*>(q_area) + hl * D;
+    half8v qraw[NJ];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+      qraw[j] = *reinterpret_cast<const half8v*>(qh + C::a_group(j, kq) * kGroup + C::a_word(j, kq) * 8);
+    half8v qgrp[NA][4];
+#pragma unroll
+    for (int a = 0; a < NA; ++a)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) qgrp[a][i] = *reinterpret_cast<const half8v*>(qh + (rep * NA + a) * kGroup + i * 8);
+
+    // (SPLIT) Half of the operand's elements are q over 16 (below), and those of a small query would lose bits in fp16's
+    // subnormals, which the fp32 queries of the generic kernel do not.  So a row with no element of 2 or more is taken 16
+    // times (every fp16 is a whole number of 2^-24: q and 16 q are exact), and in the others what is lost lies 2^-22
+    // below the row's largest element.  (A power of two that brings the largest element near 2^14 costs a short step 0.9 us.)
+    if constexpr (SPLIT) {
+      uint32_t any = 0;
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        const uint4v w = __builtin_bit_cast(uint4v, qraw[j]);
+        any |= (w[0] | w[1]) | (w[2] | w[3]);
+      }
+      // (bit 14 of an fp16: 2 or more; a row's elements are spread over the four 16-lane rows)
+      q_up = blocks_max((any & 0x40004000u) != 0 ? 1.0f : 0.0f) > 0.0f ? 1.0f : 16.0f;
+    }
+    const _Float16 q_lo = (_Float16)q_up, q_hi = (_Float16)(q_up * 0.0625f);
+
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
-      const uint4v w = __builtin_bit_cast(uint4v, qraw[j]);
-      any |= (w[0] | w[1]) | (w[2] | w[3]);
+      const bool mine = (C::a_group(j, kq) == rep * NA + C::acc(j)) && hl < G;
+      const half8v x = qraw[j];
+      // k-slot order of unpack_word: nibbles 0,4,1,5,2,6,3,7; the "hi" slots carry c*2^-20, so pre-divide by 16
+      half8v y = {x[0], x[4], x[1] * (_Float16)0.0625f, x[5] * (_Float16)0.0625f,
+                  x[2], x[6], x[3] * (_Float16)0.0625f, x[7] * (_Float16)0.0625f};
+      if constexpr (SPLIT)
+        y = half8v{x[0] * q_lo, x[4] * q_lo, x[1] * q_hi, x[5] * q_hi, x[2] * q_lo, x[6] * q_lo, x[3] * q_hi, x[7] * q_hi};
+      if (!mine) y = half8v{0, 0, 0, 0, 0, 0, 0, 0};
+      qb[j] = y;
     }
-    // (bit 14 of an fp16: 2 or more; a row's elements are spread over the four 16-lane rows)
-    q_up = blocks_max((any & 0x40004000u) != 0 ? 1.0f : 0.0f) > 0.0f ? 1.0f : 16.0f;
+#pragma unroll
+    for (int a = 0; a < NA; ++a) {
+      float s = 0.0f;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s += (float)qgrp[a][i][e];
+      qsum[a] = (hl < G) ? s * (SPLIT ? 0x1p-24f * q_up : 0x1p-24f) : 0.0f;
+    }
   }
-  const _Float16 q_lo = (_Float16)q_up, q_hi = (_Float16)(q_up * 0.0625f);
 
-  half8v qb[NJ];
-#pragma unroll
-  for (int j = 0; j < NJ; ++j) {
-    const bool mine = (C::a_group(j, kq) == rep * NA + C::acc(j)) && hl < G;
-    const half8v x = qraw[j];
-    // k-slot order of unpack_word: nibbles 0,4,1,5,2,6,3,7; the "hi" slots carry c*2^-20, so pre-divide by 16
-    half8v y = {x[0], x[4], x[1] * (_Float16)0.0625f, x[5] * (_Float16)0.0625f,
-                x[2], x[6], x[3] * (_Float16)0.0625f, x[7] * (_Float16)0.0625f};
-    if constexpr (SPLIT)
-      y = half8v{x[0] * q_lo, x[4] * q_lo, x[1] * q_hi, x[5] * q_hi, x[2] * q_lo, x[6] * q_lo, x[3] * q_hi, x[7] * q_hi};
-    if (!mine) y = half8v{0, 0, 0, 0, 0, 0, 0, 0};
-    qb[j] = y;
-  }
-  float qsum[NA];                                 // 2^-24 * sum of the operand's q over each of this lane's groups
-#pragma unroll
-  for (int a = 0; a < NA; ++a) {
-    float s = 0.0f;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) s += (float)qgrp[a][i][e];
-    qsum[a] = (hl < G) ? s * (SPLIT ? 0x1p-24f * q_up : 0x1p-24f) : 0.0f;
-  }
   uint32_t new_w = 0;                             // the new token: this lane's packed word, its group's scale and
   half2v new_sz = {0, 0};                         // zero-point, and (lane h of the first 16) its score against row h
   float new_score = 0.0f;
@@ -1247,45 +1258,50 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
     const int copies = takes_v ? COPIES / 2 : COPIES, row_of = lane / PIECES + new_piece * copies;   // the row this lane's score is of
     if (takes_k && lane / PIECES < copies && row_of < GP) lds_new[D + row_of] = new_score * p.scale_log2;
   }
-  if constexpr (C::WIDE) {
-    // row 4 kq + i = head; group g's zero-point sum of that head sits in column g (any column c with c % 4 == g)
-    // of zacc[g]; this lane's column is byte c / 4 of word c % 4 of every group: two neighbouring dims per group
+  if (busy) {
+    if constexpr (C::WIDE) {
+      // row 4 kq + i = head; group g's zero-point sum of that head sits in column g (any column c with c % 4 == g)
+      // of zacc[g]; this lane's column is byte c / 4 of word c % 4 of every group: two neighbouring dims per group
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int g = 0; g < NG; ++g) {
-        const float zc = __shfl(zacc[g][i], (lane & 48) | g);
-        const float even = oacc[0][2 * g][0][i], mixed = oacc[0][2 * g + 1][0][i];
-        float2 o2;
-        o2.x = fmaf(even, 0x1p24f, -zc);
-        o2.y = fmaf(mixed - even, 0x1p20f, -zc);
-        *reinterpret_cast<float2*>(lds_o + (wave * GP + 4 * kq + i) * D + (4 * g + (c & 3)) * 8 + 2 * (c >> 2)) = o2;
-      }
-  }
+        for (int g = 0; g < NG; ++g) {
+          const float zc = __shfl(zacc[g][i], (lane & 48) | g);
+          const float even = oacc[0][2 * g][0][i], mixed = oacc[0][2 * g + 1][0][i];
+          float2 o2;
+          o2.x = fmaf(even, 0x1p24f, -zc);
+          o2.y = fmaf(mixed - even, 0x1p20f, -zc);
+          *reinterpret_cast<float2*>(lds_o + (wave * GP + 4 * kq + i) * D + (4 * g + (c & 3)) * 8 + 2 * (c >> 2)) = o2;
+        }
+    }
 #pragma unroll
-  for (int i = 0; i < (C::WIDE ? 0 : 4); ++i) {
-    const int r = 4 * kq + i, h = r % GP, rp = r / GP;       // accumulator row -> (head, replica)
+    for (int i = 0; i < (C::WIDE ? 0 : 4); ++i) {
+      const int r = 4 * kq + i, h = r % GP, rp = r / GP;       // accumulator row -> (head, replica)
 #pragma unroll
-    for (int cs = 0; cs < NCS; ++cs) {
-      const int word = c * NCS + cs;              // packed word (8 dims) this lane's column stands for
-      const int a_mine = (word >> 2) - rp * NA;
-      const bool second = NA == 2 && a_mine == 1;
-      const float zc = second ? zacc[NA - 1][i] : zacc[0][i];
-      float4v lo, hi;
-      float acc[8];
+      for (int cs = 0; cs < NCS; ++cs) {
+        const int word = c * NCS + cs;              // packed word (8 dims) this lane's column stands for
+        const int a_mine = (word >> 2) - rp * NA;
+        const bool second = NA == 2 && a_mine == 1;
+        const float zc = second ? zacc[NA - 1][i] : zacc[0][i];
+        float4v lo, hi;
+        float acc[8];
 #pragma unroll
-      for (int m = 0; m < 8; ++m) acc[m] = second ? oacc[cs][m][NAO - 1][i] : oacc[cs][m][0][i];
+        for (int m = 0; m < 8; ++m) acc[m] = second ? oacc[cs][m][NAO - 1][i] : oacc[cs][m][0][i];
 #pragma unroll
-      for (int m = 0; m < 4; ++m) {               // dim m: the even sum, or (mixed - even) / 16, in units of 2^-24
-        lo[m] = fmaf((m & 1) ? acc[m] - acc[m - (m & 1)] : acc[m], (m & 1) ? 0x1p20f : 0x1p24f, -zc);
-        hi[m] = fmaf((m & 1) ? acc[m + 4] - acc[m + 4 - (m & 1)] : acc[m + 4], (m & 1) ? 0x1p20f : 0x1p24f, -zc);
-      }
-      if (a_mine >= 0 && a_mine < NA) {
-        float4v* dst = reinterpret_cast<float4v*>(lds_o + (wave * GP + h) * D + word * 8);
-        dst[0] = lo;
-        dst[1] = hi;
+        for (int m = 0; m < 4; ++m) {               // dim m: the even sum, or (mixed - even) / 16, in units of 2^-24
+          lo[m] = fmaf((m & 1) ? acc[m] - acc[m - (m & 1)] : acc[m], (m & 1) ? 0x1p20f : 0x1p24f, -zc);
+          hi[m] = fmaf((m & 1) ? acc[m + 4] - acc[m + 4 - (m & 1)] : acc[m + 4], (m & 1) ? 0x1p20f : 0x1p24f, -zc);
+        }
+        if (a_mine >= 0 && a_mine < NA) {
+          float4v* dst = reinterpret_cast<float4v*>(lds_o + (wave * GP + h) * D + word * 8);
+          dst[0] = lo;
+          dst[1] = hi;
+        }
       }
     }
+  } else {                                        // (its sums carry no weight in the merge, but what lies there might be Inf or NaN)
+#pragma unroll
+    for (int u = 0; u < GP * D / 256; ++u) *reinterpret_cast<float4v*>(lds_o + wave * GP * D + (u * 64 + lane) * 4) = float4v{0, 0, 0, 0};
   }
   __syncthreads();
 

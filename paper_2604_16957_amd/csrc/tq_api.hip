@@ -336,6 +336,42 @@ Ranked ranked_rows(const tq_kv_cache* cache, int n_q_heads, int seq_len, float a
   return {waves, spread};
 }
 
+// Sequences with their own lengths, up to eight query rows to a block, one query token, no window: the device deals the waves of one
+// round of blocks to the sequences in proportion to their lengths (DecodeParams::listed), a sequence's waves in a block merge among themselves and
+// its blocks in place.  Every wave has the same share to a tile, where the chunk list has one chunk length for all and a block or half of one
+// per chunk (so that half a chunk per sequence is idle time), and there is no merge launch.  0: not this way; else slots (waves) to a KV head.
+// us per step, chunk list / this, 64 heads over 8, d = 128: 24 sequences of 1000 .. 16384 in pages 42.5 / 38.3, 8 of 4386 .. 32768 40.6 / 39.2,
+// 16 of 300 .. 3000 18.4 / 13.8, 48 of 300 .. 6000 42.1 / 30.8, 32 of 1000 19.2 / 14.3; 32 over 32: 8 of 500 .. 6000 27.1 / 22.0; 32 over 8:
+// 32 of 100 .. 8000 26.1 / 20.3; 32 over 16, d = 256: 16 of 500 .. 8000 57.2 / 48.1, 20 of 1500 49.2 / 36.4.
+// Where every row can have a block of its own (ranked_waves: 512 rows and more) that is the shorter way for short sequences of about one
+// length: no sequence is cut there, and the plan is shorter.  us per step, a block per row or (where that has no line) chunk list / this, for all
+// lengths at the bound | uniform from half of it | spread over the logarithm from a 16th:
+//   64 sequences (512 rows)  2048  34.4 / 34.8 | 27.9 / 31.0 | 23.0 / 22.6     4096  57.9 / 59.2 | 51.4 / 52.9 | 31.8 / 27.7 (from a 32nd)
+//   80 (640)                 1024  30.3 / 31.3 | 28.7 / 27.1 | 21.7 / 19.2     2048  49.3 / 46.5 | 45.2 / 39.0 | 25.9 / 25.9
+//   96 (768)                 3500  90.6 / 94.4 | 83.5 / 72.9 | 49.6 / 39.0     128 (1024)  3500  112 / 114 | 93.4 / 100 | 53.8 / 51.6
+//   176 (1408)               3500  183 / 179   | 163 / 143   | 94.5 / 76.2
+// and at d = 256, 32 heads over 16: 32 (512) 2048 60.6 / 63.8 | 52.3 / 52.5 | 35.5 / 29.3, 2500 81.4 / 76.8 | 70.2 / 61.9 | 40.4 / 36.0; 40 (640)
+// 1024 52.0 / 44.9 | 41.3 / 36.7 | 23.0 / 22.9; 64 (1024) 3000 170 / 164 | 144 / 135.
+// One sequence at the bound among short ones gains everywhere (64 sequences, one of 4096, the others 96: 25.3 / 14.4).
+bool listed_lengths(int64_t rows, int tokens, bool d256) {
+  constexpr int C = kBlocksMfma;
+  if (rows < 2 * C) return true;
+  if (rows == 2 * C) return tokens > (d256 ? 2048 : 3072);
+  if (rows <= 11 * C / 4) return tokens > (d256 ? 0 : 1024);
+  if (rows <= 4 * C) return d256 && tokens > 2048;
+  return tokens > (rows <= 8 * C ? 2048 : 1024);
+}
+int listed_slots(const tq_kv_cache* cache, int n_q_heads, int seq_len, float attn_scale, const tq_decode_opts* opts) {
+  if (opts && (opts->n_splits > 0 || opts->window > 0 || opts->n_queries > 1)) return 0;
+  const Route r = route_of(cache, n_q_heads, seq_len, attn_scale, opts, Call::kLengths);
+  if (!r.ok || !r.use_mfma || !r.small_tile || mfma_share_of(cache, n_q_heads, opts) != 1 || cache->n_kv_heads > kBlocksMfma) return 0;
+  const int slots = kBlocksMfma / cache->n_kv_heads * 8;
+  // (an eighth of the slots over one per sequence; what the device's plan keeps in registers, and sums in 32 bits)
+  if (slots <= cache->batch + cache->batch / 8 || cache->batch > tq::kListMaxBatch || (int64_t)cache->batch * seq_len >= (1ll << 31)) return 0;
+  if (!tq::mfma_can_merge((int64_t)cache->batch * n_q_heads)) return 0;
+  return listed_lengths((int64_t)cache->batch * cache->n_kv_heads, seq_len, cache->head_dim == 256) ? slots : 0;
+}
+
 // One launch of phase 1: what to attend, and what came of it.
 struct PartialRequest {
   const tq_kv_cache* cache;            // validated; for a paged pool: the view with batch = sequences
@@ -380,8 +416,11 @@ int run_partial(PartialRequest& rq) {
   const int row_tiles = r.wide ? tq::wide_row_tiles(cache->head_dim, rows_of(cache, n_q_heads, opts)) : 1;
   const int mfma_share = use_mfma ? mfma_share_of(cache, n_q_heads, opts) : 1;
   const int rows_per_batch = cache->n_kv_heads * (use_mfma ? mfma_share : row_tiles);
-  const Ranked rank = seq_lens && rq.out != nullptr ? ranked_rows(cache, n_q_heads, seq_len, rq.attn_scale, opts)
-                                                    : Ranked{0, -1};
+  int merge_slot = -1;
+  int slots = seq_lens && rq.out != nullptr ? listed_slots(cache, n_q_heads, seq_len, rq.attn_scale, opts) : 0;
+  if (slots > 0 && (merge_slot = tq::mfma_merge_slot_of(rq.workspace)) < 0) slots = 0;     // (no arrival counters left: the other ways)
+  const Ranked rank = seq_lens && rq.out != nullptr && slots == 0 ? ranked_rows(cache, n_q_heads, seq_len, rq.attn_scale, opts)
+                                                                  : Ranked{0, -1};
   const bool ranked = rank.waves > 0;
   const int asked = ranked ? 1 : opts ? opts->n_splits : 0;
   Plan plan = plan_splits(cache->batch, rows_per_batch, attended, asked, target, use_mfma ? 8 : 1);
@@ -390,7 +429,6 @@ int run_partial(PartialRequest& rq) {
                        std::min(plan.n_splits, tq::wide_max_chunks(cache->head_dim, (attended + tq::kTile - 1) / tq::kTile)), target, 1);
   // (the chunks of one token fewer may be shorter, and then up to twice as many as the route counted)
   rq.merged = ranked || (rq.out != nullptr && (rq.step ? r.merge_step : r.merge) && !seq_lens && plan.n_splits <= tq::kMergeMaxChunks);
-  int merge_slot = -1;
   if (rq.merged) {
     const int fine = ranked || asked > 0 || !r.small_tile ? 1 : fine_splits(cache->batch, rows_per_batch, attended, target);
     // several chunks: the arrival counters of this workspace (none left: the merge kernel does it); rows that are
@@ -419,7 +457,15 @@ int run_partial(PartialRequest& rq) {
     p.max_blocks = rq.paged->max_blocks;
     p.page_shift = rq.paged->page_shift;
   }
-  if (seq_lens && !(opts && opts->n_splits > 0) && !ranked) {
+  if (slots > 0) {
+    p.listed = 1;
+    p.var_chunks = slots;
+    // a sequence spans at most 32 blocks, whose partials one wave merges a row of (with 64 and more it is the merge kernel that is shorter)
+    p.var_min_chunk = (seq_len + 31 * 8 * tq::kTile - 1) / (31 * 8 * tq::kTile) * tq::kTile;
+    p.n_splits = tq::kMaxSplits;
+    p.waves_per_row = 8;
+    rq.merged = true;
+  } else if (seq_lens && !(opts && opts->n_splits > 0) && !ranked) {
     // per-sequence lengths, no chunk count asked for: the kernels plan the chunks themselves from the lengths,
     // `target` chunks over all sequences of a KV head (a requested n_splits keeps the fixed chunking)
     // per KV head: r rounds of target / H_kv chunks, r the smallest count that leaves at least half of them
@@ -449,7 +495,7 @@ int run_partial(PartialRequest& rq) {
     p.ranked = 1;
     p.waves_per_row = rank.waves;
     p.rank_spread = rank.spread;
-  } else if (rq.merged && use_mfma && plan.n_splits == 1 && !rq.paged) {
+  } else if (rq.merged && use_mfma && plan.n_splits == 1 && !rq.paged && slots == 0) {
     // more single-chunk rows than the chip holds blocks: pack 2, 4 or 8 of them into a block
     p.waves_per_row = waves_per_packed_row((int64_t)cache->batch * rows_per_batch, target);
   }
@@ -566,6 +612,10 @@ int32_t tq_internal_decode_kernel(const tq_kv_cache* cache, int32_t n_q_heads, i
                                   const tq_decode_opts* opts, int32_t call) {
   const Route r = route_of(cache, n_q_heads, seq_len, attn_scale, opts, call == 0 ? Call::kDecode : call == 1 ? Call::kStep : Call::kLengths);
   return !r.ok ? 0 : r.wide ? 4 : !r.use_mfma ? 1 : r.small_tile ? 2 : 3;
+}
+
+int32_t tq_internal_listed_slots(const tq_kv_cache* cache, int32_t n_q_heads, int32_t max_seq_len, float attn_scale, const tq_decode_opts* opts) {
+  return listed_slots(cache, n_q_heads, max_seq_len, attn_scale, opts);
 }
 
 const char* tq_status_string(int status) {

@@ -290,7 +290,14 @@ __device__ __forceinline__ void wait_loads() {               // until at most N 
 //
 // PAGED = a pool of pages (with PLAIN: never).  An instance of its own keeps the page look-ups out of the others'
 // scalar registers, of which the general instance has none to spare.
-enum Mode { kPlain, kPlainStep, kGeneral, kPaged };   // kPlainStep: see LEAN
+//
+// LISTED: sequences with lengths of their own, one query token, no window (DecodeParams::listed), in a contiguous cache or in pages.
+// With a wave to a slot a short sequence has one or two waves where it had eight, and as many references of the exponentials, each of
+// which makes the weight of its largest score exact in fp16.  So the weights of sequences of fewer than kTwoBelow slots go in two parts
+// (TWO, d = 128; a loop of its own, the other waves' is as it was), and at d = 256 all of them do (SPLIT).  Error against 64 bits, 64 sequences
+// of 128 .. 4096 tokens: before 2.33e-4, one operand 2.60e-4, this 2.19e-4, two for all 2.08e-4 (but 0.2 us per tile: the 24
+// paged sequences 38.5 -> 42.4 us per step); 2048 .. 4096 2.56e-4 / - / 2.56e-4; d = 256 2.87e-4 / 2.89e-4 / 2.07e-4 at 2 - 4 % of the time.
+enum Mode { kPlain, kPlainStep, kGeneral, kPaged, kListed, kListedPaged };   // kPlainStep: see LEAN
 // LEAN: the 16-row tile's instances for plain launches and for blocks that share a KV head take no new token and come to
 // the masked last supertile at the end.  Two stretches of code that few waves run, between the prologue and the loop, are
 // two cold jumps for the instruction cache on every launch, and these launches are short: 128 heads over 8, 8K tokens,
@@ -302,10 +309,11 @@ template <int GP, bool NT, Mode MODE, int GS>
 constexpr bool lean_tile() { return GP == 16 && GS == 0 && (MODE == kPlain || !NT); }
 template <int D, int GP, int NW, bool NT, Mode MODE, int GS = 0>
 __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_kernel(DecodeParams p) {
-  constexpr bool PLAIN = MODE == kPlain || MODE == kPlainStep, paged = MODE == kPaged;
+  constexpr bool PLAIN = MODE == kPlain || MODE == kPlainStep, LISTED = MODE == kListed || MODE == kListedPaged;
+  constexpr bool paged = MODE == kPaged || MODE == kListedPaged;
   using C = Cfg<D, GP, NW, GS>;
   static_assert(GS == 0 || D == 256 || ((C::PERM || C::WIDE) && !PLAIN), "larger groups at d = 128: the gathered layouts");
-  constexpr bool SPLIT = GS > 0 && D == 256;
+  constexpr bool SPLIT = D == 256 && (GS > 0 || LISTED), MAY_TWO = D == 128 && LISTED;
   constexpr bool LEAN = lean_tile<GP, NT, MODE, GS>();
   constexpr int NGM = C::NGM;
   constexpr int SZB = (D / kGroup * 2) >> GS;     // bytes of one metadata array per token
@@ -331,13 +339,14 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   // slot of the chunk list, and blockIdx.x counts groups of slots.  A wave past the end of its list has no tokens
   // and only keeps the barriers company.
   int W = PLAIN ? NW : p.waves_per_row;           // NW: the whole block on one unit
+  int tokens_chunk = 0;                           // (LISTED: tokens of the block's part of the sequence)
   bool row_valid = true;
   // Rows of their own lengths, the longest first (`ranked`), a block of n_waves waves each: the launch holds about two
   // rounds of blocks, and what evens out the mix is the machine itself: a compute unit that is done with a row takes
   // the next longest one.  Where the lengths are too even for that to pay (the second round costs a row's fixed time
   // once more), a block takes two rows that follow each other, half its waves each, in one round, and the other half
   // of the blocks ends at once.  blockIdx.z: the place in the order of lengths (of a row, or of a pair).
-  const bool ranked = !PLAIN && p.ranked;
+  const bool ranked = !PLAIN && !LISTED && p.ranked;
   const int n_waves = ranked ? W : NW, n_units = ranked ? 2 : NW;
   if (ranked) {
     int rank = blockIdx.z;
@@ -358,9 +367,44 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
     // ordered 39.7; 512 of 64 .. 1024, 64 heads over 8, 76.8 / 66.0; 512 of 64 .. 4096, 8 heads over 1, 41.1 / 33.1)
     if (!(__builtin_expect(p.batch <= 256, 1) ? place(RankedRows<4>(p)) : place(RankedRows<kRankMaxBatch / 64>(p)))) return;
   }
+  int planned_len = -1;                           // (known from the plan: the lengths need not be fetched again)
+  // (LISTED) the waves of this block that hold the same sequence as this one: they share the block's part of it like the waves of a
+  // block share a chunk; that sequence's partials (one per block that holds any of it), and which of them this block's is
+  int first_mate = 0, n_parts = 1, part_at = 0;
+  bool two = false;
+  if constexpr (LISTED) {
+    kvv = blockIdx.x;
+    VarPlan vp;
+    vp.b = 0;
+    vp.chunk = 0;
+    vp.len = 0;
+    row_valid = var_plan<true, MAY_TWO>(p, (int)blockIdx.y * NW + wave, vp);
+    const int lg = vp.waves == NW ? 3 : 0, per = NW >> lg, slot0 = (int)blockIdx.y * per, slot = slot0 + (wave >> lg);
+    if (!row_valid && slot0 >= vp.chunks) return;  // (the whole block lies past the end of the list)
+    planned_len = __builtin_amdgcn_readfirstlane(vp.len);
+    b = __builtin_amdgcn_readfirstlane(vp.b);
+    tokens_per_split = __builtin_amdgcn_readfirstlane(vp.chunk_tokens);
+    part_stride = kMaxSplits;
+    split = __builtin_amdgcn_readfirstlane(vp.chunk);
+    if (row_valid) {
+      const int first = slot - split, end = first + __builtin_amdgcn_readfirstlane(vp.chunks);      // the sequence's slots
+      const int from = max(first, slot0), to = min(end, slot0 + per);                               // those of them in this block
+      part_at = (int)blockIdx.y - (first >> (3 - lg));
+      n_parts = ((end - 1) >> (3 - lg)) - (first >> (3 - lg)) + 1;
+      first_mate = (from - slot0) << lg;
+      W = (to - from) << lg;
+      split = from - first;
+      two = __builtin_amdgcn_readfirstlane(vp.two ? 1 : 0) != 0;
+      tokens_chunk = (to - from) * tokens_per_split;
+    } else {
+      first_mate = wave;
+      W = 1;
+    }
+    static_assert(NW == 8, "a slot is one wave or a block");
+  }
   const bool whole = W == NW;
-  const int sub = wave % W;                       // (several rows per block: the W waves of a row take its supertiles in turn)
-  if (!PLAIN && !whole && !ranked && p.var_chunks == 0) {
+  const int sub = LISTED ? wave - first_mate : wave % W;       // (several rows per block: the W waves of a row take its supertiles in turn)
+  if (!PLAIN && !LISTED && !whole && !ranked && p.var_chunks == 0) {
     const int rows_y = p.n_kv_heads * p.kv_share, total = p.batch * rows_y;
     const int row = blockIdx.y * (NW / W) + wave / W;
     row_valid = row < total;
@@ -368,10 +412,9 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
     b = __builtin_amdgcn_readfirstlane(r / rows_y);
     kvv = __builtin_amdgcn_readfirstlane(r - (r / rows_y) * rows_y);
   }
-  const int kv_share = PLAIN ? 1 : p.kv_share;
-  const int kv = PLAIN ? kvv : kvv / kv_share;    // the KV head whose rows are read
-  int planned_len = -1;                           // (known from the plan: the lengths need not be fetched again)
-  if (!PLAIN && p.var_chunks > 0) {                         // per-sequence lengths: which (sequence, chunk) is this block's
+  const int kv_share = PLAIN || LISTED ? 1 : p.kv_share;
+  const int kv = PLAIN || LISTED ? kvv : kvv / kv_share;       // the KV head whose rows are read
+  if (!PLAIN && !LISTED && p.var_chunks > 0) {    // per-sequence lengths: which (sequence, chunk) is this block's
     VarPlan vp;
     vp.b = 0;
     vp.chunk = 0;
@@ -389,7 +432,7 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   // Several query tokens per sequence (they are the sequence's last NQ tokens and causal among themselves):
   // a KV head then has NQ * GF query rows, row r = t * GF + g for query token t and head g of the group,
   // cut into kv_share parts of G rows; this block holds rows part * G .. part * G + G - 1.
-  const int NQ = PLAIN ? 1 : p.n_queries, GF = PLAIN ? G : p.gqa_full;
+  const int NQ = PLAIN || LISTED ? 1 : p.n_queries, GF = PLAIN || LISTED ? G : p.gqa_full;
   const int part = kvv - kv * kv_share;
   auto query_token = [&](int h) { return NQ > 1 ? min(part * G + h, NQ * GF - 1) / GF : 0; };
   auto query_row = [&](int h) -> int64_t {        // row of q / out / the partials that tile row h stands for
@@ -404,26 +447,26 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   // ---- addressing: wave-uniform bases (scalar registers) + per-lane 32-bit byte offsets
   // tokens this sequence attends: the common length, or its own (a chunk past its end is empty); with a
   // sliding window the row simply starts `start` tokens later
-  const bool var_lens = !PLAIN && p.seq_lens != nullptr;
+  const bool var_lens = LISTED || (!PLAIN && p.seq_lens != nullptr);
   // a decode step (p.k_new set): the step's new token is not among the tokens the chunks cover; the block of the
   // sequence's first chunk takes it in (see `takes`).  A sequence may hold nothing but its new token.
   const bool new_here = !LEAN && p.k_new != nullptr && split == 0 && row_valid;
   const int new_pos = !var_lens ? p.append_pos : p.k_new == nullptr ? -1 : max(1, min(p.seq_lens[b], p.seq_len)) - 1;
   const int seq = !row_valid || (var_lens && new_pos == 0) ? 0 : !var_lens ? p.seq_len : planned_len >= 0 ? planned_len : var_len(p, b);
-  const int start = !var_lens ? p.start : p.window > 0 ? var_start(p, b) : 0;
+  const int start = LISTED ? 0 : !var_lens ? p.start : p.window > 0 ? var_start(p, b) : 0;
   // first row of the six arrays this block reads from: the sequence's own row (contiguous cache), or the
   // pool's row 0 (paged cache: the page's rows are added supertile by supertile)
   // paged cache: token indices below count from `start` as well, but the rows are found page by page; the
   // window's first token may lie up to 31 tokens after `start` (see var_start)
-  const int lead = (paged && var_lens && p.window > 0) ? var_first(p, b) - start : 0;
+  const int lead = (paged && !LISTED && var_lens && p.window > 0) ? var_first(p, b) - start : 0;
   const int pstart = paged ? start : 0;           // added to a token index where a page is looked up
   const int64_t row0 = paged ? 0 : (int64_t)(b * p.n_kv_heads + kv) * p.row_stride + start;
   const int begin0 = split * tokens_per_split;    // first token of the chunk
   // A chunk past the end of its sequence has nothing to emit: the merge kernel works out from the same
   // lengths which chunks exist.  (With the in-kernel merge the block still has to be counted in, so it
   // goes through and publishes an empty partial.)
-  if (!PLAIN && whole && begin0 >= seq && p.merge_slot < 0 && !new_here) return;
-  const int end = max(begin0, min(seq, begin0 + tokens_per_split));
+  if (!PLAIN && !LISTED && whole && begin0 >= seq && p.merge_slot < 0 && !new_here) return;
+  const int end = max(begin0, min(seq, begin0 + (LISTED ? tokens_chunk : tokens_per_split)));
   // Several query tokens under a sliding window: the rows start at different tokens (row t one token after
   // row t - 1); the supertile that holds those starts takes the masked path too (wave 0, after its other work)
   // and the fast path starts behind it.  The same goes for a paged cache under a window, whose first supertile
@@ -584,7 +627,7 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   const bool tail_last = n_tail > 0 && count_of(n_full + 1) != count_of(n_full);
   // A short chunk has no supertile for every wave: its first ones are its first waves', one each, and the others only keep
   // the barriers company (and take their rows of the merges).
-  const bool busy = !PLAIN || n_mine > 0 || tail_last;
+  const bool busy = (!PLAIN && !LISTED) || n_mine > 0 || tail_last;
   const int n_busy = PLAIN ? min(NW, n_full + n_tail) : NW;
   // ---- prologue: the query rows of this KV head's group come in by direct load as well (so that every
   //      vector-memory operation of the kernel is one of the counted loads), then the ring is filled.
@@ -807,7 +850,7 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   // column c stands for byte c / 4 of the group's word c % 4; one accumulator each.
   constexpr int NAO = C::WIDE ? 1 : NA;
   static_assert(!SPLIT || NA == 1, "one group per lane");
-  constexpr int NPA = SPLIT ? 2 : NA;             // A operands of P V: one per group of the lane, or the two parts of one
+  constexpr int NPA = SPLIT ? 2 : MAY_TWO ? 2 * NA : NA;   // A operands of P V: one per group of the lane, or the two parts of one, of each
   float4v oacc[NCS][8][NAO];
 #pragma unroll
   for (int a = 0; a < NA; ++a) zacc[a] = float4v{0, 0, 0, 0};
@@ -982,7 +1025,8 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
 #pragma unroll
         for (int a = 0; a < NAO; ++a) oacc[cs][m][a] = -oacc[cs][m][a];
   };
-  auto softmax = [&](const float (&sc)[2][4], const VRegs& r, half8v (&pa)[NPA]) {
+  auto softmax = [&](const float (&sc)[2][4], const VRegs& r, half8v (&pa)[NPA], auto two_tag) {
+    constexpr bool TWO = decltype(two_tag)::value;
     const float mx = fmaxf(fmaxf(fmaxf(sc[0][0], sc[0][1]), fmaxf(sc[0][2], sc[0][3])),
                            fmaxf(fmaxf(sc[1][0], sc[1][1]), fmaxf(sc[1][2], sc[1][3])));
     bool move = mx > m_run + slack;
@@ -1053,6 +1097,17 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
         pa[NPA - 1][2 * i] = lo[0]; pa[NPA - 1][2 * i + 1] = lo[1];
         continue;
       }
+      if constexpr (TWO) {                        // (both rounded towards zero: what the first leaves out the second takes)
+#pragma unroll
+        for (int a = 0; a < NA; ++a) {
+          const float w0 = pr[0][i] * (float)sz_half(r.vs[a >> 1][0][i], a & 1), w1 = -pr[1][i] * (float)sz_half(r.vs[a >> 1][1][i], a & 1);
+          const auto hi = __builtin_amdgcn_cvt_pkrtz(w0, w1);
+          const auto lo = __builtin_amdgcn_cvt_pkrtz(__builtin_fmaf((float)hi[0], -1.0f, w0), __builtin_fmaf((float)hi[1], -1.0f, w1));
+          pa[a][2 * i] = hi[0]; pa[a][2 * i + 1] = hi[1];
+          pa[NPA / 2 + a][2 * i] = lo[0]; pa[NPA / 2 + a][2 * i + 1] = lo[1];
+        }
+        continue;
+      }
 #pragma unroll
       for (int a = 0; a < NA; ++a) {
         pa[a][2 * i] = (_Float16)__builtin_fmaf(pr[0][i], (float)sz_half(r.vs[a >> 1][0][i], a & 1), 0.0f);
@@ -1071,10 +1126,16 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
         zb[2 * i + 1] = -sz_half(r.zb[4 + i], 0);
       }
     }
+    constexpr int NPZ = TWO ? NA : NPA;
 #pragma unroll
-    for (int a = 0; a < NPA; ++a) zacc[SPLIT ? 0 : a] = mfma16(pa[a], zb, zacc[SPLIT ? 0 : a]);
+    for (int a = 0; a < NPZ; ++a) zacc[SPLIT ? 0 : a] = mfma16(pa[a], zb, zacc[SPLIT ? 0 : a]);
 #pragma unroll
-    for (int a = 0; a < NPA; ++a) zacc[SPLIT ? 0 : a] = mfma16(pa[a], pos15_odd, zacc[SPLIT ? 0 : a]);
+    for (int a = 0; a < NPZ; ++a) zacc[SPLIT ? 0 : a] = mfma16(pa[a], pos15_odd, zacc[SPLIT ? 0 : a]);
+    if constexpr (TWO) {
+      const half8v zb15 = zb + pos15_odd;         // (one operand is enough for the rest, 2^-11 of the whole)
+#pragma unroll
+      for (int a = 0; a < NA; ++a) zacc[a] = mfma16(pa[NPA / 2 + a], zb15, zacc[a]);
+    }
   };
 
   // -- V codes: each lane holds the same packed word (8 dims) of 8 tokens and needs, per dim, the 8 tokens in
@@ -1090,7 +1151,8 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   //    (mixed - even) / 16 carries the same -15 sum_t1 w that the zero-point sum cancels.
   //    WIDE: the 16 columns of a matrix instruction are the 4 words x 4 bytes of ONE group (column c = byte c / 4
   //    of word c % 4), so the lane holds that word of every group and picks its byte with a selector of its own.
-  auto pv = [&](const VRegs& r, const half8v (&pa)[NPA]) {
+  auto pv = [&](const VRegs& r, const half8v (&pa)[NPA], auto two_tag) {
+    constexpr bool TWO = decltype(two_tag)::value;
     if constexpr (C::WIDE) {
 #pragma unroll
       for (int g = 0; g < NG; ++g) {
@@ -1122,6 +1184,13 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
           oacc[cs][2 * j][a] = mfma16(pa[a], v_even, oacc[cs][2 * j][a]);
           oacc[cs][2 * j + 1][a] = mfma16(pa[a], v_mixed, oacc[cs][2 * j + 1][a]);
         }
+        if constexpr (TWO) {
+#pragma unroll
+          for (int a = 0; a < NA; ++a) {
+            oacc[cs][2 * j][a] = mfma16(pa[NPA / 2 + a], v_even, oacc[cs][2 * j][a]);
+            oacc[cs][2 * j + 1][a] = mfma16(pa[NPA / 2 + a], v_mixed, oacc[cs][2 * j + 1][a]);
+          }
+        }
         if constexpr (SPLIT) {
           oacc[cs][2 * j][0] = mfma16(pa[NPA - 1], v_even, oacc[cs][2 * j][0]);
           oacc[cs][2 * j + 1][0] = mfma16(pa[NPA - 1], v_mixed, oacc[cs][2 * j + 1][0]);
@@ -1136,7 +1205,7 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   KRegs kr;
   VRegs vr;
   static_assert(C::PFK && NS == 2, "the waits below count one or two stages");
-  auto masked = [&](int sidx) {                   // supertile sidx, whose stage sits in slot 0, by the masked path
+  auto masked = [&](int sidx, auto two_tag) {     // supertile sidx, whose stage sits in slot 0, by the masked path
     load_k(0, kr);
     load_v(0, vr);
     if constexpr (GS == 2 && D == 128) {
@@ -1155,70 +1224,78 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
     float sc[2][4];
     scores(kr, sidx, std::true_type{}, sc);
     half8v pa[NPA];
-    softmax(sc, vr, pa);
-    pv(vr, pa);
+    softmax(sc, vr, pa, two_tag);
+    pv(vr, pa, two_tag);
   };
-  int slot = 0;
-  if (tail0) {
-    if (n_mine > 0) wait_loads<LPS>();            // (loads land in order: the tail is in, the first full supertile may be out)
-    else wait_loads<0>();
-    masked(n_full);
-    if (n_mine > 1) {
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // slot 0 has been read
-      issue(0, sidx_of(1));
-    }
-    slot = 1;
-  }
-  if (n_mine > 0) {
-    if ((tail0 || !kSecondAfterFirstLanded) && n_mine > 1) wait_loads<LPS>();   // (the first full supertile is in)
-    else wait_loads<0>();
-    load_k(slot, kr);
-    if (!tail0 && kSecondAfterFirstLanded && n_mine > 1) issue(1, sidx_of(1));
-  }
-  for (int i = 0; i < n_mine; ++i) {
-    const int next = (slot + 1 == NS) ? 0 : slot + 1;
-    if constexpr (SPLIT) {
-      if (2 * i >= n_mine && sgn == sgn0) negate_sums();
-    }
-    load_v(slot, vr);
-    // The slot's bytes all sit in registers from here on; its refill with supertile i + NS is issued after the
-    // softmax all the same.  (Measured at 128K / at the d = 256 instance: issued here, +0.4 / +0.6 us; issued after
-    // the P V phase, +0.4 / +0.3 us; a ring of three stages, +1.0 us: the memory system is at its limit, and
-    // requests queued earlier than needed only delay the ones a wave is waiting for.  Issued here AND waited for
-    // stage by stage, so that two stages are in flight: the kernel alone unchanged, the decode call 1 us slower.)
-    auto refill = [&] {
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // every LDS read of this slot has returned
-      if (i + NS < n_mine) {
-        issue_tok(ring_lds + slot * C::STAGE, nx_tok, paged ? page_of(nx_tok) : 0, koff, lane16, szoff);
-        // next supertile of the pattern: of every PERIOD the older wave holds k = 0, 2, .., PERIOD-2 and PERIOD-1,
-        // the younger k = 1, 3, .., PERIOD-3
-        const int step = young ? (nx_j < YNG - 1 ? 2 : 4) : (nx_j < PERIOD / 2 - 1 ? 2 : 1);
-        nx_j = (nx_j == (young ? YNG - 1 : OLD - 1)) ? 0 : nx_j + 1;
-        nx_tok += whole ? step * (4 * 32) : W * 32;
+  auto supertiles = [&](auto two_tag) {
+    int slot = 0;
+    if (tail0) {
+      if (n_mine > 0) wait_loads<LPS>();            // (loads land in order: the tail is in, the first full supertile may be out)
+      else wait_loads<0>();
+      masked(n_full, two_tag);
+      if (n_mine > 1) {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // slot 0 has been read
+        issue(0, sidx_of(1));
       }
-    };
-    float sc[2][4];
-    // (the wave asks for issue priority while it unpacks K, feeds the matrix cores and scales the scores: the two
-    //  waves of a SIMD then take turns phase by phase rather than instruction by instruction, 0 - 1 % faster at
-    //  128K from box to box, 0.4 % at the d = 256 instance)
-    __builtin_amdgcn_s_setprio(1);
-    scores(kr, 0, std::false_type{}, sc);
-    __builtin_amdgcn_s_setprio(0);
-    // The only stage out is the next supertile's.  Past the last supertile there is nothing to wait for and the
-    // fetch reads unused bytes; skipping it there takes a branch in the loop, which the d = 128 instances pay for in
-    // registers and schedule (16-row tile 33.3 -> 35.4 us, 8-row 28.7 -> 28.95) and the d = 256 instance gains by.
-    if (D == 128 || i + 1 < n_mine) {
-      wait_loads<0>();
-      load_k(next, kr);
+      slot = 1;
     }
-    half8v pa[NPA];
-    softmax(sc, vr, pa);
-    refill();
-    pv(vr, pa);
-    slot = next;
+    if (n_mine > 0) {
+      if ((tail0 || !kSecondAfterFirstLanded) && n_mine > 1) wait_loads<LPS>();   // (the first full supertile is in)
+      else wait_loads<0>();
+      load_k(slot, kr);
+      if (!tail0 && kSecondAfterFirstLanded && n_mine > 1) issue(1, sidx_of(1));
+    }
+    for (int i = 0; i < n_mine; ++i) {
+      const int next = (slot + 1 == NS) ? 0 : slot + 1;
+      if constexpr (SPLIT) {
+        if (2 * i >= n_mine && sgn == sgn0) negate_sums();
+      }
+      load_v(slot, vr);
+      // The slot's bytes all sit in registers from here on; its refill with supertile i + NS is issued after the
+      // softmax all the same.  (Measured at 128K / at the d = 256 instance: issued here, +0.4 / +0.6 us; issued after
+      // the P V phase, +0.4 / +0.3 us; a ring of three stages, +1.0 us: the memory system is at its limit, and
+      // requests queued earlier than needed only delay the ones a wave is waiting for.  Issued here AND waited for
+      // stage by stage, so that two stages are in flight: the kernel alone unchanged, the decode call 1 us slower.)
+      auto refill = [&] {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // every LDS read of this slot has returned
+        if (i + NS < n_mine) {
+          issue_tok(ring_lds + slot * C::STAGE, nx_tok, paged ? page_of(nx_tok) : 0, koff, lane16, szoff);
+          // next supertile of the pattern: of every PERIOD the older wave holds k = 0, 2, .., PERIOD-2 and PERIOD-1,
+          // the younger k = 1, 3, .., PERIOD-3
+          const int step = young ? (nx_j < YNG - 1 ? 2 : 4) : (nx_j < PERIOD / 2 - 1 ? 2 : 1);
+          nx_j = (nx_j == (young ? YNG - 1 : OLD - 1)) ? 0 : nx_j + 1;
+          nx_tok += whole ? step * (4 * 32) : W * 32;
+        }
+      };
+      float sc[2][4];
+      // (the wave asks for issue priority while it unpacks K, feeds the matrix cores and scales the scores: the two
+      //  waves of a SIMD then take turns phase by phase rather than instruction by instruction, 0 - 1 % faster at
+      //  128K from box to box, 0.4 % at the d = 256 instance)
+      __builtin_amdgcn_s_setprio(1);
+      scores(kr, 0, std::false_type{}, sc);
+      __builtin_amdgcn_s_setprio(0);
+      // The only stage out is the next supertile's.  Past the last supertile there is nothing to wait for and the
+      // fetch reads unused bytes; skipping it there takes a branch in the loop, which the d = 128 instances pay for in
+      // registers and schedule (16-row tile 33.3 -> 35.4 us, 8-row 28.7 -> 28.95) and the d = 256 instance gains by.
+      if (D == 128 || i + 1 < n_mine) {
+        wait_loads<0>();
+        load_k(next, kr);
+      }
+      half8v pa[NPA];
+      softmax(sc, vr, pa, two_tag);
+      refill();
+      pv(vr, pa, two_tag);
+      slot = next;
+    }
+  };
+  if constexpr (MAY_TWO) {
+    if (two) supertiles(std::true_type{});
+    else supertiles(std::false_type{});
+  } else {
+    supertiles(std::false_type{});
   }
   wait_loads<0>();                                           // (nothing is out any more: the rings are quiet)
-  if constexpr (!PLAIN || LEAN) {
+  if constexpr ((!PLAIN && !LISTED) || LEAN) {
 #pragma unroll 1
     for (int u = LEAN ? 0 : 1; u < (PLAIN ? 1 : 4); ++u) {   // further masked supertiles: the last but one with several
       if (!tail_mine[u]) continue;                           // query tokens, under a window the first (or first two)
@@ -1226,7 +1303,7 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
       issue_tail(0, sidx);
       wait_loads<0>();
-      masked(sidx);
+      masked(sidx, std::false_type{});
     }
   }
 
@@ -1240,7 +1317,7 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   float* const lds_o = reinterpret_cast<float*>(smem + off_merge);     // [n_waves][GP][D]   sum_t p_t v^_t
   float* const lds_m = lds_o + n_waves * GP * D;                       // [GP][NW]
   float* const lds_l = lds_m + NW * GP;                                // [GP][NW]
-  float* const lds_new = lds_l + NW * GP + (whole ? 0 : wave / W) * C::NEWTOK;   // [D] V of this unit's new token, [GP] scores
+  float* const lds_new = lds_l + NW * GP + (LISTED ? first_mate : whole ? 0 : wave / W) * C::NEWTOK;   // [D] V of this unit's new token, [GP] scores
   if constexpr (C::ALIAS) __syncthreads();                   // everybody is done reading the rings
   const bool active = n_mine > 0 || tail_mine[0] || tail_mine[1] || tail_mine[2] || tail_mine[3];
   const float l_tot = blocks_sum(l_run);
@@ -1303,17 +1380,25 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
 #pragma unroll
     for (int u = 0; u < GP * D / 256; ++u) *reinterpret_cast<float4v*>(lds_o + wave * GP * D + (u * 64 + lane) * 4) = float4v{0, 0, 0, 0};
   }
+  // 512 bytes for every wave, where its ring was (d = 256: behind the block-merge area): chunk weights, then (LISTED) what the
+  // whole block has to know to share the rows of all its sequences: of the first of a sequence's waves, how many they are, the
+  // sequence, its partial's place and their number (0 waves: not the first)
+  static_assert(!C::ALIAS || (C::MERGE + 255) / 256 * 256 + NW * 512 <= C::RING, "behind the block-merge area");
+  auto wave_area = [&](int w) { return smem + (C::ALIAS ? (C::MERGE + 255) / 256 * 256 + w * 512 : w * (NS * C::STAGE)); };
+  typedef int int4v __attribute__((ext_vector_type(4)));
+  if constexpr (LISTED) {
+    if (lane == 0) *reinterpret_cast<int4v*>(wave_area(wave) + 256) = int4v{row_valid && sub == 0 ? W : 0, b, part_at, n_parts};
+  }
   __syncthreads();
 
   // ---- merge the waves, write one partial per query row (Sec. 3.2); where the sequence is a single
   //      chunk and the kernel is to produce the output, that partial, normalised, IS the output.
   //      A wave takes a row, a lane two neighbouring dims of it (d = 256: four): the waves' maxima and sums of that row
   //      arrive as 16-byte reads, the same for the whole wave.
-  const bool direct = p.merge_slot >= 0 && p.n_splits == 1;
   constexpr int DPL = D / 64;                     // dims of a lane
   typedef float float_dims __attribute__((ext_vector_type(DPL)));
-  // row h of the waves first .. first + count - 1
-  auto merge_row = [&](int h, int first, int count) {
+  // row h of the waves first .. first + count - 1, output row `row`; written as the output (direct), or as partial `part` of it
+  auto merge_row = [&](int h, int first, int count, int64_t row, bool direct, int part, bool with_new, const float* new_at) {
     const int j = lane * DPL;
     float_dims ow[NW];                            // (asked for first: their latency hides behind the weights' arithmetic)
 #pragma unroll
@@ -1331,13 +1416,13 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
     for (int w = 0; w < NW; ++w) mg = (w >= first && w < first + count) ? fmaxf(mg, mw[w]) : mg;
     float_dims num = 0.0f;
     float den = 0.0f;
-    if (new_here) {
-      const float sn = lds_new[D + h];
+    if (with_new) {
+      const float sn = new_at[D + h];
       mg = fmaxf(mg, sn);
       den = __builtin_amdgcn_exp2f(sn - mg);
 #pragma unroll
       for (int e2 = 0; e2 < DPL; e2 += 2) {       // (8-byte reads: a later unit's token is no better aligned)
-        const float2 vn = *reinterpret_cast<const float2*>(lds_new + j + e2);
+        const float2 vn = *reinterpret_cast<const float2*>(new_at + j + e2);
         num[e2] = vn.x * den;
         num[e2 + 1] = vn.y * den;
       }
@@ -1356,25 +1441,50 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
         half2v r;
         r[0] = (_Float16)(num[e2] / den);
         r[1] = (_Float16)(num[e2 + 1] / den);
-        *reinterpret_cast<half2v*>(p.out + query_row(h) * D + j + e2) = r;
+        *reinterpret_cast<half2v*>(p.out + row * D + j + e2) = r;
       }
     } else {
       // device-scope stores: they go through to where every compute die sees them (the L2 caches of
       // different dies are not coherent with each other), so no cache-wide write-back is needed later
-      const int64_t ph = query_row(h) * part_stride + split;
+      const int64_t ph = row * part_stride + part;
 #pragma unroll
       for (int e2 = 0; e2 < DPL; e2 += 2) st_dev2(p.part_o + ph * D + j + e2, num[e2], num[e2 + 1]);
       if (j == 0) st_dev2(p.part_ml + ph * 2, mg, den);
     }
   };
-  if (!whole) {                                   // several units per block: the W waves of one merge among themselves
-    // (a single-chunk row: the output; a slot of the chunk list: its partial)
-    if (row_valid)
-      for (int h = sub; h < G; h += W) merge_row(h, wave - sub, W);
-    return;
+  int my_row = 0, my_n = 0, n_mine_rows = 0;      // lane i: the i-th row this wave has a partial of, and how many partials it has
+  if constexpr (LISTED) {
+    // the rows of all the block's sequences, dealt to all its waves
+    const int4v entry = *reinterpret_cast<const int4v*>(wave_area(lane & (NW - 1)) + 256);
+    int u = wave;                                 // this wave's next row, counted from the sequence's first
+    for (uint64_t leads = __builtin_amdgcn_ballot_w64(lane < NW && entry[0] > 0); leads != 0; leads &= leads - 1, u -= G) {
+      const int lead = __builtin_ctzll(leads);
+      const int count = __builtin_amdgcn_readlane(entry[0], lead), bb = __builtin_amdgcn_readlane(entry[1], lead);
+      const int part = __builtin_amdgcn_readlane(entry[2], lead), parts = __builtin_amdgcn_readlane(entry[3], lead);
+      for (; u < G; u += NW) {
+        const int row = bb * p.n_q_heads + kv * G + u;
+        merge_row(u, lead, count, row, parts == 1, part, p.k_new != nullptr && part == 0, lds_l + NW * GP + lead * C::NEWTOK);
+        if (parts == 1) continue;
+        if (lane == n_mine_rows) {
+          my_row = row;
+          my_n = parts;
+        }
+        ++n_mine_rows;
+      }
+    }
+    if (n_mine_rows == 0) return;
+  } else {
+    const bool direct = p.merge_slot >= 0 && p.n_splits == 1;
+    const int first = whole ? 0 : wave - sub, count = whole ? NW : W;
+    if (!whole) {                                 // several units per block: the W waves of one merge among themselves
+      // (a single-chunk row: the output; a slot of the chunk list: its partial)
+      if (row_valid)
+        for (int h = sub; h < G; h += W) merge_row(h, first, count, query_row(h), direct, split, new_here, lds_new);
+      return;
+    }
+    for (int h = wave; h < G; h += NW) merge_row(h, 0, NW, query_row(h), direct, split, new_here, lds_new);
+    if (p.merge_slot < 0 || direct || wave >= G) return;
   }
-  for (int h = wave; h < G; h += NW) merge_row(h, 0, NW);
-  if (p.merge_slot < 0 || direct) return;
 
   // ---- chunk merge (Eq. 6), row by row, by whichever wave that has this row finishes last.  A wave publishes
   //      its row's partial (device-scope stores, waited for), then counts itself in; the one that sees all
@@ -1395,74 +1505,87 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   // costs (13.1 us), for no access that the atomics do not already cover.
   if constexpr (GP <= 8) {                        // (a 16-row tile's chunks go to the merge kernel)
     static_assert(GP <= NW && kMergeMaxChunks <= 64, "a wave per row, a lane per chunk");
-    if (wave >= G) return;
-    const int n = p.n_splits;
-    const int64_t row = query_row(wave);
-    wait_loads<0>();                              // vmcnt counts stores too: this wave's partial has landed
-    unsigned int seen = 0;
-    if (lane == 0)
-      seen = atomicInc(&g_arrivals[p.merge_slot * kCountersPerSlot + arrival_counter((int)row)], (unsigned int)(n - 1));   // wraps to 0 on the last arrival
-    if (__builtin_amdgcn_readfirstlane((int)seen) != n - 1) return;
-    asm volatile("" ::: "memory");                // (no load below may move above the count)
+    wait_loads<0>();                              // vmcnt counts stores too: this wave's partials have landed
     // Everything is asked for at once: the row's (m, l), a chunk per lane, and the chunks' outputs, sixteen bytes a lane (D / 4
     // lanes to a chunk, PARTS chunks to an instruction).  The row's partials are addressed as a buffer of n chunks: what lies
     // past the last one reads as zero, and its weight is zero.
-    constexpr int PARTS = 256 / D;
-    float* const c_w = reinterpret_cast<float*>(smem + (C::ALIAS ? NW / 2 + wave : wave) * (NS * C::STAGE));   // [kMergeMaxChunks], a ring that is quiet
-    static_assert(!C::ALIAS || (GP <= NW / 2 && C::MERGE <= NW / 2 * NS * C::STAGE), "the rings behind the block-merge area");
-    const int cpart = PARTS == 2 ? lane >> 5 : 0, j = (lane % (D / 4)) * 4;
-    float2 ml = {kNegBig, 0.0f};
-    if (lane < n) ml = ld_dev2(p.part_ml + (row * n + lane) * 2);
-    const auto rows = __builtin_amdgcn_make_buffer_rsrc(p.part_o + row * n * D, 0, n * D * 4, 0x00020000);
-    auto fetch = [&](auto count_tag, int c0, float4v* o) {   // chunks c0 + cpart * U ..
-      constexpr int U = decltype(count_tag)::value;
+    auto merge_chunks = [&](int64_t row, int n) {
+      constexpr int PARTS = 256 / D;
+      float* const c_w = reinterpret_cast<float*>(wave_area(wave));          // [kMergeMaxChunks]
+      const int cpart = PARTS == 2 ? lane >> 5 : 0, j = (lane % (D / 4)) * 4;
+      float2 ml = {kNegBig, 0.0f};
+      if (lane < n) ml = ld_dev2(p.part_ml + (row * part_stride + lane) * 2);
+      const auto rows = __builtin_amdgcn_make_buffer_rsrc(p.part_o + row * part_stride * D, 0, n * D * 4, 0x00020000);
+      auto fetch = [&](auto count_tag, int c0, float4v* o) {   // chunks c0 + cpart * U ..
+        constexpr int U = decltype(count_tag)::value;
 #pragma unroll
-      for (int u = 0; u < U; ++u)
-        o[u] = __builtin_bit_cast(float4v, __builtin_amdgcn_raw_buffer_load_b128(rows, ((c0 + cpart * U) * D + j) * 4, u * D * 4, 16));   // 16: device scope
-    };
-    float4v num = {0, 0, 0, 0};
-    auto add = [&](auto count_tag, int c0, const float4v* o) {
-      constexpr int U = decltype(count_tag)::value;
-      const float* const w = c_w + c0 + cpart * U;
+        for (int u = 0; u < U; ++u)
+          o[u] = __builtin_bit_cast(float4v, __builtin_amdgcn_raw_buffer_load_b128(rows, ((c0 + cpart * U) * D + j) * 4, u * D * 4, 16));   // 16: device scope
+      };
+      float4v num = {0, 0, 0, 0};
+      auto add = [&](auto count_tag, int c0, const float4v* o) {
+        constexpr int U = decltype(count_tag)::value;
+        const float* const w = c_w + c0 + cpart * U;
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const float e = w[u];
+        for (int u = 0; u < U; ++u) {
+          const float e = w[u];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) num[k] = fmaf(o[u][k], e, num[k]);
+          for (int k = 0; k < 4; ++k) num[k] = fmaf(o[u][k], e, num[k]);
+        }
+      };
+      float den = 0.0f;
+      auto all = [&](auto count_tag) {
+        constexpr int U = decltype(count_tag)::value;
+        float4v o[U];
+        fetch(count_tag, 0, o);
+        const float top = wave_fmax(ml.x);          // (every lane takes part)
+        const float w = lane < n ? __builtin_amdgcn_exp2f(ml.x - top) : 0.0f;
+        c_w[lane] = w;
+        den = wave_fsum(ml.y * w);
+        add(count_tag, 0, o);
+        for (int c0 = U * PARTS; c0 < n; c0 += U * PARTS) {
+          fetch(count_tag, c0, o);
+          add(count_tag, c0, o);
+        }
+      };
+      if (n <= 4 * PARTS) all(std::integral_constant<int, 4>{});
+      else if (n <= 8 * PARTS) all(std::integral_constant<int, 8>{});
+      else all(std::integral_constant<int, 16>{});
+      if constexpr (PARTS == 2) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          float a, b2;
+          swap32(num[k], a, b2);
+          num[k] = a + b2;
+        }
+      }
+      if (cpart == 0) {
+        typedef _Float16 half4v __attribute__((ext_vector_type(4)));
+        half4v r;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) r[k] = (_Float16)(num[k] / den);
+        *reinterpret_cast<half4v*>(p.out + row * D + j) = r;
       }
     };
-    float den = 0.0f;
-    auto all = [&](auto count_tag) {
-      constexpr int U = decltype(count_tag)::value;
-      float4v o[U];
-      fetch(count_tag, 0, o);
-      const float top = wave_fmax(ml.x);          // (every lane takes part)
-      const float w = lane < n ? __builtin_amdgcn_exp2f(ml.x - top) : 0.0f;
-      c_w[lane] = w;
-      den = wave_fsum(ml.y * w);
-      add(count_tag, 0, o);
-      for (int c0 = U * PARTS; c0 < n; c0 += U * PARTS) {
-        fetch(count_tag, c0, o);
-        add(count_tag, c0, o);
-      }
+    auto arrived = [&](int row, int n) {          // whether all other partials of the row have been counted in (wraps to 0 on the last)
+      return atomicInc(&g_arrivals[p.merge_slot * kCountersPerSlot + arrival_counter(row)], (unsigned int)(n - 1)) == (unsigned int)(n - 1);
     };
-    if (n <= 4 * PARTS) all(std::integral_constant<int, 4>{});
-    else if (n <= 8 * PARTS) all(std::integral_constant<int, 8>{});
-    else all(std::integral_constant<int, 16>{});
-    if constexpr (PARTS == 2) {
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        float a, b2;
-        swap32(num[k], a, b2);
-        num[k] = a + b2;
+    if constexpr (LISTED) {                       // all of the wave's rows at once
+      bool last = false;
+      if (lane < n_mine_rows) last = arrived(my_row, my_n);
+      uint64_t rows_last = __builtin_amdgcn_ballot_w64(last);
+      asm volatile("" ::: "memory");              // (no load may move above the count)
+      for (; rows_last != 0; rows_last &= rows_last - 1) {
+        const int i = __builtin_ctzll(rows_last);
+        merge_chunks(__builtin_amdgcn_readlane(my_row, i), __builtin_amdgcn_readlane(my_n, i));
       }
-    }
-    if (cpart == 0) {
-      typedef _Float16 half4v __attribute__((ext_vector_type(4)));
-      half4v r;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) r[k] = (_Float16)(num[k] / den);
-      *reinterpret_cast<half4v*>(p.out + row * D + j) = r;
+    } else {
+      const int64_t row = query_row(wave);
+      int last = 0;
+      if (lane == 0) last = arrived((int)row, p.n_splits);
+      if (__builtin_amdgcn_readfirstlane(last) == 0) return;
+      asm volatile("" ::: "memory");
+      merge_chunks(row, p.n_splits);
     }
   }
 }
@@ -1520,6 +1643,9 @@ hipError_t launch_nt(const DecodeParams& p, dim3 grid, hipStream_t s) {
 }
 template <int D, int GP, int GS>
 hipError_t launch_mode(const DecodeParams& p, dim3 grid, hipStream_t s) {
+  if constexpr (GP <= 8) {
+    if (p.listed) return p.block_table ? launch_as<D, GP, true, kListedPaged, GS>(p, grid, s) : launch_as<D, GP, true, kListed, GS>(p, grid, s);
+  }
   if (p.block_table != nullptr) return launch_nt<D, GP, kPaged, GS>(p, grid, s);
   const bool plain = p.kv_share == 1 && p.n_queries == 1 && p.waves_per_row == 8 && p.var_chunks == 0 && p.seq_lens == nullptr;
   if constexpr (GS == 0 || D == 256) {            // (no plain instances of the larger groups at d = 128)
@@ -1592,17 +1718,22 @@ hipError_t launch_partial_mfma(const DecodeParams& p_in, int batch, int head_dim
   if (p.waves_per_row != 1 && p.waves_per_row != 2 && p.waves_per_row != 4) p.waves_per_row = 8;
   if (p.ranked && (p.seq_lens == nullptr || p.merge_slot < 0 || p.n_splits != 1 || p.var_chunks > 0)) return hipErrorInvalidValue;
   if (p.ranked && p.waves_per_row == 1 && p.rank_spread >= 0) return hipErrorInvalidValue;   // (a wave is not shared by two rows)
+  if (p.listed && (p.seq_lens == nullptr || p.merge_slot < 0 || p.ranked || p.n_queries > 1 || p.window > 0 || p.kv_share != 1 ||
+                   batch > kListMaxBatch || (int64_t)batch * p.seq_len >= (1ll << 31) || p.var_chunks % 8 != 0 || p.var_chunks <= batch ||
+                   !mfma_can_merge((int64_t)batch * p.n_q_heads) || padded_gqa(head_dim, p.gqa) > 8))
+    return hipErrorInvalidValue;
   // several units per block: single-chunk rows whose output the kernel writes itself, or the slots of a chunk list
   if (p.waves_per_row != 8 && !p.ranked && p.var_chunks == 0 && (p.merge_slot < 0 || p.n_splits != 1 || p.block_table))
     return hipErrorInvalidValue;
   const int per_block = p.ranked ? 1 : 8 / p.waves_per_row;
-  const dim3 grid = p.var_chunks > 0 ? dim3((p.var_chunks + per_block - 1) / per_block, rows_y, 1)
+  const dim3 grid = p.listed ? dim3(rows_y, p.var_chunks / 8, 1)
+                    : p.var_chunks > 0 ? dim3((p.var_chunks + per_block - 1) / per_block, rows_y, 1)
                     : per_block > 1  ? dim3(1, (batch * rows_y + per_block - 1) / per_block, 1)
                                      : dim3(p.n_splits, rows_y, batch);
   int gp = padded_gqa(head_dim, p.gqa);
   // (a 16-row tile has no chunk merge of its own: `out` would stay unwritten)
   if (gp == 16 && p.merge_slot >= 0 && p.n_splits > 1) return hipErrorInvalidValue;
-  if (p.merge_slot >= 0 && p.n_splits > kMergeMaxChunks) return hipErrorInvalidValue;
+  if (p.merge_slot >= 0 && !p.listed && p.n_splits > kMergeMaxChunks) return hipErrorInvalidValue;
   if (p.k_new != nullptr && !mfma_takes_token(head_dim, p.group, rows)) return hipErrorInvalidValue;
   if (p.group != kGroup && gp == 4) gp = 8;       // (larger groups at d = 128: the 8- and 16-row layouts only)
   if (head_dim == 128 && gp == 16) return launch<128, 16>(p, grid, s);

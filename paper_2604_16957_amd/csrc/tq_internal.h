@@ -15,6 +15,7 @@ constexpr int kGroup = 32;        // elements per quantisation group (Sec. 2.1):
 constexpr int kMaxSplits = 128;   // upper bound on sequence chunks (Sec. 3.2); sizes the workspace
 constexpr int kMergeMaxChunks = 64;  // chunks of a row that the matrix-core kernel can merge in place (a lane each)
 constexpr int kTile = 32;         // chunk boundaries are multiples of this many tokens
+constexpr int kListMaxBatch = 256;   // sequences whose lengths the device's plan keeps in registers (kPlanTiles)
 constexpr int kRankMaxBatch = 512;   // sequences a launch can order by their lengths (RankedRows)
 constexpr int kMaxQueries = 8;    // query tokens per sequence in one call (the masked path covers two supertiles)
 
@@ -84,6 +85,10 @@ struct DecodeParams {
   // counts the sequences from the longest to the shortest.  rank_spread: by how many tiles the longest sequence may
   // exceed the average for the lengths to count as even (negative: they never do).
   int32_t ranked, rank_spread;
+  // Matrix-core kernel, per-sequence lengths, one query token, no window: the slots of the device-planned list (var_chunks of them
+  // to a KV head) are single waves and lie side by side in the blocks (blockIdx.y; blockIdx.x: the KV head); the waves of one sequence
+  // in a block share the block's part of it, and the blocks of a sequence merge in place (merge_slot).
+  int32_t listed;
   int32_t merge_slot;       // matrix-core kernel: >= 0 selects a set of arrival counters and makes the last
                             // block of every (b, kv head) merge the chunks and write `out`; < 0: partials only
 };
@@ -207,7 +212,9 @@ __device__ inline uint32_t quantize_word_fast(const half_t* x, const QuantFast& 
 // below), so that the list "all chunks of sequence 0, then of sequence 1, ..." has at most p.var_chunks
 // entries: the grid.  Slot s of that list -> (b, chunk); returns false past the end of the list.
 // Everything here is wave-uniform.
-struct VarPlan { int chunk_tokens, b, chunk, len; };   // len: var_len of sequence b
+// len: var_len of sequence b; chunks: how many it has (past the end of the list: the list's); waves: of a slot (LISTED)
+// two: its weights go in two parts (TWO)
+struct VarPlan { int chunk_tokens, b, chunk, len, chunks, waves; bool two; };
 __device__ inline int var_full_len(const DecodeParams& p, int b) {
   return max(1, min(p.seq_lens[b], p.seq_len) + p.len_bias);
 }
@@ -259,6 +266,7 @@ __device__ inline int var_len_of_lane(const DecodeParams& p, int tile) {
 // The planner keeps one sequence per lane: the lengths of the first 64 * kPlanTiles sequences stay in registers
 // (batches up to 256), those of larger batches are re-read where needed.
 constexpr int kPlanTiles = 4;
+static_assert(kListMaxBatch == 64 * kPlanTiles, "a listed launch's lengths sit in registers");
 struct VarLens { int len[kPlanTiles]; };
 __device__ inline void var_lens_load(const DecodeParams& p, VarLens& L) {
 #pragma unroll
@@ -286,14 +294,25 @@ __device__ inline bool var_exact_floats(const DecodeParams& p) { return p.seq_le
 // total / var_chunks (too short unless every sequence ends on a chunk boundary) and
 // total / (var_chunks - batch) (always enough: a sequence wastes less than one chunk).  Called by whole waves
 // at the start of a kernel; every wave of a launch gets the same answer.
+// LISTED (DecodeParams::listed): the host's lower bound as it is (it keeps a sequence within the blocks that the merge in place takes).
+// TWO (LISTED): a sequence of fewer than kTwoBelow such chunks has its weights in two parts, which takes an eighth more time per tile:
+// its chunks are an eighth shorter (in whole tiles).
+constexpr int kTwoBelow = 3;
+__device__ inline int short_chunk(int c) { return c - c / (8 * kTile) * kTile; }
+template <bool TWO>
+__device__ inline int listed_chunks_of(int len, int c, float rc, float rshort, bool exact_floats) {
+  const int n = var_chunks_of(len, c, rc, exact_floats);
+  return TWO && n < kTwoBelow ? var_chunks_of(len, short_chunk(c), rshort, exact_floats) : n;
+}
+template <bool LISTED, bool TWO = false>
 __device__ inline int var_chunk_tokens(const DecodeParams& p, const VarLens& L) {
   const int tiles = (p.batch + 63) >> 6;
   long long mine = 0;
 #pragma unroll
   for (int t = 0; t < kPlanTiles; ++t) mine += L.len[t];
-  for (int t = kPlanTiles; t < tiles; ++t) mine += var_len_of_lane(p, t);
-  const long long total = ((long long)wave_sum((int)(mine >> 24)) << 24) + wave_sum((int)(mine & 0xFFFFFF));
-  const int floor_c = max(p.var_min_chunk, (p.seq_len + kMaxSplits - 1) / kMaxSplits);
+  if (!LISTED) for (int t = kPlanTiles; t < tiles; ++t) mine += var_len_of_lane(p, t);     // (LISTED: at most 256 sequences, and 2^31 tokens)
+  const long long total = LISTED ? wave_sum((int)mine) : ((long long)wave_sum((int)(mine >> 24)) << 24) + wave_sum((int)(mine & 0xFFFFFF));
+  const int floor_c = LISTED ? p.var_min_chunk : max(p.var_min_chunk, (p.seq_len + kMaxSplits - 1) / kMaxSplits);
   auto round_up = [](long long c) { return (int)((c + kTile - 1) / kTile * kTile); };
   const int budget = p.var_chunks - p.batch;      // >= var_chunks / 2 by the host's choice of var_chunks
   const bool fl = var_exact_floats(p);
@@ -302,10 +321,10 @@ __device__ inline int var_chunk_tokens(const DecodeParams& p, const VarLens& L) 
     // (nearly always; estimates by the float reciprocal instead of 64-bit divisions of some hundred and fifty
     // instructions: the upper one is never too small, a tile too many costs a step of the search, and a lower one that
     // is a tile too small is ruled out by the count like any other candidate)
-    hi = round_up(max(floor_c, (int)((float)(int)total * __builtin_amdgcn_rcpf((float)budget)) + 2));
+    hi = round_up(max(floor_c, (int)((float)(int)total * (TWO ? 8.0f / 7.0f : 1.0f) * __builtin_amdgcn_rcpf((float)budget)) + 2));
     lo = round_up(max(floor_c, (int)((float)(int)total * __builtin_amdgcn_rcpf((float)p.var_chunks))));
   } else {
-    hi = round_up(max((long long)floor_c, (total + budget - 1) / budget));
+    hi = round_up(max((long long)floor_c, ((TWO ? total * 8 / 7 + 1 : total) + budget - 1) / budget));
     lo = round_up(max((long long)floor_c, (total + p.var_chunks - 1) / p.var_chunks));
   }
   while (lo < hi) {
@@ -314,8 +333,9 @@ __device__ inline int var_chunk_tokens(const DecodeParams& p, const VarLens& L) 
     int n = 0;
 #pragma unroll
     for (int t = 0; t < kPlanTiles; ++t)
-      if (t < tiles) n += var_chunks_of(L.len[t], mid, rmid, fl);
-    for (int t = kPlanTiles; t < tiles; ++t) n += var_chunks_of(var_len_of_lane(p, t), mid, rmid, fl);
+      if (t < tiles) n += LISTED ? listed_chunks_of<TWO>(L.len[t], mid, rmid, __builtin_amdgcn_rcpf((float)short_chunk(mid)), fl)
+                                 : var_chunks_of(L.len[t], mid, rmid, fl);
+    if (!LISTED) for (int t = kPlanTiles; t < tiles; ++t) n += var_chunks_of(var_len_of_lane(p, t), mid, rmid, fl);
     if (wave_sum(n) <= p.var_chunks) hi = mid;
     else lo = mid + kTile;
   }
@@ -324,26 +344,51 @@ __device__ inline int var_chunk_tokens(const DecodeParams& p, const VarLens& L) 
 // Slot of the chunk list -> (sequence, chunk of it); false past the end of the list.  The chunk counts sit one
 // sequence per lane; the tile of 64 sequences that holds the slot is found with wave-wide sums, the sequence
 // inside it with a prefix sum over the lanes.  The chunk length goes to p.plan for the merge kernel.
+template <bool LISTED = false, bool TWO = false>
 __device__ inline bool var_plan(const DecodeParams& p, int slot, VarPlan& out) {
   VarLens L;
   var_lens_load(p, L);
-  const int c = var_chunk_tokens(p, L);
+  int c = var_chunk_tokens<LISTED, TWO>(p, L);
+  if constexpr (LISTED) {
+    // A slot is one wave, so that the sequences' shares are even to a tile; but a block that holds several sequences, or parts of
+    // them, works out more rows, so whole blocks to a slot where that takes no more tiles per wave (one more: 32 heads over 32, 8
+    // sequences of 500 .. 6000 tokens 21.8 -> 22.0 us per step; 16 over 8, d = 256, 8 of 300 .. 9000 in pages 18.9 -> 21.0).
+    out.waves = 1;
+    const float rw = __builtin_amdgcn_rcpf((float)(8 * c));
+    int n = 0;
+#pragma unroll
+    for (int t = 0; t < kPlanTiles; ++t) n += t * 64 < p.batch ? var_chunks_of(L.len[t], 8 * c, rw, var_exact_floats(p)) : 0;
+    if (wave_sum(n) * 8 <= p.var_chunks) {
+      out.waves = 8;
+      c *= 8;
+      slot = blockIdx.y;
+    }
+  }
   out.chunk_tokens = c;
-  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *p.plan = c;
+  if (!LISTED && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *p.plan = c;
   const int tiles = (p.batch + 63) >> 6;
   int first = 0;
   bool found = false;
   const float rc = __builtin_amdgcn_rcpf((float)c);
   const bool fl = var_exact_floats(p);
+  const float rshort = __builtin_amdgcn_rcpf((float)short_chunk(c));
+  const bool single = LISTED && out.waves == 1;   // (a slot is a wave)
+  out.two = false;
   auto visit = [&](int t, int len) {              // tile t: does it hold the slot?  (wave-uniform)
-    const int n = var_chunks_of(len, c, rc, fl);  // this lane's sequence: its chunks
+    // this lane's sequence: its chunks
+    const int n = TWO && single ? listed_chunks_of<TWO>(len, c, rc, rshort, fl) : var_chunks_of(len, c, rc, fl);
     const int in_tile = wave_sum(n);
     if (slot < first + in_tile) {
       const int incl = wave_scan(n);
       const int i = __ffsll((unsigned long long)__ballot(slot < first + incl)) - 1;   // first lane past the slot
       out.b = t * 64 + i;
       out.len = __builtin_amdgcn_readlane(len, i);
-      out.chunk = slot - first - (__builtin_amdgcn_readlane(incl, i) - __builtin_amdgcn_readlane(n, i));
+      if (TWO && single && var_chunks_of(out.len, c, rc, fl) < kTwoBelow) {
+        out.two = true;
+        out.chunk_tokens = short_chunk(c);
+      }
+      out.chunks = __builtin_amdgcn_readlane(n, i);
+      out.chunk = slot - first - (__builtin_amdgcn_readlane(incl, i) - out.chunks);
       found = true;
     }
     first += in_tile;
@@ -351,7 +396,8 @@ __device__ inline bool var_plan(const DecodeParams& p, int slot, VarPlan& out) {
 #pragma unroll
   for (int t = 0; t < kPlanTiles; ++t)
     if (t < tiles && !found) visit(t, L.len[t]);
-  for (int t = kPlanTiles; t < tiles && !found; ++t) visit(t, var_len_of_lane(p, t));
+  if (!LISTED) for (int t = kPlanTiles; t < tiles && !found; ++t) visit(t, var_len_of_lane(p, t));
+  if (!found) out.chunks = first;
   return found;
 }
 // The sequences in the order of their lengths in 32-token tiles, the longest first (ties by index), and whether those
@@ -459,3 +505,8 @@ bool reduce_is_grouped(int head_dim, int64_t out_rows, int n_q_heads, int gqa);
 // public ABI: results agree on either side of a rule, so only this shows a test which side it is on.
 extern "C" int32_t tq_internal_decode_kernel(const tq_kv_cache* cache, int32_t n_q_heads, int32_t seq_len, float attn_scale,
                                              const tq_decode_opts* opts, int32_t call);
+
+// Slots (waves) to a KV head where a call with per-sequence lengths (at most max_seq_len) deals its waves to the sequences
+// (DecodeParams::listed), 0 where it does not; not part of the public ABI.
+extern "C" int32_t tq_internal_listed_slots(const tq_kv_cache* cache, int32_t n_q_heads, int32_t max_seq_len, float attn_scale,
+                                            const tq_decode_opts* opts);

@@ -114,3 +114,14 @@ def kernel_of(batch, n_q_heads, n_kv_heads, head_dim, seq_len, call="decode", sc
     ask.restype = ctypes.c_int32
     ask.argtypes = [ctypes.c_void_p, ctypes.c_int32, ctypes.c_int32, ctypes.c_float, ctypes.c_void_p, ctypes.c_int32]
     return KERNELS[ask(ctypes.byref(struct), n_q_heads, seq_len, scale, ctypes.byref(opts), ("decode", "step", "lengths").index(call))]
+
+
+def listed_slots(batch, n_q_heads, n_kv_heads, head_dim, max_seq_len, group=32, n_queries=1, window=0, n_splits=0, variant=0):
+    """Waves to a KV head that a call with per-sequence lengths deals to its sequences, 0 where it goes another way; asked on the host."""
+    fake = 0x10000
+    struct = binding.TqKvCacheStruct(fake, fake, fake, fake, fake, fake, batch, n_kv_heads, head_dim, group, max_seq_len + max_seq_len % 2, 0)
+    opts = binding.TqDecodeOptsStruct(n_splits, variant, window, n_queries)
+    ask = binding.raw().tq_internal_listed_slots
+    ask.restype = ctypes.c_int32
+    ask.argtypes = [ctypes.c_void_p, ctypes.c_int32, ctypes.c_int32, ctypes.c_float, ctypes.c_void_p]
+    return ask(ctypes.byref(struct), n_q_heads, max_seq_len, 1.0, ctypes.byref(opts))

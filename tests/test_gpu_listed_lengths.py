@@ -1,0 +1,46 @@
+"""Sequences with lengths of their own whose waves are dealt out by the device (rules: tests/test_routes.py): one sequence over many
+blocks, several to a block, whole blocks and single waves to a slot, sequences of one token, the fewest slots a call may have."""
+import pytest
+import torch
+
+import paper_2604_16957_amd as tq
+import tq_workloads as wl
+from gpu_common import errors, gpu_cache_from, listed_slots, make, oracle_cache_from
+from test_gpu_uneven_lengths import _reference, _uneven, check
+
+pytestmark = pytest.mark.gpu
+
+
+# one sequence; lengths around a tile, a sequence of nothing but its new token among them; two that take whole blocks
+@pytest.mark.parametrize("Hq,Hkv,d,group", [(16, 2, 128, 32), (8, 8, 128, 32), (64, 8, 128, 128), (32, 16, 256, 32), (8, 4, 256, 64)])
+@pytest.mark.parametrize("lens", [[4097], [1, 2, 31, 32, 33, 34, 64, 65, 1, 96], [2049, 2049], [700, 3, 1500, 40, 1]])
+def test_few_sequences(Hq, Hkv, d, group, lens):
+    S = max(lens) + 1
+    assert listed_slots(len(lens), Hq, Hkv, d, S, group) == 2048 // Hkv
+    check(len(lens), Hq, Hkv, d, lens, S, group=group)
+    check(len(lens), Hq, Hkv, d, lens, S, group=group, page=64)
+
+
+# many sequences to a block, waves of their own; 56 on 32 KV heads: eight slots over one for each
+@pytest.mark.parametrize("B,Hq,Hkv,d,longest,group,page", [
+    (24, 64, 8, 128, 2500, 32, 256), (63, 16, 8, 128, 900, 64, 0), (80, 32, 8, 128, 1100, 32, 0), (56, 32, 32, 128, 2049, 32, 0),
+    (40, 32, 16, 256, 600, 32, 0), (40, 16, 16, 256, 600, 128, 32), (256, 8, 1, 128, 1000, 32, 0)])
+def test_many_sequences(B, Hq, Hkv, d, longest, group, page):
+    assert listed_slots(B, Hq, Hkv, d, longest, group) == 2048 // Hkv
+    check(B, Hq, Hkv, d, _uneven(B, longest, 5 + B), longest, group=group, page=page)
+
+
+# Sequences of one or two waves' shares have fewer references of the exponentials than when eight waves shared each, and with one fp16
+# operand per weight 12 % more error than then (2.60e-4 for 2.33e-4 on 64 sequences of 128 .. 4096 tokens); their weights go in two parts.  The output's own rounding
+# is 2.07e-4, the long sequences' single operand at most 2.56e-4, and the mix of both below 2.33e-4: a bound between that and one operand for all.
+def test_short_sequences_weights_in_two_parts():
+    B, Hq, Hkv, S = 40, 32, 4, 2000
+    w = wl.custom(batch=B, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=128, seq_len=S, seed=77, outlier_channels=4)
+    q, k, v = make(w)
+    lens = [int(round(60 * (S / 60) ** (i / (B - 1)))) for i in range(B)]
+    ref = _reference(q, oracle_cache_from(k, v), lens, w.attn_scale, 0)
+    cache = gpu_cache_from(k, v)
+    out = tq.tq_sdpa_int4_decode_varlen(cache, q.cuda(), torch.tensor(lens, dtype=torch.int32).cuda(), S, w.attn_scale)
+    torch.cuda.synchronize()
+    assert listed_slots(B, Hq, Hkv, 128, S) == 512
+    assert errors(out, ref)[1] <= 2.35e-4

@@ -37,6 +37,16 @@ int main() {
   r.n_splits = 1; r.tokens_per_split = 64; r.seq_lens = reinterpret_cast<const int32_t*>(256);
   r.ranked = 1; r.waves_per_row = 1; r.rank_spread = 0;
   ask("one_wave_two_rows", r, 0);
+  DecodeParams l = plain;                   // waves dealt to the sequences: only with counters, a slot for each, one query token, no window
+  l.seq_lens = reinterpret_cast<const int32_t*>(256); l.listed = 1; l.var_chunks = 2048; l.var_min_chunk = 32;
+  ask("listed_no_merge", l, -1);
+  DecodeParams w = l;
+  w.window = 32;
+  ask("listed_window", w, 0);
+  w = l; w.batch = 257;
+  ask("listed_many", w, 0);
+  w = l; w.gqa = 16; w.n_q_heads = 16;
+  ask("listed_tile16", w, 0);
   return 0;
 }
 """
@@ -61,6 +71,7 @@ def test_a_request_that_is_covered_gets_past_the_checks(answers):
         assert answers["plain"] not in (0, INVALID_VALUE)
 
 
-@pytest.mark.parametrize("request_", ["tile16_merge", "merge_of_65_chunks", "shared_tile_new_token", "one_wave_two_rows"])
+@pytest.mark.parametrize("request_", ["tile16_merge", "merge_of_65_chunks", "shared_tile_new_token", "one_wave_two_rows",
+                                      "listed_no_merge", "listed_window", "listed_many", "listed_tile16"])
 def test_a_request_no_instance_implements_is_refused(answers, request_):
     assert answers[request_] == INVALID_VALUE

@@ -3,7 +3,7 @@ import math
 
 import pytest
 
-from gpu_common import kernel_of
+from gpu_common import kernel_of, listed_slots
 
 WIDE, SIXTEEN, EIGHT, GENERIC, REFUSED = "wide rows", "16 rows", "8 rows", "generic", "refused"
 
@@ -67,3 +67,22 @@ def test_always_at_512():
         assert kernel_of(1, 32, 1, 512, 300, call, group=64) == GENERIC
         assert kernel_of(1, 32, 1, 512, 300, call, scale=math.inf) == GENERIC
         assert kernel_of(1, 32, 1, 512, 300, call, variant=2, scale=0.0) == REFUSED
+
+
+# (sequences, heads, KV heads, head dim, the longest bound that does not deal its waves to the sequences; 0: every bound does)
+@pytest.mark.parametrize("B,heads,kv,d,last", [
+    (63, 64, 8, 128, 0), (64, 64, 8, 128, 3072), (65, 64, 8, 128, 1024), (88, 64, 8, 128, 1024), (129, 64, 8, 128, 2048), (31, 32, 16, 256, 0),
+    (32, 32, 16, 256, 2048), (33, 32, 16, 256, 0), (45, 32, 16, 256, 2048), (56, 32, 32, 128, 2048)])
+def test_lengths_that_are_dealt_to_waves(B, heads, kv, d, last):
+    slots = 2048 // kv
+    assert listed_slots(B, heads, kv, d, last + 1) == slots and (last == 0 or listed_slots(B, heads, kv, d, last) == 0)
+    for more in (dict(window=100), dict(n_splits=2), dict(variant=1), dict(n_queries=2)):
+        assert listed_slots(B, heads, kv, d, 5000, **more) == 0
+
+
+def test_lengths_that_are_not_dealt_to_waves():
+    assert listed_slots(57, 32, 32, 128, 5000) == 0                       # too few slots for that many sequences
+    assert listed_slots(89, 64, 8, 128, 50000) == 0 and listed_slots(128, 64, 8, 128, 50000) == 0
+    assert listed_slots(256, 8, 1, 128, 5000) == 2048 and listed_slots(257, 8, 1, 128, 5000) == 0
+    assert listed_slots(4, 128, 8, 128, 60000) == 0 and listed_slots(4, 32, 4, 256, 5000) == 0   # 16-row tile, rows in several blocks
+    assert listed_slots(4, 32, 1, 512, 5000) == 0

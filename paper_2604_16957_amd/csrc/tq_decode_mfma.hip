@@ -1393,13 +1393,14 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
 
   // ---- merge the waves, write one partial per query row (Sec. 3.2); where the sequence is a single
   //      chunk and the kernel is to produce the output, that partial, normalised, IS the output.
-  //      A wave takes a row, a lane two neighbouring dims of it (d = 256: four): the waves' maxima and sums of that row
-  //      arrive as 16-byte reads, the same for the whole wave.
-  constexpr int DPL = D / 64;                     // dims of a lane
-  typedef float float_dims __attribute__((ext_vector_type(DPL)));
-  // row h of the waves first .. first + count - 1, output row `row`; written as the output (direct), or as partial `part` of it
-  auto merge_row = [&](int h, int first, int count, int64_t row, bool direct, int part, bool with_new, const float* new_at) {
-    const int j = lane * DPL;
+  //      A wave takes a row, a lane two neighbouring dims of it (d = 256: four, or half a row and two): the waves' maxima and
+  //      sums of that row arrive as 16-byte reads, the same for the whole wave.
+  // row h of the waves first .. first + count - 1, its dims from j0 on, DPL of them a lane; output row `row`; written as the output
+  // (direct), or as partial `part` of it
+  auto merge_row = [&](auto dpl_tag, int h, int j0, int first, int count, int64_t row, bool direct, int part, bool with_new, const float* new_at) {
+    constexpr int DPL = decltype(dpl_tag)::value;
+    typedef float float_dims __attribute__((ext_vector_type(DPL)));
+    const int j = j0 + lane * DPL;
     float_dims ow[NW];                            // (asked for first: their latency hides behind the weights' arithmetic)
 #pragma unroll
     for (int w = 0; w < NW; ++w) ow[w] = *reinterpret_cast<const float_dims*>(lds_o + (min(w, n_waves - 1) * GP + h) * D + j);
@@ -1463,7 +1464,7 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
       const int part = __builtin_amdgcn_readlane(entry[2], lead), parts = __builtin_amdgcn_readlane(entry[3], lead);
       for (; u < G; u += NW) {
         const int row = bb * p.n_q_heads + kv * G + u;
-        merge_row(u, lead, count, row, parts == 1, part, p.k_new != nullptr && part == 0, lds_l + NW * GP + lead * C::NEWTOK);
+        merge_row(std::integral_constant<int, D / 64>{}, u, 0, lead, count, row, parts == 1, part, p.k_new != nullptr && part == 0, lds_l + NW * GP + lead * C::NEWTOK);
         if (parts == 1) continue;
         if (lane == n_mine_rows) {
           my_row = row;
@@ -1478,11 +1479,16 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
     const int first = whole ? 0 : wave - sub, count = whole ? NW : W;
     if (!whole) {                                 // several units per block: the W waves of one merge among themselves
       // (a single-chunk row: the output; a slot of the chunk list: its partial)
+      // (halves of rows at d = 256, where the rows are as few as the waves)
       if (row_valid)
-        for (int h = sub; h < G; h += W) merge_row(h, first, count, query_row(h), direct, split, new_here, lds_new);
+        for (int u = sub; u < G * (D / 128); u += W) {
+          const int h = u / (D / 128);
+          merge_row(std::integral_constant<int, 2>{}, h, u % (D / 128) * 128, first, count, query_row(h), direct, split, new_here, lds_new);
+        }
       return;
     }
-    for (int h = wave; h < G; h += NW) merge_row(h, 0, NW, query_row(h), direct, split, new_here, lds_new);
+    for (int h = wave; h < G; h += NW)
+      merge_row(std::integral_constant<int, D / 64>{}, h, 0, 0, NW, query_row(h), direct, split, new_here, lds_new);
     if (p.merge_slot < 0 || direct || wave >= G) return;
   }
 

@@ -157,10 +157,10 @@ int hip_rc(hipError_t e) { return e == hipSuccess ? TQ_OK : TQ_ERR_HIP; }
 // wide: the matrix-core kernel for many query rows (head_dim 512; 256 and 128 by wide_rows); small_tile: at most eight query rows to a block.
 struct Route { bool ok, use_mfma, merge, merge_step, wide, small_tile; };
 // The in-kernel merge ends the kernel with a chain of device-wide round trips (publish the partial, count in, read
-// all partials) that one block per KV head walks alone: about 2.5 us for up to 32 chunks, against about 3.5 us for the
+// the row's partials) that one wave per row walks: about 1.3 us for 4 chunks and 2.5 us for 32, against about 3.3 us for the
 // separate merge kernel plus its launch; with 64 and 128 chunks to a row that one compute unit pulls in for too long
-// (one KV head, 8 heads, us per step, in place / merge kernel: 16K tokens, 64 chunks, 13.0 / 11.4; 128K, 128 chunks,
-// 20.9 / 15.8).  A decode step merges in place wherever that holds (128K tokens, 64 heads over 8, 33.3 -> 32.6 us;
+// (one KV head, 8 heads, us per step, in place / merge kernel: 14K tokens, 55 chunks, 9.4 / 9.0; 16K,
+// 64 chunks, 9.7 / 9.1).  A decode step merges in place wherever that holds (128K tokens, 64 heads over 8, 33.3 -> 32.6 us;
 // 8 sequences of 8K 21.9 -> 20.6; 32 heads over 32, 32K, 31.4 -> 29.9); the decode alone up to this many packed bytes per
 // call.  Above, and at head_dim 256 with larger groups, it keeps two launches, although one would be the faster there too
 // (32 heads over 16, d = 256, 32K tokens: the step's one launch 33.0 us, the decode's two 33.9): callers that ask tq_decode_launches, and the
@@ -300,6 +300,7 @@ int waves_per_packed_row(int64_t total_rows, int target) {
 // and at d = 256, 32 heads over 16: 32 sequences, 2048, 8 waves 32.6 / 33.3 | 25.8 / 22.2 | 58.0 / 69.3, 3072 39.0 / 41.1 |
 // 35.2 / 22.4 | 83.4 / 90.6; 64, 2048, 4 waves 47.0 / 55.3 | 29.2 / 31.2 | 110 / 130; 80, 2048, 4 waves 57.5 / 87.6 |
 // 29.7 / 36.6 | 136 / 207.
+// (One query token and no window: listed_lengths first; what is past its lines comes here, and from there to the chunk list.)
 // Sequences past what a launch can order come in the given order: half the tokens per wave (600 sequences, 8 heads over 1,
 // 2048, 4 waves 32.8 / 41.8 | 21.8 / 26.9 | 49.1 / 66.3).
 int ranked_waves(int64_t rows, int batch, int tokens, bool d256) {

@@ -1,5 +1,5 @@
-// Matrix-core fused int4 decode attention for gfx950 (phase 1 of Sec. 3.2: per-chunk partials; for
-// short sequences also phase 2, the chunk merge of Eq. 6, done by the block that finishes last).
+// Matrix-core fused int4 decode attention for gfx950 (phase 1 of Sec. 3.2: per-chunk partials; up to 32 chunks
+// to a row also phase 2, the chunk merge of Eq. 6, done by the wave that has the row last).
 //
 // Why matrix cores: with a GQA group of G query heads every stored element is used by G heads;
 // at G=8 and d=128 that is 25.6 flop per HBM byte, above the vector-ALU ridge of the chip, so the
@@ -56,7 +56,8 @@
 // and the younger wave of a SIMD, see the kernel), keep private online-softmax state, and are merged through
 // LDS so that the block writes one partial (o_c, m_c, l_c) per query row.  Where there are more rows, or slots of a
 // device-planned chunk list, than the chip holds blocks, 2, 4 or 8 of them share a block; many rows of their own
-// lengths get blocks of 8, 4, 2 or 1 waves, one per row, longest first (`ranked` in the kernel).
+// lengths get blocks of 8, 4, 2 or 1 waves, one per row, longest first (`ranked` in the kernel); and where that does not
+// pay, the waves of one round of blocks are dealt to the sequences in proportion to their lengths (LISTED).
 //
 // Query rows: the tile's GP columns take the G heads of the GQA group (Sec. 3.1), or, with several query
 // tokens per sequence (the sequence's last n_queries tokens, causal among themselves), the n_queries * G
@@ -299,8 +300,8 @@ __device__ __forceinline__ void wait_loads() {               // until at most N 
 // paged sequences 38.5 -> 42.4 us per step); 2048 .. 4096 2.56e-4 / - / 2.56e-4; d = 256 2.87e-4 / 2.89e-4 / 2.07e-4 at 2 - 4 % of the time.
 enum Mode { kPlain, kPlainStep, kGeneral, kPaged, kListed, kListedPaged };   // kPlainStep: see LEAN
 // LEAN: the 16-row tile's instances for plain launches and for blocks that share a KV head take no new token and come to
-// the masked last supertile at the end.  Two stretches of code that few waves run, between the prologue and the loop, are
-// two cold jumps for the instruction cache on every launch, and these launches are short: 128 heads over 8, 8K tokens,
+// the masked last supertile at the end.  Two stretches of code that few waves run, between the prologue and the loop, cost
+// these launches, which are short, half a microsecond (why is open: the instruction cache is warm from launch to launch): 128 heads over 8, 8K tokens,
 // decode 13.54 us with both, 13.5 with either, 13.02 with neither; 3.3K 12.87 / 12.40; 4 query tokens, 64 heads over 8,
 // 32K, 26.5 / 26.1 per step.  (With up to eight rows the steps gain more by both than this costs.)  The step of one short
 // sequence, whose only launch takes the token in, keeps a plain instance with both: 128 heads over 8, 300 tokens, 11.3 us,

@@ -1127,7 +1127,8 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
         zb[2 * i + 1] = -sz_half(r.zb[4 + i], 0);
       }
     }
-    constexpr int NPZ = TWO ? NA : NPA;
+    constexpr int NPZ = SPLIT ? NPA : NA;         // (TWO: the rest goes with zb15 below)
+    static_assert(SPLIT || NPZ <= NA, "a zero-point sum for every operand");
 #pragma unroll
     for (int a = 0; a < NPZ; ++a) zacc[SPLIT ? 0 : a] = mfma16(pa[a], zb, zacc[SPLIT ? 0 : a]);
 #pragma unroll

@@ -461,8 +461,6 @@ int run_partial(PartialRequest& rq) {
   if (slots > 0) {
     p.listed = 1;
     p.var_chunks = slots;
-    // a sequence spans at most 32 blocks, whose partials one wave merges a row of (with 64 and more it is the merge kernel that is shorter)
-    p.var_min_chunk = (seq_len + 31 * 8 * tq::kTile - 1) / (31 * 8 * tq::kTile) * tq::kTile;
     p.n_splits = tq::kMaxSplits;
     p.waves_per_row = 8;
     rq.merged = true;

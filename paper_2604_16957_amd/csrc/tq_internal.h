@@ -16,6 +16,8 @@ constexpr int kMaxSplits = 128;   // upper bound on sequence chunks (Sec. 3.2); 
 constexpr int kMergeMaxChunks = 64;  // chunks of a row that the matrix-core kernel can merge in place (a lane each)
 constexpr int kTile = 32;         // chunk boundaries are multiples of this many tokens
 constexpr int kListMaxBatch = 256;   // sequences whose lengths the device's plan keeps in registers (kPlanTiles)
+constexpr int kListMaxParts = 32;    // blocks that the waves dealt to one sequence may span (with more of them it is the merge
+                                     // kernel that is shorter): a wave's share is at least the longest length over 31 * 8 waves
 constexpr int kRankMaxBatch = 512;   // sequences a launch can order by their lengths (RankedRows)
 constexpr int kMaxQueries = 8;    // query tokens per sequence in one call (the masked path covers two supertiles)
 
@@ -294,7 +296,10 @@ __device__ inline bool var_exact_floats(const DecodeParams& p) { return p.seq_le
 // total / var_chunks (too short unless every sequence ends on a chunk boundary) and
 // total / (var_chunks - batch) (always enough: a sequence wastes less than one chunk).  Called by whole waves
 // at the start of a kernel; every wave of a launch gets the same answer.
-// LISTED (DecodeParams::listed): the host's lower bound as it is (it keeps a sequence within the blocks that the merge in place takes).
+// LISTED (DecodeParams::listed): the lower bound comes from the longest LENGTH, not from the host's bound of them, which a
+// program that passes its cache's capacity has far above them.  us per step, a bound of 131072, least share by the bound / by the lengths:
+// 64 heads over 8, one sequence of 4000 tokens 23.7 / 10.1 (bound 4096: 10.0), 8 of 1000 .. 4000 24.1 / 12.8, 16 of 300 .. 3000 20.5 / 16.7;
+// 8 over 1, one of 8000 26.3 / 10.9; d = 256, 32 over 16, 8 of 1000 .. 4000 47.0 / 28.7.
 // TWO (LISTED): a sequence of fewer than kTwoBelow such chunks has its weights in two parts, which takes an eighth more time per tile:
 // its chunks are an eighth shorter (in whole tiles).
 constexpr int kTwoBelow = 3;
@@ -312,9 +317,18 @@ __device__ inline int var_chunk_tokens(const DecodeParams& p, const VarLens& L) 
   for (int t = 0; t < kPlanTiles; ++t) mine += L.len[t];
   if (!LISTED) for (int t = kPlanTiles; t < tiles; ++t) mine += var_len_of_lane(p, t);     // (LISTED: at most 256 sequences, and 2^31 tokens)
   const long long total = LISTED ? wave_sum((int)mine) : ((long long)wave_sum((int)(mine >> 24)) << 24) + wave_sum((int)(mine & 0xFFFFFF));
-  const int floor_c = LISTED ? p.var_min_chunk : max(p.var_min_chunk, (p.seq_len + kMaxSplits - 1) / kMaxSplits);
+  int floor_c;
+  if constexpr (LISTED) {
+    int longest = 0;
+#pragma unroll
+    for (int t = 0; t < kPlanTiles; ++t) longest = max(longest, L.len[t]);
+    constexpr int kSpan = (kListMaxParts - 1) * 8 * kTile;      // (8 waves to a block; the first need not start one)
+    floor_c = (wave_max(longest) + kSpan - 1) / kSpan * kTile;
+  } else {
+    floor_c = max(p.var_min_chunk, (p.seq_len + kMaxSplits - 1) / kMaxSplits);
+  }
   auto round_up = [](long long c) { return (int)((c + kTile - 1) / kTile * kTile); };
-  const int budget = p.var_chunks - p.batch;      // >= var_chunks / 2 by the host's choice of var_chunks
+  const int budget = p.var_chunks - p.batch;      // >= var_chunks / 2 by the host's choice of var_chunks (LISTED: >= 1)
   const bool fl = var_exact_floats(p);
   int hi, lo;
   if (total < (1 << 23) && p.var_chunks < (1 << 16)) {

@@ -30,6 +30,28 @@ def test_many_sequences(B, Hq, Hkv, d, longest, group, page):
     check(B, Hq, Hkv, d, _uneven(B, longest, 5 + B), longest, group=group, page=page)
 
 
+# max_seq_len only bounds the lengths: the waves are dealt by the lengths alone, so a program that passes its cache's capacity gets
+# the same shares, and the same bits, as one that passes the longest length.
+@pytest.mark.parametrize("Hq,Hkv,d,lens", [(64, 8, 128, [4000]), (16, 2, 128, [1000, 4000, 2077, 33]), (16, 8, 256, [300, 2999, 1410])])
+def test_a_bound_far_above_the_lengths(Hq, Hkv, d, lens):
+    B, S, page = len(lens), max(lens), 64
+    w = wl.custom(batch=B, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=d, seq_len=S, seed=300 + S, outlier_channels=4)
+    q, k, v = make(w)
+    blocks = -(-S // page)
+    cache = tq.KVCache(B * blocks, Hkv, d, page)
+    near = torch.randperm(B * blocks, generator=torch.Generator().manual_seed(S)).to(torch.int32).reshape(B, blocks).cuda()
+    far = torch.cat([near, torch.zeros(B, 2048 - blocks, dtype=torch.int32, device="cuda")], 1).contiguous()
+    tq.tq_quantize_kv_paged(cache, near, k.cuda(), v.cuda(), torch.zeros(B, dtype=torch.int32, device="cuda"))
+    lens_dev = torch.tensor(lens, dtype=torch.int32).cuda()
+    outs = []
+    for table, bound in ((near, S), (far, 131072)):
+        assert listed_slots(B, Hq, Hkv, d, bound) == 2048 // Hkv
+        outs.append(tq.tq_sdpa_int4_decode_paged(cache, table, q.cuda(), lens_dev, bound, w.attn_scale))
+    torch.cuda.synchronize()
+    assert errors(outs[0], _reference(q, oracle_cache_from(k, v), lens, w.attn_scale, 0))[1] <= 1e-3
+    assert torch.equal(outs[0], outs[1])
+
+
 # Sequences of one or two waves' shares have fewer references of the exponentials than when eight waves shared each, and with one fp16
 # operand per weight 12 % more error than then (2.60e-4 for 2.33e-4 on 64 sequences of 128 .. 4096 tokens); their weights go in two parts.  The output's own rounding
 # is 2.07e-4, the long sequences' single operand at most 2.56e-4, and the mix of both below 2.33e-4: a bound between that and one operand for all.

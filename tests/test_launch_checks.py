@@ -38,7 +38,7 @@ int main() {
   r.ranked = 1; r.waves_per_row = 1; r.rank_spread = 0;
   ask("one_wave_two_rows", r, 0);
   DecodeParams l = plain;                   // waves dealt to the sequences: only with counters, a slot for each, one query token, no window
-  l.seq_lens = reinterpret_cast<const int32_t*>(256); l.listed = 1; l.var_chunks = 2048; l.var_min_chunk = 32;
+  l.seq_lens = reinterpret_cast<const int32_t*>(256); l.listed = 1; l.var_chunks = 2048;
   ask("listed_no_merge", l, -1);
   DecodeParams w = l;
   w.window = 32;

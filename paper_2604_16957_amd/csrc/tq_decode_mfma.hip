@@ -625,10 +625,6 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
     return young ? YNG * (K / PERIOD) + (r >> 1) : OLD * (K / PERIOD) + ((r + 1) >> 1);
   };
   const int n_mine = count_of(n_full);
-  const bool tail_last = n_tail > 0 && count_of(n_full + 1) != count_of(n_full);
-  // A short chunk has no supertile for every wave: its first ones are its first waves', one each, and the others only keep
-  // the barriers company (and take their rows of the merges).
-  const bool busy = (!PLAIN && !LISTED) || n_mine > 0 || tail_last;
   const int n_busy = PLAIN ? min(NW, n_full + n_tail) : NW;
   // ---- prologue: the query rows of this KV head's group come in by direct load as well (so that every
   //      vector-memory operation of the kernel is one of the counted loads), then the ring is filled.
@@ -689,11 +685,15 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   // A wave whose share includes the ragged (or partly masked) last supertile takes that one FIRST: its loads then leave
   // with the prologue's and its masked path runs while the wave's first full supertile is on its way.  (At the end it
   // was a memory round trip of its own for one wave of the launch, 2 - 3 us of a short sequence's time.)
+  const bool tail_last = n_tail > 0 && count_of(n_full + 1) != count_of(n_full);
   const bool tail0 = !LEAN && tail_last;
   if (tail0) issue_tail(0, n_full);
   else if (n_mine > 0) issue(0, sidx_of(0));
   // (the first loads are on their way: whatever they do not need is worked out behind them)
   __builtin_amdgcn_sched_barrier(0);
+  // A short chunk has no supertile for every wave: its first ones are its first waves', one each, and the others only keep
+  // the barriers company (and take their rows of the merges).
+  const bool busy = (!PLAIN && !LISTED) || n_mine > 0 || tail_last;
   bool tail_mine[4];                              // [2], [3]: the masked FIRST supertile(s) (see `head`), the one just
                                                   // before `begin` and the one before that
   tail_mine[0] = tail_last;

@@ -73,14 +73,18 @@ Plan plan_splits(int batch, int n_kv_heads, int seq_len, int requested, int targ
 // as good as no spread to wait for; against that a chunk more is 4 KB more for the waves that merge.  So two or three tiles
 // to a chunk up to 16 chunks, then four and more up to 32; a sequence of up to eight tiles stays one chunk (no merge at all), and one of up to
 // 15, which would be, is cut only where there are compute units for two tiles a chunk.  us per step, eight tiles and more to a chunk / this:
-// 8 heads over 1, 300 tokens 6.2 / 6.1, 1024 7.7 / 6.3, 4096 8.0 / 7.5; 64 over 8, 600 tokens 8.0 / 6.5, 2048 8.0 / 7.0, 4096 8.4 / 7.9,
-// 4 sequences of 600 8.1 / 6.7, 8 of 600 8.2 / 7.8; 32 over 32, 600 6.7 / 5.7; d = 256: 32 over 16, 600 9.2 / 6.9, a window of 1024
+// 8 heads over 1, 300 tokens 6.3 / 6.05, 1024 7.7 / 6.3, 4096 8.0 / 7.5; 64 over 8, 600 tokens 8.0 / 6.5, 2048 8.0 / 7.0, 4096 8.4 / 7.9,
+// 4 sequences of 600 8.1 / 6.7, 8 of 600 8.2 / 7.8; 32 over 32, 600 6.7 / 5.7; d = 256: 32 over 16, 300 8.1 / 6.6, 600 9.2 / 6.9, a window of 1024
 // 8.6 / 7.0, 16 over 8, 3000 10.1 / 8.5.  (64 over 8, 200 tokens in four chunks 6.7, in one 6.4; 2048 tokens in 32 chunks 7.5, in 16 7.2;
 // 16 sequences of 300 in two chunks each 8.0, in one 7.3.)
-int fine_splits(int batch, int n_kv_heads, int seq_len, int target_blocks) {
+// `light`: at d = 128 the second tile of a wave costs less than the merge where a block has up to four rows or the launch is not a plain one
+// (groups of 64 and 128, several query tokens): up to twelve tiles stay one chunk.  us per step | decode, one chunk / two tiles each:
+// 32 heads over 8, 300 tokens 5.2 / 5.7 | 4.9 / 5.65, 384 5.7 / 5.7 | 5.1 / 5.6, 416 5.8 / 5.7 | 5.6 / 5.6, 480 6.0 / 5.6 | 5.8 / 5.6;
+// 64 over 8, groups of 64, 288 7.9 / 8.0 | 7.6 / 8.0, 416 8.55 / 8.15 | 8.25 / 7.95; decode of 2 query tokens, 32 over 8, 384 8.0 / 8.15, 416 8.5 / 8.1.
+int fine_splits(int batch, int n_kv_heads, int seq_len, int target_blocks, bool light) {
   const int tiles = (seq_len + tq::kTile - 1) / tq::kTile;
   const int64_t most = (int64_t)target_blocks / ((int64_t)batch * n_kv_heads);
-  if (tiles <= 8) return 1;
+  if (tiles <= (light ? 12 : 8)) return 1;
   for (int t = 2; t <= (tiles < 16 ? 2 : 8); ++t) {
     const int n = (tiles + t - 1) / t;
     if (n <= most && n <= (t < 4 ? 16 : 32)) return n;
@@ -93,6 +97,11 @@ int queries_of(const tq_decode_opts* opts) { return (opts && opts->n_queries > 1
 // query rows that share one KV head
 int rows_of(const tq_kv_cache* c, int n_q_heads, const tq_decode_opts* opts) {
   return n_q_heads / c->n_kv_heads * queries_of(opts);
+}
+// fine_splits of a call over `tokens` tokens (up to eight rows to a block, rows_per_batch blocks to a chunk of every sequence)
+int fine_splits_of(const tq_kv_cache* c, int n_q_heads, const tq_decode_opts* opts, int rows_per_batch, int tokens) {
+  const bool light = c->head_dim == 128 && (rows_of(c, n_q_heads, opts) <= 4 || c->group_size != tq::kGroup || queries_of(opts) > 1);
+  return fine_splits(c->batch, rows_per_batch, tokens, kBlocksMfma, light);
 }
 
 // `room`: tokens a sequence can hold (the cache's capacity, or max_blocks pages of a paged pool)
@@ -431,7 +440,7 @@ int run_partial(PartialRequest& rq) {
   // (the chunks of one token fewer may be shorter, and then up to twice as many as the route counted)
   rq.merged = ranked || (rq.out != nullptr && (rq.step ? r.merge_step : r.merge) && !seq_lens && plan.n_splits <= tq::kMergeMaxChunks);
   if (rq.merged) {
-    const int fine = ranked || asked > 0 || !r.small_tile ? 1 : fine_splits(cache->batch, rows_per_batch, attended, target);
+    const int fine = ranked || asked > 0 || !r.small_tile ? 1 : fine_splits_of(cache, n_q_heads, opts, rows_per_batch, attended);
     // several chunks: the arrival counters of this workspace (none left: the merge kernel does it); rows that are
     // single chunks count nothing
     merge_slot = std::max(plan.n_splits, fine) > 1 ? tq::mfma_merge_slot_of(rq.workspace) : 0;
@@ -611,6 +620,10 @@ int32_t tq_internal_decode_kernel(const tq_kv_cache* cache, int32_t n_q_heads, i
                                   const tq_decode_opts* opts, int32_t call) {
   const Route r = route_of(cache, n_q_heads, seq_len, attn_scale, opts, call == 0 ? Call::kDecode : call == 1 ? Call::kStep : Call::kLengths);
   return !r.ok ? 0 : r.wide ? 4 : !r.use_mfma ? 1 : r.small_tile ? 2 : 3;
+}
+
+int32_t tq_internal_fine_chunks(const tq_kv_cache* cache, int32_t n_q_heads, int32_t tokens, const tq_decode_opts* opts) {
+  return fine_splits_of(cache, n_q_heads, opts, cache->n_kv_heads * mfma_share_of(cache, n_q_heads, opts), tokens);
 }
 
 int32_t tq_internal_listed_slots(const tq_kv_cache* cache, int32_t n_q_heads, int32_t max_seq_len, float attn_scale, const tq_decode_opts* opts) {

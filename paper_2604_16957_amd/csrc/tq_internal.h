@@ -520,6 +520,10 @@ bool reduce_is_grouped(int head_dim, int64_t out_rows, int n_q_heads, int gqa);
 extern "C" int32_t tq_internal_decode_kernel(const tq_kv_cache* cache, int32_t n_q_heads, int32_t seq_len, float attn_scale,
                                              const tq_decode_opts* opts, int32_t call);
 
+// Chunks that the finer cut of short sequences makes of so many attended tokens, where the matrix-core kernel with up to eight query rows to a
+// block merges in place (1: the cut tq_plan_splits answers); not part of the public ABI.
+extern "C" int32_t tq_internal_fine_chunks(const tq_kv_cache* cache, int32_t n_q_heads, int32_t tokens, const tq_decode_opts* opts);
+
 // Slots (waves) to a KV head where a call with per-sequence lengths (at most max_seq_len) deals its waves to the sequences
 // (DecodeParams::listed), 0 where it does not; not part of the public ABI.
 extern "C" int32_t tq_internal_listed_slots(const tq_kv_cache* cache, int32_t n_q_heads, int32_t max_seq_len, float attn_scale,

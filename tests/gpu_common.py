@@ -125,3 +125,14 @@ def listed_slots(batch, n_q_heads, n_kv_heads, head_dim, max_seq_len, group=32, 
     ask.restype = ctypes.c_int32
     ask.argtypes = [ctypes.c_void_p, ctypes.c_int32, ctypes.c_int32, ctypes.c_float, ctypes.c_void_p]
     return ask(ctypes.byref(struct), n_q_heads, max_seq_len, 1.0, ctypes.byref(opts))
+
+
+def fine_chunks(batch, n_q_heads, n_kv_heads, head_dim, tokens, group=32, n_queries=1):
+    """Chunks that a short sequence is cut into where the decode kernel merges them itself (1: no finer than otherwise); asked on the host."""
+    fake = 0x10000
+    struct = binding.TqKvCacheStruct(fake, fake, fake, fake, fake, fake, batch, n_kv_heads, head_dim, group, tokens + tokens % 2, 0)
+    opts = binding.TqDecodeOptsStruct(0, 0, 0, n_queries)
+    ask = binding.raw().tq_internal_fine_chunks
+    ask.restype = ctypes.c_int32
+    ask.argtypes = [ctypes.c_void_p, ctypes.c_int32, ctypes.c_int32, ctypes.c_void_p]
+    return ask(ctypes.byref(struct), n_q_heads, tokens, ctypes.byref(opts))

@@ -10,8 +10,9 @@ from gpu_common import assert_cache_bit_exact, assert_close, gpu_cache_from, mak
 
 pytestmark = pytest.mark.gpu
 
-# tiles: 8 | 9 .. 15 (one chunk, or two tiles each) | 16, 32 | 33, 48 (three) | 49, 128 (four) | 129 (five, where 32 chunks fit)
-LENGTHS = [256, 257, 289, 480, 481, 512, 1024, 1025, 1536, 1537, 4096, 4097]
+# tiles: 8 | 9 .. 15 (one chunk, or two tiles each; 13: the first that every instance cuts) | 16, 32 | 33, 48 (three) | 49, 128 (four) |
+# 129 (five, where 32 chunks fit)
+LENGTHS = [256, 257, 289, 384, 385, 480, 481, 512, 1024, 1025, 1536, 1537, 4096, 4097]
 SHAPES = [(1, 8, 1, 128, 32), (1, 8, 8, 128, 32), (3, 40, 5, 128, 32), (1, 16, 2, 128, 128), (1, 4, 2, 256, 32), (2, 16, 8, 256, 64)]
 
 

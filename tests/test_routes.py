@@ -3,7 +3,7 @@ import math
 
 import pytest
 
-from gpu_common import kernel_of, listed_slots
+from gpu_common import fine_chunks, kernel_of, listed_slots
 
 WIDE, SIXTEEN, EIGHT, GENERIC, REFUSED = "wide rows", "16 rows", "8 rows", "generic", "refused"
 
@@ -86,3 +86,15 @@ def test_lengths_that_are_not_dealt_to_waves():
     assert listed_slots(256, 8, 1, 128, 5000) == 2048 and listed_slots(257, 8, 1, 128, 5000) == 0
     assert listed_slots(4, 128, 8, 128, 60000) == 0 and listed_slots(4, 32, 4, 256, 5000) == 0   # 16-row tile, rows in several blocks
     assert listed_slots(4, 32, 1, 512, 5000) == 0
+
+
+# (heads, KV heads, head dim, group, query tokens, the longest sequence that stays one chunk): the merge is dearer than a wave's second tile
+# in the 4-row tile and outside the plain instances of head_dim 128
+@pytest.mark.parametrize("heads,kv,d,group,nq,last", [
+    (8, 1, 128, 32, 1, 256), (64, 8, 128, 32, 1, 256), (32, 8, 128, 32, 1, 384), (32, 32, 128, 32, 1, 384), (64, 8, 128, 64, 1, 384),
+    (32, 8, 128, 128, 1, 384), (32, 8, 128, 32, 2, 384), (32, 16, 256, 32, 1, 256), (32, 16, 256, 64, 1, 256)])
+def test_short_sequences_that_stay_one_chunk(heads, kv, d, group, nq, last):
+    assert fine_chunks(1, heads, kv, d, last, group, nq) == 1
+    assert fine_chunks(1, heads, kv, d, last + 1, group, nq) == (last // 32 + 2) // 2
+    assert fine_chunks(1, heads, kv, d, 480, group, nq) == 8
+    assert fine_chunks(256 // kv, heads, kv, d, 480, group, nq) == 1              # (no compute units for a second chunk)

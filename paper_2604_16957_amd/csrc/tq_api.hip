@@ -353,33 +353,50 @@ Ranked ranked_rows(const tq_kv_cache* cache, int n_q_heads, int seq_len, float a
 // us per step, chunk list / this, 64 heads over 8, d = 128: 24 sequences of 1000 .. 16384 in pages 42.5 / 38.3, 8 of 4386 .. 32768 40.6 / 39.2,
 // 16 of 300 .. 3000 18.4 / 13.8, 48 of 300 .. 6000 42.1 / 30.8, 32 of 1000 19.2 / 14.3; 32 over 32: 8 of 500 .. 6000 27.1 / 22.0; 32 over 8:
 // 32 of 100 .. 8000 26.1 / 20.3; 32 over 16, d = 256: 16 of 500 .. 8000 57.2 / 48.1, 20 of 1500 49.2 / 36.4.
-// Where every row can have a block of its own (ranked_waves: 512 rows and more) that is the shorter way for short sequences of about one
-// length: no sequence is cut there, and the plan is shorter.  us per step, a block per row or (where that has no line) chunk list / this, for all
-// lengths at the bound | uniform from half of it | spread over the logarithm from a 16th:
-//   64 sequences (512 rows)  2048  34.4 / 34.8 | 27.9 / 31.0 | 23.0 / 22.6     4096  57.9 / 59.2 | 51.4 / 52.9 | 31.8 / 27.7 (from a 32nd)
-//   80 (640)                 1024  30.3 / 31.3 | 28.7 / 27.1 | 21.7 / 19.2     2048  49.3 / 46.5 | 45.2 / 39.0 | 25.9 / 25.9
-//   96 (768)                 3500  90.6 / 94.4 | 83.5 / 72.9 | 49.6 / 39.0     128 (1024)  3500  112 / 114 | 93.4 / 100 | 53.8 / 51.6
-//   176 (1408)               3500  183 / 179   | 163 / 143   | 94.5 / 76.2
-// and at d = 256, 32 heads over 16: 32 (512) 2048 60.6 / 63.8 | 52.3 / 52.5 | 35.5 / 29.3, 2500 81.4 / 76.8 | 70.2 / 61.9 | 40.4 / 36.0; 40 (640)
-// 1024 52.0 / 44.9 | 41.3 / 36.7 | 23.0 / 22.9; 64 (1024) 3000 170 / 164 | 144 / 135.
+// Where every row can have a block of its own (ranked_waves: 512 rows and more) no sequence is cut and the plan is shorter; and a sequence is
+// one wave's at least, so with few slots to a sequence the waves' shares are uneven again: three sequences of one length on eight slots are two
+// waves each and two idle.  So the lines go by slots per sequence, each drawn by the mean over three mixes, all lengths at the bound | uniform from half of it |
+// spread over the logarithm from a 32nd.  us per step, a block per row or (where that has no line) chunk list / this, 64 heads over 8, d = 128:
+//   64 sequences (4 slots each; in pairs they fill the chip as blocks of their own, which 65 no longer do)
+//       2048  34.4 / 34.8 | 27.9 / 31.0 | 23.0 / 22.6     3072  48.3 / 49.0 | 41.1 / 42.3 | 29.6 / 24.6
+//       4096  58.1 / 59.1 | 50.8 / 51.7 | 32.2 / 28.3     6000  87.8 / 84.5 | 78.6 / 73.0 | 40.5 / 37.0
+//   80 (3.2)    1024  30.3 / 31.3 | 28.7 / 27.1 | 21.7 / 19.2
+//   85 (3.01)   2048  48.5 / 48.6 | 47.2 / 41.8 | 24.4 / 25.1     4096  88.4 / 81.6 | 75.2 / 73.0 | 40.0 / 36.4
+//   88 (2.9)    2048  48.9 / 58.4 | 47.5 / 42.8 | 24.7 / 25.2     4096  89.9 / 107  | 75.3 / 74.7 | 41.3 / 37.3
+//   96 (2.7)    4096  104 / 112   | 99.8 / 81.9 | 51.0 / 38.4    16384  356 / 411   | 312 / 282   | 138 / 111
+//   128 (2)     2048  60.5 / 74.0 | 54.2 / 66.7 | 33.8 / 31.5     8192  230 / 255   | 193 / 215   | 85.9 / 81.4
+//   (more: the chunk list's waves are as short of work)
+//   130 (1.97)  2200  115 / 109   | 105 / 72.7  | 60.7 / 37.1     8192  339 / 358   | 293 / 217   | 132 / 84.8
+//   192 (1.33)  3500  184 / 182   | 170 / 149   | 87.8 / 72.4     (32 heads over 32: 48, 4096  195 / 168 | 167 / 152 | 76.3 / 66.4)
+//   220 (1.16)  3500  195 / 198   | 174 / 168   | 89.8 / 94.4     (56 (1.14), 4096  198 / 183 | 166 / 162 | 77.8 / 95.3)
+// and at d = 256, 32 heads over 16: 32 (4) 2048 60.6 / 63.8 | 52.3 / 52.5 | 35.5 / 29.3, 2500 81.4 / 76.8 | 70.2 / 61.9 | 40.4 / 36.0; 33 (3.9) 400 21.9 / 23.6 |
+// 17.6 / 19.4 | 14.9 / 16.3, 700 32.4 / 32.9 | 27.8 / 26.1 | 16.7 / 17.1, 1024 42.3 / 42.4 | 33.6 / 35.6 | 19.6 / 19.6; 40 (3.2) 700 39.3 / 35.7 | 32.5 / 31.0 | 19.5 / 19.7;
+// 44 (2.9) 1024 53.4 / 54.7 | 44.4 / 41.9 | 22.4 / 22.4, 3000 146 / 143 | 121 / 98.9 | 57.8 / 43.0; 64 (2) 3000 170 / 164 | 144 / 135; 110 (1.16) 3000
+// 307 / 296 | 252 / 235 | 117 / 112, lengths from a 150th on, 109 97.4 / 89.4, 113 97.1 / 102.8.
+// More than 128 KV heads have a block each and leave up to half the chip without one: 129 heads over 129, 4 sequences, 4000 77.7 / 78.8 | 58.4 / 81.4 | 30.9 / 37.4
+// (3, where the chunk list leaves as much: 74.9 / 75.3 | 73.8 / 53.3 | 40.5 / 32.3).
 // One sequence at the bound among short ones gains everywhere (64 sequences, one of 4096, the others 96: 25.3 / 14.4).
-bool listed_lengths(int64_t rows, int tokens, bool d256) {
+bool listed_lengths(const tq_kv_cache* cache, int slots, int tokens) {
   constexpr int C = kBlocksMfma;
+  const int batch = cache->batch;
+  const int64_t rows = (int64_t)batch * cache->n_kv_heads;
+  const bool d256 = cache->head_dim == 256;
   if (rows < 2 * C) return true;
+  if (cache->n_kv_heads > C / 2) return false;
   if (rows == 2 * C) return tokens > (d256 ? 2048 : 3072);
-  if (rows <= 11 * C / 4) return tokens > (d256 ? 0 : 1024);
+  if (slots >= 3 * batch) return tokens > (d256 ? 768 : 1024);
   if (rows <= 4 * C) return d256 && tokens > 2048;
-  return tokens > (rows <= 8 * C ? 2048 : 1024);
+  return tokens > 2048 && 6 * slots >= (d256 ? 7 : 8) * batch;
 }
 int listed_slots(const tq_kv_cache* cache, int n_q_heads, int seq_len, float attn_scale, const tq_decode_opts* opts) {
   if (opts && (opts->n_splits > 0 || opts->window > 0 || opts->n_queries > 1)) return 0;
   const Route r = route_of(cache, n_q_heads, seq_len, attn_scale, opts, Call::kLengths);
   if (!r.ok || !r.use_mfma || !r.small_tile || mfma_share_of(cache, n_q_heads, opts) != 1 || cache->n_kv_heads > kBlocksMfma) return 0;
   const int slots = kBlocksMfma / cache->n_kv_heads * 8;
-  // (an eighth of the slots over one per sequence; what the device's plan keeps in registers, and sums in 32 bits)
-  if (slots <= cache->batch + cache->batch / 8 || cache->batch > tq::kListMaxBatch || (int64_t)cache->batch * seq_len >= (1ll << 31)) return 0;
+  // (a slot for every sequence and one more; what the device's plan keeps in registers, and sums in 32 bits)
+  if (slots <= cache->batch || cache->batch > tq::kListMaxBatch || (int64_t)cache->batch * seq_len >= (1ll << 31)) return 0;
   if (!tq::mfma_can_merge((int64_t)cache->batch * n_q_heads)) return 0;
-  return listed_lengths((int64_t)cache->batch * cache->n_kv_heads, seq_len, cache->head_dim == 256) ? slots : 0;
+  return listed_lengths(cache, slots, seq_len) ? slots : 0;
 }
 
 // One launch of phase 1: what to attend, and what came of it.

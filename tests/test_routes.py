@@ -71,18 +71,26 @@ def test_always_at_512():
 
 # (sequences, heads, KV heads, head dim, the longest bound that does not deal its waves to the sequences; 0: every bound does)
 @pytest.mark.parametrize("B,heads,kv,d,last", [
-    (63, 64, 8, 128, 0), (64, 64, 8, 128, 3072), (65, 64, 8, 128, 1024), (88, 64, 8, 128, 1024), (129, 64, 8, 128, 2048), (31, 32, 16, 256, 0),
-    (32, 32, 16, 256, 2048), (33, 32, 16, 256, 0), (45, 32, 16, 256, 2048), (56, 32, 32, 128, 2048)])
+    (63, 64, 8, 128, 0), (64, 64, 8, 128, 3072), (65, 64, 8, 128, 1024), (85, 64, 8, 128, 1024), (129, 64, 8, 128, 2048), (192, 64, 8, 128, 2048),
+    (48, 32, 32, 128, 2048), (31, 32, 16, 256, 0), (32, 32, 16, 256, 2048), (33, 32, 16, 256, 768), (42, 32, 16, 256, 768),
+    (43, 32, 16, 256, 2048), (65, 32, 16, 256, 2048), (109, 32, 16, 256, 2048), (8, 72, 72, 128, 1024), (5, 96, 96, 128, 0), (3, 129, 129, 128, 0)])
 def test_lengths_that_are_dealt_to_waves(B, heads, kv, d, last):
-    slots = 2048 // kv
+    slots = 256 // kv * 8
     assert listed_slots(B, heads, kv, d, last + 1) == slots and (last == 0 or listed_slots(B, heads, kv, d, last) == 0)
     for more in (dict(window=100), dict(n_splits=2), dict(variant=1), dict(n_queries=2)):
         assert listed_slots(B, heads, kv, d, 5000, **more) == 0
 
 
+# too few slots to a sequence (fewer than three up to 1024 rows, four to three or, head_dim 256, seven to six beyond), or half the chip without a block
+@pytest.mark.parametrize("B,heads,kv,d", [
+    (86, 64, 8, 128), (128, 64, 8, 128), (193, 64, 8, 128), (49, 32, 32, 128), (56, 32, 32, 128), (220, 64, 8, 128), (110, 64, 16, 128),
+    (28, 64, 64, 128), (110, 32, 16, 256), (6, 96, 96, 128), (4, 129, 129, 128), (4, 256, 256, 128)])
+def test_too_few_slots_to_deal(B, heads, kv, d):
+    assert all(listed_slots(B, heads, kv, d, bound) == 0 for bound in (100, 1500, 3500, 8000, 131072))
+
+
 def test_lengths_that_are_not_dealt_to_waves():
-    assert listed_slots(57, 32, 32, 128, 5000) == 0                       # too few slots for that many sequences
-    assert listed_slots(89, 64, 8, 128, 50000) == 0 and listed_slots(128, 64, 8, 128, 50000) == 0
+    assert listed_slots(192, 8, 1, 128, 5000) == 2048
     assert listed_slots(256, 8, 1, 128, 5000) == 2048 and listed_slots(257, 8, 1, 128, 5000) == 0
     assert listed_slots(4, 128, 8, 128, 60000) == 0 and listed_slots(4, 32, 4, 256, 5000) == 0   # 16-row tile, rows in several blocks
     assert listed_slots(4, 32, 1, 512, 5000) == 0

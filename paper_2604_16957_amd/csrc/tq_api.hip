@@ -399,6 +399,16 @@ int listed_slots(const tq_kv_cache* cache, int n_q_heads, int seq_len, float att
   return listed_lengths(cache, slots, seq_len) ? slots : 0;
 }
 
+// The device-planned chunk list of sequences with their own lengths, per KV head: r rounds of target / rows_per_batch slots, r the smallest count
+// that leaves at least half of them once every sequence has been granted its partial last chunk.  Many sequences: the slots of several
+// rounds share blocks (2, 4 or 8 to a block, `waves` each; matrix-core kernel) and run in one.
+struct ChunkList { int slots, waves; };
+ChunkList chunk_list(int batch, int rows_per_batch, int target) {
+  const int per_round = std::max(1, target / rows_per_batch);            // (one round never spills into a second)
+  const int rounds = std::max(1, (2 * batch + per_round - 1) / per_round);
+  return {rounds * per_round, rounds > 4 ? 1 : rounds > 2 ? 2 : rounds > 1 ? 4 : 8};
+}
+
 // One launch of phase 1: what to attend, and what came of it.
 struct PartialRequest {
   const tq_kv_cache* cache;            // validated; for a paged pool: the view with batch = sequences
@@ -491,17 +501,13 @@ int run_partial(PartialRequest& rq) {
     p.waves_per_row = 8;
     rq.merged = true;
   } else if (seq_lens && !(opts && opts->n_splits > 0) && !ranked) {
-    // per-sequence lengths, no chunk count asked for: the kernels plan the chunks themselves from the lengths,
-    // `target` chunks over all sequences of a KV head (a requested n_splits keeps the fixed chunking)
-    // per KV head: r rounds of target / H_kv chunks, r the smallest count that leaves at least half of them
-    // once every sequence has been granted its partial last chunk
-    const int per_round = std::max(1, target / rows_per_batch);          // (one round never spills into a second)
-    const int rounds = std::max(1, (2 * cache->batch + per_round - 1) / per_round);
-    p.var_chunks = rounds * per_round;
+    // per-sequence lengths, no chunk count asked for: the kernels plan the chunks themselves from the lengths (a requested n_splits
+    // keeps the fixed chunking)
+    const ChunkList list = chunk_list(cache->batch, rows_per_batch, target);
+    p.var_chunks = list.slots;
     p.var_min_chunk = use_mfma ? 8 * tq::kTile : r.wide ? 2 * tq::kTile : tq::kTile;
     p.n_splits = tq::kMaxSplits;
-    // many sequences: the slots of several rounds share blocks (2, 4 or 8 to a block) and run in one
-    if (use_mfma) p.waves_per_row = rounds > 4 ? 1 : rounds > 2 ? 2 : rounds > 1 ? 4 : 8;
+    if (use_mfma) p.waves_per_row = list.waves;
   }
   rq.n_splits = plan.n_splits;
   hipStream_t s = static_cast<hipStream_t>(rq.stream);
@@ -646,6 +652,15 @@ int32_t tq_internal_fine_chunks(const tq_kv_cache* cache, int32_t n_q_heads, int
 int32_t tq_internal_listed_slots(const tq_kv_cache* cache, int32_t n_q_heads, int32_t max_seq_len, float attn_scale, const tq_decode_opts* opts) {
   return listed_slots(cache, n_q_heads, max_seq_len, attn_scale, opts);
 }
+
+int32_t tq_internal_lengths_waves(const tq_kv_cache* cache, int32_t n_q_heads, int32_t max_seq_len, float attn_scale, const tq_decode_opts* opts) {
+  const Route r = route_of(cache, n_q_heads, max_seq_len, attn_scale, opts, Call::kLengths);
+  if (!r.ok || !r.use_mfma || (opts && opts->n_splits > 0)) return 0;
+  const int waves = ranked_rows(cache, n_q_heads, max_seq_len, attn_scale, opts).waves;
+  return waves > 0 ? waves : -chunk_list(cache->batch, cache->n_kv_heads * mfma_share_of(cache, n_q_heads, opts), kBlocksMfma).waves;
+}
+
+int32_t tq_internal_counter_sets_left() { return tq::mfma_merge_slots_left(); }
 
 const char* tq_status_string(int status) {
   switch (status) {

@@ -1695,16 +1695,32 @@ bool mfma_takes_token(int head_dim, int group, int rows) {
 
 bool mfma_can_merge(int64_t out_rows) { return out_rows <= kCountersPerSlot; }
 
+namespace {
+struct MergeSlots {
+  std::mutex guard;
+  std::unordered_map<const void*, int> of;        // workspace -> set
+};
+MergeSlots& merge_slots() {
+  static MergeSlots slots;
+  return slots;
+}
+}  // namespace
+
 int mfma_merge_slot_of(const void* workspace) {
-  static std::mutex guard;
-  static std::unordered_map<const void*, int> slots;
-  std::lock_guard<std::mutex> lock(guard);
-  const auto it = slots.find(workspace);
-  if (it != slots.end()) return it->second;
-  if ((int)slots.size() >= kCounterSlots) return -1;
-  const int slot = (int)slots.size();
-  slots.emplace(workspace, slot);
+  MergeSlots& slots = merge_slots();
+  std::lock_guard<std::mutex> lock(slots.guard);
+  const auto it = slots.of.find(workspace);
+  if (it != slots.of.end()) return it->second;
+  if ((int)slots.of.size() >= kCounterSlots) return -1;
+  const int slot = (int)slots.of.size();
+  slots.of.emplace(workspace, slot);
   return slot;
+}
+
+int mfma_merge_slots_left() {
+  MergeSlots& slots = merge_slots();
+  std::lock_guard<std::mutex> lock(slots.guard);
+  return kCounterSlots - (int)slots.of.size();
 }
 
 hipError_t launch_partial_mfma(const DecodeParams& p_in, int batch, int head_dim, int merge_slot, hipStream_t s) {

@@ -502,6 +502,7 @@ bool mfma_takes_token(int head_dim, int group_size, int rows);
 // A launch whose rows are single chunks counts nothing and takes any slot >= 0.
 bool mfma_can_merge(int64_t out_rows);
 int mfma_merge_slot_of(const void* workspace);
+int mfma_merge_slots_left();
 hipError_t launch_partial_mfma(const DecodeParams& p, int batch, int head_dim, int merge_slot, hipStream_t s);
 // Matrix-core kernel whose blocks take a tile of 16 query rows of one KV head (head_dim 128: 32, where there are more than 16)
 // (p.kv_share = row tiles per KV head, from wide_row_tiles; p.gqa = H_q / H_kv; p.n_queries query tokens; p.k_new / p.v_new: see there).
@@ -528,3 +529,11 @@ extern "C" int32_t tq_internal_fine_chunks(const tq_kv_cache* cache, int32_t n_q
 // (DecodeParams::listed), 0 where it does not; not part of the public ABI.
 extern "C" int32_t tq_internal_listed_slots(const tq_kv_cache* cache, int32_t n_q_heads, int32_t max_seq_len, float attn_scale,
                                             const tq_decode_opts* opts);
+
+// Where the waves are not dealt out so (or the workspace gets no arrival counters), on the matrix-core kernel: the waves of a block that a row has to
+// itself, or, negative, of a slot of the device-planned chunk list; 0 on another kernel.  Not part of the public ABI.
+extern "C" int32_t tq_internal_lengths_waves(const tq_kv_cache* cache, int32_t n_q_heads, int32_t max_seq_len, float attn_scale,
+                                             const tq_decode_opts* opts);
+
+// Sets of arrival counters that no workspace has taken yet; not part of the public ABI.
+extern "C" int32_t tq_internal_counter_sets_left();

@@ -127,6 +127,23 @@ def listed_slots(batch, n_q_heads, n_kv_heads, head_dim, max_seq_len, group=32, 
     return ask(ctypes.byref(struct), n_q_heads, max_seq_len, 1.0, ctypes.byref(opts))
 
 
+def lengths_waves(batch, n_q_heads, n_kv_heads, head_dim, max_seq_len, group=32, window=0):
+    """Where a call with per-sequence lengths does not deal its waves out (see listed_slots): waves of a block that a row has to itself, or, negative,
+    of a slot of the chunk list; asked on the host."""
+    fake = 0x10000
+    struct = binding.TqKvCacheStruct(fake, fake, fake, fake, fake, fake, batch, n_kv_heads, head_dim, group, max_seq_len + max_seq_len % 2, 0)
+    opts = binding.TqDecodeOptsStruct(0, 0, window, 1)
+    ask = binding.raw().tq_internal_lengths_waves
+    ask.restype = ctypes.c_int32
+    ask.argtypes = [ctypes.c_void_p, ctypes.c_int32, ctypes.c_int32, ctypes.c_float, ctypes.c_void_p]
+    return ask(ctypes.byref(struct), n_q_heads, max_seq_len, 1.0, ctypes.byref(opts))
+
+
+def counter_sets_left():
+    """Sets of arrival counters that no workspace has taken: with none left, calls merge in a launch of their own."""
+    return binding.raw().tq_internal_counter_sets_left()
+
+
 def fine_chunks(batch, n_q_heads, n_kv_heads, head_dim, tokens, group=32, n_queries=1):
     """Chunks that a short sequence is cut into where the decode kernel merges them itself (1: no finer than otherwise); asked on the host."""
     fake = 0x10000
@@ -136,3 +153,25 @@ def fine_chunks(batch, n_q_heads, n_kv_heads, head_dim, tokens, group=32, n_quer
     ask.restype = ctypes.c_int32
     ask.argtypes = [ctypes.c_void_p, ctypes.c_int32, ctypes.c_int32, ctypes.c_void_p]
     return ask(ctypes.byref(struct), n_q_heads, tokens, ctypes.byref(opts))
+
+
+def lengths_route(batch, n_q_heads, n_kv_heads, head_dim, max_seq_len, group=32, window=0):
+    """How a call with per-sequence lengths (one query token, a workspace with arrival counters) spreads its sequences, in words; asked on the host."""
+    if listed_slots(batch, n_q_heads, n_kv_heads, head_dim, max_seq_len, group, window=window):
+        return "waves dealt"
+    waves = lengths_waves(batch, n_q_heads, n_kv_heads, head_dim, max_seq_len, group, window)
+    return f"{waves} waves a row" if waves > 0 else f"{-waves} waves a slot" if waves < 0 else "another kernel"
+
+
+_workspace = None
+
+
+def shared_workspace(batch, n_q_heads, head_dim):
+    """The same workspace for every test that asks for one, filled with NaNs (nothing that the call has not written may count): the library has
+    a limited number of sets of arrival counters, one for each workspace it ever sees, and a call without one merges in a launch of its own."""
+    global _workspace
+    need = tq.tq_workspace_bytes(batch, n_q_heads, head_dim)
+    if _workspace is None or _workspace.numel() < need:
+        _workspace = torch.empty(max(need, 1 << 30), dtype=torch.uint8, device="cuda")
+    _workspace[:need].fill_(0xFF)
+    return _workspace[:need]

@@ -10,8 +10,8 @@ import oracle
 import paper_2604_16957_amd as tq
 import tq_workloads as wl
 from gpu_common import (MAX_ABS, REL_L2, assert_cache_bit_exact, assert_close, assert_close_elementwise, assert_comparator_close,
-                        errors, gpu_cache_from, make, np16, oracle_attend,
-                        oracle_cache_from)
+                        counter_sets_left, errors, gpu_cache_from, lengths_route, make, np16, oracle_attend,
+                        oracle_cache_from, shared_workspace)
 
 pytestmark = pytest.mark.gpu
 
@@ -529,19 +529,24 @@ def test_rows_of_their_own_length_are_each_taken_once(B, Hkv):
     assert torch.equal(out, again)
 
 
-@pytest.mark.parametrize("route", ["own_blocks", "one_block", "planned_chunks"])
+@pytest.mark.parametrize("route", ["own_blocks", "one_block", "planned_chunks", "dealt_waves"])
 def test_sharp_softmax_every_head_keeps_its_own_reference(route):
     """Scores with a spread of tens of log2 units (attn_scale 1 on N(0,1) queries and keys): new maxima keep turning
     up, for one head or another of the group, all along a wave's tokens.  A head's exp2 reference must move only
     when its OWN maximum outgrows it: one that follows every move of a neighbour ends tens of units above the head's
     scores and its weights p * s_v sink into fp16's subnormals (percent-level errors on single rows).  Routes: many
-    rows of their own length, a block of four waves each; one long chunk per block; the device-planned chunks."""
+    rows of their own length, a block of four waves each; one long chunk per block; the device-planned chunks (a window over
+    everything leads there); waves dealt to the sequences."""
     if route == "own_blocks":
-        B, Hkv, S, n_splits = 131, 4, 1025, 0
+        B, Hkv, S, n_splits = 131, 4, 1024, 0
     elif route == "one_block":
         B, Hkv, S, n_splits = 3, 2, 6000, 1
     else:
         B, Hkv, S, n_splits = 9, 4, 6000, 0
+    window = S if route == "planned_chunks" else 0
+    if n_splits == 0:
+        how = {"own_blocks": "4 waves a row", "planned_chunks": "8 waves a slot", "dealt_waves": "waves dealt"}[route]
+        assert lengths_route(B, 8 * Hkv, Hkv, 128, S, window=window) == how
     rng = np.random.default_rng(4052)
     lens = [int(x) for x in rng.integers(S // 2, S + 1, B)]
     w = wl.custom(batch=B, n_q_heads=8 * Hkv, n_kv_heads=Hkv, head_dim=128, seq_len=S, seed=54052, attn_scale=1.0,
@@ -551,7 +556,7 @@ def test_sharp_softmax_every_head_keeps_its_own_reference(route):
     ocache = oracle_cache_from(k, v)
     ref = _oracle_varlen(q, ocache, lens, w.attn_scale)
     out = tq.tq_sdpa_int4_decode_varlen(cache, q.cuda(), torch.tensor(lens, dtype=torch.int32, device="cuda"), S,
-                                        w.attn_scale, n_splits=n_splits)
+                                        w.attn_scale, n_splits=n_splits, window=window, workspace=shared_workspace(B, 8 * Hkv, 128))
     torch.cuda.synchronize()
     assert_close_elementwise(out, ref, route)
 
@@ -964,21 +969,27 @@ def test_graph_capture_and_replay():
             assert torch.equal(out1, want1) and torch.equal(out2, want2)
 
 
-@pytest.mark.parametrize("route", ["d512", "own_lengths_planned", "own_lengths_own_blocks"])
+@pytest.mark.parametrize("route", ["d512", "own_lengths_planned", "own_lengths_dealt", "own_lengths_own_blocks"])
 def test_graph_capture_and_replay_of_the_other_routes(route):
     """The one-call step captured and replayed on the routes the test above does not take: the head_dim 512 kernel
-    (its ring is static LDS above 64 KB), per-sequence lengths with device-planned chunks (the plan is redone by
-    every replay), and many rows of their own length with a block each; in both the decode kernel takes the token in."""
+    (its ring is static LDS above 64 KB), per-sequence lengths with device-planned chunks (a window over everything leads there) or with waves
+    dealt to the sequences (either plan is redone by every replay), and many rows of their own length with a block each; in all three the
+    decode kernel takes the token in."""
+    window = 0
     if route == "d512":
         w = wl.custom(seq_len=1500, seed=93, **SHAPES["g32_d512"])
         lens = None
-    elif route == "own_lengths_planned":
+    elif route in ("own_lengths_planned", "own_lengths_dealt"):
         w = wl.custom(batch=6, n_q_heads=16, n_kv_heads=2, head_dim=128, seq_len=3000, seed=94)
         lens = [3000, 1, 77, 2049, 1000, 2999]
+        window = 3000 if route == "own_lengths_planned" else 0
     else:
         w = wl.custom(batch=70, n_q_heads=32, n_kv_heads=8, head_dim=128, seq_len=600, seed=95)
         lens = [int(x) for x in np.random.default_rng(95).integers(2, 601, 70)]
     S, B = w.seq_len, w.batch
+    if lens is not None:
+        how = {"own_lengths_planned": "8 waves a slot", "own_lengths_dealt": "waves dealt", "own_lengths_own_blocks": "4 waves a row"}[route]
+        assert lengths_route(B, w.n_q_heads, w.n_kv_heads, w.head_dim, S, window=window) == how and counter_sets_left() > 0
     q, k, v = make(w)
     ocache = oracle_cache_from(k, v)
     cache = gpu_cache_from(k, v, capacity=S)
@@ -987,7 +998,7 @@ def test_graph_capture_and_replay_of_the_other_routes(route):
     vn = torch.stack([v[b, :, own[b] - 1:own[b]] for b in range(B)]).contiguous().cuda()
     qd = q.cuda()
     out = torch.empty_like(qd)
-    ws = torch.empty(tq.tq_workspace_bytes(B, w.n_q_heads, w.head_dim), dtype=torch.uint8, device="cuda")
+    ws = shared_workspace(B, w.n_q_heads, w.head_dim)
     lens_dev = None if lens is None else torch.tensor(lens, dtype=torch.int32, device="cuda")
 
     def wipe():                                   # the step has to write every sequence's last token again
@@ -999,7 +1010,7 @@ def test_graph_capture_and_replay_of_the_other_routes(route):
         if lens is None:
             tq.tq_sdpa_int4_append_decode(cache, kn, vn, qd, S, w.attn_scale, out=out, workspace=ws)
         else:
-            tq.tq_sdpa_int4_append_decode_varlen(cache, kn, vn, qd, lens_dev, S, w.attn_scale, out=out, workspace=ws)
+            tq.tq_sdpa_int4_append_decode_varlen(cache, kn, vn, qd, lens_dev, S, w.attn_scale, out=out, workspace=ws, window=window)
 
     wipe()
     step()
@@ -1767,12 +1778,15 @@ def test_more_rows_than_blocks_are_packed_several_to_a_block(shape):
                 assert_close(out, _oracle_causal(q4, ocache, [S] * batch, w.attn_scale), f"{shape} batch={batch} S={S}, 2 queries")
 
 
-@pytest.mark.parametrize("S,bound", [(1800, 1800), (2600, 4500)])
-def test_eighty_sequences_with_their_own_lengths_and_a_step(S, bound):
-    """640 (sequence, KV head) rows with their own lengths.  With a bound of up to 3072 tokens every row is one chunk of a
-    block of its own, and the decode kernel writes the output itself (no chunk plan, no merge kernel); beyond 4096
-    the device plans chunks whose slots share blocks.  Either way the decode kernel takes the step's token in.  Plain
-    decode, a window (which then is the bound), and the one-call step, against the oracle."""
+@pytest.mark.parametrize("S,bound,window,how", [(900, 1024, 300, "4 waves a row"), (1800, 1800, 300, "waves dealt"), (2600, 4500, 300, "waves dealt"),
+                                                (2600, 4500, 4400, "waves dealt")])
+def test_eighty_sequences_with_their_own_lengths_and_a_step(S, bound, window, how):
+    """640 (sequence, KV head) rows with their own lengths.  With a bound of up to 1024 tokens every row is one chunk of a
+    block of its own, and the decode kernel writes the output itself (no chunk plan, no merge kernel); beyond, the waves of one round
+    of blocks are dealt to the sequences.  A window is the bound then, and beyond 4096 the device plans chunks whose slots share blocks.  Each way
+    the decode kernel takes the step's token in.  Plain decode, a window, and the one-call step, against the oracle."""
+    assert lengths_route(80, 64, 8, 128, bound) == how and counter_sets_left() > 0
+    assert lengths_route(80, 64, 8, 128, bound, window=window) == ("4 waves a row" if window == 300 else "1 waves a slot")
     rng = np.random.default_rng(80)
     B = 80
     lens = [int(x) for x in rng.integers(1, S + 1, B)]
@@ -1783,19 +1797,20 @@ def test_eighty_sequences_with_their_own_lengths_and_a_step(S, bound):
     ocache = oracle_cache_from(k, v)
     lens_dev = torch.tensor(lens, dtype=torch.int32, device="cuda")
     ref = _oracle_varlen(q, ocache, lens, w.attn_scale)
-    out = tq.tq_sdpa_int4_decode_varlen(cache, q.cuda(), lens_dev, bound, w.attn_scale)
+    out = tq.tq_sdpa_int4_decode_varlen(cache, q.cuda(), lens_dev, bound, w.attn_scale, workspace=shared_workspace(B, 64, 128))
     torch.cuda.synchronize()
     assert_close(out, ref, "80 sequences, own lengths")
-    out = tq.tq_sdpa_int4_decode_varlen(cache, q.cuda(), lens_dev, bound, w.attn_scale, window=300)
+    out = tq.tq_sdpa_int4_decode_varlen(cache, q.cuda(), lens_dev, bound, w.attn_scale, window=window, workspace=shared_workspace(B, 64, 128))
     torch.cuda.synchronize()
-    assert_close(out, _oracle_window(q, ocache, lens, 300, w.attn_scale), "80 sequences, own lengths, window 300")
+    assert_close(out, _oracle_window(q, ocache, lens, window, w.attn_scale), f"80 sequences, own lengths, window {window}")
     # the step: wipe every sequence's last token, hand it over as the new one
     kn = torch.stack([k[b, :, lens[b] - 1:lens[b]] for b in range(B)]).contiguous()
     vn = torch.stack([v[b, :, lens[b] - 1:lens[b]] for b in range(B)]).contiguous()
     for t in cache.tensors():
         for b in range(B):
             t.view(torch.uint8)[b, :, lens[b] - 1] = 0xEE
-    out = tq.tq_sdpa_int4_append_decode_varlen(cache, kn.cuda(), vn.cuda(), q.cuda(), lens_dev, bound, w.attn_scale)
+    out = tq.tq_sdpa_int4_append_decode_varlen(cache, kn.cuda(), vn.cuda(), q.cuda(), lens_dev, bound, w.attn_scale,
+                                               workspace=shared_workspace(B, 64, 128))
     torch.cuda.synchronize()
     assert_close(out, ref, "80 sequences, own lengths, append + decode")
     for name, g, o in zip(("k_codes", "k_scale", "k_zero", "v_codes", "v_scale", "v_zero"), cache.tensors(), ocache):

@@ -1,6 +1,6 @@
 """Many sequences with lengths of their own: the launches in which every (sequence, KV head) row is one chunk of a block
-of its own, longest row first, and where they give way to the device-planned chunk list.  Every row against the oracle;
-and, for the mixes that an ordering or a bound exists for, that it does what it is there for."""
+of its own, longest row first, and where they give way to the device-planned chunk list or to waves dealt to the sequences.  Every
+row against the oracle; and, for the mixes that an ordering or a bound exists for, that it does what it is there for."""
 import math
 
 import numpy as np
@@ -10,7 +10,7 @@ import torch
 import oracle
 import paper_2604_16957_amd as tq
 import tq_workloads as wl
-from gpu_common import assert_close_elementwise, gpu_cache_from, make, np16, oracle_cache_from
+from gpu_common import assert_close_elementwise, counter_sets_left, gpu_cache_from, lengths_route, make, np16, oracle_cache_from, shared_workspace
 
 pytestmark = pytest.mark.gpu
 
@@ -34,8 +34,12 @@ def _reference(q, ocache, lens, alpha, window):
     return np.concatenate(rows, axis=0)
 
 
-def check(B, Hq, Hkv, d, lens, S, group=32, page=0, window=0):
-    """A decode, twice (bit for bit alike), and a step that brings every sequence's last token, against the oracle."""
+def check(B, Hq, Hkv, d, lens, S, group=32, page=0, window=0, route=None, workspace=None):
+    """A decode, twice (bit for bit alike), and a step that brings every sequence's last token, against the oracle, in a workspace of NaNs
+    (the shared one, or `workspace`).  route: how the call has to spread its sequences (see lengths_route)."""
+    if route is not None:
+        assert lengths_route(B, Hq, Hkv, d, S, group, window) == route
+        assert route != "waves dealt" or counter_sets_left() > 0
     w = wl.custom(batch=B, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=d, seq_len=max(lens), seed=9000 + B + Hkv + S + group)
     q, k, v = make(w)
     ocache = oracle_cache_from(k, v, group=group)
@@ -43,17 +47,18 @@ def check(B, Hq, Hkv, d, lens, S, group=32, page=0, window=0):
     lens_dev = torch.tensor(lens, dtype=torch.int32).cuda()
     k_new = torch.stack([k[b, :, n - 1:n] for b, n in enumerate(lens)]).contiguous().cuda()
     v_new = torch.stack([v[b, :, n - 1:n] for b, n in enumerate(lens)]).contiguous().cuda()
+    more = lambda: dict(window=window, workspace=shared_workspace(B, Hq, d) if workspace is None else workspace.fill_(0xFF))
     if page:
         blocks = -(-S // page)
         cache = tq.KVCache(B * blocks, Hkv, d, page, group_size=group)
         table = torch.randperm(B * blocks, generator=torch.Generator().manual_seed(B + S)).to(torch.int32).reshape(B, blocks).cuda()
         tq.tq_quantize_kv_paged(cache, table, k.cuda(), v.cuda(), torch.zeros(B, dtype=torch.int32, device="cuda"))
-        decode = lambda: tq.tq_sdpa_int4_decode_paged(cache, table, q.cuda(), lens_dev, S, w.attn_scale, window=window)
-        step = lambda: tq.tq_sdpa_int4_append_decode_paged(cache, table, k_new, v_new, q.cuda(), lens_dev, S, w.attn_scale, window=window)
+        decode = lambda: tq.tq_sdpa_int4_decode_paged(cache, table, q.cuda(), lens_dev, S, w.attn_scale, **more())
+        step = lambda: tq.tq_sdpa_int4_append_decode_paged(cache, table, k_new, v_new, q.cuda(), lens_dev, S, w.attn_scale, **more())
     else:
         cache = gpu_cache_from(k, v, capacity=S + (S & 1), group=group)
-        decode = lambda: tq.tq_sdpa_int4_decode_varlen(cache, q.cuda(), lens_dev, S, w.attn_scale, window=window)
-        step = lambda: tq.tq_sdpa_int4_append_decode_varlen(cache, k_new, v_new, q.cuda(), lens_dev, S, w.attn_scale, window=window)
+        decode = lambda: tq.tq_sdpa_int4_decode_varlen(cache, q.cuda(), lens_dev, S, w.attn_scale, **more())
+        step = lambda: tq.tq_sdpa_int4_append_decode_varlen(cache, k_new, v_new, q.cuda(), lens_dev, S, w.attn_scale, **more())
     what = f"{B} sequences, {Hq}/{Hkv} heads, d={d}, bound {S}, g={group}, page={page}, window={window}"
     out = decode()
     again = decode()
@@ -79,58 +84,63 @@ def test_hundreds_of_sequences_each_row_once(B, Hkv, longest):
     check(B, 2 * Hkv, Hkv, 128, _uneven(B, longest, 31 + B), longest)
 
 
-# Which blocks the rows get follows from their number and the bound alone: (sequences, query heads, KV heads, d, longest,
-# bound); "even": all lengths within two tiles of each other.
+# How the sequences are spread follows from their number, the heads, the bound and the window alone: (sequences, query heads, KV heads, d, longest,
+# bound, window, how); "even": all lengths within two tiles of each other.  A window next to the bound (everything is attended) is one of the
+# ways to the chunk list.
 ROUTES = {
-    "one round of 4 waves a row": (64, 16, 8, 128, 1100, 2048),
-    "8 waves a row": (64, 16, 8, 128, 2300, 4096),
-    "8 waves a row, two rounds and a bit": (72, 16, 8, 128, 700, 4096),
-    "4 waves a row": (97, 16, 8, 128, 1100, 3072),
-    "4 waves a row, past two rounds": (129, 16, 8, 128, 700, 2048),
-    "2 waves a row": (161, 16, 8, 128, 900, 1024),
-    "1 wave a row": (261, 16, 8, 128, 600, 1024),
-    "sixteen rows to a tile, 4 waves": (64, 96, 8, 128, 400, 1024),
-    "sixteen rows to a tile, 8 waves": (64, 128, 8, 128, 300, 4000),
-    "sixteen rows to a tile, two tiles to a KV head": (64, 96, 4, 128, 400, 1024),
-    "d = 256, 4 waves": (32, 32, 16, 256, 600, 1024),
-    "d = 256, 8 waves": (32, 32, 16, 256, 1500, 2048),
-    "d = 256, 2 waves": (80, 32, 16, 256, 300, 1000),
-    "d = 256, 1 wave": (130, 16, 16, 256, 200, 500),
-    # (below 512 rows, or the bound too far: slots of the chunk list, 8, 4, 2 and 1 waves each)
-    "chunk list, 8 waves a slot": (12, 16, 8, 128, 1500, 6000),
-    "chunk list, 4 waves a slot": (30, 16, 8, 128, 900, 6000),
-    "chunk list, 2 waves a slot": (61, 16, 8, 128, 700, 3000),
-    "chunk list, 1 wave a slot": (65, 16, 8, 128, 900, 6000),
-    "chunk list, 1 wave a slot, d = 256": (33, 32, 16, 256, 500, 2500),
+    "one round of 4 waves a row": (64, 16, 8, 128, 1100, 2048, 0, "4 waves a row"),
+    "8 waves a row": (64, 16, 8, 128, 2300, 3072, 0, "8 waves a row"),
+    "8 waves a row, two rounds and a bit": (88, 16, 8, 128, 700, 4096, 0, "8 waves a row"),
+    "4 waves a row": (97, 16, 8, 128, 1100, 3072, 0, "4 waves a row"),
+    "4 waves a row, past two rounds": (129, 16, 8, 128, 700, 2048, 0, "4 waves a row"),
+    "2 waves a row": (161, 16, 8, 128, 900, 1024, 0, "2 waves a row"),
+    "1 wave a row": (261, 16, 8, 128, 600, 1024, 0, "1 waves a row"),
+    "sixteen rows to a tile, 4 waves": (64, 96, 8, 128, 400, 1024, 0, "4 waves a row"),
+    "sixteen rows to a tile, 8 waves": (64, 128, 8, 128, 300, 4000, 0, "8 waves a row"),
+    "sixteen rows to a tile, two tiles to a KV head": (64, 96, 4, 128, 400, 1024, 0, "4 waves a row"),
+    "d = 256, 4 waves": (32, 32, 16, 256, 600, 1024, 0, "4 waves a row"),
+    "d = 256, 8 waves": (32, 32, 16, 256, 1500, 2048, 0, "8 waves a row"),
+    "d = 256, 2 waves": (80, 32, 16, 256, 300, 1000, 0, "2 waves a row"),
+    "d = 256, 1 wave": (130, 16, 16, 256, 200, 500, 0, "1 waves a row"),
+    "chunk list, 8 waves a slot": (12, 16, 8, 128, 1500, 6000, 5999, "8 waves a slot"),
+    "chunk list, 4 waves a slot": (30, 16, 8, 128, 900, 6000, 5999, "4 waves a slot"),
+    "chunk list, 2 waves a slot": (61, 16, 8, 128, 700, 3000, 2999, "2 waves a slot"),
+    "chunk list, 1 wave a slot": (97, 16, 8, 128, 900, 6000, 0, "1 waves a slot"),
+    "chunk list, 1 wave a slot, d = 256": (115, 16, 16, 256, 400, 2500, 0, "1 waves a slot"),
+    "waves dealt, 256 slots for 12": (12, 16, 8, 128, 1500, 6000, 0, "waves dealt"),
+    "waves dealt, 256 slots for 61": (61, 16, 8, 128, 700, 3000, 0, "waves dealt"),
+    "waves dealt, past 512 rows": (65, 16, 8, 128, 900, 6000, 0, "waves dealt"),
+    "waves dealt, d = 256": (33, 32, 16, 256, 500, 2500, 0, "waves dealt"),
 }
 
 
 @pytest.mark.parametrize("mix", ["uneven", "even"])
 @pytest.mark.parametrize("route", ROUTES)
 def test_every_kind_of_block(route, mix):
-    B, Hq, Hkv, d, longest, S = ROUTES[route]
+    B, Hq, Hkv, d, longest, S, window, how = ROUTES[route]
     lens = _uneven(B, longest, 77 + B)
     if mix == "even":
         lens = [int(n) for n in np.random.default_rng(B).integers(130, 194, B)]
-    check(B, Hq, Hkv, d, lens, S)
+    check(B, Hq, Hkv, d, lens, S, window=window, route=how)
 
 
 @pytest.mark.parametrize("group", [64, 128])
 @pytest.mark.parametrize("route", ["one round of 4 waves a row", "2 waves a row", "sixteen rows to a tile, 4 waves", "d = 256, 4 waves",
-                                   "d = 256, 2 waves", "chunk list, 1 wave a slot"])
+                                   "d = 256, 2 waves", "chunk list, 1 wave a slot", "chunk list, 1 wave a slot, d = 256", "waves dealt, past 512 rows"])
 def test_larger_groups_in_every_kind_of_block(route, group):
-    B, Hq, Hkv, d, longest, S = ROUTES[route]
-    check(B, Hq, Hkv, d, _uneven(B, min(longest, 400), 78 + B), S, group=group)
+    B, Hq, Hkv, d, longest, S, window, how = ROUTES[route]
+    check(B, Hq, Hkv, d, _uneven(B, min(longest, 400), 78 + B), S, group=group, window=window, route=how)
 
 
 @pytest.mark.parametrize("window", [0, 77])
 @pytest.mark.parametrize("page", [32, 64])
 @pytest.mark.parametrize("route", ["one round of 4 waves a row", "4 waves a row", "2 waves a row", "1 wave a row",
-                                   "sixteen rows to a tile, 4 waves", "d = 256, 4 waves", "chunk list, 1 wave a slot"])
+                                   "sixteen rows to a tile, 4 waves", "d = 256, 4 waves", "chunk list, 1 wave a slot", "chunk list, 4 waves a slot",
+                                   "waves dealt, past 512 rows"])
 def test_pages_and_windows_in_every_kind_of_block(route, page, window):
     """(Under a window the bound is the window: the same rows, then, are ranked with the fewest tokens to a wave.)"""
-    B, Hq, Hkv, d, longest, S = ROUTES[route]
-    check(B, Hq, Hkv, d, _uneven(B, min(longest, 500), 79 + B), S, page=page, window=window)
+    B, Hq, Hkv, d, longest, S, own_window, how = ROUTES[route]
+    check(B, Hq, Hkv, d, _uneven(B, min(longest, 500), 79 + B), S, page=page, window=window or own_window, route=None if window else how)
 
 
 # chunks of more than 64 pages: the kernel keeps 64 page numbers at hand and fetches on as it goes.  (B, query heads, KV

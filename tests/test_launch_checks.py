@@ -45,7 +45,7 @@ int main() {
   ask("listed_window", w, 0);
   w = l; w.batch = 257;
   ask("listed_many", w, 0);
-  w = l; w.gqa = 16; w.n_q_heads = 16;
+  w = l; w.gqa = 16; w.n_q_heads = 16; w.n_splits = 1;        // (one chunk: nothing else refuses a sixteen-row tile)
   ask("listed_tile16", w, 0);
   return 0;
 }

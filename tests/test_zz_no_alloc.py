@@ -11,7 +11,9 @@ import paper_2604_16957_amd as tq
 import tq_workloads as wl
 from paper_2604_16957_amd import binding as B
 
-from gpu_common import MAX_ABS, REL_L2, assert_close, gpu_cache_from, make, np16, oracle_attend, oracle_cache_from
+from gpu_common import (MAX_ABS, REL_L2, assert_cache_bit_exact, assert_close, counter_sets_left, gpu_cache_from, lengths_waves, make, np16, oracle_attend,
+                        oracle_cache_from)
+from test_gpu_uneven_lengths import _uneven, check
 
 pytestmark = pytest.mark.gpu
 
@@ -82,3 +84,45 @@ def test_more_workspaces_than_counter_sets_take_the_merge_kernel():
     torch.cuda.synchronize()
     for i, o in enumerate(outs):
         assert_close(o, ref, f"workspace {i}")
+
+
+def _without_counters(batch, hq, d):
+    """A workspace that finds every set of arrival counters taken (any that are left are taken here first), and those that took them."""
+    w, q, cache, _ = _case(1, 8, 1, 128, 1000, 76)
+    nbytes, taken = max(tq.tq_workspace_bytes(1, 8, 128), 1 << 20), []
+    while counter_sets_left() > 0:
+        taken.append(torch.empty(nbytes, dtype=torch.uint8, device="cuda"))
+        tq.tq_sdpa_int4_decode(cache, q.cuda(), 1000, w.attn_scale, workspace=taken[-1])
+    torch.cuda.synchronize()
+    # (an odd 256 bytes into an allocation of its own: an address that no workspace has had)
+    return torch.empty(tq.tq_workspace_bytes(batch, hq, d) + 768, dtype=torch.uint8, device="cuda")[768:], taken
+
+
+# (sequences, query heads, KV heads, d, longest, bound, group, page, waves of a slot): calls that deal their waves to the sequences, without counters
+@pytest.mark.parametrize("B,Hq,Hkv,d,longest,S,group,page,waves", [
+    (12, 16, 8, 128, 1500, 6000, 32, 0, 8), (30, 16, 8, 128, 900, 6000, 32, 64, 4), (61, 16, 8, 128, 700, 3000, 32, 0, 2),
+    (65, 16, 8, 128, 500, 6000, 64, 0, 1), (33, 32, 16, 256, 500, 2500, 32, 32, 1)])
+def test_lengths_without_counters_take_the_chunk_list(B, Hq, Hkv, d, longest, S, group, page, waves):
+    workspace, _taken = _without_counters(B, Hq, d)
+    assert counter_sets_left() == 0 and lengths_waves(B, Hq, Hkv, d, S, group) == -waves
+    check(B, Hq, Hkv, d, _uneven(B, longest, 77 + B), S, group=group, page=page, workspace=workspace)
+    assert counter_sets_left() == 0
+
+
+# one chunk that would be cut with counters; several chunks (the merge kernel)
+@pytest.mark.parametrize("hq,hkv,d,S", [(64, 8, 128, 480), (32, 16, 256, 300), (32, 8, 128, 2000)])
+def test_short_sequences_without_counters(hq, hkv, d, S):
+    w, q, cache, ocache = _case(1, hq, hkv, d, S, 78)
+    workspace, _taken = _without_counters(1, hq, d)
+    workspace.fill_(0xFF)
+    assert counter_sets_left() == 0
+    out = tq.tq_sdpa_int4_decode(cache, q.cuda(), S, w.attn_scale, workspace=workspace)
+    assert_close(out, oracle_attend(q, ocache, S, w.attn_scale), "decode")
+    k, v = make(w)[1:]
+    for t in cache.tensors():
+        t[:, :, S - 1].view(torch.uint8).fill_(0xEE)
+    out = tq.tq_sdpa_int4_append_decode(cache, k[:, :, S - 1:].contiguous().cuda(), v[:, :, S - 1:].contiguous().cuda(), q.cuda(), S, w.attn_scale,
+                                        workspace=workspace)
+    torch.cuda.synchronize()
+    assert_close(out, oracle_attend(q, ocache, S, w.attn_scale), "step")
+    assert_cache_bit_exact(cache, ocache, S)

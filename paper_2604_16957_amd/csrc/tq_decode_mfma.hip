@@ -625,7 +625,6 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
     return young ? YNG * (K / PERIOD) + (r >> 1) : OLD * (K / PERIOD) + ((r + 1) >> 1);
   };
   const int n_mine = count_of(n_full);
-  const int n_busy = PLAIN ? min(NW, n_full + n_tail) : NW;
   // ---- prologue: the query rows of this KV head's group come in by direct load as well (so that every
   //      vector-memory operation of the kernel is one of the counted loads), then the ring is filled.
   //      Where the query block has to borrow the last ring slot, that slot is filled once the query
@@ -637,6 +636,12 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   // the 128K launch; at d = 256 the later point costs 0.3 us).
   constexpr int NPRE = NS - 1;
   const bool kSecondAfterFirstLanded = D == 128 && whole;   // (rows packed several to a block: 256 x 512 tokens 39.2 -> 40.0 us with it)
+  // (a borrowed slot: behind its K tiles where the block fits there, else from the slot's start)
+  constexpr int Q_IN_SLOT = C::QAREA <= C::STAGE - C::OFF_V ? C::OFF_V : 0;
+  // (a block of fewer waves, see `ranked`: the areas behind the rings move up)
+  const int off_merge = C::ALIAS ? 0 : n_waves * NS * C::STAGE;
+  const int off_qblk = off_merge + (n_waves * GP * D + 2 * NW * GP + n_units * C::NEWTOK) * 4;
+  char* const q_area = C::QSEP ? smem + off_qblk + wave * C::QAREA : ring + (NS - 1) * C::STAGE + Q_IN_SLOT;
   // A decode step's new token (one query token; its K and V rows in p.k_new / p.v_new): one wave of the block that
   // holds its sequence's first chunk quantises it while the first stage of the stream is on its way, stores it, works
   // out its scores against the block's query rows, and brings it to the block merge as one more wave would: m = the
@@ -651,33 +656,26 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   // that wave 2.0 us behind the others; us per step 8 heads over 1, 1024 tokens 8.62 -> 7.94, 64 over 8, 8K 10.77 -> 10.02,
   // 32 over 16, d = 256, a window of 1024 9.31 -> 8.78; the decode alone 7.83, 10.01, 8.80.)
   // (A chunk of few supertiles leaves the younger waves idle: then they.)
-  const int taker = n_busy <= NW / 2 ? NW - 1 : NW / 2 - 1;
-  const bool takes_k = new_here && (whole ? wave == taker : sub == 0);
-  const bool takes_v = new_here && (whole ? wave == taker - 1 : sub == (W > 1 ? 1 : 0));
-  const bool takes = takes_k || takes_v;
+  // The choice stands in front of the first loads, like all up to here, and every instruction delays them: nothing that can wait
+  // (which waves are idle, whose the last supertile is) is worked out here.  (50 - 80 more: us per decode 32 heads over 32, 8 sequences of 200
+  // tokens 5.3 -> 5.7, 64 over 8, groups of 64, 200 7.35 -> 7.6.)
+  const int taker = PLAIN && n_full + n_tail <= NW / 2 ? NW - 1 : NW / 2 - 1;
+  const bool one_takes = !PLAIN && W == 1;        // a single wave takes both
+  const int new_part = whole ? taker - wave : sub;             // 0: K, 1: V
+  const bool takes = new_here && (uint32_t)new_part < (one_takes ? 1u : 2u);
+  const bool takes_k = takes && new_part == 0, takes_v = takes && (one_takes || new_part == 1);
   constexpr int PIECES = D / 8, COPIES = 64 / PIECES;
-  const int new_piece = lane % PIECES, new_v = takes_k && takes_v ? lane >> 5 : takes_v;
-  // (a borrowed slot: behind its K tiles where the block fits there, else from the slot's start)
-  constexpr int Q_IN_SLOT = C::QAREA <= C::STAGE - C::OFF_V ? C::OFF_V : 0;
-  // (a block of fewer waves, see `ranked`: the areas behind the rings move up)
-  const int off_merge = C::ALIAS ? 0 : n_waves * NS * C::STAGE;
-  const int off_qblk = off_merge + (n_waves * GP * D + 2 * NW * GP + n_units * C::NEWTOK) * 4;
-  char* const q_area = C::QSEP ? smem + off_qblk + wave * C::QAREA : ring + (NS - 1) * C::STAGE + Q_IN_SLOT;
-  {
-    const uint32_t l = C::QSEP ? (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem + off_qblk +
-                                     wave * C::QAREA
-                               : ring_lds + (NS - 1) * C::STAGE + Q_IN_SLOT;
-    {
+  const int new_piece = lane % PIECES, new_v = one_takes ? lane >> 5 : new_part;
+  const uint32_t q_lds = C::QSEP ? (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem + off_qblk + wave * C::QAREA
+                                 : ring_lds + (NS - 1) * C::STAGE + Q_IN_SLOT;
 #pragma unroll
-      for (int u = 0; u < GP * D * 2 / 1024; ++u) {
-        const int chunk = u * 64 + lane;          // 16-byte chunk of the [GP][D] fp16 query block
-        const int h = min(chunk / (D / 8), G - 1);
-        dma16_lane(p.q + query_row(h) * D + (chunk % (D / 8)) * 8, l + u * 1024);
-      }
-    }
-    if (takes)                                    // the new token's K row, or its V row (one wave for both: half the lanes each)
-      dma16_lane((new_v ? p.v_new : p.k_new) + (int64_t)(b * p.n_kv_heads + kv) * D + new_piece * 8, l + C::QBLK);
+  for (int u = 0; u < GP * D * 2 / 1024; ++u) {
+    const int chunk = u * 64 + lane;              // 16-byte chunk of the [GP][D] fp16 query block
+    const int h = min(chunk / (D / 8), G - 1);
+    dma16_lane(p.q + query_row(h) * D + (chunk % (D / 8)) * 8, q_lds + u * 1024);
   }
+  if (takes)                                      // the new token's K row, or its V row (one wave for both: half the lanes each)
+    dma16_lane((new_v ? p.v_new : p.k_new) + (int64_t)(b * p.n_kv_heads + kv) * D + new_piece * 8, q_lds + C::QBLK);
   // A wave has up to NS stages out before its loop and issues one per supertile while it has supertiles left.
   // (Stand-in loads that kept the count of outstanding loads the same to the end were taken out: the one issued in
   // a wave's last iteration made it wait a whole memory round trip for bytes nobody reads, 0.3 us per launch at

@@ -1514,7 +1514,8 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
     wait_loads<0>();                              // vmcnt counts stores too: this wave's partials have landed
     // Everything is asked for at once: the row's (m, l), a chunk per lane, and the chunks' outputs, sixteen bytes a lane (D / 4
     // lanes to a chunk, PARTS chunks to an instruction).  The row's partials are addressed as a buffer of n chunks: what lies
-    // past the last one reads as zero, and its weight is zero.
+    // past the last one reads as zero, and its weight is zero.  (The whole offset goes in per lane: it is what a raw buffer's bound is
+    // promised to be checked against, the scalar offset is not.)
     auto merge_chunks = [&](int64_t row, int n) {
       constexpr int PARTS = 256 / D;
       float* const c_w = reinterpret_cast<float*>(wave_area(wave));          // [kMergeMaxChunks]
@@ -1526,7 +1527,7 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
         constexpr int U = decltype(count_tag)::value;
 #pragma unroll
         for (int u = 0; u < U; ++u)
-          o[u] = __builtin_bit_cast(float4v, __builtin_amdgcn_raw_buffer_load_b128(rows, ((c0 + cpart * U) * D + j) * 4, u * D * 4, 16));   // 16: device scope
+          o[u] = __builtin_bit_cast(float4v, __builtin_amdgcn_raw_buffer_load_b128(rows, ((c0 + cpart * U + u) * D + j) * 4, 0, 16));   // 16: device scope
       };
       float4v num = {0, 0, 0, 0};
       auto add = [&](auto count_tag, int c0, const float4v* o) {

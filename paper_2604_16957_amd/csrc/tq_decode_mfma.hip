@@ -1487,6 +1487,13 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
         }
       return;
     }
+    if (D == 256 && (direct || p.merge_slot < 0)) {      // (no row to count in: a wave to half a row, where the rows are as few as two)
+      for (int u = wave; u < G * (D / 128); u += NW) {
+        const int h = u / (D / 128);
+        merge_row(std::integral_constant<int, 2>{}, h, u % (D / 128) * 128, 0, NW, query_row(h), direct, split, new_here, lds_new);
+      }
+      return;
+    }
     for (int h = wave; h < G; h += NW)
       merge_row(std::integral_constant<int, D / 64>{}, h, 0, 0, NW, query_row(h), direct, split, new_here, lds_new);
     if (p.merge_slot < 0 || direct || wave >= G) return;

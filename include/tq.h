@@ -133,9 +133,9 @@ int tq_quantize_kv_varlen(const tq_kv_cache* cache, const void* k_new, const voi
  * memory owned by the library, one set per WORKSPACE address (kept for the life of the process, left zero by
  * every launch).  Calls that may run at the same time must not share a workspace (they would overwrite each
  * other's partials), so they never share counters either, whether issued eagerly or replayed from a captured
- * graph.  There are 256 sets; a call whose workspace is the 257th distinct address the library sees takes the
- * merge kernel (two launches) instead, with the same result up to the summation order of the merge: results are
- * bit-for-bit repeatable per workspace, not across workspaces.
+ * graph.  There are 256 sets (16 MB on every GPU the library is loaded on); a call whose workspace is the 257th distinct
+ * address the library sees takes the merge kernel (two launches) instead, and cuts a short sequence less finely, with the
+ * same result up to the order of the sums: results are bit-for-bit repeatable per workspace, not across workspaces.
  * Errors: NULL, SHAPE, EMPTY (seq_len < 1), CAPACITY (seq_len > capacity), WORKSPACE,
  * UNSUPPORTED, HIP. */
 int tq_sdpa_int4_decode(const tq_kv_cache* cache, const void* q, int32_t n_q_heads, int32_t seq_len,
@@ -182,12 +182,16 @@ int tq_sdpa_int4_append_decode(const tq_kv_cache* cache, const void* k_new, cons
  * common N, Alg. 1): sequence b attends tokens [0, seq_lens[b]).  seq_lens: DEVICE int32 [batch],
  * read by the kernels (the host never sees the values); each is clamped to [1, max_seq_len].
  * max_seq_len (host, <= capacity) only bounds them.  With opts->n_splits == 0 the kernels plan the
- * chunks themselves from the lengths, so that every block gets about the same number of tokens
+ * work themselves from the lengths, so that every block gets about the same number of tokens
  * whatever the mix (the cost follows the SUM of the lengths); with n_splits > 0 the sequence range
- * [0, max_seq_len) is cut into that many chunks and those past a sequence's end do no work.  Two
- * launches (partial kernel + merge kernel), or one where many sequences of moderate length make every
- * (sequence, KV head) row a block of its own.  Other arguments and errors as for
- * tq_sdpa_int4_decode (EMPTY / CAPACITY refer to max_seq_len). */
+ * [0, max_seq_len) is cut into that many chunks and those past a sequence's end do no work.
+ * Launches: ONE for most calls of one query token without a window on the matrix-core kernel for few
+ * query rows (the waves of the chip are dealt to the sequences and a sequence's blocks merge in place, for
+ * which the workspace takes a set of arrival counters as in tq_sdpa_int4_decode), and where many sequences
+ * of moderate length make every (sequence, KV head) row a block of its own; else two (partial kernel + merge
+ * kernel), also where the workspace finds all sets taken.  Results are bit-for-bit repeatable per workspace,
+ * not across workspaces.  Other arguments and errors as for tq_sdpa_int4_decode (EMPTY / CAPACITY refer to
+ * max_seq_len). */
 int tq_sdpa_int4_decode_varlen(const tq_kv_cache* cache, const void* q, int32_t n_q_heads,
                                const int32_t* seq_lens, int32_t max_seq_len, float attn_scale,
                                void* out, void* workspace, size_t workspace_bytes,
@@ -210,11 +214,11 @@ int tq_sdpa_int4_append_decode_varlen(const tq_kv_cache* cache, const void* k_ne
  * tokens (a power of two >= 32), arrays [n_pages][n_kv_heads][page_tokens][...] in the canonical
  * layout.  block_table: DEVICE int32 [batch][max_blocks]; token t of sequence b lives in page
  * block_table[b][t / page_tokens] at row t % page_tokens; only the entries a sequence's tokens
- * reach are read, and they must name pages of the pool (not checked).  `batch` counts sequences
+ * reach are used, and they must name pages of the pool (not checked).  `batch` counts sequences
  * (q, out, seq_lens, positions, k_new, v_new and the workspace are sized by it).
  * tq_quantize_kv_paged: as tq_quantize_kv_varlen; a sequence whose tokens would not fit into its
  * max_blocks pages is skipped.  tq_sdpa_int4_decode_paged: as tq_sdpa_int4_decode_varlen (device
- * seq_lens, chunks planned on the device, two launches, opts->window and opts->n_queries as there);
+ * seq_lens, work planned on the device, launches, counters, opts->window and opts->n_queries as there);
  * max_seq_len <= max_blocks * page_tokens.  Errors as for the varlen calls; SHAPE also for a page
  * length that is not a power of two >= 32. */
 int tq_quantize_kv_paged(const tq_kv_cache* pool, const int32_t* block_table, int32_t max_blocks,

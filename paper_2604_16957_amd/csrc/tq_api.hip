@@ -40,7 +40,9 @@ constexpr int kBlocksWide = 256;   // matrix-core kernel for wide rows: 8-wave b
 // A chunk is never longer than this many tokens under the heuristic, which bounds the rounding that the fp32 accumulators of one
 // wave pick up however long the sequence is: at most 64 tiles in the matrix-core kernel; in the kernel for wide rows, whose waves take
 // their dims of every tile, every second, every fourth (head_dim 512, 256, 128), 512, 256, 128 tiles.  Relative error against 64 bits of 16384
-// tokens, planned / as one chunk: 2.90e-4 / 2.91e-4, 2.88e-4 / 2.91e-4, 2.06e-4 / 2.07e-4.
+// tokens, planned / as one chunk: 2.90e-4 / 2.91e-4, 2.88e-4 / 2.91e-4, 2.06e-4 / 2.07e-4.  (Sequences with lengths of their own have no such bound: the
+// device cuts them by the total, and a wave may hold a whole one.  5 sequences of 16000 .. 20000 tokens, 128 heads over 128, dealt to waves, some 210
+// tiles each: 2.61e-4, by the chunk list 2.65e-4.)
 constexpr int kMaxChunkTokens = 16384;
 
 // Chunks of whole 32-token tiles, never an empty chunk.  The blocks of a launch run in rounds of

@@ -298,6 +298,8 @@ __device__ __forceinline__ void wait_loads() {               // until at most N 
 // (TWO, d = 128; a loop of its own, the other waves' is as it was), and at d = 256 all of them do (SPLIT).  Error against 64 bits, 64 sequences
 // of 128 .. 4096 tokens: before 2.33e-4, one operand 2.60e-4, this 2.19e-4, two for all 2.08e-4 (but 0.2 us per tile: the 24
 // paged sequences 38.5 -> 42.4 us per step); 2048 .. 4096 2.56e-4 / - / 2.56e-4; d = 256 2.87e-4 / 2.89e-4 / 2.07e-4 at 2 - 4 % of the time.
+// Sequences of three slots and more, each by itself (six mixes, three seeds): 2.36e-4 .. 2.67e-4 before, 2.31e-4 .. 2.62e-4 now, by the number of their slots
+// 0.96 .. 1.03 of what they had, three to seven slots 0.98 .. 1.015, on the whole the same.
 enum Mode { kPlain, kPlainStep, kGeneral, kPaged, kListed, kListedPaged };   // kPlainStep: see LEAN
 // LEAN: the 16-row tile's instances for plain launches and for blocks that share a KV head take no new token and come to
 // the masked last supertile at the end.  Two stretches of code that few waves run, between the prologue and the loop, cost

@@ -91,8 +91,8 @@ struct DecodeParams {
   // to a KV head) are single waves and lie side by side in the blocks (blockIdx.y; blockIdx.x: the KV head); the waves of one sequence
   // in a block share the block's part of it, and the blocks of a sequence merge in place (merge_slot).
   int32_t listed;
-  int32_t merge_slot;       // matrix-core kernel: >= 0 selects a set of arrival counters and makes the last
-                            // block of every (b, kv head) merge the chunks and write `out`; < 0: partials only
+  int32_t merge_slot;       // matrix-core kernel: >= 0 selects a set of arrival counters and makes the wave that has an output
+                            // row last merge that row's chunks and write it to `out`; < 0: partials only
 };
 
 #ifdef __HIPCC__

@@ -68,8 +68,8 @@ def test_short_sequences_weights_in_two_parts():
     assert errors(out, ref)[1] <= 2.35e-4
 
 
-# Sequences of three to seven waves keep one operand: each of them at what eight waves to a sequence had (2.46e-4 .. 2.67e-4 each, over three seeds;
-# now 2.40e-4 .. 2.63e-4).  The output's rounding and a weight's (2^-12 at most, evenly spread: 1.4e-4 .. 1.6e-4) make 2.6e-4; an eighth of that for one sequence's spread.
+# Sequences of three to seven waves keep one operand, and the error they had with eight waves (grouped by the number of waves 2.46e-4 .. 2.65e-4 either
+# way).  The output's rounding, 2.07e-4, and that of the weights (2^-12 at most, evenly spread: 1.4e-4 .. 1.6e-4) make 2.6e-4; an eighth of that for one sequence's spread.
 def test_each_sequence_of_three_to_seven_waves():
     B, Hq, Hkv, S = 48, 64, 8, 2500
     w = wl.custom(batch=B, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=128, seq_len=S, seed=78, outlier_channels=4)

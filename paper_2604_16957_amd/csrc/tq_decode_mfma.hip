@@ -652,7 +652,7 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   // rows, and like this: one sequence of 1024 tokens, 8 heads on 1, 12.5 -> 11.3 us per call; a window of 1024, d = 256,
   // 13.1 -> 10.9; 32K tokens, d = 256, 35.3 -> 33.9; 128 sequences of 512 .. 1024 tokens 35.3 -> 32.6.)
   // What the token costs is the chain of instructions of the wave that takes it: the block waits for that wave.  So its K
-  // and its V go to two waves (where a row has one wave only: to its two halves), of the older ones of their SIMDs, which are
+  // and its V go to two waves (or the two halves of one, see `one_takes`), of the older ones of their SIMDs, which are
   // 0.6 us ahead of the younger at this point, and a wave's lanes hold the row several times over, eight elements a lane, so
   // that the copies of K share the query rows' scores between them.  (One younger wave for all of it, half of its lanes idle:
   // that wave 2.0 us behind the others; us per step 8 heads over 1, 1024 tokens 8.62 -> 7.94, 64 over 8, 8K 10.77 -> 10.02,
@@ -662,7 +662,12 @@ __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void decode_partial_mfma_ker
   // (which waves are idle, whose the last supertile is) is worked out here.  (50 - 80 more: us per decode 32 heads over 32, 8 sequences of 200
   // tokens 5.3 -> 5.7, 64 over 8, groups of 64, 200 7.35 -> 7.6.)
   const int taker = PLAIN && n_full + n_tail <= NW / 2 ? NW - 1 : NW / 2 - 1;
-  const bool one_takes = !PLAIN && W == 1;        // a single wave takes both
+  // One wave takes both where a row has no other, and at d = 256 wherever a block holds several rows: all its waves have work of their own
+  // then, so what counts is the sum of the instructions, and two waves quantise in twice as many as one does both rows in, for the scores
+  // of only two query rows.  (us per step, two waves / one, 16 heads over 8: 79 sequences of 146 .. 214 tokens in pages 17.71 / 17.09,
+  // contiguous 17.07 / 16.38, 64 of 600 21.67 / 21.38; 32 over 16, 79 of 146 .. 900 in pages 40.0 / 39.4.  At d = 128 it is the other way
+  // round or even, 64 over 8: 64 of 64 .. 2000 22.53 / 22.79, 96 of 64 .. 1500 25.4 / 25.3.)
+  const bool one_takes = !PLAIN && (D == 256 ? !whole : W == 1);
   const int new_part = whole ? taker - wave : sub;             // 0: K, 1: V
   const bool takes = new_here && (uint32_t)new_part < (one_takes ? 1u : 2u);
   const bool takes_k = takes && new_part == 0, takes_v = takes && (one_takes || new_part == 1);

@@ -364,31 +364,42 @@ Ranked ranked_rows(const tq_kv_cache* cache, int n_q_heads, int seq_len, float a
 //       4096  58.1 / 59.1 | 50.8 / 51.7 | 32.2 / 28.3     6000  87.8 / 84.5 | 78.6 / 73.0 | 40.5 / 37.0
 //   80 (3.2)    1024  30.3 / 31.3 | 28.7 / 27.1 | 21.7 / 19.2
 //   85 (3.01)   2048  48.5 / 48.6 | 47.2 / 41.8 | 24.4 / 25.1     4096  88.4 / 81.6 | 75.2 / 73.0 | 40.0 / 36.4
-//   88 (2.9)    2048  48.9 / 58.4 | 47.5 / 42.8 | 24.7 / 25.2     4096  89.9 / 107  | 75.3 / 74.7 | 41.3 / 37.3
+//   88 (2.9)    3000  71.0 / 80.1 | 62.4 / 57.9 | 32.9 / 32.7     4096  89.9 / 107  | 75.3 / 74.7 | 41.3 / 37.3     5000  119 / 130 | 106 / 90.3 | 57.4 / 43.9
+//       (the older way up to 4096 a block per row, beyond the chunk list)
 //   96 (2.7)    4096  104 / 112   | 99.8 / 81.9 | 51.0 / 38.4    16384  356 / 411   | 312 / 282   | 138 / 111
 //   128 (2)     2048  60.5 / 74.0 | 54.2 / 66.7 | 33.8 / 31.5     8192  230 / 255   | 193 / 215   | 85.9 / 81.4
 //   (more: the chunk list's waves are as short of work)
 //   130 (1.97)  2200  115 / 109   | 105 / 72.7  | 60.7 / 37.1     8192  339 / 358   | 293 / 217   | 132 / 84.8
-//   192 (1.33)  3500  184 / 182   | 170 / 149   | 87.8 / 72.4     (32 heads over 32: 48, 4096  195 / 168 | 167 / 152 | 76.3 / 66.4)
-//   220 (1.16)  3500  195 / 198   | 174 / 168   | 89.8 / 94.4     (56 (1.14), 4096  198 / 183 | 166 / 162 | 77.8 / 95.3)
-// and at d = 256, 32 heads over 16: 32 (4) 2048 60.6 / 63.8 | 52.3 / 52.5 | 35.5 / 29.3, 2500 81.4 / 76.8 | 70.2 / 61.9 | 40.4 / 36.0; 33 (3.9) 400 21.9 / 23.6 |
-// 17.6 / 19.4 | 14.9 / 16.3, 700 32.4 / 32.9 | 27.8 / 26.1 | 16.7 / 17.1, 1024 42.3 / 42.4 | 33.6 / 35.6 | 19.6 / 19.6; 40 (3.2) 700 39.3 / 35.7 | 32.5 / 31.0 | 19.5 / 19.7;
-// 44 (2.9) 1024 53.4 / 54.7 | 44.4 / 41.9 | 22.4 / 22.4, 3000 146 / 143 | 121 / 98.9 | 57.8 / 43.0; 64 (2) 3000 170 / 164 | 144 / 135; 110 (1.16) 3000
-// 307 / 296 | 252 / 235 | 117 / 112, lengths from a 150th on, 109 97.4 / 89.4, 113 97.1 / 102.8.
+//   192 (1.33)  3500  184 / 182   | 170 / 149   | 87.8 / 72.4     8192  394 / 418   | 337 / 328   | 156 / 155
+//   200 (1.28)  3000  173 / 171   | 148 / 139   | 80.3 / 75.2     8192  399 / 431   | 330 / 343   | 153 / 170
+//   212 (1.21)  2200  139 / 136   | 118 / 114   | 69.6 / 64.6     3500  199 / 202   | 169 / 169   | 87.7 / 92.5
+// With up to four query rows to a KV head (`light`: a wave's tile is cheaper against the rest) the dealt waves gain for longer:
+//   32 over 32  22 (2.9)   1100  28.1 / 29.9 | 25.1 / 23.6 | 18.1 / 15.3     4096  81.6 / 83.2 | 66.2 / 65.5 | 37.3 / 32.9
+//               54 (1.19)  4096   202 / 182  | 173 / 163   | 83.5 / 90.8     8000   358 / 350  | 299 / 314   | 140 / 168       56 (1.14)  4096  198 / 183 | 166 / 162 | 77.8 / 95.3
+//   64 over 16  44 (2.9)   3000  63.5 / 64.9 | 55.0 / 51.1 | 30.7 / 26.6     105 (1.22)  4096  202 / 186 | 165 / 162 | 87.1 / 89.0     8000  363 / 354 | 301 / 311 | 141 / 160
+//   32 over 8   88 (2.9)   2048  44.1 / 50.5 | 41.9 / 38.4 | 22.6 / 22.2     200 (1.28)  2200  122 / 109 | 105 / 93.0 | 58.6 / 48.5     8000  359 / 344 | 302 / 303 | 134 / 139
+// and at d = 256, 32 heads over 16: 32 (4) 2048 60.6 / 63.8 | 52.3 / 52.5 | 35.5 / 29.3, 2500 81.4 / 76.8 | 70.2 / 61.9 | 40.4 / 36.0; 33 (3.9) 200 15.0 / 17.3 |
+// 13.5 / 15.8 | 11.7 / 13.0, 400 21.5 / 23.1 | 18.1 / 19.6 | 15.5 / 14.5, 700 32.4 / 32.8 | 26.6 / 26.2 | 16.7 / 17.3 (the one batch that has little of it up to 768);
+// 37 (3.5) 256 18.7 / 19.9 | 16.9 / 17.9 | 14.7 / 13.9, 300 21.0 / 20.8 | 19.1 / 19.0 | 15.8 / 14.3, 700 39.0 / 33.8 | 32.2 / 28.5 | 18.6 / 18.3; 42 (3) 256 19.0 / 20.6 |
+// 17.4 / 18.8 | 15.3 / 14.9, 300 21.4 / 21.7 | 19.7 / 19.5 | 17.2 / 15.8, 700 39.9 / 36.4 | 33.5 / 30.6 | 20.7 / 19.3; 44 (2.9) 500 31.8 / 32.0 | 27.7 / 25.6 | 19.6 / 18.2,
+// 2048 99.0 / 98.9 | 71.8 / 71.4 | 36.7 / 36.3; 64 (2) 3000 170 / 164 | 144 / 135; 109 (1.17) 4096 416 / 393 | 343 / 313 | 163 / 170, 6000 581 / 580 | 501 / 483 | 232 / 247.
 // More than 128 KV heads have a block each and leave up to half the chip without one: 129 heads over 129, 4 sequences, 4000 77.7 / 78.8 | 58.4 / 81.4 | 30.9 / 37.4
 // (3, where the chunk list leaves as much: 74.9 / 75.3 | 73.8 / 53.3 | 40.5 / 32.3).
 // One sequence at the bound among short ones gains everywhere (64 sequences, one of 4096, the others 96: 25.3 / 14.4).
-bool listed_lengths(const tq_kv_cache* cache, int slots, int tokens) {
+bool listed_lengths(const tq_kv_cache* cache, int n_q_heads, int slots, int tokens) {
   constexpr int C = kBlocksMfma;
   const int batch = cache->batch;
   const int64_t rows = (int64_t)batch * cache->n_kv_heads;
   const bool d256 = cache->head_dim == 256;
+  const bool light = !d256 && cache->group_size == tq::kGroup && n_q_heads / cache->n_kv_heads <= 4;
   if (rows < 2 * C) return true;
   if (cache->n_kv_heads > C / 2) return false;
   if (rows == 2 * C) return tokens > (d256 ? 2048 : 3072);
-  if (slots >= 3 * batch) return tokens > (d256 ? 768 : 1024);
+  if (11 * slots >= 32 * batch) return tokens > (d256 ? 256 : light || slots >= 3 * batch ? 1024 : 4096);
   if (rows <= 4 * C) return d256 && tokens > 2048;
-  return tokens > 2048 && 6 * slots >= (d256 ? 7 : 8) * batch;
+  // slots to a sequence, in sixtieths
+  const int least = d256 ? 70 : light ? (tokens <= 4096 ? 70 : 75) : tokens <= 3072 ? 72 : 80;
+  return tokens > 2048 && 60 * slots >= least * batch;
 }
 int listed_slots(const tq_kv_cache* cache, int n_q_heads, int seq_len, float attn_scale, const tq_decode_opts* opts) {
   if (opts && (opts->n_splits > 0 || opts->window > 0 || opts->n_queries > 1)) return 0;
@@ -398,7 +409,7 @@ int listed_slots(const tq_kv_cache* cache, int n_q_heads, int seq_len, float att
   // (a slot for every sequence and one more; what the device's plan keeps in registers, and sums in 32 bits)
   if (slots <= cache->batch || cache->batch > tq::kListMaxBatch || (int64_t)cache->batch * seq_len >= (1ll << 31)) return 0;
   if (!tq::mfma_can_merge((int64_t)cache->batch * n_q_heads)) return 0;
-  return listed_lengths(cache, slots, seq_len) ? slots : 0;
+  return listed_lengths(cache, n_q_heads, slots, seq_len) ? slots : 0;
 }
 
 // The device-planned chunk list of sequences with their own lengths, per KV head: r rounds of target / rows_per_batch slots, r the smallest count

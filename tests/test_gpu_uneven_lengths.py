@@ -90,7 +90,7 @@ def test_hundreds_of_sequences_each_row_once(B, Hkv, longest):
 ROUTES = {
     "one round of 4 waves a row": (64, 16, 8, 128, 1100, 2048, 0, "4 waves a row"),
     "8 waves a row": (64, 16, 8, 128, 2300, 3072, 0, "8 waves a row"),
-    "8 waves a row, two rounds and a bit": (88, 16, 8, 128, 700, 4096, 0, "8 waves a row"),
+    "8 waves a row, two rounds and a bit": (88, 64, 8, 128, 700, 4096, 0, "8 waves a row"),
     "4 waves a row": (97, 16, 8, 128, 1100, 3072, 0, "4 waves a row"),
     "4 waves a row, past two rounds": (129, 16, 8, 128, 700, 2048, 0, "4 waves a row"),
     "2 waves a row": (161, 16, 8, 128, 900, 1024, 0, "2 waves a row"),

@@ -71,9 +71,10 @@ def test_always_at_512():
 
 # (sequences, heads, KV heads, head dim, the longest bound that does not deal its waves to the sequences; 0: every bound does)
 @pytest.mark.parametrize("B,heads,kv,d,last", [
-    (63, 64, 8, 128, 0), (64, 64, 8, 128, 3072), (65, 64, 8, 128, 1024), (85, 64, 8, 128, 1024), (129, 64, 8, 128, 2048), (192, 64, 8, 128, 2048),
-    (48, 32, 32, 128, 2048), (31, 32, 16, 256, 0), (32, 32, 16, 256, 2048), (33, 32, 16, 256, 768), (42, 32, 16, 256, 768),
-    (43, 32, 16, 256, 2048), (65, 32, 16, 256, 2048), (109, 32, 16, 256, 2048), (8, 72, 72, 128, 1024), (5, 96, 96, 128, 0), (3, 129, 129, 128, 0)])
+    (63, 64, 8, 128, 0), (64, 64, 8, 128, 3072), (65, 64, 8, 128, 1024), (85, 64, 8, 128, 1024), (86, 64, 8, 128, 4096),
+    (88, 64, 8, 128, 4096), (88, 32, 8, 128, 1024), (44, 64, 16, 128, 1024), (22, 32, 32, 128, 1024), (129, 64, 8, 128, 2048), (192, 64, 8, 128, 2048),
+    (48, 32, 32, 128, 2048), (31, 32, 16, 256, 0), (32, 32, 16, 256, 2048), (33, 32, 16, 256, 256), (42, 32, 16, 256, 256),
+    (44, 32, 16, 256, 256), (45, 32, 16, 256, 2048), (65, 32, 16, 256, 2048), (109, 32, 16, 256, 2048), (8, 72, 72, 128, 1024), (5, 96, 96, 128, 0), (3, 129, 129, 128, 0)])
 def test_lengths_that_are_dealt_to_waves(B, heads, kv, d, last):
     slots = 256 // kv * 8
     assert listed_slots(B, heads, kv, d, last + 1) == slots and (last == 0 or listed_slots(B, heads, kv, d, last) == 0)
@@ -81,12 +82,20 @@ def test_lengths_that_are_dealt_to_waves(B, heads, kv, d, last):
         assert listed_slots(B, heads, kv, d, 5000, **more) == 0
 
 
-# too few slots to a sequence (fewer than three up to 1024 rows, four to three or, head_dim 256, seven to six beyond), or half the chip without a block
+# (sequences, heads, KV heads, head dim, group, the longest bound that deals its waves to the sequences): beyond it the slots are too few
+@pytest.mark.parametrize("B,heads,kv,d,group,most", [
+    (193, 64, 8, 128, 32, 3072), (213, 64, 8, 128, 32, 3072), (193, 32, 8, 128, 64, 3072), (205, 32, 8, 128, 32, 4096), (219, 32, 8, 128, 32, 4096),
+    (52, 32, 32, 128, 32, 4096), (54, 32, 32, 128, 32, 4096), (109, 64, 16, 128, 32, 4096)])
+def test_slots_that_are_enough_up_to_a_bound(B, heads, kv, d, group, most):
+    assert [listed_slots(B, heads, kv, d, bound, group) > 0 for bound in (2048, 2049, most, most + 1, 50000)] == [False, True, True, False, False]
+
+
+# too few slots to a sequence, at any bound, or half the chip without a block
 @pytest.mark.parametrize("B,heads,kv,d", [
-    (86, 64, 8, 128), (128, 64, 8, 128), (193, 64, 8, 128), (49, 32, 32, 128), (56, 32, 32, 128), (220, 64, 8, 128), (110, 64, 16, 128),
+    (89, 64, 8, 128), (128, 64, 8, 128), (214, 64, 8, 128), (55, 32, 32, 128), (56, 32, 32, 128), (220, 64, 8, 128), (110, 64, 16, 128),
     (28, 64, 64, 128), (110, 32, 16, 256), (6, 96, 96, 128), (4, 129, 129, 128), (4, 256, 256, 128)])
 def test_too_few_slots_to_deal(B, heads, kv, d):
-    assert all(listed_slots(B, heads, kv, d, bound) == 0 for bound in (100, 1500, 3500, 8000, 131072))
+    assert all(listed_slots(B, heads, kv, d, bound) == 0 for bound in (100, 1500, 2500, 3500, 8000, 131072))
 
 
 def test_lengths_that_are_not_dealt_to_waves():

@@ -395,6 +395,7 @@ bool listed_lengths(const tq_kv_cache* cache, int n_q_heads, int slots, int toke
   if (rows < 2 * C) return true;
   if (cache->n_kv_heads > C / 2) return false;
   if (rows == 2 * C) return tokens > (d256 ? 2048 : 3072);
+  // (2.9 slots to a sequence and more)
   if (11 * slots >= 32 * batch) return tokens > (d256 ? 256 : light || slots >= 3 * batch ? 1024 : 4096);
   if (rows <= 4 * C) return d256 && tokens > 2048;
   // slots to a sequence, in sixtieths
